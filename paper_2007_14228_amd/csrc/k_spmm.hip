@@ -21,6 +21,8 @@
 // them lane to lane and issues U neighbour loads back to back before any
 // arithmetic.  Control flow around the broadcasts is uniform across the wave
 // (loop bounds use the wave's longest row; rows past n just have no entries).
+#include <algorithm>
+
 #include "common.hpp"
 
 // Tuning: neighbour loads in flight per wave for one-column-chunk rows, and
@@ -441,477 +443,310 @@ __global__ __launch_bounds__(256) void k_spmv_dot(int64_t n, const int64_t *__re
 }
 
 // ---------------------------------------------------------------------------
-// LDS-halo SpMM.  Block b owns the consecutive rows [row0[b], row0[b+1]) (at
-// most HALO_RMAX, each with at most 64 entries) and their halo: the distinct
-// columns of those rows together with the rows themselves in ascending order,
-// hoff[b+1] - hoff[b] <= HALO_MAX rows of X listed at halo[b HALO_STRIDE ...]
-// (padded to the stride with the last one), so the block's rows sit at slots
-// rbase[b], rbase[b] + 1, ...  brp[b HALO_BRP + k] is the CSR row pointer of
-// row row0[b] + k, for k = 0 .. HALO_RMAX (padded with row0[b+1]'s, so rows
-// past the block have no entries).  lcol[e] is the halo slot of CSR entry e.
-// Every per-block address depends on b alone: the block's metadata loads all
-// issue at once instead of one after another.  Wave v of the block takes rows row0[b] + v + HALO_WAVES i; it
-// loads their entries (slot, weight pair) once, one entry per lane, and keeps
-// them in registers.  For each 512-byte slice of the columns the block stages
-// its halo rows of X in LDS; every wave then forms its rows from LDS, reading
-// each row's entries back from a per-wave LDS area at uniform addresses (an
-// LDS broadcast).  X is gathered from L2 about (halo size / rows) times
-// instead of once per nonzero, and consecutive blocks (one XCD's slab, in
-// dispatch order) share their halos in that XCD's L2.
+// LDS-halo SpMM.  Plan block b owns the consecutive rows [row0[b], row0[b+1])
+// (at most HALO_RMAX, each with at most 64 entries) and their halo: the
+// distinct columns of those rows together with the rows themselves in
+// ascending order, at most HALO_MAX rows of X, listed at halo[b HALO_STRIDE
+// ...] (padded to the stride with the last one).  info[b] packs the halo's
+// size, the number of rows and the halo slot of the first row (the rows sit at
+// consecutive slots).  brp[b HALO_BRP + k] is the CSR row pointer of row
+// row0[b] + k, for k = 0 .. HALO_RMAX (padded with row0[b+1]'s, so rows past
+// the block have no entries).  lcol[e] is the halo slot of CSR entry e.
+// Every per-block address depends on b alone, so the metadata loads issue
+// together.
+//
+// One workgroup per plan block (and column range of cw, a whole number of
+// slices: where the plan has too few blocks to fill the device, the slices are
+// spread over workgroups); consecutive plan blocks run on one XCD, in
+// dispatch order, so neighbouring blocks' halos meet in that XCD's L2.  For
+// each 256-byte slice of the columns the workgroup stages its halo rows of X
+// in LDS with direct global-to-LDS loads (no registers).  A wave then forms
+// four rows at once, sixteen lanes a row and 16 bytes a lane.  A row's
+// entries sit one per lane of its sixteen lanes, loaded once for all slices,
+// and are handed round by DPP row broadcasts on the vector units: the LDS
+// serves nothing but X.  (With one row per wave and the entries broadcast
+// through LDS, the broadcasts took 2.5 times the LDS cycles of X and set the
+// time.)  Entries past a row's end point to a slot of zeros, since a zero
+// weight on a neighbour's row would turn its infinities into NaN.  ROUNDS (1,
+// or 2 where some row has more than sixteen entries) times sixteen entries of
+// a row are held in registers; later ones are loaded as they come.
 //  MODE 0: Y1 = A1 X and Y2 = A2 X (or, Y2 = NULL, A1 X or A2 X by sel).
 //  MODE 1: Y1 = Q = (A1 - lam_c A2) D on active columns (0 elsewhere), and
 //          part[b][c] = <D_c, Q_c> over the block's rows.
+// SEGB: bytes per staging lane, 16 where the rows of X are 16-byte aligned,
+// else 4.  Columns at or past p in a ragged last slice stage in-bounds data of
+// the row's first segment; no output reads them.
+//
+// Measured (n = 1e6, p = 128, FP64; before: 16-row blocks of 76 halo rows in
+// 512-byte slices, entries broadcast through LDS): shifted product 877 -> 615
+// us, dual product 945 -> 745 us; n = 5.1e5, p = 128, FP32: 286 -> 192 and 297
+// -> 189 us.  The shifted product moves 2.7 GB (1.24 times what it must) at
+// 4.4 TB/s, the dual product 3.8 GB at 5.0 TB/s (a copy: 4.8), so memory
+// bounds it.  Block shapes tried, FP64 shifted product in us: (halo rows,
+// rows, waves per SIMD) (200, 64, 3) 741 with the call around it, (120, 32, 4)
+// 788, (148, 48, 4) 835, (240, 64, 2) 818, (76, 16, 6) 851; workgroups that
+// walk several blocks with the next one's loads in flight drift apart, and
+// the widened window misses L2 (794, 2.4 to 3.4 GB fetched instead of 1.7).
 // ---------------------------------------------------------------------------
-// Tunables: halo rows (LDS = HALO_MAX x 512 B), rows per block, waves per
-// block, and the waves per SIMD the register budget is cut for (set by how
-// many blocks the LDS admits per CU).
+// Tunables: halo rows (LDS = (HALO_MAX + 1) x 256 B and the dot partials,
+// three workgroups a CU) and rows per block.
 #ifndef OFKS_HALO_MAX
-#define OFKS_HALO_MAX 76   // with the DMA kernel's separate dot area, three blocks still fit a CU's LDS
+#define OFKS_HALO_MAX 200
 #endif
 #ifndef OFKS_HALO_RMAX
-#define OFKS_HALO_RMAX 16   // an 80-row halo holds about 16 Morton-ordered rows' neighbours anyway
-#endif
-#ifndef OFKS_HALO_WAVES
-#define OFKS_HALO_WAVES 8
-#endif
-#ifndef OFKS_HALO_DMA
-#define OFKS_HALO_DMA 1   // 0: stage every slice through registers (the unaligned-row kernel)
+#define OFKS_HALO_RMAX 64
 #endif
 #ifndef OFKS_HALO_WPE
-#define OFKS_HALO_WPE 6
+#define OFKS_HALO_WPE 3
 #endif
-constexpr int HALO_MAX = OFKS_HALO_MAX, HALO_RMAX = OFKS_HALO_RMAX, HALO_WAVES = OFKS_HALO_WAVES, HALO_EMAX = 64;
-constexpr int HALO_RPW = HALO_RMAX / HALO_WAVES;   // rows per wave
-// Each block's halo row list is padded to HALO_STRIDE entries (repeating its
-// last row), so its address depends on the block index alone: the staging
-// threads' row lookups need no offset load first.  Both precisions stage
-// 32 sixteen-byte segments per slot, HALO_SST slots per pass.
-constexpr int HALO_SST = 64 * HALO_WAVES / 32;
+constexpr int HALO_MAX = OFKS_HALO_MAX, HALO_RMAX = OFKS_HALO_RMAX, HALO_WAVES = 4, HALO_EMAX = 64;
+constexpr int HALO_SETS = HALO_RMAX / (4 * HALO_WAVES);   // row sets (four rows each) per wave
+constexpr int HALO_SST = 4 * HALO_WAVES;   // halo slots filled by one 16-byte load of every wave
 constexpr int HALO_STRIDE = (HALO_MAX + HALO_SST - 1) / HALO_SST * HALO_SST;
-constexpr int HALO_BRP = HALO_RMAX + 1;            // per-block row pointer stride
-static_assert(HALO_RMAX % HALO_WAVES == 0, "whole rows per wave");
+constexpr int HALO_BRP = HALO_RMAX + 1;    // per-block row pointer stride
+static_assert(HALO_RMAX % (4 * HALO_WAVES) == 0, "whole row sets per wave");
+static_assert(HALO_MAX % 4 == 0, "a wave fills four slots at a time");
+static_assert(HALO_MAX < 256 && HALO_RMAX < 256, "info fields");
 
-
-// the register cap keeps every block the LDS admits resident
-template <typename T, int MODE>
-__global__ __launch_bounds__(64 * HALO_WAVES) __attribute__((amdgpu_waves_per_eu(OFKS_HALO_WPE))) void k_spmm_halo(
-    int64_t nb, int p, const int64_t *__restrict__ row0, const int64_t *__restrict__ hoff,
-    const int32_t *__restrict__ halo, const int32_t *__restrict__ rbase, const int64_t *__restrict__ brp,
-    const uint16_t *__restrict__ lcol,
-    const typename pair_t<T>::type *__restrict__ w, const T *__restrict__ X, T *__restrict__ Y1,
-    T *__restrict__ Y2, int sel, const T *__restrict__ lam, const uint8_t *__restrict__ active,
-    double *__restrict__ part) {
-    using P2 = typename pair_t<T>::type;
-    constexpr int CP = 512 / sizeof(T);   // columns per slice: 64 (f64) or 128 (f32)
-    constexpr int VW = 16 / sizeof(T);    // one 16-byte load
-    constexpr int LPC = CP / 64;          // columns per lane in a slice
-    constexpr int SEG = CP / VW;
-    __shared__ T Xs[HALO_MAX * CP];
-    // per-wave broadcast area: the current row's entries, read back by every
-    // lane at a uniform address (an LDS broadcast instead of VALU readlanes)
-    __shared__ int ent_off[HALO_WAVES][64];
-    __shared__ P2 ent_w[HALO_WAVES][64];
-    // MODE 1 per-wave dot partials reuse the slice's LDS once it is consumed
-    static_assert(HALO_WAVES * CP * sizeof(double) <= sizeof(T) * HALO_MAX * CP, "partials fit in the slice");
-    double *red = reinterpret_cast<double *>(Xs);
-    const int64_t b = xcd_block(blockIdx.x, gridDim.x);
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (b >= nb) {   // padding block of the XCD mapping: a zero partial row
-        if (MODE == 1)
-            for (int c = threadIdx.x; c < p; c += blockDim.x) part[b * p + c] = 0.0;
-        return;
-    }
-    // 16-byte loads need every row start 16-byte aligned
-    const bool vec = p % VW == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
-    // staging: thread t always moves 16-byte segment t % SEG of halo slots
-    // t / SEG + SST u; the slots' rows of X are looked up once per block
-    constexpr int SST = 64 * HALO_WAVES / SEG;
-    constexpr int SPT = (HALO_MAX + SST - 1) / SST;
-    static_assert((64 * HALO_WAVES) % SEG == 0, "whole slot rows per pass");
-    static_assert(SST == HALO_SST && SPT * SST == HALO_STRIDE, "padded halo stride");
-    const int sg = threadIdx.x % SEG, ss = threadIdx.x / SEG;
-    // (halo is padded per block; slots past the block's halo repeat its last
-    // row and are never stored)
-    int hrow[SPT];
+template <typename T> __device__ __forceinline__ void stream_store16(T *p, const T (&in)[16 / sizeof(T)]) {
+    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+    vec v;
 #pragma unroll
-    for (int u = 0; u < SPT; ++u) hrow[u] = halo[b * HALO_STRIDE + ss + SST * u];
-    // the halo loads go out first; the block's metadata loads below then all
-    // issue together, without the scheduler sinking the halo loads behind them
-    __builtin_amdgcn_sched_barrier(0);
-    const int64_t r0 = row0[b], r1 = row0[b + 1];
-    const int hn = (int)(hoff[b + 1] - hoff[b]);
-    const int rb = MODE == 1 ? rbase[b] : 0;   // the block's rows sit at halo slots rb, rb + 1, ...
-    // this wave's rows: entry k of row i sits in lane k (lanes past the row
-    // re-read entry 0, which every allocation holds, and are never used)
-    int len[HALO_RPW], off[HALO_RPW];
-    T wa[HALO_RPW], wb[HALO_RPW];
-    const int64_t *bp = brp + b * HALO_BRP;
-#pragma unroll
-    for (int i = 0; i < HALO_RPW; ++i) {
-        const int k = wave + HALO_WAVES * i;
-        const int64_t e0 = bp[k];
-        len[i] = (int)(bp[k + 1] - e0);
-        const int64_t e = lane < len[i] ? e0 + lane : 0;
-        const P2 ww = w[e];
-        off[i] = (int)lcol[e] * CP;
-        wa[i] = ww.x;
-        wb[i] = ww.y;
-    }
-    for (int c0 = 0; c0 < p; c0 += CP) {
-        const int c = c0 + sg * VW;
-        if (vec && c0 + CP <= p) {
-            // whole aligned slice: every load of the slice in flight before
-            // the first LDS write
-            T v[SPT][VW];
-#pragma unroll
-            for (int u = 0; u < SPT; ++u) load_vec<T, VW>(X + (int64_t)hrow[u] * p + c, v[u]);
-#pragma unroll
-            for (int u = 0; u < SPT; ++u) {
-                const int sl = ss + SST * u;
-                if (sl < hn) {
-#pragma unroll
-                    for (int j = 0; j < VW; ++j) Xs[sl * CP + sg * VW + j] = v[u][j];
-                }
-            }
-        } else if (vec) {
-            // ragged last slice of aligned rows: p is a multiple of VW, so a
-            // segment lies wholly inside or wholly past p.  Segments past p
-            // load their row's first segment instead (in bounds, no branch)
-            // and store zeros.
-            const bool in = c < p;
-            const int cc = in ? c : 0;
-            T v[SPT][VW];
-#pragma unroll
-            for (int u = 0; u < SPT; ++u) load_vec<T, VW>(X + (int64_t)hrow[u] * p + cc, v[u]);
-#pragma unroll
-            for (int u = 0; u < SPT; ++u) {
-                const int sl = ss + SST * u;
-                if (sl < hn) {
-#pragma unroll
-                    for (int j = 0; j < VW; ++j) Xs[sl * CP + sg * VW + j] = in ? v[u][j] : T(0);
-                }
-            }
-        } else {
-            // unaligned rows: element loads, zeros past p
-#pragma unroll
-            for (int u = 0; u < SPT; ++u) {
-                const int sl = ss + SST * u;
-                const T *src = X + (int64_t)hrow[u] * p + c;
-                if (sl < hn) {
-#pragma unroll
-                    for (int j = 0; j < VW; ++j) Xs[sl * CP + sg * VW + j] = c + j < p ? src[j] : T(0);
-                }
-            }
-        }
-        __syncthreads();
-        T lm[LPC];
-        bool on[LPC];
-        double dot[LPC];
-#pragma unroll
-        for (int j = 0; j < LPC; ++j) {
-            const int c = c0 + lane + 64 * j;
-            dot[j] = 0.0;
-            lm[j] = (MODE == 1 && c < p) ? lam[c] : T(0);
-            on[j] = (MODE == 1 && c < p) ? active[c] != 0 : false;
-        }
-#pragma unroll
-        for (int i = 0; i < HALO_RPW; ++i) {
-            const int64_t row = r0 + wave + HALO_WAVES * i;
-            if (row >= r1) break;
-            T dv[LPC];   // D's own row, staged with the halo
-            if (MODE == 1) {
-#pragma unroll
-                for (int j = 0; j < LPC; ++j) dv[j] = Xs[(rb + (int)(row - r0)) * CP + lane + 64 * j];
-            }
-            T a1[LPC], a2[LPC];
-#pragma unroll
-            for (int j = 0; j < LPC; ++j) { a1[j] = T(0); a2[j] = T(0); }
-            const int m = len[i];
-            // the row's entries into this wave's broadcast area (LDS keeps a
-            // wave's accesses in order; the wave barriers keep the compiler's)
-            __builtin_amdgcn_wave_barrier();
-            ent_off[wave][lane] = off[i];
-            ent_w[wave][lane] = P2{wa[i], wb[i]};
-            __builtin_amdgcn_wave_barrier();
-            constexpr int UN = 4;   // entries in flight per step
-            int k = 0;
-            for (; k + UN <= m; k += UN) {
-                T x[UN][LPC];
-                P2 ww[UN];
-#pragma unroll
-                for (int u = 0; u < UN; ++u) {
-                    const int o = ent_off[wave][k + u];
-                    ww[u] = ent_w[wave][k + u];
-#pragma unroll
-                    for (int j = 0; j < LPC; ++j) x[u][j] = Xs[o + lane + 64 * j];
-                }
-#pragma unroll
-                for (int u = 0; u < UN; ++u)
-#pragma unroll
-                    for (int j = 0; j < LPC; ++j) {
-                        a1[j] = fma(ww[u].x, x[u][j], a1[j]);
-                        a2[j] = fma(ww[u].y, x[u][j], a2[j]);
-                    }
-            }
-            for (; k < m; ++k) {
-                const int o = ent_off[wave][k];
-                const P2 ww = ent_w[wave][k];
-#pragma unroll
-                for (int j = 0; j < LPC; ++j) {
-                    const T x = Xs[o + lane + 64 * j];
-                    a1[j] = fma(ww.x, x, a1[j]);
-                    a2[j] = fma(ww.y, x, a2[j]);
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < LPC; ++j) {
-                const int c = c0 + lane + 64 * j;
-                if (c >= p) continue;
-                if (MODE == 0) {
-                    if (Y2) {
-                        Y1[row * p + c] = a1[j];
-                        Y2[row * p + c] = a2[j];
-                    } else {
-                        Y1[row * p + c] = sel ? a2[j] : a1[j];
-                    }
-                } else {
-                    const T q = on[j] ? fma(-lm[j], a2[j], a1[j]) : T(0);
-                    dot[j] += (double)dv[j] * (double)q;
-                    Y1[row * p + c] = q;
-                }
-            }
-        }
-        __syncthreads();   // the slice is consumed
-        if (MODE == 1) {
-#pragma unroll
-            for (int j = 0; j < LPC; ++j) red[wave * CP + lane + 64 * j] = dot[j];
-            __syncthreads();
-            for (int cl = threadIdx.x; cl < CP; cl += blockDim.x) {
-                const int c = c0 + cl;
-                if (c >= p) continue;
-                double sum = 0.0;
-#pragma unroll
-                for (int k2 = 0; k2 < HALO_WAVES; ++k2) sum += red[k2 * CP + cl];
-                part[b * p + c] = sum;
-            }
-            __syncthreads();
-        }
-    }
+    for (int i = 0; i < 16 / (int)sizeof(T); ++i) v[i] = in[i];
+    __builtin_nontemporal_store(v, (vec *)p);
 }
 
-// The same products for blocks whose rows of X are 16-byte aligned, with the
-// halo staged by the direct global-to-LDS loads of gfx950
-// (global_load_lds_dwordx4): lane t of a wave instruction writes its 16 bytes
-// at the wave's LDS base + 16 t, so a wave fills two consecutive 512-byte
-// halo slots (lanes 0-31, 32-63) without passing the data through registers.
-// The next slice's loads are issued as soon as every wave has consumed the
-// current one, before this slice's results are stored, so the stores stay in
-// flight while a wave waits only for its own loads (vector memory operations
-// complete in issue order).  The shifted product's per-wave dot partials have
-// an LDS area of their own.  Per slice: wait for the own loads, barrier,
-// compute, barrier, issue the next slice, store, sum the partials.
-// Columns at or past p in a ragged last slice stage in-bounds data of the
-// row's first segment; no output reads them (each lane's columns are
-// independent).
-template <typename T, int MODE>
-__global__ __launch_bounds__(64 * HALO_WAVES) __attribute__((amdgpu_waves_per_eu(OFKS_HALO_WPE))) void
-k_spmm_halo_dma(int64_t nb, int p, const int64_t *__restrict__ row0, const int64_t *__restrict__ hoff,
-                const int32_t *__restrict__ halo, const int32_t *__restrict__ rbase, const int64_t *__restrict__ brp,
-                const uint16_t *__restrict__ lcol, const typename pair_t<T>::type *__restrict__ w,
-                const T *__restrict__ X, T *__restrict__ Y1, T *__restrict__ Y2, int sel, const T *__restrict__ lam,
-                const uint8_t *__restrict__ active, double *__restrict__ part) {
+// lane K of each 16 lanes, to all of them
+template <int K> __device__ __forceinline__ int row_bcast(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, 0x150 + K, 0xf, 0xf, true);
+}
+template <int K> __device__ __forceinline__ float row_bcast(float v) {
+    return __builtin_amdgcn_update_dpp(0.0f, v, 0x150 + K, 0xf, 0xf, true);
+}
+template <int K> __device__ __forceinline__ double row_bcast(double v) {
+    return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + K, 0xf, 0xf, true);
+}
+
+// sum over the wave's four rows of sixteen lanes, to all of them: (r0 + r1)
+// + (r2 + r3) on the vector units (a lane exchange through LDS costs its cycles)
+__device__ __forceinline__ double rows_sum(double v) {
+    // swap(x, x): the odd rows of the first and the even rows of the second
+    // change places, so the two hold each row pair's even and odd row twice
+    const auto a = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double(b[0], a[0]) + __hiloint2double(b[1], a[1]);
+    const auto c = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto d = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double(d[0], c[0]) + __hiloint2double(d[1], c[1]);
+}
+
+// entries K .. K + 3 of the sixteen: all LDS reads, then the FMAs in entry order
+template <int K, typename T>
+__device__ __forceinline__ void halo_four(const char *__restrict__ xs, int off, T wx, T wy, T (&a1)[16 / sizeof(T)],
+                                          T (&a2)[16 / sizeof(T)]) {
+    constexpr int VW = 16 / (int)sizeof(T);
+    T x[4][VW];
+    const int o[4] = {row_bcast<K>(off), row_bcast<K + 1>(off), row_bcast<K + 2>(off), row_bcast<K + 3>(off)};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) load_vec<T, VW>((const T *)(xs + o[u]), x[u]);
+    const T w1[4] = {row_bcast<K>(wx), row_bcast<K + 1>(wx), row_bcast<K + 2>(wx), row_bcast<K + 3>(wx)};
+    const T w2[4] = {row_bcast<K>(wy), row_bcast<K + 1>(wy), row_bcast<K + 2>(wy), row_bcast<K + 3>(wy)};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int v = 0; v < VW; ++v) {
+            a1[v] = fma(w1[u], x[u][v], a1[v]);
+            a2[v] = fma(w2[u], x[u][v], a2[v]);
+        }
+}
+// a round of sixteen entries, of which the first cnt are some row's (cnt the same in the whole wave)
+template <typename T>
+__device__ __forceinline__ void halo_round(const char *__restrict__ xs, int cnt, int off, T wx, T wy,
+                                           T (&a1)[16 / sizeof(T)], T (&a2)[16 / sizeof(T)]) {
+    halo_four<0, T>(xs, off, wx, wy, a1, a2);
+    if (cnt > 4) halo_four<4, T>(xs, off, wx, wy, a1, a2);
+    if (cnt > 8) halo_four<8, T>(xs, off, wx, wy, a1, a2);
+    if (cnt > 12) halo_four<12, T>(xs, off, wx, wy, a1, a2);
+}
+
+template <typename T, int MODE, int SEGB, int ROUNDS>
+__global__ __launch_bounds__(64 * HALO_WAVES) __attribute__((amdgpu_waves_per_eu(OFKS_HALO_WPE, OFKS_HALO_WPE))) void
+k_spmm_halo(int64_t nb, int p, int cw, const int64_t *__restrict__ row0, const int32_t *__restrict__ info,
+            const int32_t *__restrict__ halo, const int64_t *__restrict__ brp, const uint16_t *__restrict__ lcol,
+            const typename pair_t<T>::type *__restrict__ w, const T *__restrict__ X, T *__restrict__ Y1,
+            T *__restrict__ Y2, int sel, const T *__restrict__ lam, const uint8_t *__restrict__ active,
+            double *__restrict__ part) {
     using P2 = typename pair_t<T>::type;
-    constexpr int CP = 512 / sizeof(T);   // columns per slice
-    constexpr int VW = 16 / sizeof(T);    // one 16-byte segment
-    constexpr int LPC = CP / 64;          // columns per lane in a slice
-    constexpr int SEG = CP / VW;          // 32 segments per slot
-    constexpr int SST = 64 * HALO_WAVES / SEG;
-    constexpr int SPT = (HALO_MAX + SST - 1) / SST;
-    static_assert(SEG == 32, "a wave instruction fills two slots");
-    static_assert(SST == HALO_SST && SPT * SST == HALO_STRIDE, "padded halo stride");
-    // an instruction is issued only when its first (even) slot is below the
-    // halo size <= HALO_MAX, so with HALO_MAX even it never writes past it
-    static_assert(HALO_MAX % 2 == 0, "even halo capacity");
-    __shared__ T Xs[HALO_MAX * CP];
-    __shared__ int ent_off[HALO_WAVES][64];
-    __shared__ P2 ent_w[HALO_WAVES][64];
+    constexpr int CP = 256 / sizeof(T);   // columns per slice: 32 (f64) or 64 (f32)
+    constexpr int VW = 16 / sizeof(T);    // columns per lane
+    constexpr int NSLOT = HALO_STRIDE / HALO_SST;   // slots a thread stages, in 16-byte pieces
+    static_assert(HALO_STRIDE / HALO_WAVES <= 64, "a wave's slots fit its lanes");
+    __shared__ __align__(16) char Xs[(HALO_MAX + 1) * 256];
     __shared__ double red[MODE == 1 ? HALO_WAVES * CP : 1];
-    const int64_t b = xcd_block(blockIdx.x, gridDim.x);
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (b >= nb) {
+    const int64_t b = xcd_block(blockIdx.x, gridDim.x);
+    const int cb = blockIdx.y * cw, ce = min(p, cb + cw);   // this workgroup's columns
+    if (b >= nb) {   // padding block of the XCD mapping: a zero partial row
         if (MODE == 1)
-            for (int c = threadIdx.x; c < p; c += blockDim.x) part[b * p + c] = 0.0;
+            for (int c = cb + threadIdx.x; c < ce; c += blockDim.x) part[b * p + c] = 0.0;
         return;
     }
-    const int sg = threadIdx.x % SEG, ss = threadIdx.x / SEG;   // ss = 2 wave + lane / 32
-    int hrow[SPT];
+    // this thread's halo rows (SEGB 4: lane u holds the wave's u-th slot's),
+    // then the rows' entry ranges, all in flight together
+    int hrow[NSLOT];
+    const int32_t *hp = halo + b * HALO_STRIDE;
+    if (SEGB == 16) {
 #pragma unroll
-    for (int u = 0; u < SPT; ++u) hrow[u] = halo[b * HALO_STRIDE + ss + SST * u];
+        for (int u = 0; u < NSLOT; ++u) hrow[u] = hp[HALO_SST * u + 4 * wave + g];
+    } else {
+        hrow[0] = hp[min(HALO_WAVES * lane + wave, HALO_STRIDE - 1)];
+    }
     __builtin_amdgcn_sched_barrier(0);
-    const int64_t r0 = row0[b], r1 = row0[b + 1];
-    const int hn = (int)(hoff[b + 1] - hoff[b]);
-    const int rb = MODE == 1 ? rbase[b] : 0;
-    // the wave's rows' entries, loaded with the halo rows; both are pinned in
-    // registers before the first halo load is issued (empty asm operands: no
-    // instruction), so the compiler neither sinks these loads into the slice
-    // loop nor waits between the halo loads (a value loaded before an LDS
-    // load that is still in flight is otherwise waited for with vmcnt(0))
-    int len[HALO_RPW];
-    int lc[HALO_RPW];
-    P2 we[HALO_RPW];
-    const int64_t *bp = brp + b * HALO_BRP;
+    // set i of this lane's wave: row 16 wave + 4 i + g of the block
+    const int64_t *bp = brp + b * HALO_BRP + 4 * HALO_SETS * wave + g;
+    int64_t e0[HALO_SETS];
+    int len[HALO_SETS];
 #pragma unroll
-    for (int i = 0; i < HALO_RPW; ++i) {
-        const int k = wave + HALO_WAVES * i;
-        const int64_t e0 = bp[k];
-        len[i] = (int)(bp[k + 1] - e0);
-        const int64_t e = lane < len[i] ? e0 + lane : 0;
-        we[i] = w[e];
-        lc[i] = (int)lcol[e];
+    for (int i = 0; i < HALO_SETS; ++i) {
+        e0[i] = bp[4 * i];
+        len[i] = (int)(bp[4 * i + 1] - e0[i]);
     }
-    // staging of the slice at columns c0: wave instruction u fills slots
-    // SST u + 2 wave and + 1; instructions wholly past the halo are skipped.
-    // All addresses are formed before the first load is issued.
-    int64_t hoffs[SPT];
-#pragma unroll
-    for (int u = 0; u < SPT; ++u) {
-        hoffs[u] = (int64_t)hrow[u] * p;
-        asm volatile("" : "+v"(hoffs[u]));
+    const int inf = info[b];
+    const int64_t r0 = row0[b];
+    const int hn = inf & 255, nrows = (inf >> 8) & 255, rb = (inf >> 16) & 255;
+    if (threadIdx.x < 16) {
+        const T z[VW] = {};
+        store_vec<T, VW>((T *)(Xs + HALO_MAX * 256 + 16 * threadIdx.x), z);
     }
-#pragma unroll
-    for (int i = 0; i < HALO_RPW; ++i) asm volatile("" : "+v"(lc[i]), "+v"(we[i].x), "+v"(we[i].y));
-    auto stage = [&](int c0) {
-        const int c = c0 + sg * VW;
-        const int cc = c < p ? c : 0;
+    auto stage = [&](int c0) __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
+        if (SEGB == 16) {
 #pragma unroll
-        for (int u = 0; u < SPT; ++u) {
-            const int s0 = SST * u + 2 * wave;
-            if (s0 < hn)
-                __builtin_amdgcn_global_load_lds((const void *)(X + hoffs[u] + cc),
-                                                 (__attribute__((address_space(3))) void *)(Xs + s0 * CP), 16, 0, 0);
+            for (int u = 0; u < NSLOT; ++u) asm volatile("" : "+v"(hrow[u]));   // no addresses kept from slice to slice
+            const int c = c0 + VW * li;
+            const T *base = X + (c < p ? c : 0);
+#pragma unroll
+            for (int u = 0; u < NSLOT; ++u) {
+                const int s0 = HALO_SST * u + 4 * wave;
+                if (s0 < hn)
+                    __builtin_amdgcn_global_load_lds((const void *)(base + (int64_t)hrow[u] * p),
+                                                     (__attribute__((address_space(3))) void *)(Xs + s0 * 256), 16, 0, 0);
+            }
+        } else {
+            constexpr int DW = sizeof(T) / 4;   // dwords per column
+            const int c = c0 + lane / DW;
+            const uint32_t *base = (const uint32_t *)(X + (c < p ? c : 0)) + lane % DW;
+            for (int s0 = wave, u = 0; s0 < hn; s0 += HALO_WAVES, ++u)
+                __builtin_amdgcn_global_load_lds(
+                    (const void *)(base + (int64_t)__builtin_amdgcn_readlane(hrow[0], u) * p * DW),
+                    (__attribute__((address_space(3))) void *)(Xs + s0 * 256), 4, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    stage(0);
-    for (int c0 = 0; c0 < p; c0 += CP) {
-        T lm[LPC];
-        bool on[LPC];
+    stage(cb);
+    // the first ROUNDS rounds of sixteen entries of each row, in registers:
+    // LDS offset and weights of this lane's entry (past the row's end: entry
+    // 0, which exists, for the load, the slot of zeros and weights of zero)
+    auto entry = [&](int64_t e0, int len, int base, int &off, T &wx, T &wy) __attribute__((always_inline)) {
+        const bool in = base + li < len;
+        const int64_t e = in ? e0 + base + li : 0;
+        const P2 ww = w[e];
+        const int lc = lcol[e];
+        off = (in ? lc : HALO_MAX) * 256;
+        wx = in ? ww.x : T(0);
+        wy = in ? ww.y : T(0);
+    };
+    int off[ROUNDS][HALO_SETS], m[HALO_SETS];
+    T wx[ROUNDS][HALO_SETS], wy[ROUNDS][HALO_SETS];
 #pragma unroll
-        for (int j = 0; j < LPC; ++j) {
-            const int c = c0 + lane + 64 * j;
-            lm[j] = (MODE == 1 && c < p) ? lam[c] : T(0);
-            on[j] = (MODE == 1 && c < p) ? active[c] != 0 : false;
+    for (int i = 0; i < HALO_SETS; ++i) {
+        m[i] = max(max(__builtin_amdgcn_readlane(len[i], 0), __builtin_amdgcn_readlane(len[i], 16)),
+                   max(__builtin_amdgcn_readlane(len[i], 32), __builtin_amdgcn_readlane(len[i], 48)));
+        entry(e0[i], len[i], 0, off[0][i], wx[0][i], wy[0][i]);
+        if (ROUNDS == 2) entry(e0[i], len[i], 16, off[ROUNDS - 1][i], wx[ROUNDS - 1][i], wy[ROUNDS - 1][i]);
+    }
+    for (int c0 = cb; c0 < ce; c0 += CP) {
+        const int c = c0 + VW * li;   // this lane's columns
+        T lm[VW];
+        bool on[VW];
+        double dot[VW];
+#pragma unroll
+        for (int v = 0; v < VW; ++v) {
+            lm[v] = (MODE == 1 && c + v < p) ? lam[c + v] : T(0);
+            on[v] = (MODE == 1 && c + v < p) ? active[c + v] != 0 : false;
+            dot[v] = 0.0;
         }
-        __builtin_amdgcn_s_waitcnt(0);   // this thread's loads (and everything before them)
+        __builtin_amdgcn_s_waitcnt(0);   // this thread's loads
         __builtin_amdgcn_s_barrier();    // every wave's: the slice is in LDS
         __builtin_amdgcn_sched_barrier(0);
-        T q1[HALO_RPW][LPC], q2[HALO_RPW][LPC];
-        double dot[LPC];
+        const char *xs = Xs + 16 * li;
 #pragma unroll
-        for (int j = 0; j < LPC; ++j) dot[j] = 0.0;
+        for (int i = 0; i < HALO_SETS; ++i) {
+            const int k = 4 * HALO_SETS * wave + 4 * i + g;
+            T a1[VW], a2[VW];
 #pragma unroll
-        for (int i = 0; i < HALO_RPW; ++i) {
-            const int64_t row = r0 + wave + HALO_WAVES * i;
-#pragma unroll
-            for (int j = 0; j < LPC; ++j) { q1[i][j] = T(0); q2[i][j] = T(0); }
-            if (row >= r1) continue;
-            T dv[LPC];
+            for (int v = 0; v < VW; ++v) a1[v] = a2[v] = T(0);
+            halo_round<T>(xs, m[i], off[0][i], wx[0][i], wy[0][i], a1, a2);
+            if (ROUNDS == 2 && m[i] > 16)
+                halo_round<T>(xs, m[i] - 16, off[ROUNDS - 1][i], wx[ROUNDS - 1][i], wy[ROUNDS - 1][i], a1, a2);
+            for (int base = 16 * ROUNDS; base < m[i]; base += 16) {
+                int oo;
+                T x1, x2;
+                const int64_t ee = bp[4 * i];
+                entry(ee, (int)(bp[4 * i + 1] - ee), base, oo, x1, x2);
+                halo_round<T>(xs, m[i] - base, oo, x1, x2, a1, a2);
+            }
             if (MODE == 1) {
+                T dv[VW];   // D's own row, staged with the halo
+                load_vec<T, VW>((const T *)(xs + (k < nrows ? rb + k : HALO_MAX) * 256), dv);
 #pragma unroll
-                for (int j = 0; j < LPC; ++j) dv[j] = Xs[(rb + (int)(row - r0)) * CP + lane + 64 * j];
-            }
-            T a1[LPC], a2[LPC];
-#pragma unroll
-            for (int j = 0; j < LPC; ++j) { a1[j] = T(0); a2[j] = T(0); }
-            const int m = len[i];
-            __builtin_amdgcn_wave_barrier();
-            ent_off[wave][lane] = lc[i];
-            ent_w[wave][lane] = we[i];
-            __builtin_amdgcn_wave_barrier();
-            constexpr int UN = 4;
-            int k = 0;
-            for (; k + UN <= m; k += UN) {
-                T x[UN][LPC];
-                P2 ww[UN];
-#pragma unroll
-                for (int u = 0; u < UN; ++u) {
-                    const int o = ent_off[wave][k + u] * CP;
-                    ww[u] = ent_w[wave][k + u];
-#pragma unroll
-                    for (int j = 0; j < LPC; ++j) x[u][j] = Xs[o + lane + 64 * j];
+                for (int v = 0; v < VW; ++v) {
+                    const T q = on[v] ? fma(-lm[v], a2[v], a1[v]) : T(0);
+                    dot[v] = on[v] ? fma((double)dv[v], (double)q, dot[v]) : dot[v];
+                    a1[v] = q;
                 }
-#pragma unroll
-                for (int u = 0; u < UN; ++u)
-#pragma unroll
-                    for (int j = 0; j < LPC; ++j) {
-                        a1[j] = fma(ww[u].x, x[u][j], a1[j]);
-                        a2[j] = fma(ww[u].y, x[u][j], a2[j]);
+            }
+            if (k < nrows && c < p) {
+                T *y = Y1 + (r0 + k) * p + c;
+                T *y2 = Y2 + (r0 + k) * p + c;
+                if (SEGB == 16) {   // p is a multiple of VW: a piece lies wholly inside or past p
+                    if (MODE == 0 && !Y2 && sel) {
+                        stream_store16(y, a2);
+                    } else {
+                        stream_store16(y, a1);
+                        if (MODE == 0 && Y2) stream_store16(y2, a2);
                     }
-            }
-            for (; k < m; ++k) {
-                const int o = ent_off[wave][k] * CP;
-                const P2 ww = ent_w[wave][k];
-#pragma unroll
-                for (int j = 0; j < LPC; ++j) {
-                    const T x = Xs[o + lane + 64 * j];
-                    a1[j] = fma(ww.x, x, a1[j]);
-                    a2[j] = fma(ww.y, x, a2[j]);
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < LPC; ++j) {
-                if (MODE == 0) {
-                    q1[i][j] = a1[j];
-                    q2[i][j] = a2[j];
                 } else {
-                    const int c = c0 + lane + 64 * j;
-                    const T q = on[j] ? fma(-lm[j], a2[j], a1[j]) : T(0);
-                    if (c < p) dot[j] += (double)dv[j] * (double)q;
-                    q1[i][j] = q;
+#pragma unroll
+                    for (int v = 0; v < VW; ++v) {
+                        if (c + v >= p) continue;
+                        if (MODE == 0 && !Y2 && sel) {
+                            y[v] = a2[v];
+                        } else {
+                            y[v] = a1[v];
+                            if (MODE == 0 && Y2) y2[v] = a2[v];
+                        }
+                    }
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);   // one set's LDS reads in flight at a time (registers)
         }
         if (MODE == 1) {
 #pragma unroll
-            for (int j = 0; j < LPC; ++j) red[wave * CP + lane + 64 * j] = dot[j];
+            for (int v = 0; v < VW; ++v) {   // over the wave's four rows in flight, then one LDS slot per wave
+                dot[v] = rows_sum(dot[v]);
+                if (g == 0) red[wave * CP + VW * li + v] = dot[v];
+            }
         }
         __builtin_amdgcn_s_waitcnt(0xc07f);   // LDS done (lgkmcnt 0); vector memory untouched
         __builtin_amdgcn_s_barrier();         // the slice is consumed and the partials written
         __builtin_amdgcn_sched_barrier(0);
-        if (c0 + CP < p) stage(c0 + CP);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < HALO_RPW; ++i) {
-            const int64_t row = r0 + wave + HALO_WAVES * i;
-            if (row >= r1) continue;
-#pragma unroll
-            for (int j = 0; j < LPC; ++j) {
-                const int c = c0 + lane + 64 * j;
-                if (c >= p) continue;
-                if (MODE == 0) {
-                    if (Y2) {
-                        Y1[row * p + c] = q1[i][j];
-                        Y2[row * p + c] = q2[i][j];
-                    } else {
-                        Y1[row * p + c] = sel ? q2[i][j] : q1[i][j];
-                    }
-                } else {
-                    Y1[row * p + c] = q1[i][j];
-                }
-            }
-        }
+        if (c0 + CP < ce) stage(c0 + CP);
         if (MODE == 1) {
-            for (int cl = threadIdx.x; cl < CP; cl += blockDim.x) {
-                const int c = c0 + cl;
-                if (c >= p) continue;
-                double sum = 0.0;
-#pragma unroll
-                for (int k2 = 0; k2 < HALO_WAVES; ++k2) sum += red[k2 * CP + cl];
-                part[b * p + c] = sum;
-            }
+            const int cl = threadIdx.x;
+            if (cl < CP && c0 + cl < p)
+                part[b * p + c0 + cl] = ((red[cl] + red[CP + cl]) + red[2 * CP + cl]) + red[3 * CP + cl];
         }
     }
 }
@@ -924,6 +759,7 @@ __global__ __launch_bounds__(256) void k_part_rows(int64_t nb, int p, int G, con
     const int64_t b0 = g * G, b1 = min(nb, b0 + G);
     for (int c = threadIdx.x; c < p; c += blockDim.x) {
         double sum = 0.0;
+#pragma unroll 8
         for (int64_t b = b0; b < b1; ++b) sum += in[b * p + c];
         out[g * p + c] = sum;
     }
@@ -1064,8 +900,8 @@ hipError_t launch_spmv_dot(hipStream_t s, int grid, int64_t n, const int64_t *rp
 
 // Halo-SpMM launch: nb blocks of the plan (grid padded to whole XCD slabs).
 // MODE 1 leaves the per-block dots after room for ceil(nbp / HALO_G) group
-// sums in part; launch_halo_part_rows then writes the group sums to its start
-// and the caller's column sum takes *rows_out rows.  part_capacity in doubles.
+// sums in part, then writes the group sums to its start; the caller's column
+// sum takes *rows_out rows.  part_capacity in doubles.
 constexpr int HALO_G = 64;
 static int64_t halo_grid(int64_t nb) { return (nb + 7) / 8 * 8; }
 
@@ -1075,54 +911,50 @@ size_t spmm_halo_part_doubles(int64_t nb, int p) {
 }
 
 template <typename T>
-hipError_t launch_spmm_halo(hipStream_t s, int mode, int64_t nb, int p, const int64_t *row0, const int64_t *hoff,
-                            const int32_t *halo, const int32_t *rbase, const int64_t *brp, const uint16_t *lcol,
-                            const void *wv,
-                            const T *X, T *Y1, T *Y2, int sel, const T *lam, const uint8_t *active, double *part,
+hipError_t launch_spmm_halo(hipStream_t s, int mode, int64_t nb, int maxlen, int p, const int64_t *row0, const int32_t *info,
+                            const int32_t *halo, const int64_t *brp, const uint16_t *lcol, const void *wv, const T *X,
+                            T *Y1, T *Y2, int sel, const T *lam, const uint8_t *active, double *part,
                             size_t part_capacity, int *rows_out) {
     using P2 = typename pair_t<T>::type;
     const P2 *w = (const P2 *)wv;
-    const int64_t nbp = halo_grid(nb);
+    const int64_t nbp = halo_grid(nb), ng = (nbp + HALO_G - 1) / HALO_G;
     if (nbp <= 0 || nbp > 0x7fffffff) return hipErrorInvalidValue;
-    // rows of X 16-byte aligned: the DMA-staged kernel
-    const bool dma = OFKS_HALO_DMA && p % (16 / (int)sizeof(T)) == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
+    // rows of X, Y1 and Y2 16-byte aligned: 16-byte pieces
+    const bool vec = p % (16 / (int)sizeof(T)) == 0 &&
+                     (reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y1) | reinterpret_cast<uintptr_t>(Y2)) % 16 == 0;
+    if (mode == 1 && (size_t)(ng + nbp) * p > part_capacity) return hipErrorInvalidValue;
+    double *bpart = part + ng * p;
+    // slices per workgroup: all of them once the plan's blocks fill the device
+    // (three workgroups on each of 256 CUs), fewer below that
+    const int cp = 256 / (int)sizeof(T), ns = (p + cp - 1) / cp;
+    const int gy = (int)std::min<int64_t>(ns, (767 + nbp) / nbp), cw = (ns + gy - 1) / gy * cp;
+    const dim3 grid((unsigned)nbp, (unsigned)((p + cw - 1) / cw));
+#define OFKS_HALO(M_, S_)                                                                                          \
+    if (maxlen > 16)                                                                                               \
+        hipLaunchKernelGGL((k_spmm_halo<T, M_, S_, 2>), grid, dim3(64 * HALO_WAVES), 0, s, nb, p, cw, row0, \
+                           info, halo, brp, lcol, w, X, Y1, Y2, sel, lam, active, bpart);                          \
+    else                                                                                                           \
+        hipLaunchKernelGGL((k_spmm_halo<T, M_, S_, 1>), grid, dim3(64 * HALO_WAVES), 0, s, nb, p, cw, row0, \
+                           info, halo, brp, lcol, w, X, Y1, Y2, sel, lam, active, bpart)
     if (mode == 0) {
-        if (dma)
-            hipLaunchKernelGGL((k_spmm_halo_dma<T, 0>), dim3((unsigned)nbp), dim3(64 * HALO_WAVES), 0, s, nb, p, row0,
-                               hoff, halo, rbase, brp, lcol, w, X, Y1, Y2, sel, lam, active, part);
-        else
-            hipLaunchKernelGGL((k_spmm_halo<T, 0>), dim3((unsigned)nbp), dim3(64 * HALO_WAVES), 0, s, nb, p, row0,
-                               hoff, halo, rbase, brp, lcol, w, X, Y1, Y2, sel, lam, active, part);
+        if (vec) { OFKS_HALO(0, 16); }
+        else { OFKS_HALO(0, 4); }
         return hipGetLastError();
     }
-    const int64_t ng = (nbp + HALO_G - 1) / HALO_G;
-    if ((size_t)(ng + nbp) * p > part_capacity) return hipErrorInvalidValue;
-    double *bpart = part + ng * p;
-    if (dma)
-        hipLaunchKernelGGL((k_spmm_halo_dma<T, 1>), dim3((unsigned)nbp), dim3(64 * HALO_WAVES), 0, s, nb, p, row0, hoff,
-                           halo, rbase, brp, lcol, w, X, Y1, (T *)nullptr, 0, lam, active, bpart);
-    else
-        hipLaunchKernelGGL((k_spmm_halo<T, 1>), dim3((unsigned)nbp), dim3(64 * HALO_WAVES), 0, s, nb, p, row0, hoff,
-                           halo, rbase, brp, lcol, w, X, Y1, (T *)nullptr, 0, lam, active, bpart);
+    if (vec) { OFKS_HALO(1, 16); }
+    else { OFKS_HALO(1, 4); }
+#undef OFKS_HALO
+    hipLaunchKernelGGL(k_part_rows, dim3((unsigned)ng), dim3(256), 0, s, nbp, p, HALO_G, bpart, part);
     *rows_out = (int)ng;
     return hipGetLastError();
 }
 
-// The group sums of a MODE 1 halo launch's per-block dots (fixed order).
-hipError_t launch_halo_part_rows(hipStream_t s, int64_t nb, int p, double *part) {
-    const int64_t nbp = halo_grid(nb), ng = (nbp + HALO_G - 1) / HALO_G;
-    hipLaunchKernelGGL(k_part_rows, dim3((unsigned)ng), dim3(256), 0, s, nbp, p, HALO_G, part + ng * p, part);
-    return hipGetLastError();
-}
-
-template hipError_t launch_spmm_halo<double>(hipStream_t, int, int64_t, int, const int64_t *, const int64_t *,
-                                             const int32_t *, const int32_t *, const int64_t *, const uint16_t *,
-                                             const void *,
+template hipError_t launch_spmm_halo<double>(hipStream_t, int, int64_t, int, int, const int64_t *, const int32_t *,
+                                             const int32_t *, const int64_t *, const uint16_t *, const void *,
                                              const double *, double *, double *, int, const double *,
                                              const uint8_t *, double *, size_t, int *);
-template hipError_t launch_spmm_halo<float>(hipStream_t, int, int64_t, int, const int64_t *, const int64_t *,
-                                            const int32_t *, const int32_t *, const int64_t *, const uint16_t *,
-                                            const void *,
+template hipError_t launch_spmm_halo<float>(hipStream_t, int, int64_t, int, int, const int64_t *, const int32_t *,
+                                            const int32_t *, const int64_t *, const uint16_t *, const void *,
                                             const float *, float *, float *, int, const float *, const uint8_t *,
                                             double *, size_t, int *);
 int halo_max_rows() { return HALO_MAX; }

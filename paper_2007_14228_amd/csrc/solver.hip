@@ -64,11 +64,10 @@ hipError_t launch_spmm_shift(hipStream_t, int, int64_t, int, const int64_t *, co
 hipError_t launch_spmv_dot(hipStream_t, int, int64_t, const int64_t *, const int32_t *, const double *,
                            const double *, double *, double *);
 template <typename T>
-hipError_t launch_spmm_halo(hipStream_t, int, int64_t, int, const int64_t *, const int64_t *, const int32_t *,
-                            const int32_t *, const int64_t *, const uint16_t *, const void *, const T *, T *, T *, int,
-                            const T *, const uint8_t *, double *, size_t, int *);
+hipError_t launch_spmm_halo(hipStream_t, int, int64_t, int, int, const int64_t *, const int32_t *, const int32_t *,
+                            const int64_t *, const uint16_t *, const void *, const T *, T *, T *, int, const T *,
+                            const uint8_t *, double *, size_t, int *);
 size_t spmm_halo_part_doubles(int64_t nb, int p);
-hipError_t launch_halo_part_rows(hipStream_t, int64_t, int, double *);
 int halo_max_rows();
 int halo_max_block_rows();
 int halo_max_row_entries();
@@ -257,10 +256,11 @@ struct ofks_ctx {
     float2 *hb32 = nullptr, *lb32 = nullptr;
     // LDS-halo SpMM plan: blocks of consecutive rows, their sorted distinct
     // columns (halo) and each entry's slot in its block's halo
+    int halo_maxlen = 0;                  // the longest row's entries
     int64_t halo_nb = 0;                  // 0: no plan (a row alone exceeds the halo capacity)
-    int64_t *halo_row0 = nullptr, *halo_off = nullptr;
+    int64_t *halo_row0 = nullptr;
+    int32_t *halo_info = nullptr;         // per block: halo rows | rows << 8 | halo slot of its first row << 16
     int32_t *halo_idx = nullptr;          // per block: its halo rows, padded to a fixed stride
-    int32_t *halo_rbase = nullptr;        // per block: halo slot of its first row
     int64_t *halo_brp = nullptr;          // per block: its rows' CSR row pointers, padded to a fixed stride
     uint16_t *halo_lcol = nullptr;
 
@@ -626,17 +626,20 @@ size_t partials_needed(ofks_ctx *c, int p) {
     return need;
 }
 
-// SpMM kernel choice (spmm_mode 0), as measured: the LDS-halo kernel for
-// FP64 blocks with p >= 64 (faster at p = 64, 96, 128, 160 and 512) and FP32
-// blocks with p >= 96 (faster at p = 96, 128, 160, 192 and 512; at p = 64 the
-// half-empty 128-column slice loses); the row-gather kernel otherwise.
+// SpMM kernel choice (spmm_mode 0), as measured on Kuhn grids of 1e3 to 1e6
+// rows and an irregular pattern: the LDS-halo kernel for FP64 blocks with p >= 4
+// (dual product at n = 3.4e5: p = 11 76 against 101 us, 32 79 against 135, 64
+// 147 against 257, 128 259 against 466; level at p = 8 and 16) and FP32 blocks
+// with p >= 33 (33: 84 against 252 us, 64: 71 against 122, 128: 113 against
+// 236).  Below, a row of X fills a small part of the staged 256-byte slots
+// (FP32 p = 16: 55 against 50 us) and the row-gather kernel serves.
 // spmm_mode 1 (gather) or 2 (halo) forces one.  Returns 1: halo, 0: gather,
 // -1: halo forced but no plan exists.
 int halo_choice(ofks_ctx *c, int p, size_t elem) {
     const int m = c->prm.spmm_mode;
     if (m == 1) return 0;
     if (m == 2) return c->halo_nb ? 1 : -1;
-    return c->halo_nb && (elem == 8 ? p >= 64 : p >= 96) ? 1 : 0;
+    return c->halo_nb && (elem == 8 ? p >= 4 : p >= 33) ? 1 : 0;
 }
 
 // Y1 = A1 X, Y2 = A2 X (Y2 = NULL: A1 X or A2 X by sel) for the pair matrix w.
@@ -645,30 +648,24 @@ int spmm_pair(ofks_ctx *c, int p, const void *w, const T *X, T *Y1, T *Y2, int s
     const int h = halo_choice(c, p, sizeof(T));
     if (h < 0) return fail(c, OFKS_ESTATE, "spmm_mode halo: no halo plan for this matrix");
     if (h)
-        HIPCHK(launch_spmm_halo<T>(c->stream, 0, c->halo_nb, p, c->halo_row0, c->halo_off, c->halo_idx, c->halo_rbase,
-                                   c->halo_brp, c->halo_lcol, w, X, Y1, Y2, sel, nullptr, nullptr, nullptr, 0,
-                                   nullptr));
+        HIPCHK(launch_spmm_halo<T>(c->stream, 0, c->halo_nb, c->halo_maxlen, p, c->halo_row0, c->halo_info, c->halo_idx, c->halo_brp,
+                                   c->halo_lcol, w, X, Y1, Y2, sel, nullptr, nullptr, nullptr, 0, nullptr));
     else
         HIPCHK(launch_spmm_pair<T>(c->stream, c->n, p, c->rp, c->col, w, X, Y1, Y2, sel));
     return OFKS_OK;
 }
 
 // Q = (L/2 - lam B) D on active columns and per-block <D, Q> partials in
-// c->part; *used = partial rows for the column sum.  The product kernel is
-// timed as "spmm_shift", the halo kernel's partial-row sums apart from it.
+// c->part; *used = partial rows for the column sum.
 template <typename T>
 int spmm_shift(ofks_ctx *c, int p, const void *lb, const T *lam, const uint8_t *act, const T *D, T *Q, int *used) {
     const int h = halo_choice(c, p, sizeof(T));
     if (h < 0) return fail(c, OFKS_ESTATE, "spmm_mode halo: no halo plan for this matrix");
     if (h) {
         CHK(ensure_part(c, spmm_halo_part_doubles(c->halo_nb, p)));
-        {
-            Scope sc(c, "spmm_shift");
-            HIPCHK(launch_spmm_halo<T>(c->stream, 1, c->halo_nb, p, c->halo_row0, c->halo_off, c->halo_idx,
-                                       c->halo_rbase, c->halo_brp, c->halo_lcol, lb, D, Q, nullptr, 0, lam, act,
-                                       c->part, c->part_cap, used));
-        }
-        HIPCHK(launch_halo_part_rows(c->stream, c->halo_nb, p, c->part));
+        Scope sc(c, "spmm_shift");
+        HIPCHK(launch_spmm_halo<T>(c->stream, 1, c->halo_nb, c->halo_maxlen, p, c->halo_row0, c->halo_info, c->halo_idx, c->halo_brp,
+                                   c->halo_lcol, lb, D, Q, nullptr, 0, lam, act, c->part, c->part_cap, used));
         return OFKS_OK;
     }
     CHK(ensure_part(c, (size_t)c->shift_grid * p));
@@ -1451,9 +1448,8 @@ int ensure_f32_matrices(ofks_ctx *c) {
 
 void free_halo(ofks_ctx *c) {
     dfree(c, c->halo_row0);
-    dfree(c, c->halo_off);
+    dfree(c, c->halo_info);
     dfree(c, c->halo_idx);
-    dfree(c, c->halo_rbase);
     dfree(c, c->halo_brp);
     dfree(c, c->halo_lcol);
     c->halo_nb = 0;
@@ -1483,8 +1479,14 @@ int build_halo_plan(ofks_ctx *c) {
     if (rc != HALO_OK || halo_plan_check(n, rp.data(), col.data(), HM, RM, EM, P, &where) != HALO_OK)
         return fail(c, OFKS_EINTERNAL, "halo plan: consistency check failed at %lld", (long long)where);
     const int64_t nb = P.nb();
+    int64_t longest = 0;
+    for (int64_t r = 0; r < n; ++r) longest = std::max(longest, rp[r + 1] - rp[r]);
+    c->halo_maxlen = (int)longest;   // at most EM
     CHK(dalloc(c, &c->halo_row0, nb + 1));
-    CHK(dalloc(c, &c->halo_off, nb + 1));
+    CHK(dalloc(c, &c->halo_info, nb));
+    std::vector<int32_t> info(nb);
+    for (int64_t k = 0; k < nb; ++k)   // each field is below 256 (the plan check)
+        info[k] = (int32_t)(P.hoff[k + 1] - P.hoff[k]) | (int32_t)(P.row0[k + 1] - P.row0[k]) << 8 | P.rbase[k] << 16;
     // the kernel reads each block's halo rows at a fixed stride, padded with its last row
     const int HS = halo_pad_stride();
     std::vector<int32_t> hpad((size_t)nb * HS);
@@ -1499,14 +1501,12 @@ int build_halo_plan(ofks_ctx *c) {
         for (int j = 0; j < BS; ++j) bpad[(size_t)k * BS + j] = rp[std::min(P.row0[k] + j, P.row0[k + 1])];
     CHK(dalloc(c, &c->halo_idx, hpad.size()));
     CHK(dalloc(c, &c->halo_brp, bpad.size()));
-    CHK(dalloc(c, &c->halo_rbase, nb));
     CHK(dalloc(c, &c->halo_lcol, nnz));
     HIPCHK(hipMemcpyAsync(c->halo_row0, P.row0.data(), (nb + 1) * sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(c->halo_off, P.hoff.data(), (nb + 1) * sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
+    HIPCHK(hipMemcpyAsync(c->halo_info, info.data(), nb * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(c->halo_idx, hpad.data(), hpad.size() * sizeof(int32_t), hipMemcpyHostToDevice,
                           c->stream));
     HIPCHK(hipMemcpyAsync(c->halo_lcol, P.lcol.data(), nnz * sizeof(uint16_t), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(c->halo_rbase, P.rbase.data(), nb * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(c->halo_brp, bpad.data(), bpad.size() * sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     c->halo_nb = nb;
