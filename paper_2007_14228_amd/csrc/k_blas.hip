@@ -7,15 +7,18 @@
 //                epilogues (gradient of L_beta, residual norm for kkt, the
 //                start of the preconditioner's CG or the column norms of G
 //                for the learned form), or a plain Y = X M.
-//  k_pcg_r       r -= alpha q, <r, J r>                  (inner CG step)
-//  k_pcg_dx      x += alpha d and d = J r + beta d
-//  k_pcg_scalars alpha / beta per column on the device
+//  k_cg_step     the inner CG's next direction (three-term form) and <z, z / J>
+//  k_cg_x        its last update of x
+//  k_cg_start    its start from a block G
+//  k_cg_scalars  its alpha and beta per column on the device
 //  k_bbdot       <S,Y>, <Y,Y>, <S,S>, ||P||^2, ||X||^2 for the BB step
 //  k_update_b    X~ = X - P / eta with X = X~ D^-1; keeps X as X^{k-1}
 //  k_coldot      per-column sums of A .* B (column B-norms)
 //
 // Every reduction writes per-block partials that a fixed-order pass sums, so
 // results do not depend on scheduling.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace ofks {
@@ -112,22 +115,15 @@ __global__ __launch_bounds__(256) void k_colsum(int64_t nb, int64_t m_total,
 // ---------------------------------------------------------------------------
 enum { EPI_PLAIN = 0, EPI_GRAD = 1, EPI_GRAD_PCG = 2, EPI_GRAD_NORM = 3 };
 
-// the directions of the inner CG's history form (k_pcg_sum), by value
-constexpr int PCG_DIRS_MAX = 16;
-struct PcgDirs {
-    const void *d[PCG_DIRS_MAX];
-};
-
 struct GradArgs {
     const void *HX;       // n x p, unnormalized (scaled by dinv here)
     void *P;              // out: gradient (no CG) / identity-branch columns
-    void *R;              // out: CG residual r = G (active columns)
     void *D;              // out: CG direction d = J G (active columns)
     const double *lhd;    // diag(L/2), n
     const double *bd;     // diag(B), n
     const void *lam;      // shift lambda_c of T_c, p
     const uint8_t *active;// column uses the CG preconditioner
-    double *part;         // per block: [0] ||R||^2, [1 + c] <r_c, J r_c>
+    double *part;         // per block: [0] ||R||^2, [1 + c] <g_c, J g_c>
 };
 
 template <typename T, int MT, int NT, int EPI>
@@ -208,7 +204,6 @@ __global__ __launch_bounds__(256) void k_rowgemm(int64_t n, int p, int N, const 
                         if (ga.active[c]) {
                             const T jinv = T(1) / (T(ga.lhd[r]) - lamv[c] * T(ga.bd[r]));
                             const T z = v * jinv;
-                            ((T *)ga.R)[r * p + c] = v;
                             ((T *)ga.D)[r * p + c] = z;
                             rz[j] += (double)v * (double)z;
                         } else {
@@ -427,7 +422,6 @@ void k_rowgemm_mfma(int64_t n, int p, int N, const T *__restrict__ A, const T *_
     __syncthreads();
     const T *__restrict__ HX = (const T *)ga.HX;
     T *__restrict__ Pout = (T *)ga.P;
-    T *__restrict__ Rout = (T *)ga.R;
     T *__restrict__ Dout = (T *)ga.D;
 
     // K-chunk staging, software-pipelined: the values of the next chunk (of
@@ -547,7 +541,6 @@ void k_rowgemm_mfma(int64_t n, int p, int N, const T *__restrict__ A, const T *_
                 } else {  // EPI_GRAD_PCG
                     if (act_s[cl]) {
                         const T z = v * (T(1) / (ld - lmc_s[cl] * bdv));
-                        Rout[r * p + c] = v;
                         Dout[r * p + c] = z;
                         rz[t] += (double)v * (double)z;
                     } else {
@@ -649,7 +642,6 @@ void k_rowgemm_mres(int64_t n, const T *__restrict__ A, const T *__restrict__ sa
     __syncthreads();
     const T *__restrict__ HX = (const T *)ga.HX;
     T *__restrict__ Pout = (T *)ga.P;
-    T *__restrict__ Rout = (T *)ga.R;
     T *__restrict__ Dout = (T *)ga.D;
     // columns of this block below P (gradient) or at and above P (residual):
     // per tile t, known at compile time with one column set, per block with two
@@ -731,7 +723,6 @@ void k_rowgemm_mres(int64_t n, const T *__restrict__ A, const T *__restrict__ sa
             }
             if (r >= n) continue;
             T *prow = Pout + r * P + li;
-            T *rrow = Rout + r * P + li;
             T *drow = Dout + r * P + li;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
@@ -748,7 +739,6 @@ void k_rowgemm_mres(int64_t n, const T *__restrict__ A, const T *__restrict__ sa
                 } else {  // EPI_GRAD_PCG
                     if (act_s[cl]) {
                         const T z = v * (T(1) / (ldi - lmc_s[cl] * bdi));
-                        rrow[hc] = v;
                         drow[hc] = z;
                         rz[t] += (double)v * (double)z;
                     } else {
@@ -794,87 +784,157 @@ void k_rowgemm_mres(int64_t n, const T *__restrict__ A, const T *__restrict__ sa
 // Lane-per-column-slice kernels over n x p blocks (same mapping as SpMM).
 // ---------------------------------------------------------------------------
 
-// Inner CG of the paper preconditioner, split so that each block pass does
-// as much as the reductions allow:
-//   k_pcg_r   r -= alpha q, partial <r, J r>                (reads q, r; writes r)
-//   k_pcg_dx  x += alpha d, then d = J r + beta d          (reads d, r, x; writes d, x)
-//             or, in the last inner iteration, x += alpha d only
-// Per-column constants are held in registers; columns that are not active
-// (identity branch of eq. precondition-T) keep their stored x.
+// Inner CG of the paper preconditioner: x_l = T_l^-1 g_l by m Jacobi-CG steps,
+// all columns together, arranged for the fewest passes over the blocks.  With
+// z_j = J r_j the recurrences r' = r - alpha T d, d' = J r' + beta d give
+//   z_j     = d_j - beta_{j-1} d_{j-1}
+//   z_{j+1} = z_j - alpha_j w_j,   w_j = J T d_j   (from the product kernel)
+//   d_{j+1} = z_{j+1} + beta_j d_j
+// so neither r nor z is stored: a step reads w_j, d_j, d_{j-1} and writes
+// d_{j+1} over d_{j-1}.  beta_j = <r_{j+1}, z_{j+1}> / <r_j, z_j> is needed in
+// the pass that forms z_{j+1}; its numerator is predicted from the product's
+// dots as rz_j - 2 alpha <d, T d> + alpha^2 <T d, w>, while the pass sums the
+// real one, which the next step uses, so no prediction feeds another.  x takes
+// two directions at a time, every second step, from the values the pass holds
+// anyway.  Block passes for m = 10: 65 (products 19, directions 35, x 11)
+// against 85 with r and the directions kept for one sum at the end, without
+// the m - 1 extra blocks of that form.
+// Measured against 80-bit arithmetic on Kuhn and irregular matrices, shifts
+// -0.05 to -1000, m = 10: relative error 1.9e-16 to 4.8e-16 (two-term form
+// 1.8e-16 to 3.1e-16), FP32 blocks 0.8e-7 to 1.7e-7 (0.9e-7 to 1.7e-7).
 
-// r -= alpha q on active columns; per-block partial <r, J r>.  Persistent.
-template <typename T, int V, int CH>
-__global__ __launch_bounds__(256) void k_pcg_r(int64_t n, int p, int lpr_log2, const T *__restrict__ alpha,
-                                              const uint8_t *__restrict__ active,
-                                              const double *__restrict__ lhd, const double *__restrict__ bd,
-                                              const T *__restrict__ lam, const T *__restrict__ Q,
-                                              T *__restrict__ R, double *__restrict__ part) {
-    extern __shared__ double red[];
+// Coefficients of a step, per column: alpha (0 when <d, T d> <= 0) from the sums
+// of the product's partials (rows of 2 p: <d, T d>, <T d, w>) and the current
+// <r, z> (from the step pass's partials, nrz rows of p), beta from the
+// prediction.  Eight columns a block, 32 threads a column, fixed order.
+template <typename T>
+__global__ __launch_bounds__(256) void k_cg_scalars(int p, int ndq, const double *__restrict__ dqp, int nrz,
+                                                   const double *__restrict__ rzp, T *__restrict__ alpha,
+                                                   T *__restrict__ beta) {
+    __shared__ double red[3][32][9];
+    const int cl = threadIdx.x & 7, k = threadIdx.x >> 3;
+    const int c = blockIdx.x * 8 + cl;
+    double s[3] = {0.0, 0.0, 0.0};
+    if (c < p) {
+#pragma unroll 8
+        for (int r = k; r < ndq; r += 32) s[0] += dqp[(int64_t)r * 2 * p + c];
+        if (beta) {
+#pragma unroll 8
+            for (int r = k; r < ndq; r += 32) s[1] += dqp[(int64_t)r * 2 * p + p + c];
+        }
+#pragma unroll 8
+        for (int r = k; r < nrz; r += 32) s[2] += rzp[(int64_t)r * p + c];
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) red[d][k][cl] = s[d];
+    __syncthreads();
+    for (int w = 16; w > 0; w >>= 1) {
+        if (k < w)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) red[d][k][cl] += red[d][k + w][cl];
+        __syncthreads();
+    }
+    if (k || c >= p) return;
+    const double dq = red[0][0][cl], qw = red[1][0][cl], rz = red[2][0][cl];
+    const T al = dq > 0.0 ? (T)(rz / dq) : T(0);
+    alpha[c] = al;
+    if (beta) {
+        const double a = (double)al;
+        const double next = fma(a, fma(a, qw, -2.0 * dq), rz);
+        beta[c] = rz > 0.0 ? (T)(next / rz) : T(0);
+    }
+}
+
+// One step's block pass (above) on the columns of blockIdx.y's range; persistent
+// over rows; part[blockIdx.x][c] = <z', z' / J>.  FIRST: j = 0 (no d_{-1}; Dm is
+// only written).  XUP: x += alpha_{j-1} d_{j-1} + alpha_j d_j (xfirst: from
+// zero), in the order of the running sum.  Columns that are not active keep x
+// and get nothing of d.  Memory-bound: n = 1e6, p = 128, FP64 4 passes (6 with
+// x) at the rate of a large copy.
+template <typename T, int V, bool FIRST, bool XUP>
+__global__ __launch_bounds__(256) void k_cg_step(int64_t n, int p, int lpr_log2, int xfirst,
+                                                const T *__restrict__ alpha, const T *__restrict__ beta,
+                                                const T *__restrict__ alpham, const T *__restrict__ betam,
+                                                const uint8_t *__restrict__ active, const double *__restrict__ lhd,
+                                                const double *__restrict__ bd, const T *__restrict__ lam,
+                                                const T *__restrict__ W, const T *__restrict__ D, T *Dm,
+                                                T *__restrict__ X, double *__restrict__ part) {
+    __shared__ double red[256 * V];
     const int lpr = 1 << lpr_log2;
     const int groups = blockDim.x >> lpr_log2;
     const int g = threadIdx.x >> lpr_log2;
     const int lane = threadIdx.x & (lpr - 1);
-    double dot[CH][V];
-    T al[CH][V], lm[CH][V];
-    bool on[CH][V];
+    const int c0 = ((int)blockIdx.y * lpr + lane) * V;
+    const bool in = c0 < p;
+    T al[V], be[V], am[V], bm[V], lm[V];
+    double dot[V];
+    bool on[V], all = true, any = false;
 #pragma unroll
-    for (int ch = 0; ch < CH; ++ch)
+    for (int v = 0; v < V; ++v) {
+        const int c = in ? c0 + v : 0;
+        on[v] = in && active[c] != 0;
+        all &= on[v];
+        any |= on[v];
+        dot[v] = 0.0;
+        al[v] = alpha[c];
+        be[v] = beta[c];
+        am[v] = XUP ? alpham[c] : T(0);
+        bm[v] = FIRST ? T(0) : betam[c];
+        lm[v] = lam[c];
+    }
+    if (any)
+        for (int64_t row = (int64_t)blockIdx.x * groups + g; row < n; row += (int64_t)gridDim.x * groups) {
+            const int64_t o = row * p + c0;
+            T w[V], d[V], dm[V], x[V];
+            load_vec<T, V>(W + o, w);
+            load_vec<T, V>(D + o, d);
+            if (!FIRST) load_vec<T, V>(Dm + o, dm);
+            if (XUP) {
+                if (xfirst && all) {
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-            const int c = (lane + ch * lpr) * V + v;
-            on[ch][v] = c < p && active[c];
-            dot[ch][v] = 0.0;
-            al[ch][v] = on[ch][v] ? alpha[c] : T(0);   // inactive: r unchanged
-            lm[ch][v] = c < p ? lam[c] : T(0);
-        }
-    for (int64_t row = (int64_t)blockIdx.x * groups + g; row < n; row += (int64_t)gridDim.x * groups) {
-        const T ld = (T)lhd[row], bdv = (T)bd[row];
-#pragma unroll
-        for (int ch = 0; ch < CH; ++ch) {
-            const int c0 = (lane + ch * lpr) * V;
-            if (c0 >= p) continue;
-            T q[V], r[V];
-            load_vec<T, V>(Q + row * p + c0, q);
-            load_vec<T, V>(R + row * p + c0, r);
+                    for (int v = 0; v < V; ++v) x[v] = T(0);
+                } else {
+                    load_vec<T, V>(X + o, x);
+                }
+            }
+            const T ld = (T)lhd[row], bdv = (T)bd[row];
 #pragma unroll
             for (int v = 0; v < V; ++v) {   // selects, not branches, per column
-                r[v] = fma(-al[ch][v], q[v], r[v]);
-                const double t = (double)r[v] * (double)(r[v] / (ld - lm[ch][v] * bdv));
-                dot[ch][v] = on[ch][v] ? dot[ch][v] + t : dot[ch][v];
+                const T z = fma(-al[v], w[v], FIRST ? d[v] : fma(-bm[v], dm[v], d[v]));
+                const double zd = (double)z;
+                const double t = zd * zd * (double)(ld - lm[v] * bdv);
+                dot[v] = on[v] ? dot[v] + t : dot[v];
+                if (XUP) {
+                    const T x1 = xfirst ? am[v] * dm[v] : fma(am[v], dm[v], x[v]);
+                    x[v] = on[v] ? fma(al[v], d[v], x1) : x[v];
+                }
+                dm[v] = on[v] ? fma(be[v], d[v], z) : (FIRST ? T(0) : dm[v]);
             }
-            store_vec<T, V>(R + row * p + c0, r);
+            store_vec<T, V>(Dm + o, dm);
+            if (XUP) store_vec<T, V>(X + o, x);
         }
-    }
 #pragma unroll
-    for (int ch = 0; ch < CH; ++ch) {
-        const int c0 = (lane + ch * lpr) * V;
-        if (c0 < p) {
-#pragma unroll
-            for (int v = 0; v < V; ++v) red[g * p + c0 + v] = dot[ch][v];
-        }
-    }
+    for (int v = 0; v < V; ++v) red[threadIdx.x * V + v] = dot[v];
     __syncthreads();
-    for (int c = threadIdx.x; c < p; c += blockDim.x) {
-        double s = 0.0;
-        for (int k = 0; k < groups; ++k) s += red[k * p + c];
-        part[(int64_t)blockIdx.x * p + c] = s;
+    for (int cl = threadIdx.x; cl < lpr * V; cl += blockDim.x) {
+        const int c = (int)blockIdx.y * lpr * V + cl;
+        if (c >= p) continue;
+        double sum = 0.0;
+        for (int k = 0; k < groups; ++k) sum += red[k * lpr * V + cl];
+        part[(int64_t)blockIdx.x * p + c] = sum;
     }
 }
 
-// x = (first ? 0 : x) + alpha d on active columns; with DIR also
-// d = J r + beta d.  One lane group per row.
-template <typename T, int V, int DIR>
-__global__ __launch_bounds__(256) void k_pcg_dx(int64_t n, int p, int lpr_log2, int first,
-                                               const T *__restrict__ alpha, const T *__restrict__ beta,
-                                               const uint8_t *__restrict__ active,
-                                               const double *__restrict__ lhd, const double *__restrict__ bd,
-                                               const T *__restrict__ lam, const T *__restrict__ R,
-                                               T *__restrict__ D, T *__restrict__ X) {
+// The last update of x: x += alpha d, or x += alpham dm + alpha d (Dm not
+// null); xfirst: from zero.  Active columns; one lane group per row.
+template <typename T, int V>
+__global__ __launch_bounds__(256) void k_cg_x(int64_t n, int p, int lpr_log2, int xfirst, const T *__restrict__ alpham,
+                                             const T *__restrict__ alpha, const uint8_t *__restrict__ active,
+                                             const T *__restrict__ Dm, const T *__restrict__ D, T *__restrict__ X) {
     const int lpr = 1 << lpr_log2;
     const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> lpr_log2;
     const int lane = threadIdx.x & (lpr - 1);
     if (row >= n) return;
-    const T ld = (T)lhd[row], bdv = (T)bd[row];
     for (int c0 = lane * V; c0 < p; c0 += lpr * V) {
         bool on[V], all = true, any = false;
 #pragma unroll
@@ -884,146 +944,76 @@ __global__ __launch_bounds__(256) void k_pcg_dx(int64_t n, int p, int lpr_log2, 
             any |= on[v];
         }
         if (!any) continue;
-        T d[V], x[V], r[V];
-        load_vec<T, V>(D + row * p + c0, d);
-        if (DIR) load_vec<T, V>(R + row * p + c0, r);
-        if (first && all) {
+        const int64_t o = row * p + c0;
+        T d[V], dm[V], x[V], a[V], am[V];
+        load_vec<T, V>(D + o, d);
+        if (Dm) load_vec<T, V>(Dm + o, dm);
+        if (xfirst && all) {
 #pragma unroll
             for (int v = 0; v < V; ++v) x[v] = T(0);
         } else {
-            load_vec<T, V>(X + row * p + c0, x);
+            load_vec<T, V>(X + o, x);
         }
-        T a[V], bt[V], lm[V];
         load_vec<T, V>(alpha + c0, a);
-        if (DIR) {
-            load_vec<T, V>(beta + c0, bt);
-            load_vec<T, V>(lam + c0, lm);
-        }
+        if (Dm) load_vec<T, V>(alpham + c0, am);
 #pragma unroll
-        for (int v = 0; v < V; ++v) {   // selects, not branches, per column
-            const T nx = first ? a[v] * d[v] : fma(a[v], d[v], x[v]);
+        for (int v = 0; v < V; ++v) {
+            T nx;
+            if (Dm) nx = fma(a[v], d[v], xfirst ? am[v] * dm[v] : fma(am[v], dm[v], x[v]));
+            else nx = xfirst ? a[v] * d[v] : fma(a[v], d[v], x[v]);
             x[v] = on[v] ? nx : x[v];
-            if (DIR) {
-                const T nd = fma(bt[v], d[v], r[v] / (ld - lm[v] * bdv));
-                d[v] = on[v] ? nd : d[v];
+        }
+        store_vec<T, V>(X + o, x);
+    }
+}
+
+// Start of the columnwise CG of the preconditioner from x = 0 and a block G:
+// d = J G on active columns, P = G on the others; part[blockIdx.x][c] = <g, J g>.
+// Same mapping as k_cg_step.
+template <typename T, int V>
+__global__ __launch_bounds__(256) void k_cg_start(int64_t n, int p, int lpr_log2, const uint8_t *__restrict__ active,
+                                                 const double *__restrict__ lhd, const double *__restrict__ bd,
+                                                 const T *__restrict__ lam, const T *__restrict__ G,
+                                                 T *__restrict__ D, T *__restrict__ P, double *__restrict__ part) {
+    __shared__ double red[256 * V];
+    const int lpr = 1 << lpr_log2;
+    const int groups = blockDim.x >> lpr_log2;
+    const int g = threadIdx.x >> lpr_log2;
+    const int lane = threadIdx.x & (lpr - 1);
+    const int c0 = ((int)blockIdx.y * lpr + lane) * V;
+    T lm[V];
+    double dot[V];
+    bool on[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int c = c0 < p ? c0 + v : 0;
+        on[v] = c0 < p && active[c] != 0;
+        lm[v] = lam[c];
+        dot[v] = 0.0;
+    }
+    if (c0 < p)
+        for (int64_t row = (int64_t)blockIdx.x * groups + g; row < n; row += (int64_t)gridDim.x * groups) {
+            const int64_t o = row * p + c0;
+            const T ld = (T)lhd[row], bdv = (T)bd[row];
+            T gv[V], d[V];
+            load_vec<T, V>(G + o, gv);
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                d[v] = on[v] ? gv[v] / (ld - lm[v] * bdv) : T(0);
+                dot[v] = on[v] ? fma((double)gv[v], (double)d[v], dot[v]) : 0.0;
+                if (!on[v]) P[o + v] = gv[v];
             }
+            store_vec<T, V>(D + o, d);
         }
-        store_vec<T, V>(X + row * p + c0, x);
-        if (DIR) store_vec<T, V>(D + row * p + c0, d);
-    }
-}
-
-// History form of the inner CG (memory permitting): each direction gets a
-// block of its own, so no pass reads and rewrites x; P = sum_j alpha_j d_j is
-// formed once after the last iteration (the same fmas, in the same order, as
-// the running update x += alpha_j d_j of k_pcg_dx, so the same bits).
-//   k_pcg_dnext  Dn = J r + beta D on active columns          (reads r, D; writes Dn)
-//   k_pcg_sum    X = sum_j alpha_j D_j on active columns      (reads the m D_j; writes X)
-template <typename T, int V>
-__global__ __launch_bounds__(256) void k_pcg_dnext(int64_t n, int p, int lpr_log2, const T *__restrict__ beta,
-                                                  const uint8_t *__restrict__ active,
-                                                  const double *__restrict__ lhd, const double *__restrict__ bd,
-                                                  const T *__restrict__ lam, const T *__restrict__ R,
-                                                  const T *__restrict__ D, T *__restrict__ Dn) {
-    const int lpr = 1 << lpr_log2;
-    const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> lpr_log2;
-    const int lane = threadIdx.x & (lpr - 1);
-    if (row >= n) return;
-    const T ld = (T)lhd[row], bdv = (T)bd[row];
-    for (int c0 = lane * V; c0 < p; c0 += lpr * V) {
-        bool on[V], any = false;
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-            on[v] = active[c0 + v] != 0;
-            any |= on[v];
-        }
-        if (!any) continue;
-        T d[V], r[V];
-        load_vec<T, V>(D + row * p + c0, d);
-        load_vec<T, V>(R + row * p + c0, r);
-        T bt[V], lm[V];
-        load_vec<T, V>(beta + c0, bt);
-        load_vec<T, V>(lam + c0, lm);
-#pragma unroll
-        for (int v = 0; v < V; ++v) {   // a select, not a branch, per column
-            const T nd = fma(bt[v], d[v], r[v] / (ld - lm[v] * bdv));
-            d[v] = on[v] ? nd : d[v];
-        }
-        store_vec<T, V>(Dn + row * p + c0, d);
-    }
-}
-
-// G directions j0 .. j0 + G - 1 of one lane's V columns: all G loads issued
-// before the first fma (no branch between them), then the fmas in order of j
-template <int G, typename T, int V>
-__device__ __forceinline__ void pcg_sum_group(int j0, int64_t off, int p, int c0, const T *__restrict__ alpha,
-                                              const PcgDirs &dirs, const bool (&on)[V], T (&x)[V]) {
-    T d[G][V];
-#pragma unroll
-    for (int u = 0; u < G; ++u) load_vec<T, V>((const T *)dirs.d[j0 + u] + off, d[u]);
-#pragma unroll
-    for (int u = 0; u < G; ++u) {
-        T al[V];
-        load_vec<T, V>(alpha + (int64_t)(j0 + u) * p + c0, al);
-        const bool first = j0 + u == 0;
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-            const T nv = first ? al[v] * d[u][v] : fma(al[v], d[u][v], x[v]);
-            x[v] = on[v] ? nv : x[v];
-        }
-    }
-}
-
-template <typename T, int V>
-__global__ __launch_bounds__(256) void k_pcg_sum(int64_t n, int p, int lpr_log2, int m, const T *__restrict__ alpha,
-                                                const uint8_t *__restrict__ active, PcgDirs dirs,
-                                                T *__restrict__ X) {
-    const int lpr = 1 << lpr_log2;
-    const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> lpr_log2;
-    const int lane = threadIdx.x & (lpr - 1);
-    if (row >= n) return;
-    for (int c0 = lane * V; c0 < p; c0 += lpr * V) {
-        bool on[V], all = true, any = false;
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-            on[v] = active[c0 + v] != 0;
-            all &= on[v];
-            any |= on[v];
-        }
-        if (!any) continue;
-        T x[V];
-        if (all) {
-#pragma unroll
-            for (int v = 0; v < V; ++v) x[v] = T(0);
-        } else {
-            load_vec<T, V>(X + row * p + c0, x);
-        }
-        // the directions in groups of 8, then 4, 2, 1 (m = 10: 8 + 2)
-        const int64_t off = row * p + c0;
-        int j = 0;
-        for (; j + 8 <= m; j += 8) pcg_sum_group<8>(j, off, p, c0, alpha, dirs, on, x);
-        if (j + 4 <= m) { pcg_sum_group<4>(j, off, p, c0, alpha, dirs, on, x); j += 4; }
-        if (j + 2 <= m) { pcg_sum_group<2>(j, off, p, c0, alpha, dirs, on, x); j += 2; }
-        if (j < m) pcg_sum_group<1>(j, off, p, c0, alpha, dirs, on, x);
-        store_vec<T, V>(X + row * p + c0, x);
-    }
-}
-
-// alpha_c = rz_c / dq_c (0 when dq_c <= 0);  beta_c = rz_new_c / rz_c (0 when rz_c <= 0).
-template <typename T>
-__global__ void k_pcg_alpha(int p, const double *__restrict__ dq, const double *__restrict__ rz,
-                            T *__restrict__ alpha) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < p) alpha[c] = dq[c] > 0.0 ? (T)(rz[c] / dq[c]) : T(0);
-}
-
-template <typename T>
-__global__ void k_pcg_beta(int p, const double *__restrict__ rz_new, double *__restrict__ rz,
-                           T *__restrict__ beta) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < p) {
-        beta[c] = rz[c] > 0.0 ? (T)(rz_new[c] / rz[c]) : T(0);
-        rz[c] = rz_new[c];
+    for (int v = 0; v < V; ++v) red[threadIdx.x * V + v] = dot[v];
+    __syncthreads();
+    for (int cl = threadIdx.x; cl < lpr * V; cl += blockDim.x) {
+        const int c = (int)blockIdx.y * lpr * V + cl;
+        if (c >= p) continue;
+        double sum = 0.0;
+        for (int k = 0; k < groups; ++k) sum += red[k * lpr * V + cl];
+        part[(int64_t)blockIdx.x * p + c] = sum;
     }
 }
 
@@ -1158,41 +1148,6 @@ __global__ void k_scale_copy(int64_t n, int p, const S *__restrict__ X, const S 
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
          i += (int64_t)gridDim.x * blockDim.x)
         Y[i] = (D)(X[i] * sc[i % p]);
-}
-
-// Start of the columnwise CG of the preconditioner from x = 0:
-// r = G, d = J G on active columns, P = G on the others; part[block][p] = <r, J r>.
-template <typename T>
-__global__ __launch_bounds__(256) void k_pcg_init(int64_t n, int p, const uint8_t *__restrict__ active,
-                                                 const double *__restrict__ lhd,
-                                                 const double *__restrict__ bd, const T *__restrict__ lam,
-                                                 const T *__restrict__ G, T *__restrict__ R,
-                                                 T *__restrict__ D, T *__restrict__ P,
-                                                 double *__restrict__ part) {
-    extern __shared__ double red[];   // [256]
-    for (int c = 0; c < p; ++c) {
-        double s = 0.0;
-        for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n;
-             r += (int64_t)gridDim.x * blockDim.x) {
-            const T g = G[r * p + c];
-            if (active[c]) {
-                const T z = g / (T(lhd[r]) - lam[c] * T(bd[r]));
-                R[r * p + c] = g;
-                D[r * p + c] = z;
-                s += (double)g * (double)z;
-            } else {
-                P[r * p + c] = g;
-            }
-        }
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) part[(int64_t)blockIdx.x * p + c] = red[0];
-        __syncthreads();
-    }
 }
 
 // f32 <-> f64 block conversion
@@ -1409,15 +1364,6 @@ hipError_t launch_rowgemm(hipStream_t s, int epi, int64_t n, int p, int N, int g
     } while (0)
 
 template <typename T>
-hipError_t launch_pcg_r(hipStream_t s, int grid, int64_t n, int p, const T *alpha, const uint8_t *active,
-                        const double *lhd, const double *bd, const T *lam, const T *Q, T *R, double *part) {
-#define SHM shm
-    OFKS_CH_DISPATCH(k_pcg_r, alpha, active, lhd, bd, lam, Q, R, part);
-#undef SHM
-    return hipGetLastError();
-}
-
-template <typename T>
 hipError_t launch_coldot(hipStream_t s, int grid, int64_t n, int p, const T *A, const T *B,
                          double *part) {
 #define SHM shm
@@ -1435,51 +1381,73 @@ hipError_t launch_bbdot(hipStream_t s, int grid, int64_t n, int p, const T *Xt, 
     return hipGetLastError();
 }
 
+// Rows of a column-tiled persistent kernel: column tiles of 2^l2 lanes x v
+// columns, and enough workgroups over the rows to fill `grid` (fewer where the
+// block is small).
+struct RowGrid {
+    int v, l2, gx, gy;
+};
+template <typename T> static RowGrid row_grid(int64_t n, int p, int grid) {
+    RowGrid g;
+    g.v = vwidth<T>(p);
+    g.l2 = lpr_l2(p, g.v);
+    g.gy = (p + (g.v << g.l2) - 1) / (g.v << g.l2);
+    const int64_t rounds = (n + (256 >> g.l2) - 1) / (256 >> g.l2);
+    g.gx = (int)std::max<int64_t>(1, std::min<int64_t>(rounds, grid / g.gy));
+    return g;
+}
+
+// (*rows: partial rows written, at most grid)
 template <typename T>
-hipError_t launch_pcg_dx(hipStream_t s, int64_t n, int p, int first, int dir, const T *alpha, const T *beta,
-                         const uint8_t *active, const double *lhd, const double *bd, const T *lam, const T *R,
-                         T *D, T *X) {
-    const int v = vwidth<T>(p);
-    const int l2 = lpr_l2(p, v);
-    const unsigned grid = (unsigned)(((n << l2) + 255) / 256);
-#define OFKS_DX(VV)                                                                                        \
-    do {                                                                                                   \
-        if (dir)                                                                                           \
-            hipLaunchKernelGGL((k_pcg_dx<T, VV, 1>), dim3(grid), dim3(256), 0, s, n, p, l2, first, alpha, beta, \
-                               active, lhd, bd, lam, R, D, X);                                             \
-        else                                                                                               \
-            hipLaunchKernelGGL((k_pcg_dx<T, VV, 0>), dim3(grid), dim3(256), 0, s, n, p, l2, first, alpha, beta, \
-                               active, lhd, bd, lam, R, D, X);                                             \
+hipError_t launch_cg_step(hipStream_t s, int grid, int64_t n, int p, int first, int xup, int xfirst, const T *alpha,
+                          const T *beta, const T *alpham, const T *betam, const uint8_t *active, const double *lhd,
+                          const double *bd, const T *lam, const T *W, const T *D, T *Dm, T *X, double *part, int *rows) {
+    const RowGrid g = row_grid<T>(n, p, grid);
+    *rows = g.gx;
+#define OFKS_STEP2(V_, F_, X_)                                                                                       \
+    hipLaunchKernelGGL((k_cg_step<T, V_, F_, X_>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, xfirst, alpha, beta, \
+                       alpham, betam, active, lhd, bd, lam, W, D, Dm, X, part)
+#define OFKS_STEP1(V_)                              \
+    do {                                            \
+        if (first) OFKS_STEP2(V_, true, false);     \
+        else if (xup) OFKS_STEP2(V_, false, true);  \
+        else OFKS_STEP2(V_, false, false);          \
     } while (0)
-    if (v == 1) OFKS_DX(1);
-    else if (v == 2) OFKS_DX(2);
-    else if constexpr (sizeof(T) == 4) OFKS_DX(4);
-#undef OFKS_DX
+    if (g.v == 1) OFKS_STEP1(1);
+    else if (g.v == 2) OFKS_STEP1(2);
+    else if constexpr (sizeof(T) == 4) OFKS_STEP1(4);
+#undef OFKS_STEP1
+#undef OFKS_STEP2
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_pcg_dnext(hipStream_t s, int64_t n, int p, const T *beta, const uint8_t *active,
-                            const double *lhd, const double *bd, const T *lam, const T *R, const T *D, T *Dn) {
+hipError_t launch_cg_x(hipStream_t s, int64_t n, int p, int xfirst, const T *alpham, const T *alpha,
+                       const uint8_t *active, const T *Dm, const T *D, T *X) {
     const int v = vwidth<T>(p);
     const int l2 = lpr_l2(p, v);
     const unsigned grid = (unsigned)(((n << l2) + 255) / 256);
-    if (v == 1) hipLaunchKernelGGL((k_pcg_dnext<T, 1>), dim3(grid), dim3(256), 0, s, n, p, l2, beta, active, lhd, bd, lam, R, D, Dn);
-    else if (v == 2) hipLaunchKernelGGL((k_pcg_dnext<T, 2>), dim3(grid), dim3(256), 0, s, n, p, l2, beta, active, lhd, bd, lam, R, D, Dn);
-    else if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((k_pcg_dnext<T, 4>), dim3(grid), dim3(256), 0, s, n, p, l2, beta, active, lhd, bd, lam, R, D, Dn);
+    if (v == 1) hipLaunchKernelGGL((k_cg_x<T, 1>), dim3(grid), dim3(256), 0, s, n, p, l2, xfirst, alpham, alpha, active, Dm, D, X);
+    else if (v == 2) hipLaunchKernelGGL((k_cg_x<T, 2>), dim3(grid), dim3(256), 0, s, n, p, l2, xfirst, alpham, alpha, active, Dm, D, X);
+    else if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((k_cg_x<T, 4>), dim3(grid), dim3(256), 0, s, n, p, l2, xfirst, alpham, alpha, active, Dm, D, X);
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_pcg_sum(hipStream_t s, int64_t n, int p, int m, const T *alpha, const uint8_t *active,
-                          const PcgDirs &dirs, T *X) {
-    if (m < 1 || m > PCG_DIRS_MAX) return hipErrorInvalidValue;
-    const int v = vwidth<T>(p);
-    const int l2 = lpr_l2(p, v);
-    const unsigned grid = (unsigned)(((n << l2) + 255) / 256);
-    if (v == 1) hipLaunchKernelGGL((k_pcg_sum<T, 1>), dim3(grid), dim3(256), 0, s, n, p, l2, m, alpha, active, dirs, X);
-    else if (v == 2) hipLaunchKernelGGL((k_pcg_sum<T, 2>), dim3(grid), dim3(256), 0, s, n, p, l2, m, alpha, active, dirs, X);
-    else if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((k_pcg_sum<T, 4>), dim3(grid), dim3(256), 0, s, n, p, l2, m, alpha, active, dirs, X);
+hipError_t launch_cg_start(hipStream_t s, int grid, int64_t n, int p, const uint8_t *active, const double *lhd,
+                           const double *bd, const T *lam, const T *G, T *D, T *P, double *part, int *rows) {
+    const RowGrid g = row_grid<T>(n, p, grid);
+    *rows = g.gx;
+    if (g.v == 1) hipLaunchKernelGGL((k_cg_start<T, 1>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, active, lhd, bd, lam, G, D, P, part);
+    else if (g.v == 2) hipLaunchKernelGGL((k_cg_start<T, 2>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, active, lhd, bd, lam, G, D, P, part);
+    else if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((k_cg_start<T, 4>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, active, lhd, bd, lam, G, D, P, part);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_cg_scalars(hipStream_t s, int p, int ndq, const double *dqp, int nrz, const double *rzp, T *alpha,
+                             T *beta) {
+    hipLaunchKernelGGL((k_cg_scalars<T>), dim3((unsigned)((p + 7) / 8)), dim3(256), 0, s, p, ndq, dqp, nrz, rzp, alpha, beta);
     return hipGetLastError();
 }
 
@@ -1492,14 +1460,6 @@ hipError_t launch_update_b(hipStream_t s, int64_t n, int p, const T *dinv, T eta
     if (v == 1) hipLaunchKernelGGL((k_update_b<T, 1>), dim3(grid), dim3(256), 0, s, n, p, l2, dinv, eta, P, Xt, Xp);
     else if (v == 2) hipLaunchKernelGGL((k_update_b<T, 2>), dim3(grid), dim3(256), 0, s, n, p, l2, dinv, eta, P, Xt, Xp);
     else if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((k_update_b<T, 4>), dim3(grid), dim3(256), 0, s, n, p, l2, dinv, eta, P, Xt, Xp);
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_pcg_scalars(hipStream_t s, int p, int which, const double *a, double *b, T *out) {
-    const unsigned grid = (unsigned)((p + 255) / 256);
-    if (which == 0) hipLaunchKernelGGL((k_pcg_alpha<T>), dim3(grid), dim3(256), 0, s, p, a, b, out);
-    else hipLaunchKernelGGL((k_pcg_beta<T>), dim3(grid), dim3(256), 0, s, p, a, b, out);
     return hipGetLastError();
 }
 
@@ -1518,33 +1478,19 @@ template hipError_t launch_scale_copy<double, double>(hipStream_t, int64_t, int,
 template hipError_t launch_scale_copy<float, double>(hipStream_t, int64_t, int, const float *, const float *, double *);
 template hipError_t launch_scale_copy<float, float>(hipStream_t, int64_t, int, const float *, const float *, float *);
 
-template <typename T>
-hipError_t launch_pcg_init(hipStream_t s, int grid, int64_t n, int p, const uint8_t *active, const double *lhd,
-                           const double *bd, const T *lam, const T *G, T *R, T *D, T *P, double *part) {
-    hipLaunchKernelGGL((k_pcg_init<T>), dim3(grid), dim3(256), 256 * sizeof(double), s, n, p, active, lhd, bd,
-                       lam, G, R, D, P, part);
-    return hipGetLastError();
-}
-template hipError_t launch_pcg_init<double>(hipStream_t, int, int64_t, int, const uint8_t *, const double *,
-                                            const double *, const double *, const double *, double *, double *,
-                                            double *, double *);
-template hipError_t launch_pcg_init<float>(hipStream_t, int, int64_t, int, const uint8_t *, const double *,
-                                           const double *, const float *, const float *, float *, float *,
-                                           float *, double *);
-
 #define OFKS_INST(T)                                                                                  \
     template hipError_t launch_gram<T>(hipStream_t, int64_t, int, const GramPlan &, const T *, const T *, const T *, double *, size_t); \
     template hipError_t launch_rowgemm<T>(hipStream_t, int, int64_t, int, int, int, const T *, const T *, const T *, T *, GradArgs, int *); \
-    template hipError_t launch_pcg_r<T>(hipStream_t, int, int64_t, int, const T *, const uint8_t *, const double *, const double *, const T *, const T *, T *, double *); \
     template hipError_t launch_coldot<T>(hipStream_t, int, int64_t, int, const T *, const T *, double *); \
     template hipError_t launch_bbdot<T>(hipStream_t, int, int64_t, int, const T *, const T *, const T *, const T *, const T *, double *); \
-    template hipError_t launch_pcg_dx<T>(hipStream_t, int64_t, int, int, int, const T *, const T *, const uint8_t *, const double *, const double *, const T *, const T *, T *, T *); \
-    template hipError_t launch_update_b<T>(hipStream_t, int64_t, int, const T *, T, const T *, T *, T *); \
-    template hipError_t launch_pcg_dnext<T>(hipStream_t, int64_t, int, const T *, const uint8_t *, const double *, const double *, const T *, const T *, const T *, T *); \
-    template hipError_t launch_pcg_sum<T>(hipStream_t, int64_t, int, int, const T *, const uint8_t *, const PcgDirs &, T *); \
-    template hipError_t launch_pcg_scalars<T>(hipStream_t, int, int, const double *, double *, T *);
+    template hipError_t launch_cg_step<T>(hipStream_t, int, int64_t, int, int, int, int, const T *, const T *, const T *, const T *, const uint8_t *, const double *, const double *, const T *, const T *, const T *, T *, T *, double *, int *); \
+    template hipError_t launch_cg_x<T>(hipStream_t, int64_t, int, int, const T *, const T *, const uint8_t *, const T *, const T *, T *); \
+    template hipError_t launch_cg_scalars<T>(hipStream_t, int, int, const double *, int, const double *, T *, T *); \
+    template hipError_t launch_update_b<T>(hipStream_t, int64_t, int, const T *, T, const T *, T *, T *);
 OFKS_INST(double)
 OFKS_INST(float)
+template hipError_t launch_cg_start<double>(hipStream_t, int, int64_t, int, const uint8_t *, const double *,
+                                            const double *, const double *, const double *, double *, double *, double *, int *);
 template hipError_t launch_convert<double, float>(hipStream_t, int64_t, const double *, float *);
 template hipError_t launch_convert<float, double>(hipStream_t, int64_t, const float *, double *);
 

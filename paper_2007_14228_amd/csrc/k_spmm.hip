@@ -6,8 +6,9 @@
 //                  (f64) or 8-byte (f32) load feeds both products; with one
 //                  output the caller selects which of the pair is used.
 //  k_spmm_shift  : Q[:,l] = (L/2 - lam_l B) D[:,l] (operator of the paper's
-//                  preconditioner T_l, eq. precondition-T) with the per-column
-//                  dot products <D_l, Q_l> of the CG step fused in.
+//                  preconditioner T_l, eq. precondition-T), or, for a step of
+//                  its CG, W = J Q with the per-column dot products <D_l, Q_l>
+//                  and <Q_l, W_l>.
 //  k_spmv_dot    : q = A d and <d, q> for one vector (Hartree CG).
 //
 // Work mapping (wave64).  A row is owned by a group of LPR = 2^lpr_log2 lanes;
@@ -54,6 +55,13 @@ __device__ __forceinline__ void stream_store_vec(T *__restrict__ p, const T (&in
     store_vec<T, V>(p, in);
 #endif
 }
+
+// What the shifted product forms from q = (A1 - lam_c A2) d on the active
+// columns (zero elsewhere): SHIFT writes q; SHIFT_CG writes w = J q, J the
+// inverse of the operator's diagonal (lhd - lam_c bd), and sums <d, q> and
+// <q, w> over the rows of a block (part[block][0..p), [p..2p)); SHIFT_DOT, the
+// last step of a CG, only sums <d, q>.
+enum { DUAL = 0, SHIFT = 1, SHIFT_CG = 2, SHIFT_DOT = 3 };
 
 template <typename T> struct pair_t;
 template <> struct pair_t<double> { using type = double2; };
@@ -130,6 +138,20 @@ __device__ __forceinline__ void gather_row(int64_t e0, int cnt, int lpr_log2, in
     }
 }
 
+// One element of the shifted product: returns what MODE writes and adds to the
+// dots.  Selects, so that nothing of an inactive column (whose d may be
+// anything) reaches the sums.
+template <int MODE, typename T>
+__device__ __forceinline__ T shift_value(bool on, T a1, T a2, T lm, T ld, T bdv, T d, double &dq, double &qw) {
+    const T q = on ? fma(-lm, a2, a1) : T(0);
+    if (MODE == SHIFT) return q;
+    dq = on ? fma((double)d, (double)q, dq) : dq;
+    if (MODE == SHIFT_DOT) return q;
+    const T w = on ? q / (ld - lm * bdv) : T(0);
+    qw = on ? fma((double)q, (double)w, qw) : qw;
+    return w;
+}
+
 // Workgroups are dispatched to the 8 XCDs round-robin (block b on XCD b % 8).
 // The logical block index gives each XCD a contiguous range of rows, so the
 // neighbour rows a row reads were mostly fetched into the same XCD's L2.
@@ -172,14 +194,15 @@ __global__ __launch_bounds__(256) void k_spmm_pair(int64_t n, int p, int lpr_log
 
 // Persistent grid: each wave owns a fixed sequence of row groups, so every
 // block's share and summation order are fixed by the launch shape and the
-// per-block partial dot products (part[b*p + c]) are reproducible.
-template <typename T, int V, int CH, int U>
+// per-block partial dot products are reproducible.
+template <typename T, int V, int CH, int U, int MODE>
 __global__ __launch_bounds__(256) void k_spmm_shift(int64_t n, int p, int lpr_log2,
                                                    const int64_t *__restrict__ rp,
                                                    const int32_t *__restrict__ col,
                                                    const typename pair_t<T>::type *__restrict__ lb,
                                                    const T *__restrict__ lam,
                                                    const uint8_t *__restrict__ active,
+                                                   const double *__restrict__ lhd, const double *__restrict__ bd,
                                                    const T *__restrict__ D, T *__restrict__ Q,
                                                    double *__restrict__ part) {
     extern __shared__ double red[];  // [groups][p]
@@ -188,7 +211,7 @@ __global__ __launch_bounds__(256) void k_spmm_shift(int64_t n, int p, int lpr_lo
     const int g = threadIdx.x >> lpr_log2;
     const int glane = threadIdx.x & (lpr - 1);
     const int gpw = 64 >> lpr_log2;   // row groups per wave
-    double dot[CH][V];
+    double dot[2][CH][V];
     T lm[CH][V];
     bool on[CH][V];
 #pragma unroll
@@ -196,7 +219,7 @@ __global__ __launch_bounds__(256) void k_spmm_shift(int64_t n, int p, int lpr_lo
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             const int c = (glane + ch * lpr) * V + v;
-            dot[ch][v] = 0.0;
+            dot[0][ch][v] = dot[1][ch][v] = 0.0;
             lm[ch][v] = c < p ? lam[c] : T(0);
             on[ch][v] = c < p ? active[c] != 0 : false;
         }
@@ -219,35 +242,40 @@ __global__ __launch_bounds__(256) void k_spmm_shift(int64_t n, int p, int lpr_lo
         T a1[CH][V], a2[CH][V];
         gather_row<T, V, CH, U>(e0, cnt, lpr_log2, p, col, lb, D, a1, a2);
         if (row < s1) {
+            const T ld = MODE == SHIFT_CG ? (T)lhd[row] : T(0), bdv = MODE == SHIFT_CG ? (T)bd[row] : T(0);
 #pragma unroll
             for (int ch = 0; ch < CH; ++ch) {
                 const int c0 = (glane + ch * lpr) * V;
                 if (c0 >= p) continue;
                 T q[V], dv[V];
-                load_vec<T, V>(D + row * p + c0, dv);
+                if (MODE != SHIFT) load_vec<T, V>(D + row * p + c0, dv);
 #pragma unroll
-                for (int v = 0; v < V; ++v) {
-                    q[v] = on[ch][v] ? fma(-lm[ch][v], a2[ch][v], a1[ch][v]) : T(0);
-                    dot[ch][v] += (double)dv[v] * (double)q[v];
-                }
-                store_vec<T, V>(Q + row * p + c0, q);
+                for (int v = 0; v < V; ++v)
+                    q[v] = shift_value<MODE, T>(on[ch][v], a1[ch][v], a2[ch][v], lm[ch][v], ld, bdv, dv[v],
+                                                dot[0][ch][v], dot[1][ch][v]);
+                if (MODE != SHIFT_DOT) store_vec<T, V>(Q + row * p + c0, q);
             }
         }
     }
     // block reduction over row groups, fixed order
+    if (MODE == SHIFT) return;
 #pragma unroll
-    for (int ch = 0; ch < CH; ++ch) {
-        const int c0 = (glane + ch * lpr) * V;
-        if (c0 < p) {
+    for (int d = 0; d < (MODE == SHIFT_CG ? 2 : 1); ++d) {
 #pragma unroll
-            for (int v = 0; v < V; ++v) red[g * p + c0 + v] = dot[ch][v];
+        for (int ch = 0; ch < CH; ++ch) {
+            const int c0 = (glane + ch * lpr) * V;
+            if (c0 < p) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) red[g * p + c0 + v] = dot[d][ch][v];
+            }
         }
-    }
-    __syncthreads();
-    for (int c = threadIdx.x; c < p; c += blockDim.x) {
-        double s = 0.0;
-        for (int k = 0; k < groups; ++k) s += red[k * p + c];
-        part[(int64_t)blockIdx.x * p + c] = s;
+        __syncthreads();
+        for (int c = threadIdx.x; c < p; c += blockDim.x) {
+            double s = 0.0;
+            for (int k = 0; k < groups; ++k) s += red[k * p + c];
+            part[((int64_t)blockIdx.x * 2 + d) * p + c] = s;
+        }
+        __syncthreads();
     }
 }
 
@@ -260,9 +288,9 @@ __global__ __launch_bounds__(256) void k_spmm_shift(int64_t n, int p, int lpr_lo
 // row have nearby numbers, so the rows in flight on one XCD must be a narrow
 // window of consecutive rows for their neighbour rows to stay in that XCD's
 // L2.  Rows go to XCDs in contiguous slabs (block b runs on XCD b % 8).
-//  MODE 0 (Y1 = A1 X, Y2 = A2 X, or A2 X into Y1 when sel = 1): one row per
+//  DUAL (Y1 = A1 X, Y2 = A2 X, or A2 X into Y1 when sel = 1): one row per
 //    wave, blocks in slab order, so the dispatcher sweeps each slab forward.
-//  MODE 1 (shifted operator, per-block partial dots part[block][p]):
+//  SHIFT, SHIFT_CG, SHIFT_DOT (shifted operator, per-block partial dots):
 //    persistent; the launcher sizes the grid to the blocks that can be
 //    resident at once, and round r of block j takes rows base + 4 (r B + j),
 //    so each round sweeps a window of 4 B consecutive rows per XCD.
@@ -273,13 +301,13 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int64_t n, int p, const int64
                                                   const T *__restrict__ X, T *__restrict__ Y1,
                                                   T *__restrict__ Y2, int sel, const T *__restrict__ lam,
                                                   const uint8_t *__restrict__ active,
+                                                  const double *__restrict__ lhd, const double *__restrict__ bd,
                                                   double *__restrict__ part) {
-    using P2 = typename pair_t<T>::type;
     __shared__ double red[4][64 * V * CH];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int64_t row, s1, stride;
-    if (MODE == 0) {
+    if (MODE == DUAL) {
         row = xcd_block(blockIdx.x, gridDim.x) * 4 + wave;
         s1 = n;
         stride = n;   // one row
@@ -291,7 +319,7 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int64_t n, int p, const int64
         row = s0 + (int64_t)(blockIdx.x / 8) * 4 + wave;
         stride = bpx * 4;
     }
-    double dot[CH][V];
+    double dot[2][CH][V];
     T lm[CH][V];
     bool on[CH][V];
 #pragma unroll
@@ -299,8 +327,8 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int64_t n, int p, const int64
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             const int c = (lane + ch * 64) * V + v;
-            dot[ch][v] = 0.0;
-            if (MODE == 1) {
+            dot[0][ch][v] = dot[1][ch][v] = 0.0;
+            if (MODE != DUAL) {
                 lm[ch][v] = c < p ? lam[c] : T(0);
                 on[ch][v] = c < p ? active[c] != 0 : false;
             }
@@ -351,11 +379,12 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int64_t n, int p, const int64
                         a2[ch][v] = fma(wy[u], xb[u][ch][v], a2[ch][v]);
                     }
         }
+        const T ld = MODE == SHIFT_CG ? (T)lhd[row] : T(0), bdv = MODE == SHIFT_CG ? (T)bd[row] : T(0);
 #pragma unroll
         for (int ch = 0; ch < CH; ++ch) {
             const int c0 = (lane + ch * 64) * V;
             if (c0 >= p) continue;
-            if (MODE == 0) {
+            if (MODE == DUAL) {
                 if (Y2) {
                     stream_store_vec<T, V>(Y1 + row * p + c0, a1[ch]);
                     stream_store_vec<T, V>(Y2 + row * p + c0, a2[ch]);
@@ -364,24 +393,27 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int64_t n, int p, const int64
                 }
             } else {
                 T q[V], dv[V];
-                load_vec<T, V>(X + row * p + c0, dv);
+                if (MODE != SHIFT) load_vec<T, V>(X + row * p + c0, dv);
 #pragma unroll
-                for (int v = 0; v < V; ++v) {
-                    q[v] = on[ch][v] ? fma(-lm[ch][v], a2[ch][v], a1[ch][v]) : T(0);
-                    dot[ch][v] += (double)dv[v] * (double)q[v];
-                }
-                stream_store_vec<T, V>(Y1 + row * p + c0, q);
+                for (int v = 0; v < V; ++v)
+                    q[v] = shift_value<MODE, T>(on[ch][v], a1[ch][v], a2[ch][v], lm[ch][v], ld, bdv, dv[v],
+                                                dot[0][ch][v], dot[1][ch][v]);
+                if (MODE != SHIFT_DOT) stream_store_vec<T, V>(Y1 + row * p + c0, q);
             }
         }
     }
-    if (MODE == 1) {
+    if (MODE == SHIFT_CG || MODE == SHIFT_DOT) {
 #pragma unroll
-        for (int ch = 0; ch < CH; ++ch)
+        for (int d = 0; d < (MODE == SHIFT_CG ? 2 : 1); ++d) {
 #pragma unroll
-            for (int v = 0; v < V; ++v) red[wave][(lane + ch * 64) * V + v] = dot[ch][v];
-        __syncthreads();
-        for (int c = threadIdx.x; c < p; c += blockDim.x)
-            part[(int64_t)blockIdx.x * p + c] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
+            for (int ch = 0; ch < CH; ++ch)
+#pragma unroll
+                for (int v = 0; v < V; ++v) red[wave][(lane + ch * 64) * V + v] = dot[d][ch][v];
+            __syncthreads();
+            for (int c = threadIdx.x; c < p; c += blockDim.x)
+                part[((int64_t)blockIdx.x * 2 + d) * p + c] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
+            __syncthreads();
+        }
     }
 }
 
@@ -470,9 +502,8 @@ __global__ __launch_bounds__(256) void k_spmv_dot(int64_t n, const int64_t *__re
 // weight on a neighbour's row would turn its infinities into NaN.  ROUNDS (1,
 // or 2 where some row has more than sixteen entries) times sixteen entries of
 // a row are held in registers; later ones are loaded as they come.
-//  MODE 0: Y1 = A1 X and Y2 = A2 X (or, Y2 = NULL, A1 X or A2 X by sel).
-//  MODE 1: Y1 = Q = (A1 - lam_c A2) D on active columns (0 elsewhere), and
-//          part[b][c] = <D_c, Q_c> over the block's rows.
+//  DUAL: Y1 = A1 X and Y2 = A2 X (or, Y2 = NULL, A1 X or A2 X by sel).
+//  SHIFT, SHIFT_CG, SHIFT_DOT: the shifted product into Y1, dots per plan block.
 // SEGB: bytes per staging lane, 16 where the rows of X are 16-byte aligned,
 // else 4.  Columns at or past p in a ragged last slice stage in-bounds data of
 // the row's first segment; no output reads them.
@@ -491,7 +522,7 @@ __global__ __launch_bounds__(256) void k_spmv_dot(int64_t n, const int64_t *__re
 // Tunables: halo rows (LDS = (HALO_MAX + 1) x 256 B and the dot partials,
 // three workgroups a CU) and rows per block.
 #ifndef OFKS_HALO_MAX
-#define OFKS_HALO_MAX 200
+#define OFKS_HALO_MAX 192
 #endif
 #ifndef OFKS_HALO_RMAX
 #define OFKS_HALO_RMAX 64
@@ -504,6 +535,7 @@ constexpr int HALO_SETS = HALO_RMAX / (4 * HALO_WAVES);   // row sets (four rows
 constexpr int HALO_SST = 4 * HALO_WAVES;   // halo slots filled by one 16-byte load of every wave
 constexpr int HALO_STRIDE = (HALO_MAX + HALO_SST - 1) / HALO_SST * HALO_SST;
 constexpr int HALO_BRP = HALO_RMAX + 1;    // per-block row pointer stride
+static_assert(HALO_WAVES == 4, "four partials per column");
 static_assert(HALO_RMAX % (4 * HALO_WAVES) == 0, "whole row sets per wave");
 static_assert(HALO_MAX % 4 == 0, "a wave fills four slots at a time");
 static_assert(HALO_MAX < 256 && HALO_RMAX < 256, "info fields");
@@ -575,21 +607,22 @@ k_spmm_halo(int64_t nb, int p, int cw, const int64_t *__restrict__ row0, const i
             const int32_t *__restrict__ halo, const int64_t *__restrict__ brp, const uint16_t *__restrict__ lcol,
             const typename pair_t<T>::type *__restrict__ w, const T *__restrict__ X, T *__restrict__ Y1,
             T *__restrict__ Y2, int sel, const T *__restrict__ lam, const uint8_t *__restrict__ active,
-            double *__restrict__ part) {
+            const double *__restrict__ lhd, const double *__restrict__ bd, double *__restrict__ part) {
     using P2 = typename pair_t<T>::type;
     constexpr int CP = 256 / sizeof(T);   // columns per slice: 32 (f64) or 64 (f32)
     constexpr int VW = 16 / sizeof(T);    // columns per lane
     constexpr int NSLOT = HALO_STRIDE / HALO_SST;   // slots a thread stages, in 16-byte pieces
     static_assert(HALO_STRIDE / HALO_WAVES <= 64, "a wave's slots fit its lanes");
     __shared__ __align__(16) char Xs[(HALO_MAX + 1) * 256];
-    __shared__ double red[MODE == 1 ? HALO_WAVES * CP : 1];
+    constexpr int NDOT = MODE == SHIFT_CG ? 2 : MODE == SHIFT_DOT ? 1 : 0;
+    __shared__ double red[NDOT ? NDOT * HALO_WAVES * CP : 1];
     const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t b = xcd_block(blockIdx.x, gridDim.x);
     const int cb = blockIdx.y * cw, ce = min(p, cb + cw);   // this workgroup's columns
     if (b >= nb) {   // padding block of the XCD mapping: a zero partial row
-        if (MODE == 1)
-            for (int c = cb + threadIdx.x; c < ce; c += blockDim.x) part[b * p + c] = 0.0;
+        for (int d = 0; d < NDOT; ++d)
+            for (int c = cb + threadIdx.x; c < ce; c += blockDim.x) part[(2 * b + d) * p + c] = 0.0;
         return;
     }
     // this thread's halo rows (SEGB 4: lane u holds the wave's u-th slot's),
@@ -615,6 +648,14 @@ k_spmm_halo(int64_t nb, int p, int cw, const int64_t *__restrict__ row0, const i
     const int inf = info[b];
     const int64_t r0 = row0[b];
     const int hn = inf & 255, nrows = (inf >> 8) & 255, rb = (inf >> 16) & 255;
+    // the rows' diagonals of L/2 and B: lane i of each sixteen holds set i's
+    static_assert(HALO_SETS == 4, "the broadcasts below");
+    T ldl = T(0), bdl = T(0);
+    if (MODE == SHIFT_CG) {
+        const int64_t r = r0 + min(4 * HALO_SETS * wave + 4 * (li & 3) + g, nrows - 1);
+        ldl = (T)lhd[r];
+        bdl = (T)bd[r];
+    }
     if (threadIdx.x < 16) {
         const T z[VW] = {};
         store_vec<T, VW>((T *)(Xs + HALO_MAX * 256 + 16 * threadIdx.x), z);
@@ -670,12 +711,12 @@ k_spmm_halo(int64_t nb, int p, int cw, const int64_t *__restrict__ row0, const i
         const int c = c0 + VW * li;   // this lane's columns
         T lm[VW];
         bool on[VW];
-        double dot[VW];
+        double dot[2][VW];
 #pragma unroll
         for (int v = 0; v < VW; ++v) {
-            lm[v] = (MODE == 1 && c + v < p) ? lam[c + v] : T(0);
-            on[v] = (MODE == 1 && c + v < p) ? active[c + v] != 0 : false;
-            dot[v] = 0.0;
+            lm[v] = (MODE != DUAL && c + v < p) ? lam[c + v] : T(0);
+            on[v] = (MODE != DUAL && c + v < p) ? active[c + v] != 0 : false;
+            dot[0][v] = dot[1][v] = 0.0;
         }
         __builtin_amdgcn_s_waitcnt(0);   // this thread's loads
         __builtin_amdgcn_s_barrier();    // every wave's: the slice is in LDS
@@ -697,56 +738,55 @@ k_spmm_halo(int64_t nb, int p, int cw, const int64_t *__restrict__ row0, const i
                 entry(ee, (int)(bp[4 * i + 1] - ee), base, oo, x1, x2);
                 halo_round<T>(xs, m[i] - base, oo, x1, x2, a1, a2);
             }
-            if (MODE == 1) {
-                T dv[VW];   // D's own row, staged with the halo
-                load_vec<T, VW>((const T *)(xs + (k < nrows ? rb + k : HALO_MAX) * 256), dv);
+            if (MODE != DUAL) {
+                T dv[VW];   // D's own row, staged with the halo (rows past the block: zeros, and q = 0)
+                const T ld = i == 0 ? row_bcast<0>(ldl) : i == 1 ? row_bcast<1>(ldl) : i == 2 ? row_bcast<2>(ldl) : row_bcast<3>(ldl);
+                const T bdv = i == 0 ? row_bcast<0>(bdl) : i == 1 ? row_bcast<1>(bdl) : i == 2 ? row_bcast<2>(bdl) : row_bcast<3>(bdl);
+                if (NDOT) load_vec<T, VW>((const T *)(xs + (k < nrows ? rb + k : HALO_MAX) * 256), dv);
 #pragma unroll
-                for (int v = 0; v < VW; ++v) {
-                    const T q = on[v] ? fma(-lm[v], a2[v], a1[v]) : T(0);
-                    dot[v] = on[v] ? fma((double)dv[v], (double)q, dot[v]) : dot[v];
-                    a1[v] = q;
-                }
+                for (int v = 0; v < VW; ++v)
+                    a1[v] = shift_value<MODE, T>(on[v], a1[v], a2[v], lm[v], ld, bdv, dv[v], dot[0][v], dot[1][v]);
             }
-            if (k < nrows && c < p) {
+            if (MODE != SHIFT_DOT && k < nrows && c < p) {
                 T *y = Y1 + (r0 + k) * p + c;
                 T *y2 = Y2 + (r0 + k) * p + c;
                 if (SEGB == 16) {   // p is a multiple of VW: a piece lies wholly inside or past p
-                    if (MODE == 0 && !Y2 && sel) {
+                    if (MODE == DUAL && !Y2 && sel) {
                         stream_store16(y, a2);
                     } else {
                         stream_store16(y, a1);
-                        if (MODE == 0 && Y2) stream_store16(y2, a2);
+                        if (MODE == DUAL && Y2) stream_store16(y2, a2);
                     }
                 } else {
 #pragma unroll
                     for (int v = 0; v < VW; ++v) {
                         if (c + v >= p) continue;
-                        if (MODE == 0 && !Y2 && sel) {
+                        if (MODE == DUAL && !Y2 && sel) {
                             y[v] = a2[v];
                         } else {
                             y[v] = a1[v];
-                            if (MODE == 0 && Y2) y2[v] = a2[v];
+                            if (MODE == DUAL && Y2) y2[v] = a2[v];
                         }
                     }
                 }
             }
             __builtin_amdgcn_sched_barrier(0);   // one set's LDS reads in flight at a time (registers)
         }
-        if (MODE == 1) {
+#pragma unroll
+        for (int d = 0; d < NDOT; ++d)
 #pragma unroll
             for (int v = 0; v < VW; ++v) {   // over the wave's four rows in flight, then one LDS slot per wave
-                dot[v] = rows_sum(dot[v]);
-                if (g == 0) red[wave * CP + VW * li + v] = dot[v];
+                const double sum = rows_sum(dot[d][v]);
+                if (g == 0) red[(d * HALO_WAVES + wave) * CP + VW * li + v] = sum;
             }
-        }
         __builtin_amdgcn_s_waitcnt(0xc07f);   // LDS done (lgkmcnt 0); vector memory untouched
         __builtin_amdgcn_s_barrier();         // the slice is consumed and the partials written
         __builtin_amdgcn_sched_barrier(0);
         if (c0 + CP < ce) stage(c0 + CP);
-        if (MODE == 1) {
-            const int cl = threadIdx.x;
-            if (cl < CP && c0 + cl < p)
-                part[b * p + c0 + cl] = ((red[cl] + red[CP + cl]) + red[2 * CP + cl]) + red[3 * CP + cl];
+        if (NDOT && (int)threadIdx.x < NDOT * CP) {
+            const int d = threadIdx.x / CP, cl = threadIdx.x % CP;
+            const double *rd = red + d * HALO_WAVES * CP + cl;
+            if (c0 + cl < p) part[(2 * b + d) * p + c0 + cl] = ((rd[0] + rd[CP]) + rd[2 * CP]) + rd[3 * CP];
         }
     }
 }
@@ -818,7 +858,7 @@ hipError_t launch_spmm_pair(hipStream_t s, int64_t n, int p, const int64_t *rp, 
         const unsigned grid = (unsigned)spmm_wave_blocks(n);
 #define OFKS_WAVE0(VV, CC)                                                                                   \
     hipLaunchKernelGGL((k_spmm_wave<T, VV, CC, (CC >= 8 ? 2 : OFKS_SPMM_U / CC), 0>), dim3(grid), dim3(256), 0, s, n, p, rp, col, w, X, Y1, Y2, \
-                       sel, (const T *)nullptr, (const uint8_t *)nullptr, (double *)nullptr)
+                       sel, (const T *)nullptr, (const uint8_t *)nullptr, (const double *)nullptr, (const double *)nullptr, (double *)nullptr)
         if (v == 1 && ch == 1) OFKS_WAVE0(1, 1);
         else if (v == 1 && ch <= 2) OFKS_WAVE0(1, 2);
         else if (v == 2 && ch == 1) OFKS_WAVE0(2, 1);
@@ -846,29 +886,33 @@ hipError_t launch_spmm_pair(hipStream_t s, int64_t n, int p, const int64_t *rp, 
     return hipGetLastError();
 }
 
-// Launches at most `grid` blocks (the caller's partial buffer holds grid * p
-// values) and reports the number used in *blocks_used.
-template <typename T>
-hipError_t launch_spmm_shift(hipStream_t s, int grid, int64_t n, int p, const int64_t *rp,
-                             const int32_t *col, const void *lb, const T *lam, const uint8_t *active,
-                             const T *D, T *Q, double *part, int *blocks_used) {
+// Shifted product by row gather in `mode`.  Launches at most `grid` blocks (the
+// caller's partial buffer holds 2 p values for each) and reports the number
+// used in *blocks_used.
+template <int MODE, typename T>
+static hipError_t launch_spmm_shift_mode(hipStream_t s, int grid, int64_t n, int p, const int64_t *rp, const int32_t *col,
+                                         const void *lb, const T *lam, const uint8_t *active, const double *lhd,
+                                         const double *bd, const T *D, T *Q, double *part, int *blocks_used) {
     using P2 = typename pair_t<T>::type;
     if (grid % 8 != 0 || grid < 8) return hipErrorInvalidValue;   // whole XCD slabs
-    *blocks_used = grid;
     const int v = pick_v<T>(p);
     const int l2 = lpr_log2_for(p, v);
     const int ch = (p + (v << l2) - 1) / (v << l2);
     const int bs = 256;
+    // no more blocks than there are rounds of row groups
+    const int64_t rounds = ((n + (bs >> l2) - 1) / (bs >> l2) + 7) / 8 * 8;
+    if (grid > rounds) grid = (int)rounds;
+    *blocks_used = grid;
     const size_t shm = (size_t)(bs >> l2) * p * sizeof(double);
     const P2 *w = (const P2 *)lb;
     if (l2 == 6) {
 #define OFKS_WAVE1(VV, CC)                                                                                   \
     do {                                                                                                     \
-        auto kfn = k_spmm_wave<T, VV, CC, (CC >= 8 ? 2 : OFKS_SPMM_U / CC), 1>;                                       \
+        auto kfn = k_spmm_wave<T, VV, CC, (CC >= 8 ? 2 : OFKS_SPMM_U / CC), MODE>;                            \
         const int wgrid = resident_grid(kfn, grid);                                                          \
         *blocks_used = wgrid;                                                                                \
         hipLaunchKernelGGL(kfn, dim3(wgrid), dim3(256), 0, s, n, p, rp, col, w, D, Q, (T *)nullptr, 0, lam,   \
-                           active, part);                                                                    \
+                           active, lhd, bd, part);                                                           \
     } while (0)
         if (v == 1 && ch == 1) OFKS_WAVE1(1, 1);
         else if (v == 1 && ch <= 2) OFKS_WAVE1(1, 2);
@@ -885,11 +929,23 @@ hipError_t launch_spmm_shift(hipStream_t s, int grid, int64_t n, int p, const in
 #undef OFKS_WAVE1
         return hipGetLastError();
     }
-#define OFKS_SHIFT(VV, CC, UU) \
-    hipLaunchKernelGGL((k_spmm_shift<T, VV, CC, UU>), dim3(grid), dim3(bs), shm, s, n, p, l2, rp, col, w, lam, active, D, Q, part)
+#define OFKS_SHIFT(VV, CC, UU)                                                                                        \
+    hipLaunchKernelGGL((k_spmm_shift<T, VV, CC, UU, MODE>), dim3(grid), dim3(bs), shm, s, n, p, l2, rp, col, w, lam,  \
+                       active, lhd, bd, D, Q, part)
     OFKS_VCH_DISPATCH(OFKS_SHIFT);
 #undef OFKS_SHIFT
     return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_spmm_shift(hipStream_t s, int mode, int grid, int64_t n, int p, const int64_t *rp, const int32_t *col,
+                             const void *lb, const T *lam, const uint8_t *active, const double *lhd, const double *bd,
+                             const T *D, T *Q, double *part, int *blocks_used) {
+    if (mode == SHIFT)
+        return launch_spmm_shift_mode<SHIFT, T>(s, grid, n, p, rp, col, lb, lam, active, lhd, bd, D, Q, part, blocks_used);
+    if (mode == SHIFT_CG)
+        return launch_spmm_shift_mode<SHIFT_CG, T>(s, grid, n, p, rp, col, lb, lam, active, lhd, bd, D, Q, part, blocks_used);
+    return launch_spmm_shift_mode<SHIFT_DOT, T>(s, grid, n, p, rp, col, lb, lam, active, lhd, bd, D, Q, part, blocks_used);
 }
 
 hipError_t launch_spmv_dot(hipStream_t s, int grid, int64_t n, const int64_t *rp, const int32_t *col,
@@ -899,64 +955,70 @@ hipError_t launch_spmv_dot(hipStream_t s, int grid, int64_t n, const int64_t *rp
 }
 
 // Halo-SpMM launch: nb blocks of the plan (grid padded to whole XCD slabs).
-// MODE 1 leaves the per-block dots after room for ceil(nbp / HALO_G) group
-// sums in part, then writes the group sums to its start; the caller's column
-// sum takes *rows_out rows.  part_capacity in doubles.
-constexpr int HALO_G = 64;
+// SHIFT_CG and SHIFT_DOT leave *rows_out rows of 2 p partial dots at the start
+// of part: sums over groups of HALO_G plan blocks (formed from the per-block
+// rows that follow them), or the blocks' own rows where there are few.
+// part_capacity in doubles.
+constexpr int HALO_G = 64, HALO_DIRECT = 256;
 static int64_t halo_grid(int64_t nb) { return (nb + 7) / 8 * 8; }
 
 size_t spmm_halo_part_doubles(int64_t nb, int p) {
     const int64_t nbp = halo_grid(nb);
-    return (size_t)((nbp + HALO_G - 1) / HALO_G + nbp) * p;
+    return (size_t)((nbp + HALO_G - 1) / HALO_G + nbp) * 2 * p;
 }
 
 template <typename T>
 hipError_t launch_spmm_halo(hipStream_t s, int mode, int64_t nb, int maxlen, int p, const int64_t *row0, const int32_t *info,
                             const int32_t *halo, const int64_t *brp, const uint16_t *lcol, const void *wv, const T *X,
-                            T *Y1, T *Y2, int sel, const T *lam, const uint8_t *active, double *part,
-                            size_t part_capacity, int *rows_out) {
+                            T *Y1, T *Y2, int sel, const T *lam, const uint8_t *active, const double *lhd,
+                            const double *bd, double *part, size_t part_capacity, int *rows_out) {
     using P2 = typename pair_t<T>::type;
     const P2 *w = (const P2 *)wv;
-    const int64_t nbp = halo_grid(nb), ng = (nbp + HALO_G - 1) / HALO_G;
+    const int64_t nbp = halo_grid(nb), ng = nbp <= HALO_DIRECT ? 0 : (nbp + HALO_G - 1) / HALO_G;
     if (nbp <= 0 || nbp > 0x7fffffff) return hipErrorInvalidValue;
     // rows of X, Y1 and Y2 16-byte aligned: 16-byte pieces
     const bool vec = p % (16 / (int)sizeof(T)) == 0 &&
                      (reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y1) | reinterpret_cast<uintptr_t>(Y2)) % 16 == 0;
-    if (mode == 1 && (size_t)(ng + nbp) * p > part_capacity) return hipErrorInvalidValue;
-    double *bpart = part + ng * p;
+    const bool dots = mode == SHIFT_CG || mode == SHIFT_DOT;
+    if (dots && (size_t)(ng + nbp) * 2 * p > part_capacity) return hipErrorInvalidValue;
+    double *bpart = part + ng * 2 * p;
     // slices per workgroup: all of them once the plan's blocks fill the device
     // (three workgroups on each of 256 CUs), fewer below that
     const int cp = 256 / (int)sizeof(T), ns = (p + cp - 1) / cp;
     const int gy = (int)std::min<int64_t>(ns, (767 + nbp) / nbp), cw = (ns + gy - 1) / gy * cp;
     const dim3 grid((unsigned)nbp, (unsigned)((p + cw - 1) / cw));
-#define OFKS_HALO(M_, S_)                                                                                          \
-    if (maxlen > 16)                                                                                               \
-        hipLaunchKernelGGL((k_spmm_halo<T, M_, S_, 2>), grid, dim3(64 * HALO_WAVES), 0, s, nb, p, cw, row0, \
-                           info, halo, brp, lcol, w, X, Y1, Y2, sel, lam, active, bpart);                          \
-    else                                                                                                           \
-        hipLaunchKernelGGL((k_spmm_halo<T, M_, S_, 1>), grid, dim3(64 * HALO_WAVES), 0, s, nb, p, cw, row0, \
-                           info, halo, brp, lcol, w, X, Y1, Y2, sel, lam, active, bpart)
-    if (mode == 0) {
-        if (vec) { OFKS_HALO(0, 16); }
-        else { OFKS_HALO(0, 4); }
-        return hipGetLastError();
-    }
-    if (vec) { OFKS_HALO(1, 16); }
-    else { OFKS_HALO(1, 4); }
+#define OFKS_HALO_LAUNCH(M_, S_, R_)                                                                                  \
+    hipLaunchKernelGGL((k_spmm_halo<T, M_, S_, R_>), grid, dim3(64 * HALO_WAVES), 0, s, nb, p, cw, row0, info, halo, brp, \
+                       lcol, w, X, Y1, Y2, sel, lam, active, lhd, bd, bpart)
+#define OFKS_HALO(M_)                                    \
+    do {                                                 \
+        if (vec && maxlen > 16) OFKS_HALO_LAUNCH(M_, 16, 2); \
+        else if (vec) OFKS_HALO_LAUNCH(M_, 16, 1);       \
+        else if (maxlen > 16) OFKS_HALO_LAUNCH(M_, 4, 2); \
+        else OFKS_HALO_LAUNCH(M_, 4, 1);                 \
+    } while (0)
+    if (mode == DUAL) OFKS_HALO(DUAL);
+    else if (mode == SHIFT) OFKS_HALO(SHIFT);
+    else if (mode == SHIFT_CG) OFKS_HALO(SHIFT_CG);
+    else OFKS_HALO(SHIFT_DOT);
 #undef OFKS_HALO
-    hipLaunchKernelGGL(k_part_rows, dim3((unsigned)ng), dim3(256), 0, s, nbp, p, HALO_G, bpart, part);
-    *rows_out = (int)ng;
+#undef OFKS_HALO_LAUNCH
+    if (dots) {
+        // (SHIFT_DOT leaves the second half of each row unset: its sums are not read)
+        if (ng) hipLaunchKernelGGL(k_part_rows, dim3((unsigned)ng), dim3(256), 0, s, nbp, 2 * p, HALO_G, bpart, part);
+        *rows_out = (int)(ng ? ng : nbp);
+    }
     return hipGetLastError();
 }
 
 template hipError_t launch_spmm_halo<double>(hipStream_t, int, int64_t, int, int, const int64_t *, const int32_t *,
                                              const int32_t *, const int64_t *, const uint16_t *, const void *,
                                              const double *, double *, double *, int, const double *,
-                                             const uint8_t *, double *, size_t, int *);
+                                             const uint8_t *, const double *, const double *, double *, size_t, int *);
 template hipError_t launch_spmm_halo<float>(hipStream_t, int, int64_t, int, int, const int64_t *, const int32_t *,
                                             const int32_t *, const int64_t *, const uint16_t *, const void *,
                                             const float *, float *, float *, int, const float *, const uint8_t *,
-                                            double *, size_t, int *);
+                                            const double *, const double *, double *, size_t, int *);
 int halo_max_rows() { return HALO_MAX; }
 int halo_max_block_rows() { return HALO_RMAX; }
 int halo_max_row_entries() { return HALO_EMAX; }
@@ -967,11 +1029,11 @@ template hipError_t launch_spmm_pair<double>(hipStream_t, int64_t, int, const in
                                              const void *, const double *, double *, double *, int);
 template hipError_t launch_spmm_pair<float>(hipStream_t, int64_t, int, const int64_t *, const int32_t *,
                                             const void *, const float *, float *, float *, int);
-template hipError_t launch_spmm_shift<double>(hipStream_t, int, int64_t, int, const int64_t *,
-                                              const int32_t *, const void *, const double *,
-                                              const uint8_t *, const double *, double *, double *, int *);
-template hipError_t launch_spmm_shift<float>(hipStream_t, int, int64_t, int, const int64_t *,
-                                             const int32_t *, const void *, const float *,
-                                             const uint8_t *, const float *, float *, double *, int *);
+template hipError_t launch_spmm_shift<double>(hipStream_t, int, int, int64_t, int, const int64_t *, const int32_t *,
+                                              const void *, const double *, const uint8_t *, const double *,
+                                              const double *, const double *, double *, double *, int *);
+template hipError_t launch_spmm_shift<float>(hipStream_t, int, int, int64_t, int, const int64_t *, const int32_t *,
+                                             const void *, const float *, const uint8_t *, const double *,
+                                             const double *, const float *, float *, double *, int *);
 
 }  // namespace ofks

@@ -59,14 +59,16 @@ template <typename T>
 hipError_t launch_spmm_pair(hipStream_t, int64_t, int, const int64_t *, const int32_t *, const void *, const T *,
                             T *, T *, int);
 template <typename T>
-hipError_t launch_spmm_shift(hipStream_t, int, int64_t, int, const int64_t *, const int32_t *, const void *,
-                             const T *, const uint8_t *, const T *, T *, double *, int *);
+hipError_t launch_spmm_shift(hipStream_t, int, int, int64_t, int, const int64_t *, const int32_t *, const void *,
+                             const T *, const uint8_t *, const double *, const double *, const T *, T *, double *,
+                             int *);
+enum { DUAL = 0, SHIFT = 1, SHIFT_CG = 2, SHIFT_DOT = 3 };   // product forms (k_spmm.hip)
 hipError_t launch_spmv_dot(hipStream_t, int, int64_t, const int64_t *, const int32_t *, const double *,
                            const double *, double *, double *);
 template <typename T>
 hipError_t launch_spmm_halo(hipStream_t, int, int64_t, int, int, const int64_t *, const int32_t *, const int32_t *,
                             const int64_t *, const uint16_t *, const void *, const T *, T *, T *, int, const T *,
-                            const uint8_t *, double *, size_t, int *);
+                            const uint8_t *, const double *, const double *, double *, size_t, int *);
 size_t spmm_halo_part_doubles(int64_t nb, int p);
 int halo_max_rows();
 int halo_max_block_rows();
@@ -74,14 +76,9 @@ int halo_max_row_entries();
 int halo_pad_stride();
 int halo_row_ptr_stride();
 // (k_blas.hip)
-constexpr int PCG_DIRS_MAX = 16;
-struct PcgDirs {
-    const void *d[PCG_DIRS_MAX];
-};
 struct GradArgs {
     const void *HX;
     void *P;
-    void *R;
     void *D;
     const double *lhd;
     const double *bd;
@@ -106,32 +103,27 @@ hipError_t launch_rowgemm(hipStream_t, int, int64_t, int, int, int, const T *, c
 int rowgemm_tile_cols(int N);
 int rowgemm_grid_y(int N);
 template <typename T>
-hipError_t launch_pcg_r(hipStream_t, int, int64_t, int, const T *, const uint8_t *, const double *, const double *,
-                        const T *, const T *, T *, double *);
-template <typename T>
 hipError_t launch_coldot(hipStream_t, int, int64_t, int, const T *, const T *, double *);
 template <typename T>
 hipError_t launch_bbdot(hipStream_t, int, int64_t, int, const T *, const T *, const T *, const T *, const T *,
                         double *);
 template <typename T>
-hipError_t launch_pcg_dx(hipStream_t, int64_t, int, int, int, const T *, const T *, const uint8_t *, const double *,
-                         const double *, const T *, const T *, T *, T *);
-template <typename T>
 hipError_t launch_update_b(hipStream_t, int64_t, int, const T *, T, const T *, T *, T *);
 template <typename T>
-hipError_t launch_pcg_dnext(hipStream_t, int64_t, int, const T *, const uint8_t *, const double *, const double *,
-                            const T *, const T *, const T *, T *);
+hipError_t launch_cg_step(hipStream_t, int, int64_t, int, int, int, int, const T *, const T *, const T *, const T *,
+                          const uint8_t *, const double *, const double *, const T *, const T *, const T *, T *, T *,
+                          double *, int *);
 template <typename T>
-hipError_t launch_pcg_sum(hipStream_t, int64_t, int, int, const T *, const uint8_t *, const PcgDirs &, T *);
+hipError_t launch_cg_x(hipStream_t, int64_t, int, int, const T *, const T *, const uint8_t *, const T *, const T *, T *);
 template <typename T>
-hipError_t launch_pcg_scalars(hipStream_t, int, int, const double *, double *, T *);
+hipError_t launch_cg_start(hipStream_t, int, int64_t, int, const uint8_t *, const double *, const double *, const T *,
+                           const T *, T *, T *, double *, int *);
+template <typename T>
+hipError_t launch_cg_scalars(hipStream_t, int, int, const double *, int, const double *, T *, T *);
 template <typename S, typename D>
 hipError_t launch_convert(hipStream_t, int64_t, const S *, D *);
 template <typename S, typename D>
 hipError_t launch_scale_copy(hipStream_t, int64_t, int, const S *, const S *, D *);
-template <typename T>
-hipError_t launch_pcg_init(hipStream_t, int, int64_t, int, const uint8_t *, const double *, const double *,
-                           const T *, const T *, T *, T *, T *, double *);
 // (k_mesh.hip)
 hipError_t scan_exclusive(hipStream_t, int64_t, const int32_t *, int64_t *, int64_t *);
 hipError_t launch_interior_flags(hipStream_t, int64_t, const uint8_t *, int32_t *);
@@ -214,7 +206,7 @@ struct ErrorOut {
 template <typename T> struct Blocks {
     T *Xt = nullptr, *Xp = nullptr, *P = nullptr, *Pp = nullptr, *HX = nullptr, *BX = nullptr, *R = nullptr,
       *D = nullptr;
-    T *dinv = nullptr, *CC = nullptr, *lam = nullptr, *alpha = nullptr, *beta = nullptr;
+    T *dinv = nullptr, *CC = nullptr, *lam = nullptr;
 };
 
 struct Timer {
@@ -307,14 +299,6 @@ struct ofks_ctx {
     int lp_objective = 0;        // 0: Euclidean imitation of T^-1 g, 1: energy-norm imitation
     void *lp_u = nullptr;        // T (J G) for the energy-norm samples
     size_t lp_u_bytes = 0;
-    // inner CG, history form: directions 1 .. m-1 (direction 0 is the D
-    // block) and the m x p step lengths; library memory, taken only while
-    // free memory allows (pcg_history)
-    void *pcg_dh = nullptr;
-    size_t pcg_dh_bytes = 0;
-    void *pcg_ah = nullptr;
-    size_t pcg_ah_bytes = 0;
-
     double *scratch_dev = nullptr;   // this device's copy of `scratch` (ofks_gram_noalloc)
     double poisson_tol_now = 0.0;    // > 0: the Hartree CG tolerance of the current iteration
     // caller-owned workspace (ofks_set_workspace): the iteration's device
@@ -400,7 +384,7 @@ template <typename T> int walloc(ofks_ctx *c, T **out, size_t count) {
 // `elem` bytes and their five per-column arrays (alloc_blocks' layout)
 size_t ws_piece(size_t bytes) { return (std::max<size_t>(bytes, 1) + 255) & ~size_t(255); }
 size_t ws_block_set(size_t n, size_t p, size_t elem, int nblk) {
-    return nblk * ws_piece(n * p * elem) + 3 * ws_piece(p * elem) + ws_piece(2 * p * p * elem) + ws_piece(p * elem);
+    return nblk * ws_piece(n * p * elem) + 2 * ws_piece(p * elem) + ws_piece(2 * p * p * elem);
 }
 // the region an FP32 run keeps for FP64 blocks: the start block's setup and,
 // when a refinement may follow, the whole FP64 set that replaces the FP32 one
@@ -529,8 +513,6 @@ template <typename T> int alloc_blocks(ofks_ctx *c, bool setup_only = false) {
     CHK(walloc(c, &b.dinv, c->p));
     CHK(walloc(c, &b.CC, (size_t)c->p * 2 * c->p));
     CHK(walloc(c, &b.lam, c->p));
-    CHK(walloc(c, &b.alpha, c->p));
-    CHK(walloc(c, &b.beta, c->p));
     return OFKS_OK;
 }
 
@@ -547,8 +529,6 @@ template <typename T> void free_blocks(ofks_ctx *c) {
     dfree(c, b.dinv);
     dfree(c, b.CC);
     dfree(c, b.lam);
-    dfree(c, b.alpha);
-    dfree(c, b.beta);
 }
 
 // stage bytes in pinned memory and enqueue the copy; the staging region is
@@ -615,14 +595,20 @@ int gram(ofks_ctx *c, const T *X, const T *BX, const T *HX, std::vector<double> 
     return OFKS_OK;
 }
 
+// dot partials of one CG product in either precision and through either
+// kernel (the step pass's partials follow them: both are read together)
+size_t cg_part_doubles(ofks_ctx *c, int p) {
+    return std::max((size_t)c->shift_grid * 2 * p, c->halo_nb ? spmm_halo_part_doubles(c->halo_nb, p) : (size_t)0);
+}
+
 size_t partials_needed(ofks_ctx *c, int p) {
     const GramPlan plan = gram_plan(c->n, p, 2048);
     const size_t gy = rowgemm_grid_y(2 * p);
     size_t need = (size_t)plan.splits * p * 2 * p;
     need = std::max(need, (size_t)c->gemm_rows * gy * (1 + p));
-    need = std::max(need, (size_t)std::max(c->grid, c->shift_grid) * std::max(p, 5));
+    need = std::max(need, (size_t)c->grid * std::max(p, 5));
     need = std::max(need, (size_t)3 * 1024);
-    if (c->halo_nb) need = std::max(need, spmm_halo_part_doubles(c->halo_nb, p));   // either precision
+    need = std::max(need, cg_part_doubles(c, p) + (size_t)c->grid * p);
     return need;
 }
 
@@ -648,31 +634,38 @@ int spmm_pair(ofks_ctx *c, int p, const void *w, const T *X, T *Y1, T *Y2, int s
     const int h = halo_choice(c, p, sizeof(T));
     if (h < 0) return fail(c, OFKS_ESTATE, "spmm_mode halo: no halo plan for this matrix");
     if (h)
-        HIPCHK(launch_spmm_halo<T>(c->stream, 0, c->halo_nb, c->halo_maxlen, p, c->halo_row0, c->halo_info, c->halo_idx, c->halo_brp,
-                                   c->halo_lcol, w, X, Y1, Y2, sel, nullptr, nullptr, nullptr, 0, nullptr));
+        HIPCHK(launch_spmm_halo<T>(c->stream, DUAL, c->halo_nb, c->halo_maxlen, p, c->halo_row0, c->halo_info,
+                                   c->halo_idx, c->halo_brp, c->halo_lcol, w, X, Y1, Y2, sel, nullptr, nullptr, nullptr,
+                                   nullptr, nullptr, 0, nullptr));
     else
         HIPCHK(launch_spmm_pair<T>(c->stream, c->n, p, c->rp, c->col, w, X, Y1, Y2, sel));
     return OFKS_OK;
 }
 
-// Q = (L/2 - lam B) D on active columns and per-block <D, Q> partials in
-// c->part; *used = partial rows for the column sum.
+// The shifted product with (L/2 - lam B) on active columns in one of its forms:
+// SHIFT Q = T D; SHIFT_CG Q = J T D and partials of <D, T D> and <T D, Q> in
+// c->part; SHIFT_DOT the first partials alone.  *used = partial rows (of 2 p).
 template <typename T>
-int spmm_shift(ofks_ctx *c, int p, const void *lb, const T *lam, const uint8_t *act, const T *D, T *Q, int *used) {
+int spmm_shift(ofks_ctx *c, int mode, int p, const void *lb, const T *lam, const uint8_t *act, const T *D, T *Q,
+               int *used) {
     const int h = halo_choice(c, p, sizeof(T));
     if (h < 0) return fail(c, OFKS_ESTATE, "spmm_mode halo: no halo plan for this matrix");
-    if (h) {
-        CHK(ensure_part(c, spmm_halo_part_doubles(c->halo_nb, p)));
-        Scope sc(c, "spmm_shift");
-        HIPCHK(launch_spmm_halo<T>(c->stream, 1, c->halo_nb, c->halo_maxlen, p, c->halo_row0, c->halo_info, c->halo_idx, c->halo_brp,
-                                   c->halo_lcol, lb, D, Q, nullptr, 0, lam, act, c->part, c->part_cap, used));
-        return OFKS_OK;
-    }
-    CHK(ensure_part(c, (size_t)c->shift_grid * p));
     Scope sc(c, "spmm_shift");
-    HIPCHK(launch_spmm_shift<T>(c->stream, c->shift_grid, c->n, p, c->rp, c->col, lb, lam, act, D, Q, c->part,
-                                used));
+    if (h)
+        HIPCHK(launch_spmm_halo<T>(c->stream, mode, c->halo_nb, c->halo_maxlen, p, c->halo_row0, c->halo_info,
+                                   c->halo_idx, c->halo_brp, c->halo_lcol, lb, D, Q, nullptr, 0, lam, act, c->lhd, c->bd,
+                                   c->part, c->part_cap, used));
+    else
+        HIPCHK(launch_spmm_shift<T>(c->stream, mode, c->shift_grid, c->n, p, c->rp, c->col, lb, lam, act, c->lhd, c->bd,
+                                    D, Q, c->part, used));
     return OFKS_OK;
+}
+
+// Q = T D alone (T = L/2 - lam B on active columns, zero on the others)
+template <typename T>
+int spmm_shift(ofks_ctx *c, int p, const void *lb, const T *lam, const uint8_t *act, const T *D, T *Q) {
+    int used = 0;
+    return spmm_shift<T>(c, SHIFT, p, lb, lam, act, D, Q, &used);
 }
 
 // column sums of A .* B over rows (FP64)
@@ -842,113 +835,36 @@ double bb_eta(int rule, int k, double sy, double yy, double ss, double eta_prev,
 // ---------------------------------------------------------------------------
 // one PCAL iteration
 // ---------------------------------------------------------------------------
-// (-DOFKS_PCG_HISTORY=0 keeps the running update of x everywhere)
-#ifndef OFKS_PCG_HISTORY
-#define OFKS_PCG_HISTORY 1
-#endif
-// Inner CG, history form: each direction gets a block of its own and
-// P = sum_j alpha_j d_j is formed once at the end, which saves the read and
-// write of x in every inner iteration (m - 1 extra blocks: 18 GB for FP64
-// at n = 2e6, p = 128, m = 10).  Taken only without a caller workspace and
-// while free device memory stays above a quarter of the device (or four
-// blocks) after the allocation; otherwise pcg_run keeps x up to date as it
-// goes.  The two forms give the same bits.
-void free_pcg_history(ofks_ctx *c) {
-    if (c->pcg_dh || c->pcg_ah) (void)hipStreamSynchronize(c->stream);   // queued work may still use them
-    dfree(c, c->pcg_dh);
-    dfree(c, c->pcg_ah);
-    c->pcg_dh_bytes = c->pcg_ah_bytes = 0;
-}
-
-template <typename T> bool pcg_history(ofks_ctx *c, int m, int64_t n, int p) {
-    if (c->ws_base || m < 2 || m > PCG_DIRS_MAX) return false;
-    const size_t blk = (size_t)n * p * sizeof(T);
-    const size_t need = blk * (size_t)(m - 1), need_a = (size_t)m * p * sizeof(T);
-    if (c->pcg_dh && c->pcg_dh_bytes == need && c->pcg_ah_bytes >= need_a) return true;
-    free_pcg_history(c);
-    size_t fr = 0, tot = 0;
-    if (hipMemGetInfo(&fr, &tot) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    const size_t reserve = std::max(tot / 4, 4 * blk);
-    if (fr < need + need_a + reserve) return false;
-    void *dh = nullptr, *ah = nullptr;
-    if (hipMalloc(&dh, need) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    if (hipMalloc(&ah, need_a) != hipSuccess) {
-        (void)hipGetLastError();
-        (void)hipFree(dh);
-        return false;
-    }
-    c->allocs.push_back(dh);
-    c->allocs.push_back(ah);
-    // defined contents in the columns no iteration writes (inactive ones)
-    if (hipMemsetAsync(dh, 0, need, c->stream) != hipSuccess) {
-        (void)hipGetLastError();
-        free_pcg_history(c);
-        return false;
-    }
-    c->pcg_dh = dh;
-    c->pcg_dh_bytes = need;
-    c->pcg_ah = ah;
-    c->pcg_ah_bytes = need_a;
-    return true;
-}
-
-// P = T^-1 G columnwise by m Jacobi-PCG iterations from zero (eq. precondition-T).
-// On entry R = G and D = J G on active columns, rz = <G, J G>; X holds the
-// identity-branch columns already.  Q is scratch for the operator output.
+// P = T^-1 G columnwise by m Jacobi-CG iterations from zero (eq. precondition-T),
+// in the three-term form of k_cg_step.  On entry D = J G on active columns and
+// rz (nrz rows of p) holds partials of <G, J G>; X holds the identity-branch
+// columns already.  W is scratch for the products, E for every second direction.
 template <typename T>
-int pcg_run(ofks_ctx *c, int m, int64_t n, int p, const uint8_t *act, const T *lam, const void *lb, T *D, T *Q, T *X,
-            T *R, T *alpha, T *beta, double *rz) {
-    CHK(ensure_part(c, (size_t)c->grid * p));
-    if (OFKS_PCG_HISTORY && pcg_history<T>(c, m, n, p)) {
-        PcgDirs dirs{};
-        T *dh = (T *)c->pcg_dh;
-        for (int j = 0; j < m; ++j) dirs.d[j] = j == 0 ? (const void *)D : (const void *)(dh + (size_t)(j - 1) * n * p);
-        T *ah = (T *)c->pcg_ah;
-        for (int it = 0; it < m; ++it) {
-            T *Dj = (T *)dirs.d[it];
-            T *al = ah + (size_t)it * p;
-            int used = 0;
-            CHK(spmm_shift<T>(c, p, lb, lam, act, Dj, Q, &used));
-            HIPCHK(launch_colsum(c->stream, used, p, c->part, c->red));
-            HIPCHK(launch_pcg_scalars<T>(c->stream, p, 0, c->red, rz, al));
-            if (it + 1 < m) {
-                {
-                    Scope sc(c, "pcg_r");
-                    HIPCHK(launch_pcg_r<T>(c->stream, c->grid, n, p, al, act, c->lhd, c->bd, lam, Q, R, c->part));
-                }
-                HIPCHK(launch_colsum(c->stream, c->grid, p, c->part, c->red));
-                HIPCHK(launch_pcg_scalars<T>(c->stream, p, 1, c->red, rz, beta));
-                Scope sc(c, "pcg_dx");
-                HIPCHK(launch_pcg_dnext<T>(c->stream, n, p, beta, act, c->lhd, c->bd, lam, R, Dj,
-                                           (T *)dirs.d[it + 1]));
-            }
-        }
-        Scope sc(c, "pcg_sum");
-        HIPCHK(launch_pcg_sum<T>(c->stream, n, p, m, ah, act, dirs, X));
-        return OFKS_OK;
-    }
-    for (int it = 0; it < m; ++it) {
+int pcg_run(ofks_ctx *c, int m, int64_t n, int p, const uint8_t *act, const T *lam, const void *lb, T *D, T *W, T *X,
+            T *E, const double *rz, int nrz) {
+    const size_t off = cg_part_doubles(c, p);
+    CHK(ensure_part(c, off + (size_t)c->grid * p));
+    double *rzp = c->part + off;
+    // coefficients of the current and the previous step, in the sums' scratch
+    T *coef = (T *)c->red;
+    for (int j = 0; j < m; ++j) {
+        const bool more = j + 1 < m;   // the last iteration needs no new direction
+        T *al = coef + (size_t)(j & 1) * p, *be = coef + (size_t)(2 + (j & 1)) * p;
+        T *alm = coef + (size_t)(1 - (j & 1)) * p, *bem = coef + (size_t)(3 - (j & 1)) * p;
+        T *Dj = j & 1 ? E : D, *Dm = j & 1 ? D : E;
         int used = 0;
-        CHK(spmm_shift<T>(c, p, lb, lam, act, D, Q, &used));
-        HIPCHK(launch_colsum(c->stream, used, p, c->part, c->red));
-        HIPCHK(launch_pcg_scalars<T>(c->stream, p, 0, c->red, rz, alpha));
-        const bool more = it + 1 < m;   // the last iteration needs no new residual or direction
+        CHK(spmm_shift<T>(c, more ? SHIFT_CG : SHIFT_DOT, p, lb, lam, act, Dj, W, &used));
+        HIPCHK(launch_cg_scalars<T>(c->stream, p, used, c->part, nrz, rz, al, more ? be : nullptr));
         if (more) {
-            {
-                Scope sc(c, "pcg_r");
-                HIPCHK(launch_pcg_r<T>(c->stream, c->grid, n, p, alpha, act, c->lhd, c->bd, lam, Q, R, c->part));
-            }
-            HIPCHK(launch_colsum(c->stream, c->grid, p, c->part, c->red));
-            HIPCHK(launch_pcg_scalars<T>(c->stream, p, 1, c->red, rz, beta));
+            Scope sc(c, "pcg_dx");
+            HIPCHK(launch_cg_step<T>(c->stream, c->grid, n, p, j == 0, j & 1, j == 1, al, be, alm, bem, act, c->lhd,
+                                     c->bd, lam, W, Dj, Dm, X, rzp, &nrz));
+            rz = rzp;
+        } else {
+            // x has taken the directions before this one in pairs (0, 1), (2, 3), ...
+            Scope sc(c, "pcg_sum");
+            HIPCHK(launch_cg_x<T>(c->stream, n, p, j < 2, alm, al, act, j & 1 ? Dm : nullptr, Dj, X));
         }
-        Scope sc(c, "pcg_dx");
-        HIPCHK(launch_pcg_dx<T>(c->stream, n, p, it == 0, more, alpha, beta, act, c->lhd, c->bd, lam, R, D, X));
     }
     return OFKS_OK;
 }
@@ -1129,7 +1045,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
     CHK(ensure_part(c, (size_t)c->gemm_rows * gy * (1 + p)));
     {
         // built after the partial buffer is final: it carries that pointer
-        GradArgs ga{B.HX, B.P, B.R, B.D, c->lhd, c->bd, B.lam, c->active, c->part};
+        GradArgs ga{B.HX, B.P, B.D, c->lhd, c->bd, B.lam, c->active, c->part};
         {
             Scope sc(c, "update_a");
             HIPCHK(launch_rowgemm<T>(c->stream, epi, n, p, 2 * p, c->gemm_rows, B.BX, B.dinv, B.CC, nullptr, ga,
@@ -1176,7 +1092,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
     if (c->gl_cap && std::is_same<T, double>::value && use_paper && any_active && c->gl_cap_count < c->gl_cap_max &&
         c->k % c->gl_cap_every == 0) {
         double *slot = c->gl_cap + (size_t)c->gl_cap_count * n * p;
-        GradArgs gn{B.HX, slot, B.R, B.D, c->lhd, c->bd, B.lam, c->active, c->part};
+        GradArgs gn{B.HX, slot, B.D, c->lhd, c->bd, B.lam, c->active, c->part};
         HIPCHK(launch_rowgemm<T>(c->stream, EPI_GRAD_NORM, n, p, 2 * p, c->gemm_rows, B.BX, B.dinv, B.CC, nullptr, gn,
                                  &gx));
         c->gl_cap_lam.insert(c->gl_cap_lam.end(), shift.begin(), shift.end());
@@ -1185,7 +1101,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
     // training samples: keep G (and its column norms) before the CG overwrites it
     const bool collect = c->lp_buf && use_paper && any_active && c->lp_count < c->lp_cap;
     if (collect) {
-        GradArgs gn{B.HX, B.P, B.R, B.D, c->lhd, c->bd, B.lam, c->active, c->part};
+        GradArgs gn{B.HX, B.P, B.D, c->lhd, c->bd, B.lam, c->active, c->part};
         HIPCHK(launch_rowgemm<T>(c->stream, EPI_GRAD_NORM, n, p, 2 * p, c->gemm_rows, B.BX, B.dinv, B.CC, nullptr, gn,
                                  &gx));
         HIPCHK(launch_colsum(c->stream, (int64_t)gx * gy, 1 + p, c->part, c->red));
@@ -1204,16 +1120,14 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
                 c->lp_u = u;
                 c->lp_u_bytes = bytes;
             }
-            int used = 0;
-            CHK(spmm_shift<T>(c, p, lbT<T>(c), B.lam, c->active, B.D, (T *)c->lp_u, &used));
+            CHK(spmm_shift<T>(c, p, lbT<T>(c), B.lam, c->active, B.D, (T *)c->lp_u));
         }
     }
 
     // preconditioner: columnwise Jacobi-PCG from zero, fixed iteration count
     if (use_paper && any_active) {
         CHK(upload_bytes(c, c->rz, r2.data() + 1, p * sizeof(double)));
-        CHK(pcg_run<T>(c, c->prm.pcg_iters, n, p, c->active, B.lam, lbT<T>(c), B.D, B.HX, B.P, B.R, B.alpha, B.beta,
-                       c->rz));
+        CHK(pcg_run<T>(c, c->prm.pcg_iters, n, p, c->active, B.lam, lbT<T>(c), B.D, B.HX, B.P, B.R, c->rz, 1));
     }
     if (collect) {
         // t = T^-1 g (this step's P), every lp_stride-th row; per-column weights
@@ -1249,8 +1163,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
         const int m = std::max(1, c->prm.graph_sweeps);
         T *src = B.D;
         for (int sw = 1; sw <= m; ++sw) {
-            int used = 0;
-            CHK(spmm_shift<T>(c, p, lbT<T>(c), B.lam, c->active, src, B.HX, &used));
+            CHK(spmm_shift<T>(c, p, lbT<T>(c), B.lam, c->active, src, B.HX));
             T *dst = sw == m ? B.P : (src == B.R ? B.D : B.R);
             Scope sc(c, "graph");
             HIPCHK(launch_gl_out<T>(c->stream, n, p, B.P, src, c->gl_ft, B.HX, c->lhd, c->bd, B.lam, c->active, dst,
@@ -1317,7 +1230,6 @@ int promote_to_f64_impl(ofks_ctx *c) {
     if (c->ws_base && c->ws_carve && ws_block_set(c->n, c->p, sizeof(double), 8) > c->ws_f64_cap)
         return fail(c, OFKS_ECAPACITY, "workspace: no room kept for the FP64 blocks (sized with refine_tol = 0)");
     CHK(sync(c));
-    free_pcg_history(c);   // FP32 directions; the FP64 set comes first
     dfree(c, F.P);
     dfree(c, F.HX);
     dfree(c, F.BX);
@@ -1347,8 +1259,6 @@ int promote_to_f64_impl(ofks_ctx *c) {
     CHK(walloc(c, &D.dinv, c->p));
     CHK(walloc(c, &D.CC, (size_t)c->p * 2 * c->p));
     CHK(walloc(c, &D.lam, c->p));
-    CHK(walloc(c, &D.alpha, c->p));
-    CHK(walloc(c, &D.beta, c->p));
     if (c->ws_base && c->ws_carve) c->ws_off = std::max(ws_hi, c->ws_off);
     c->prec = OFKS_F64;
     return OFKS_OK;
@@ -1396,7 +1306,6 @@ int complete_blocks(ofks_ctx *c) {
 // Releases every piece of device state a workspace may hold (those inside
 // the workspace are only forgotten); the iterate is gone afterwards.
 void release_state(ofks_ctx *c) {
-    free_pcg_history(c);
     free_blocks<double>(c);
     free_blocks<float>(c);
     dfree(c, c->active);
@@ -1555,8 +1464,7 @@ int spmm_ex_typed(ofks_ctx *c, int p, int op, const double *lam, const T *X, T *
     for (int i = 0; i < p; ++i) ah[i] = lam[i] < 0.0 ? 1 : 0;
     int rc = upload<T>(c, lamd, lv);
     if (rc >= 0) rc = upload_bytes(c, act, ah.data(), p);
-    int used = 0;
-    if (rc >= 0) rc = spmm_shift<T>(c, p, lbT<T>(c), lamd, act, X, Y1, &used);
+    if (rc >= 0) rc = spmm_shift<T>(c, p, lbT<T>(c), lamd, act, X, Y1);
     const int rs = sync(c);
     dfree(c, lamd);
     dfree(c, act);
@@ -2217,8 +2125,6 @@ int ofks_spmm_ex(ofks_ctx *c, int32_t p, int32_t precision, int32_t op, const do
     if (op == 0 && !Y2) return fail(c, OFKS_EINVAL, "spmm_ex: the dual product needs Y2");
     if (op == 1 && (!lam || !c->has_lhalf)) return fail(c, OFKS_ESTATE, "spmm_ex: the shifted product needs L/2 and lam");
     if (precision != OFKS_F64 && precision != OFKS_F32) return fail(c, OFKS_EINVAL, "spmm_ex: bad precision");
-    if (op == 1) CHK(ensure_part(c, std::max((size_t)c->shift_grid * p,
-                                             c->halo_nb ? spmm_halo_part_doubles(c->halo_nb, p) : (size_t)0)));
     if (precision == OFKS_F64) {
         CHK(spmm_ex_typed<double>(c, p, op, lam, (const double *)X, (double *)Y1, (double *)Y2));
     } else {
@@ -2280,33 +2186,27 @@ int ofks_precondition(ofks_ctx *c, int32_t p, const double *lam, const double *G
     if (m < 1) return fail(c, OFKS_EINVAL, "precondition: pcg_iters must be >= 1");
     const int64_t n = c->n;
     const size_t np = (size_t)n * p;
-    double *R = nullptr, *D = nullptr, *Q = nullptr, *lamd = nullptr, *alpha = nullptr, *betad = nullptr,
-           *rzd = nullptr;
+    double *E = nullptr, *D = nullptr, *W = nullptr, *lamd = nullptr, *rzd = nullptr;
     uint8_t *act = nullptr;
-    CHK(dalloc(c, &R, np));
+    CHK(dalloc(c, &E, np));
     CHK(dalloc(c, &D, np));
-    CHK(dalloc(c, &Q, np));
+    CHK(dalloc(c, &W, np));
     CHK(dalloc(c, &lamd, p));
-    CHK(dalloc(c, &alpha, p));
-    CHK(dalloc(c, &betad, p));
-    CHK(dalloc(c, &rzd, p));
+    CHK(dalloc(c, &rzd, (size_t)c->grid * p));
     CHK(dalloc(c, &act, p));
     std::vector<double> lv(lam, lam + p);
     std::vector<uint8_t> ah(p);
     for (int i = 0; i < p; ++i) ah[i] = lam[i] < 0.0 ? 1 : 0;
     CHK(upload<double>(c, lamd, lv));
     CHK(upload_bytes(c, act, ah.data(), p));
-    CHK(ensure_part(c, (size_t)c->grid * p));
-    HIPCHK(launch_pcg_init<double>(c->stream, c->grid, n, p, act, c->lhd, c->bd, lamd, G, R, D, P, c->part));
-    HIPCHK(launch_colsum(c->stream, c->grid, p, c->part, rzd));
-    CHK(pcg_run<double>(c, m, n, p, act, lamd, c->lb, D, Q, P, R, alpha, betad, rzd));
+    int nrz = 0;
+    HIPCHK(launch_cg_start<double>(c->stream, c->grid, n, p, act, c->lhd, c->bd, lamd, G, D, P, rzd, &nrz));
+    CHK(pcg_run<double>(c, m, n, p, act, lamd, c->lb, D, W, P, E, rzd, nrz));
     CHK(sync(c));
-    dfree(c, R);
+    dfree(c, E);
     dfree(c, D);
-    dfree(c, Q);
+    dfree(c, W);
     dfree(c, lamd);
-    dfree(c, alpha);
-    dfree(c, betad);
     dfree(c, rzd);
     dfree(c, act);
     return OFKS_OK;
@@ -2535,8 +2435,7 @@ int gl_loss_grad_dev(ofks_ctx *c, int p, const double *G, const double *lamd, co
     float *FT;
     CHK(gl_work(c, np, &Z, &QTP, &PT, &Rb, &dRb, &FT));
     CHK(ensure_part(c, std::max({(size_t)GL_GRID * 2 * p, (size_t)GL_BWD_GRID * GL_NPAR_HOST,
-                                 (size_t)c->shift_grid * p,
-                                 c->halo_nb ? spmm_halo_part_doubles(c->halo_nb, p) : (size_t)0})));
+                                 (size_t)c->grid * p})));
     // column sums: g2 for the residual feature, w = 1 / <G, J G>
     HIPCHK(launch_gl_colsums(c->stream, GL_GRID, n, p, G, c->lhd, c->bd, lamd, neg, c->part));
     HIPCHK(launch_colsum(c->stream, GL_GRID, 2 * p, c->part, c->red));
@@ -2549,14 +2448,13 @@ int gl_loss_grad_dev(ofks_ctx *c, int p, const double *G, const double *lamd, co
     }
     CHK(upload<double>(c, g2w, hw));   // g2w[0..p) = g2, g2w[p..2p) = w
     const double *g2 = g2w, *w = g2w + p;
-    int used = 0;
     // forward: Z, ft; Q = T Z; R = G - Q, P = Z + ft J R
     HIPCHK(launch_gl_heads<double>(c->stream, n, p, G, c->lhd, c->bd, c->hd, lamd, neg, g2, c->gl_W, c->gl_norm, Z,
                                    FT));
-    CHK(spmm_shift<double>(c, p, c->lb, lamd, neg, Z, QTP, &used));
+    CHK(spmm_shift<double>(c, p, c->lb, lamd, neg, Z, QTP));
     HIPCHK(launch_gl_out<double>(c->stream, n, p, G, Z, FT, QTP, c->lhd, c->bd, lamd, neg, PT, Rb));
     // T P, then dP = w (T P - G) (in place) and dR = ft J dP; loss partials
-    CHK(spmm_shift<double>(c, p, c->lb, lamd, neg, PT, QTP, &used));
+    CHK(spmm_shift<double>(c, p, c->lb, lamd, neg, PT, QTP));
     HIPCHK(launch_gl_bwd1(c->stream, GL_GRID, n, p, G, PT, QTP, FT, c->lhd, c->bd, lamd, neg, w, dRb, c->part));
     HIPCHK(launch_colsum(c->stream, GL_GRID, p, c->part, c->red));
     std::vector<double> lc;
@@ -2565,7 +2463,7 @@ int gl_loss_grad_dev(ofks_ctx *c, int p, const double *G, const double *lamd, co
     for (int l = 0; l < p; ++l) L += hw[p + l] * lc[l];
     *loss = L;
     // T dR (into PT), then the parameter gradient
-    CHK(spmm_shift<double>(c, p, c->lb, lamd, neg, dRb, PT, &used));
+    CHK(spmm_shift<double>(c, p, c->lb, lamd, neg, dRb, PT));
     HIPCHK(launch_gl_bwd2(c->stream, GL_BWD_GRID, n, p, G, QTP, Rb, Z, dRb, PT, c->lhd, c->bd, c->hd, lamd, neg, g2,
                           c->gl_W, c->gl_norm, c->part));
     HIPCHK(launch_colsum(c->stream, GL_BWD_GRID, GL_NPAR_HOST, c->part, c->red));
@@ -2604,13 +2502,10 @@ int ofks_gl_apply(ofks_ctx *c, int32_t p, const double *lam, const double *G, do
     CHK(dalloc(c, &Z, np));
     CHK(dalloc(c, &Q, np));
     CHK(dalloc(c, &FT, np));
-    CHK(ensure_part(c, std::max({(size_t)c->grid * p, (size_t)c->shift_grid * p,
-                                 c->halo_nb ? spmm_halo_part_doubles(c->halo_nb, p) : (size_t)0})));
     CHK(col_sq(c, p, G, g2));
     HIPCHK(launch_gl_heads<double>(c->stream, c->n, p, G, c->lhd, c->bd, c->hd, lamd, neg, g2, c->gl_W, c->gl_norm,
                                    Z, FT));
-    int used = 0;
-    CHK(spmm_shift<double>(c, p, c->lb, lamd, neg, Z, Q, &used));
+    CHK(spmm_shift<double>(c, p, c->lb, lamd, neg, Z, Q));
     HIPCHK(launch_gl_out<double>(c->stream, c->n, p, G, Z, FT, Q, c->lhd, c->bd, lamd, neg, P, (double *)nullptr));
     CHK(sync(c));
     dfree(c, lamd);
