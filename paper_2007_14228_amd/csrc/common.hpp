@@ -35,6 +35,23 @@ __device__ __forceinline__ void store_vec(T *__restrict__ p, const T (&in)[V]) {
     *reinterpret_cast<VT *>(p) = v;
 }
 
+// The same past the caches' retention (streamed data: read or written once)
+template <typename T, int V>
+__device__ __forceinline__ void load_nt(const T *__restrict__ p, T (&out)[V]) {
+    typedef T vec __attribute__((ext_vector_type(V)));
+    const vec v = __builtin_nontemporal_load((const vec *)p);
+#pragma unroll
+    for (int i = 0; i < V; ++i) out[i] = v[i];
+}
+template <typename T, int V>
+__device__ __forceinline__ void store_nt(T *__restrict__ p, const T (&in)[V]) {
+    typedef T vec __attribute__((ext_vector_type(V)));
+    vec v;
+#pragma unroll
+    for (int i = 0; i < V; ++i) v[i] = in[i];
+    __builtin_nontemporal_store(v, (vec *)p);
+}
+
 // Layout of a block of p columns over lanes: V columns per lane, LPR lanes
 // per row (power of two <= 64), CH column chunks per lane when p > LPR*V.
 struct ColMap {

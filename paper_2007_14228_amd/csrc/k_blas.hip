@@ -849,8 +849,12 @@ __global__ __launch_bounds__(256) void k_cg_scalars(int p, int ndq, const double
 // over rows; part[blockIdx.x][c] = <z', z' / J>.  FIRST: j = 0 (no d_{-1}; Dm is
 // only written).  XUP: x += alpha_{j-1} d_{j-1} + alpha_j d_j (xfirst: from
 // zero), in the order of the running sum.  Columns that are not active keep x
-// and get nothing of d.  Memory-bound: n = 1e6, p = 128, FP64 4 passes (6 with
-// x) at the rate of a large copy.
+// and get nothing of d.  Memory-bound (n = 1e6, p = 128, FP64: 4 or 6 passes in
+// 880 us on average, 5.7 TB/s).  W, D and Dm go past the caches (nontemporal):
+// nothing of them is read again before the next gigabyte; so kept, the pass
+// took 945 us (FP32, n = 5.1e5: 223 against 193), k_cg_x 696 against 618,
+// k_bbdot 590 against 525, k_update_b 690 against 646 (its Xt, rewritten in
+// place, is faster through the caches).
 template <typename T, int V, bool FIRST, bool XUP>
 __global__ __launch_bounds__(256) void k_cg_step(int64_t n, int p, int lpr_log2, int xfirst,
                                                 const T *__restrict__ alpha, const T *__restrict__ beta,
@@ -886,9 +890,9 @@ __global__ __launch_bounds__(256) void k_cg_step(int64_t n, int p, int lpr_log2,
         for (int64_t row = (int64_t)blockIdx.x * groups + g; row < n; row += (int64_t)gridDim.x * groups) {
             const int64_t o = row * p + c0;
             T w[V], d[V], dm[V], x[V];
-            load_vec<T, V>(W + o, w);
-            load_vec<T, V>(D + o, d);
-            if (!FIRST) load_vec<T, V>(Dm + o, dm);
+            load_nt<T, V>(W + o, w);
+            load_nt<T, V>(D + o, d);
+            if (!FIRST) load_nt<T, V>(Dm + o, dm);
             if (XUP) {
                 if (xfirst && all) {
 #pragma unroll
@@ -910,8 +914,8 @@ __global__ __launch_bounds__(256) void k_cg_step(int64_t n, int p, int lpr_log2,
                 }
                 dm[v] = on[v] ? fma(be[v], d[v], z) : (FIRST ? T(0) : dm[v]);
             }
-            store_vec<T, V>(Dm + o, dm);
-            if (XUP) store_vec<T, V>(X + o, x);
+            store_nt<T, V>(Dm + o, dm);
+            if (XUP) store_nt<T, V>(X + o, x);
         }
 #pragma unroll
     for (int v = 0; v < V; ++v) red[threadIdx.x * V + v] = dot[v];
@@ -946,13 +950,13 @@ __global__ __launch_bounds__(256) void k_cg_x(int64_t n, int p, int lpr_log2, in
         if (!any) continue;
         const int64_t o = row * p + c0;
         T d[V], dm[V], x[V], a[V], am[V];
-        load_vec<T, V>(D + o, d);
-        if (Dm) load_vec<T, V>(Dm + o, dm);
+        load_nt<T, V>(D + o, d);
+        if (Dm) load_nt<T, V>(Dm + o, dm);
         if (xfirst && all) {
 #pragma unroll
             for (int v = 0; v < V; ++v) x[v] = T(0);
         } else {
-            load_vec<T, V>(X + o, x);
+            load_nt<T, V>(X + o, x);
         }
         load_vec<T, V>(alpha + c0, a);
         if (Dm) load_vec<T, V>(alpham + c0, am);
@@ -963,7 +967,7 @@ __global__ __launch_bounds__(256) void k_cg_x(int64_t n, int p, int lpr_log2, in
             else nx = xfirst ? a[v] * d[v] : fma(a[v], d[v], x[v]);
             x[v] = on[v] ? nx : x[v];
         }
-        store_vec<T, V>(X + o, x);
+        store_nt<T, V>(X + o, x);
     }
 }
 
@@ -1037,12 +1041,12 @@ __global__ __launch_bounds__(256) void k_bbdot(int64_t n, int p, int lpr_log2,
             const int c0 = (lane + ch * lpr) * V;
             if (c0 >= p) continue;
             T xt[V], pv[V];
-            load_vec<T, V>(Xt + row * p + c0, xt);
-            load_vec<T, V>(P + row * p + c0, pv);
+            load_nt<T, V>(Xt + row * p + c0, xt);
+            load_nt<T, V>(P + row * p + c0, pv);
             T xp[V], pp[V];
             if (hist) {
-                load_vec<T, V>(Xp + row * p + c0, xp);
-                load_vec<T, V>(Pp + row * p + c0, pp);
+                load_nt<T, V>(Xp + row * p + c0, xp);
+                load_nt<T, V>(Pp + row * p + c0, pp);
             }
 #pragma unroll
             for (int v = 0; v < V; ++v) {
@@ -1085,14 +1089,14 @@ __global__ __launch_bounds__(256) void k_update_b(int64_t n, int p, int lpr_log2
     for (int c0 = lane * V; c0 < p; c0 += lpr * V) {
         T xt[V], pv[V], x[V], xn[V];
         load_vec<T, V>(Xt + row * p + c0, xt);
-        load_vec<T, V>(P + row * p + c0, pv);
+        load_nt<T, V>(P + row * p + c0, pv);
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             x[v] = xt[v] * dinv[c0 + v];
             xn[v] = x[v] - pv[v] / eta;
         }
-        if (Xp) store_vec<T, V>(Xp + row * p + c0, x);
-        store_vec<T, V>(Xt + row * p + c0, xn);
+        if (Xp) store_nt<T, V>(Xp + row * p + c0, x);
+        store_nt<T, V>(Xt + row * p + c0, xn);
     }
 }
 
@@ -1387,9 +1391,12 @@ hipError_t launch_bbdot(hipStream_t s, int grid, int64_t n, int p, const T *Xt, 
 struct RowGrid {
     int v, l2, gx, gy;
 };
-template <typename T> static RowGrid row_grid(int64_t n, int p, int grid) {
+// (caller: a block that the caller of the library owns; unless its rows are
+// aligned for wide accesses, every access takes single values)
+template <typename T> static RowGrid row_grid(int64_t n, int p, int grid, const void *caller, const void *caller2) {
     RowGrid g;
     g.v = vwidth<T>(p);
+    if ((reinterpret_cast<uintptr_t>(caller) | reinterpret_cast<uintptr_t>(caller2)) % (g.v * sizeof(T))) g.v = 1;
     g.l2 = lpr_l2(p, g.v);
     g.gy = (p + (g.v << g.l2) - 1) / (g.v << g.l2);
     const int64_t rounds = (n + (256 >> g.l2) - 1) / (256 >> g.l2);
@@ -1402,7 +1409,7 @@ template <typename T>
 hipError_t launch_cg_step(hipStream_t s, int grid, int64_t n, int p, int first, int xup, int xfirst, const T *alpha,
                           const T *beta, const T *alpham, const T *betam, const uint8_t *active, const double *lhd,
                           const double *bd, const T *lam, const T *W, const T *D, T *Dm, T *X, double *part, int *rows) {
-    const RowGrid g = row_grid<T>(n, p, grid);
+    const RowGrid g = row_grid<T>(n, p, grid, X, nullptr);
     *rows = g.gx;
 #define OFKS_STEP2(V_, F_, X_)                                                                                       \
     hipLaunchKernelGGL((k_cg_step<T, V_, F_, X_>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, xfirst, alpha, beta, \
@@ -1424,7 +1431,7 @@ hipError_t launch_cg_step(hipStream_t s, int grid, int64_t n, int p, int first, 
 template <typename T>
 hipError_t launch_cg_x(hipStream_t s, int64_t n, int p, int xfirst, const T *alpham, const T *alpha,
                        const uint8_t *active, const T *Dm, const T *D, T *X) {
-    const int v = vwidth<T>(p);
+    const int v = row_grid<T>(n, p, 1, X, nullptr).v;
     const int l2 = lpr_l2(p, v);
     const unsigned grid = (unsigned)(((n << l2) + 255) / 256);
     if (v == 1) hipLaunchKernelGGL((k_cg_x<T, 1>), dim3(grid), dim3(256), 0, s, n, p, l2, xfirst, alpham, alpha, active, Dm, D, X);
@@ -1436,7 +1443,7 @@ hipError_t launch_cg_x(hipStream_t s, int64_t n, int p, int xfirst, const T *alp
 template <typename T>
 hipError_t launch_cg_start(hipStream_t s, int grid, int64_t n, int p, const uint8_t *active, const double *lhd,
                            const double *bd, const T *lam, const T *G, T *D, T *P, double *part, int *rows) {
-    const RowGrid g = row_grid<T>(n, p, grid);
+    const RowGrid g = row_grid<T>(n, p, grid, G, P);
     *rows = g.gx;
     if (g.v == 1) hipLaunchKernelGGL((k_cg_start<T, 1>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, active, lhd, bd, lam, G, D, P, part);
     else if (g.v == 2) hipLaunchKernelGGL((k_cg_start<T, 2>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, active, lhd, bd, lam, G, D, P, part);
