@@ -1,7 +1,7 @@
 // Block (n x p) kernels of the PCAL iteration.
 //
-//  k_gram        X^T [BX | HX] as split-K partial tiles (Algorithm PCAL,
-//                eq. lambda2 needs S = X^T B X and Lambda0 = X^T H X).
+//  k_gram_mfma   X^T [BX | HX] as split-K partial tiles (Algorithm PCAL,
+//  k_gram_wave   eq. lambda2 needs S = X^T B X and Lambda0 = X^T H X).
 //  k_colsum      fixed-order reduction of per-block partials.
 //  k_rowgemm     [G | R] = (BX D^-1) [C | C'] + (HX D^-1) with the update
 //                epilogues (gradient of L_beta, residual norm for kkt, the
@@ -23,73 +23,6 @@
 
 namespace ofks {
 
-// ---------------------------------------------------------------------------
-// Gram: part[split][a][c] = sum_{rows of split} X[r][a] * Y[r][c],
-// Y = [BX | HX] (c < p -> BX[:, c], else HX[:, c - p]).
-// Tile (16*MT) x (16*NT), 256 threads as 16 x 16, thread (ty, tx) owns rows
-// a = a0 + ty + 16 i and columns c = c0 + tx + 16 j.
-// ---------------------------------------------------------------------------
-template <typename T, typename ACC, int MT, int NT>
-__global__ __launch_bounds__(256) void k_gram(int64_t n, int p, int64_t rows_per_split,
-                                             const T *__restrict__ X, const T *__restrict__ BX,
-                                             const T *__restrict__ HX, double *__restrict__ part) {
-    constexpr int TM = 16 * MT, TN = 16 * NT, KC = 16;
-    __shared__ T As[KC][TM];
-    __shared__ T Bs[KC][TN];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int a0 = blockIdx.x * TM, c0 = blockIdx.y * TN;
-    const int64_t r_begin = (int64_t)blockIdx.z * rows_per_split;
-    const int64_t r_end = min(n, r_begin + rows_per_split);
-    const int p2 = 2 * p;
-    ACC acc[MT][NT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = ACC(0);
-
-    for (int64_t r0 = r_begin; r0 < r_end; r0 += KC) {
-        for (int idx = threadIdx.x; idx < KC * TM; idx += 256) {
-            const int kr = idx / TM, cc = idx % TM;
-            const int64_t r = r0 + kr;
-            const int a = a0 + cc;
-            As[kr][cc] = (r < r_end && a < p) ? X[r * p + a] : T(0);
-        }
-        for (int idx = threadIdx.x; idx < KC * TN; idx += 256) {
-            const int kr = idx / TN, cc = idx % TN;
-            const int64_t r = r0 + kr;
-            const int c = c0 + cc;
-            T v = T(0);
-            if (r < r_end && c < p2) v = (c < p) ? BX[r * p + c] : HX[r * p + (c - p)];
-            Bs[kr][cc] = v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < KC; ++k) {
-            ACC av[MT], bv[NT];
-#pragma unroll
-            for (int i = 0; i < MT; ++i) av[i] = (ACC)As[k][ty + 16 * i];
-#pragma unroll
-            for (int j = 0; j < NT; ++j) bv[j] = (ACC)Bs[k][tx + 16 * j];
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-#pragma unroll
-                for (int j = 0; j < NT; ++j) acc[i][j] = fma(av[i], bv[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-    double *out = part + (int64_t)blockIdx.z * p * p2;
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-        const int a = a0 + ty + 16 * i;
-        if (a >= p) continue;
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            const int c = c0 + tx + 16 * j;
-            if (c < p2) out[(int64_t)a * p2 + c] = (double)acc[i][j];
-        }
-    }
-}
-
 // out[m] = sum_{b < nb} part[b * m_total + m] for m in [0, m_total); one block
 // per output, fixed strided partition then a fixed tree.
 __global__ __launch_bounds__(256) void k_colsum(int64_t nb, int64_t m_total,
@@ -106,6 +39,25 @@ __global__ __launch_bounds__(256) void k_colsum(int64_t nb, int64_t m_total,
         __syncthreads();
     }
     if (threadIdx.x == 0) out[m] = red[0];
+}
+
+// The same sums for many columns (the Gram's p x 2p): 64 columns a block, four
+// threads a column, so that every access takes whole cache lines (a block per
+// column reads 8 bytes of each).  n = 1e6, p = 128: 121 -> 11 us together with
+// the fewer row splits of the FP64 Gram.
+__global__ __launch_bounds__(256) void k_colsum_wide(int64_t nb, int64_t m_total, const double *__restrict__ part,
+                                                    double *__restrict__ out) {
+    __shared__ double red[4][64];
+    const int cl = threadIdx.x & 63, k = threadIdx.x >> 6;
+    const int64_t m = (int64_t)blockIdx.x * 64 + cl;
+    double s = 0.0;
+    if (m < m_total) {
+#pragma unroll 8
+        for (int64_t b = k; b < nb; b += 4) s += part[b * m_total + m];
+    }
+    red[k][cl] = s;
+    __syncthreads();
+    if (k == 0 && m < m_total) out[m] = (red[0][cl] + red[1][cl]) + (red[2][cl] + red[3][cl]);
 }
 
 // ---------------------------------------------------------------------------
@@ -270,14 +222,15 @@ template <typename T> __device__ __forceinline__ int mfma_row(int lk, int i) {
     return sizeof(T) == 8 ? lk + 4 * i : 4 * lk + i;
 }
 
-// Gram on the matrix cores: the same split-K partial tiles as k_gram, tile
+// Gram on the matrix cores: part[split][a][c] = sum over the split's rows of
+// X[r][a] Y[r][c], Y = [BX | HX] (c < p: BX[:, c], else HX[:, c - p]).  Tile
 // TM x TN = 128 x 128, the 4 waves as 2 x 2, each owning 64 x 64 (4 x 4
 // MFMA tiles).  Rows of X and Y are staged through a double-buffered LDS in
 // chunks of 16, the next chunk's loads in flight while the current one is
 // multiplied (one barrier per chunk).  Here the A operand is X^T (a = column
 // of X, k = row) and B is Y.
 template <typename T>
-__global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int64_t rows_per_split,
+__global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int gx, int gy, int64_t splits,
                                                   const T *__restrict__ X, const T *__restrict__ BX,
                                                   const T *__restrict__ HX, double *__restrict__ part) {
     constexpr int TM = 128, TN = 128, KC = 16, PAD = 4;
@@ -288,9 +241,17 @@ __global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int64_t row
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int li = lane & 15, lk = lane >> 4;
     const int wy = w >> 1, wx = w & 1;
-    const int a0 = blockIdx.x * TM, c0 = blockIdx.y * TN;
-    const int64_t r_begin = (int64_t)blockIdx.z * rows_per_split;
-    const int64_t r_end = min(n, r_begin + rows_per_split);
+    // the output tiles of one row split run side by side on one XCD (blocks go
+    // to the XCDs in turn), so that its L2 serves the rows to all of them
+    const int tiles = gx * gy;
+    const int64_t per = (splits + 7) / 8, q = blockIdx.x >> 3;
+    const int64_t split = (blockIdx.x & 7) * per + q / tiles;
+    if (q / tiles >= per || split >= splits) return;
+    const int tile = (int)(q % tiles);
+    const int a0 = tile % gx * TM, c0 = tile / gx * TN;
+    // a split takes every splits-th chunk of KC rows, so that all blocks read one
+    // window of rows (DRAM pages and channels evenly, whatever n is)
+    const int64_t r_begin = split * KC, stride = splits * KC;
     const int p2 = 2 * p;
     acc_t acc[4][4];
 #pragma unroll
@@ -305,7 +266,7 @@ __global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int64_t row
             const int kk = e / TM, cc = e % TM;
             const int64_t r = r0 + kk;
             const int a = a0 + cc;
-            xr[j] = (r < r_end && a < p) ? X[r * p + a] : T(0);
+            xr[j] = (r < n && a < p) ? X[r * p + a] : T(0);
         }
 #pragma unroll
         for (int j = 0; j < EY; ++j) {
@@ -314,7 +275,7 @@ __global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int64_t row
             const int64_t r = r0 + kk;
             const int c = c0 + cc;
             T v = T(0);
-            if (r < r_end && c < p2) v = c < p ? BX[r * p + c] : HX[r * p + (c - p)];
+            if (r < n && c < p2) v = c < p ? BX[r * p + c] : HX[r * p + (c - p)];
             yr[j] = v;
         }
     };
@@ -331,14 +292,14 @@ __global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int64_t row
         }
     };
     int buf = 0;
-    if (r_begin < r_end) {
+    if (r_begin < n) {
         gload(r_begin);
         lstore(0);
     }
     __syncthreads();
-    for (int64_t r0 = r_begin; r0 < r_end; r0 += KC) {
-        const bool more = r0 + KC < r_end;
-        if (more) gload(r0 + KC);
+    for (int64_t r0 = r_begin; r0 < n; r0 += stride) {
+        const bool more = r0 + stride < n;
+        if (more) gload(r0 + stride);
 #pragma unroll
         for (int s4 = 0; s4 < KC / 4; ++s4) {
             T a[4], b[4];
@@ -355,7 +316,7 @@ __global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int64_t row
         __syncthreads();
         buf ^= 1;
     }
-    double *out = part + (int64_t)blockIdx.z * p * p2;
+    double *out = part + split * p * p2;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -367,6 +328,92 @@ __global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int64_t row
                 const int a = a0 + 64 * wy + 16 * i + mfma_row<T>(lk, q);
                 if (a < p) out[(int64_t)a * p2 + c] = (double)acc[i][j][q];
             }
+        }
+}
+
+// Gram for p <= 64: every wave takes its share of the rows (every nth group of
+// 4 U, so that all waves read one window) and forms the whole product (or, BOTH false, X^T BX or X^T HX by blockIdx.y), so each element goes from memory
+// straight to the registers of one MFMA operand and nothing is staged in LDS:
+// at these widths the three blocks' bytes bound it, not the arithmetic.  NA:
+// 16-column tiles of X.  U steps of four rows are loaded while the U before
+// them are multiplied.  Columns past p read column 0 (their products are not
+// stored); rows past the range's end count as zeros.  The block's eight waves
+// are summed in FP64, in order.
+// n = 2.0e5, p = 48, FP64: 141 us (VALU tiles staged in LDS) -> 44 us, 5.1 TB/s;
+// p = 16: 15 us.
+constexpr int GW_WAVES = 8;
+template <typename T, int NA, bool BOTH, int U>
+__global__ __launch_bounds__(64 * GW_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void k_gram_wave(
+    int64_t n, int p, const T *__restrict__ X, const T *__restrict__ BX,
+    const T *__restrict__ HX, double *__restrict__ part) {
+    constexpr int NB = BOTH ? 2 * NA : NA;
+    using acc_t = typename mfma4<T>::type;
+    __shared__ double red[GW_WAVES][256];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int li = lane & 15, lk = lane >> 4;
+    const int64_t stride = (int64_t)gridDim.x * GW_WAVES * 4 * U;
+    const int64_t r_begin = ((int64_t)blockIdx.x * GW_WAVES + w) * 4 * U;
+    const T *Y[2] = {BOTH || blockIdx.y == 0 ? BX : HX, HX};
+    int ca[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) ca[i] = 16 * i + li < p ? 16 * i + li : 0;
+    acc_t acc[NA][NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = acc_t{T(0), T(0), T(0), T(0)};
+    T a[2][U][NA], b[2][U][NB];
+    auto load = [&](int f, int64_t r0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t r = r0 + 4 * u + lk;
+            const bool in = r < n;
+            const int64_t o = (in ? r : n - 1) * p;
+#pragma unroll
+            for (int i = 0; i < NA; ++i) {
+                const T v = X[o + ca[i]];
+                a[f][u][i] = in ? v : T(0);
+            }
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const T v = Y[j / NA][o + ca[j % NA]];
+                b[f][u][j] = in ? v : T(0);
+            }
+        }
+    };
+    auto mul = [&](int f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[i][j] = mfma16x16x4(a[f][u][i], b[f][u][j], acc[i][j]);
+    };
+    if (r_begin < n) {
+        load(0, r_begin);
+        for (int64_t r0 = r_begin; r0 < n; r0 += 2 * stride) {   // (rows past the end: the last row's address, zeros)
+            load(1, r0 + stride);
+            mul(0);
+            load(0, r0 + 2 * stride);
+            mul(1);
+        }
+    }
+    double *out = part + (int64_t)blockIdx.x * p * 2 * p;
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) red[w][16 * mfma_row<T>(lk, q) + li] = (double)acc[i][j][q];
+            __syncthreads();
+            if (threadIdx.x < 256) {
+                const int ar = 16 * i + (threadIdx.x >> 4), c = 16 * (j % NA) + (threadIdx.x & 15);
+                double s = 0.0;
+                for (int k = 0; k < GW_WAVES; ++k) s += red[k][threadIdx.x];
+                const int half = BOTH ? j / NA : (int)blockIdx.y;
+                if (ar < p && c < p) out[(int64_t)ar * 2 * p + half * p + c] = s;
+            }
+            __syncthreads();
         }
 }
 
@@ -1179,31 +1226,27 @@ static inline int lpr_l2(int p, int v) {
     return l > 6 ? 6 : l;
 }
 
-// Split-K plan of k_gram: output tiles (gx x gy) and row splits, so that the
+// Split-K plan of the Gram: output tiles (gx x gy) and row splits, so that the
 // caller can size the partial buffer (splits * p * 2p doubles) before launch.
+// p <= 64: k_gram_wave, one split per block of GW_WAVES waves (one block a CU
+// at most, fewer for short blocks).  Above: k_gram_mfma, target_blocks over
+// tiles and splits.
 struct GramPlan {
-    int mt, nt, gx, gy;
-    int64_t splits, rows_per_split;
+    int gx, gy;
+    int64_t splits;
 };
 
 GramPlan gram_plan(int64_t n, int p, int target_blocks) {
     GramPlan g{};
-    if (p <= 16) { g.mt = 1; g.nt = 2; }
-    else if (p <= 32) { g.mt = 2; g.nt = 4; }
-    else if (p <= 64) { g.mt = 4; g.nt = 4; }
-    else { g.mt = 8; g.nt = 8; }
-    const int tm = 16 * g.mt, tn = 16 * g.nt;
-    g.gx = (p + tm - 1) / tm;
-    g.gy = (2 * p + tn - 1) / tn;
-    int64_t splits = target_blocks / (g.gx * g.gy);
-    if (splits < 1) splits = 1;
-    int64_t rps = (n + splits - 1) / splits;
-    rps = ((rps + 15) / 16) * 16;
-    if (rps < 16) rps = 16;
-    splits = (n + rps - 1) / rps;
-    if (splits < 1) splits = 1;
-    g.splits = splits;
-    g.rows_per_split = rps;
+    if (p <= 64) {
+        g.gx = 1;
+        g.gy = p > 48 ? 2 : 1;   // four 16-column tiles: the two products in blocks of their own (registers)
+        g.splits = std::max<int64_t>(1, std::min<int64_t>(256, n / (16 * GW_WAVES)));
+        return g;
+    }
+    g.gx = (p + 127) / 128;
+    g.gy = (2 * p + 127) / 128;
+    g.splits = std::max<int64_t>(1, std::min<int64_t>(target_blocks / (g.gx * g.gy), (n + 15) / 16));
     return g;
 }
 
@@ -1211,20 +1254,28 @@ template <typename T>
 hipError_t launch_gram(hipStream_t s, int64_t n, int p, const GramPlan &g, const T *X, const T *BX,
                        const T *HX, double *part, size_t part_capacity) {
     if ((size_t)g.splits * (size_t)p * 2 * p > part_capacity) return hipErrorInvalidValue;
-    if (g.splits > 65535) return hipErrorInvalidValue;
-    dim3 grid(g.gx, g.gy, (unsigned)g.splits);
-    using ACC = T;
-    const int64_t rps = g.rows_per_split;
-    if (g.mt == 1) hipLaunchKernelGGL((k_gram<T, ACC, 1, 2>), grid, dim3(256), 0, s, n, p, rps, X, BX, HX, part);
-    else if (g.mt == 2) hipLaunchKernelGGL((k_gram<T, ACC, 2, 4>), grid, dim3(256), 0, s, n, p, rps, X, BX, HX, part);
-    else if (g.mt == 4) hipLaunchKernelGGL((k_gram<T, ACC, 4, 4>), grid, dim3(256), 0, s, n, p, rps, X, BX, HX, part);
-    else hipLaunchKernelGGL((k_gram_mfma<T>), grid, dim3(256), 0, s, n, p, rps, X, BX, HX, part);
+    if (g.splits * g.gx * g.gy > 0x7fffff) return hipErrorInvalidValue;
+    if (p <= 64) {
+#define OFKS_GW(NA_, BOTH_, U_)                                                                                     \
+    hipLaunchKernelGGL((k_gram_wave<T, NA_, BOTH_, U_>), dim3((unsigned)g.splits, (unsigned)g.gy), dim3(64 * GW_WAVES), 0, \
+                       s, n, p, X, BX, HX, part)
+        if (p <= 16) OFKS_GW(1, true, 4);
+        else if (p <= 32) OFKS_GW(2, true, 2);
+        else if (p <= 48) OFKS_GW(3, true, 1);
+        else OFKS_GW(4, false, 2);
+#undef OFKS_GW
+        return hipGetLastError();
+    }
+    const unsigned grid = (unsigned)((g.splits + 7) / 8 * 8 * g.gx * g.gy);
+    hipLaunchKernelGGL((k_gram_mfma<T>), dim3(grid), dim3(256), 0, s, n, p, g.gx, g.gy, g.splits, X, BX, HX, part);
     return hipGetLastError();
 }
 
 hipError_t launch_colsum(hipStream_t s, int64_t nb, int64_t m, const double *part, double *out) {
     if (m <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_colsum, dim3((unsigned)m), dim3(256), 0, s, nb, m, part, out);
+    // from 4096 columns on, 64 a block still leave a block for every fourth CU
+    if (m >= 4096) hipLaunchKernelGGL(k_colsum_wide, dim3((unsigned)((m + 63) / 64)), dim3(256), 0, s, nb, m, part, out);
+    else hipLaunchKernelGGL(k_colsum, dim3((unsigned)m), dim3(256), 0, s, nb, m, part, out);
     return hipGetLastError();
 }
 

@@ -90,10 +90,14 @@ enum { EPI_PLAIN = 0, EPI_GRAD = 1, EPI_GRAD_PCG = 2, EPI_GRAD_NORM = 3 };
 constexpr int LP_NPAR = 193;
 constexpr int LP_SAMPLE = 8;
 struct GramPlan {
-    int mt, nt, gx, gy;
-    int64_t splits, rows_per_split;
+    int gx, gy;
+    int64_t splits;
 };
 GramPlan gram_plan(int64_t n, int p, int target_blocks);
+// Blocks of the Gram (p > 64): FP64 one round of the two that fit on each of 256
+// CUs, which leaves a quarter of the partials of 2048 blocks (n = 1e6, p = 128:
+// 67 MB); FP32 partials are FP32 sums, so their rows per split stay few.
+constexpr int GRAM_BLOCKS_F64 = 512, GRAM_BLOCKS_F32 = 2048;
 template <typename T>
 hipError_t launch_gram(hipStream_t, int64_t, int, const GramPlan &, const T *, const T *, const T *, double *, size_t);
 hipError_t launch_colsum(hipStream_t, int64_t, int64_t, const double *, double *);
@@ -575,7 +579,7 @@ int gram(ofks_ctx *c, const T *X, const T *BX, const T *HX, std::vector<double> 
     const int p = c->p;
     const size_t pp2 = (size_t)p * 2 * p;
     // size the split-K partials from the launch plan before launching
-    const GramPlan plan = gram_plan(c->n, p, 2048);
+    const GramPlan plan = gram_plan(c->n, p, sizeof(T) == 8 ? GRAM_BLOCKS_F64 : GRAM_BLOCKS_F32);
     CHK(ensure_part(c, (size_t)plan.splits * pp2));
     const int64_t ns = plan.splits;
     {
@@ -602,7 +606,7 @@ size_t cg_part_doubles(ofks_ctx *c, int p) {
 }
 
 size_t partials_needed(ofks_ctx *c, int p) {
-    const GramPlan plan = gram_plan(c->n, p, 2048);
+    const GramPlan plan = gram_plan(c->n, p, GRAM_BLOCKS_F32);   // the larger of the two
     const size_t gy = rowgemm_grid_y(2 * p);
     size_t need = (size_t)plan.splits * p * 2 * p;
     need = std::max(need, (size_t)c->gemm_rows * gy * (1 + p));
@@ -2162,7 +2166,7 @@ int ofks_gram_noalloc(ofks_ctx *c, int32_t p, const double *X, const double *HX,
     // tiles would not fit beside their column sum
     const size_t pp2 = (size_t)p * 2 * p;
     const int64_t max_splits = (int64_t)(NOALLOC_SCRATCH_DOUBLES / pp2) - 1;
-    GramPlan plan = gram_plan(c->n, p, 2048);
+    GramPlan plan = gram_plan(c->n, p, GRAM_BLOCKS_F64);
     if (plan.splits > max_splits) plan = gram_plan(c->n, p, (int)(max_splits * plan.gx * plan.gy));
     if (plan.splits < 1 || plan.splits > max_splits)
         return fail(c, OFKS_EINTERNAL, "gram_noalloc: no split plan fits the scratch");
