@@ -303,6 +303,16 @@ struct ofks_ctx {
     int lp_objective = 0;        // 0: Euclidean imitation of T^-1 g, 1: energy-norm imitation
     void *lp_u = nullptr;        // T (J G) for the energy-norm samples
     size_t lp_u_bytes = 0;
+    // scratch of the single calls, kept between them: per-column arrays, and
+    // blocks while they stay below CALL_KEEP bytes
+    double *call_vec = nullptr;
+    char *call_blk = nullptr;
+    size_t call_blk_bytes = 0;
+    // shape of the iteration's blocks as set_x0 allocated them (0: none), so that
+    // a start block of the same shape takes them over
+    int64_t blk_n = 0;
+    int blk_p = 0, blk_prec = -1;
+    float *f32_scratch = nullptr;    // the FP32 set's HX, BX, R, D in one piece
     double *scratch_dev = nullptr;   // this device's copy of `scratch` (ofks_gram_noalloc)
     double poisson_tol_now = 0.0;    // > 0: the Hartree CG tolerance of the current iteration
     // caller-owned workspace (ofks_set_workspace): the iteration's device
@@ -408,6 +418,37 @@ template <typename T> void dfree(ofks_ctx *c, T *&ptr) {
     ptr = nullptr;
 }
 
+// Device scratch of the single calls (ofks_precondition, ofks_spmm_ex, ...).
+// One call at a time per context and everything on its stream, so a call may
+// overwrite what the one before left.
+constexpr size_t CALL_KEEP = size_t(256) << 20;
+constexpr int CALL_MAX_P = 1024;
+int call_vec(ofks_ctx *c, double **v) {   // 4 x CALL_MAX_P doubles
+    if (!c->call_vec) CHK(dalloc(c, &c->call_vec, 4 * CALL_MAX_P));
+    *v = c->call_vec;
+    return OFKS_OK;
+}
+int call_blocks(ofks_ctx *c, size_t bytes, char **out) {
+    if (c->call_blk_bytes < bytes) {
+        dfree(c, c->call_blk);   // (a call synchronizes before it returns, so nothing uses it)
+        c->call_blk_bytes = 0;
+        CHK(dalloc(c, &c->call_blk, bytes));
+        c->call_blk_bytes = bytes;
+    }
+    *out = c->call_blk;
+    return OFKS_OK;
+}
+// gives the blocks back at the end of a call, error or not, unless they are small
+struct CallBlocks {
+    ofks_ctx *c;
+    ~CallBlocks() {
+        if (c->call_blk_bytes <= CALL_KEEP) return;
+        (void)hipStreamSynchronize(c->stream);
+        dfree(c, c->call_blk);
+        c->call_blk_bytes = 0;
+    }
+};
+
 int ensure_host(ofks_ctx *c, size_t doubles) {
     if (c->hbuf_cap >= doubles) return OFKS_OK;
     if (c->hbuf) (void)hipHostFree(c->hbuf);
@@ -500,19 +541,32 @@ template <> const void *lbT<double>(ofks_ctx *c) { return c->lb; }
 template <> const void *lbT<float>(ofks_ctx *c) { return c->lb32; }
 
 // All iteration blocks, or (setup_only) just those the start block's
-// B-orthonormalization uses: X, HX, BX (an FP32 run converts and frees them).
+// B-orthonormalization uses: X, HX, BX.  The FP32 set's HX, BX, R and D are one
+// allocation, in which an FP32 run without a workspace forms its start block in
+// FP64 (two blocks).
+size_t f32_piece(size_t np) { return (np + 63) & ~size_t(63); }   // 256-byte pieces
 template <typename T> int alloc_blocks(ofks_ctx *c, bool setup_only = false) {
     Blocks<T> &b = blk<T>(c);
     const size_t np = (size_t)c->n * c->p;
     CHK(walloc(c, &b.Xt, np));
-    CHK(walloc(c, &b.HX, np));
-    CHK(walloc(c, &b.BX, np));
-    if (!setup_only) {
+    if (std::is_same<T, float>::value && !(c->ws_base && c->ws_carve)) {
+        const size_t pc = f32_piece(np);
+        CHK(walloc(c, &c->f32_scratch, 4 * pc));
+        T **piece[4] = {&b.HX, &b.BX, &b.R, &b.D};
+        for (int i = 0; i < 4; ++i) *piece[i] = (T *)c->f32_scratch + i * pc;
         CHK(walloc(c, &b.Xp, np));
         CHK(walloc(c, &b.P, np));
         CHK(walloc(c, &b.Pp, np));
-        CHK(walloc(c, &b.R, np));
-        CHK(walloc(c, &b.D, np));
+    } else {
+        CHK(walloc(c, &b.HX, np));
+        CHK(walloc(c, &b.BX, np));
+        if (!setup_only) {
+            CHK(walloc(c, &b.Xp, np));
+            CHK(walloc(c, &b.P, np));
+            CHK(walloc(c, &b.Pp, np));
+            CHK(walloc(c, &b.R, np));
+            CHK(walloc(c, &b.D, np));
+        }
     }
     CHK(walloc(c, &b.dinv, c->p));
     CHK(walloc(c, &b.CC, (size_t)c->p * 2 * c->p));
@@ -520,8 +574,16 @@ template <typename T> int alloc_blocks(ofks_ctx *c, bool setup_only = false) {
     return OFKS_OK;
 }
 
+void free_f32_scratch(ofks_ctx *c) {
+    if (!c->f32_scratch) return;
+    Blocks<float> &b = c->b32;
+    b.HX = b.BX = b.R = b.D = nullptr;
+    dfree(c, c->f32_scratch);
+}
+
 template <typename T> void free_blocks(ofks_ctx *c) {
     Blocks<T> &b = blk<T>(c);
+    if (std::is_same<T, float>::value) free_f32_scratch(c);
     dfree(c, b.Xt);
     dfree(c, b.Xp);
     dfree(c, b.P);
@@ -561,6 +623,22 @@ int upload_bytes(ofks_ctx *c, void *dst, const void *src, size_t bytes) {
 template <typename T> int upload(ofks_ctx *c, T *dst, const std::vector<double> &src) {
     std::vector<T> tmp(src.begin(), src.end());
     return upload_bytes(c, dst, tmp.data(), tmp.size() * sizeof(T));
+}
+
+// device shifts and identity-branch flags (shift < 0) of host shifts lam[p], in
+// the call scratch; *rest, if given: 2 x CALL_MAX_P doubles more
+template <typename T>
+int call_shifts(ofks_ctx *c, int p, const double *lam, T **lamd, uint8_t **neg, double **rest = nullptr) {
+    double *v = nullptr;
+    CHK(call_vec(c, &v));
+    *lamd = (T *)v;
+    *neg = (uint8_t *)(v + CALL_MAX_P);
+    if (rest) *rest = v + 2 * CALL_MAX_P;
+    std::vector<double> lv(lam, lam + p);
+    std::vector<uint8_t> nh(p);
+    for (int i = 0; i < p; ++i) nh[i] = lam[i] < 0.0 ? 1 : 0;
+    CHK(upload<T>(c, *lamd, lv));
+    return upload_bytes(c, *neg, nh.data(), p);
 }
 
 int download(ofks_ctx *c, std::vector<double> &dst, const double *src, size_t count) {
@@ -984,10 +1062,19 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
         double trl = 0.0;
         for (int i = 0; i < p; ++i) trl += L0[i * p + i];
         energy = c->prm.occupation * trl - c->scf_parts[3] - c->scf_parts[2] + c->scf_parts[1] + c->Enuc;
-    } else if (c->k % ee == 0) {
-        double tr;
-        if (dense::trace_sinv_a(S, L0, p, tr)) energy = tr;
     }
+    // fixed H: tr(S^-1 Lambda0), O(p^3) on the host (15 ms at p = 512).  The learned
+    // forms choose the preconditioner by it; the others only report it, and form
+    // it while the device works on the rest of the iteration
+    auto trace_energy = [&]() {
+        if (scf || c->k % ee != 0) return;
+        const auto te = std::chrono::steady_clock::now();
+        double tr;
+        if (dense::trace_sinv_a(c->S, c->L0, p, tr)) energy = tr;
+        if (c->timing && !learned_form)   // (there the host timer around it counts it)
+            c->timers["host"].ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - te).count();
+    };
+    if (learned_form) trace_energy();
     // learned form: fall back to the paper preconditioner for fallback_hold
     // iterations when the energy rises above the minimum (rule 0) or the
     // maximum (rule 1) of the last fallback_window iterates (no fallback when
@@ -1069,12 +1156,18 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
     c->last_rel = rel;
     c->relmin.push_back(c->relmin.empty() ? rel : std::min(rel, c->relmin.back()));
     c->last_energy = energy;
+    auto report_energy = [&]() {
+        if (learned_form || scf) return;   // known already
+        trace_energy();
+        c->last_energy = energy;
+        if (st) st->energy = energy;
+    };
     if (st) {
         st->k = c->k;
         st->kkt = kkt;
         st->fea = fea;
         st->rel = rel;
-        st->energy = energy;
+        st->energy = energy;   // (report_energy: the trace)
         st->eta = c->eta;
         st->precision = std::is_same<T, double>::value ? OFKS_F64 : OFKS_F32;
         st->precond_used = kind;
@@ -1084,6 +1177,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
         return fail(c, OFKS_ENONFINITE, "non-finite residual at k=%d: kkt=%g fea=%g kkt0=%g", c->k, kkt, fea,
                     c->kkt0);
     if (rel < c->prm.tol || c->k >= c->prm.max_iter) {
+        report_energy();
         *stop = true;
         if (st) st->ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         return OFKS_OK;
@@ -1190,6 +1284,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
                                c->have_prev ? B.Pp : nullptr, c->part));
     }
     HIPCHK(launch_colsum(c->stream, c->grid, 5, c->part, c->red));
+    report_energy();   // the device is at work up to here
     std::vector<double> s5;
     CHK(download(c, s5, c->red, 5));
     if (s5[3] == 0.0) {
@@ -1234,6 +1329,7 @@ int promote_to_f64_impl(ofks_ctx *c) {
     if (c->ws_base && c->ws_carve && ws_block_set(c->n, c->p, sizeof(double), 8) > c->ws_f64_cap)
         return fail(c, OFKS_ECAPACITY, "workspace: no room kept for the FP64 blocks (sized with refine_tol = 0)");
     CHK(sync(c));
+    free_f32_scratch(c);
     dfree(c, F.P);
     dfree(c, F.HX);
     dfree(c, F.BX);
@@ -1265,6 +1361,7 @@ int promote_to_f64_impl(ofks_ctx *c) {
     CHK(walloc(c, &D.lam, c->p));
     if (c->ws_base && c->ws_carve) c->ws_off = std::max(ws_hi, c->ws_off);
     c->prec = OFKS_F64;
+    c->blk_prec = OFKS_F64;
     return OFKS_OK;
 }
 
@@ -1323,6 +1420,7 @@ void release_state(ofks_ctx *c) {
     dfree(c, c->hb32);
     dfree(c, c->lb32);
     free_scf_work(c);
+    c->blk_n = 0;
     c->has_x = false;
 }
 
@@ -1461,18 +1559,8 @@ int spmm_ex_typed(ofks_ctx *c, int p, int op, const double *lam, const T *X, T *
     if (op == 0) return spmm_pair<T>(c, p, hbT<T>(c), X, Y1, Y2, 0);
     T *lamd = nullptr;
     uint8_t *act = nullptr;
-    CHK(dalloc(c, &lamd, p));
-    CHK(dalloc(c, &act, p));
-    std::vector<double> lv(lam, lam + p);
-    std::vector<uint8_t> ah(p);
-    for (int i = 0; i < p; ++i) ah[i] = lam[i] < 0.0 ? 1 : 0;
-    int rc = upload<T>(c, lamd, lv);
-    if (rc >= 0) rc = upload_bytes(c, act, ah.data(), p);
-    if (rc >= 0) rc = spmm_shift<T>(c, p, lbT<T>(c), lamd, act, X, Y1);
-    const int rs = sync(c);
-    dfree(c, lamd);
-    dfree(c, act);
-    return rc < 0 ? rc : rs;
+    CHK(call_shifts<T>(c, p, lam, &lamd, &act));
+    return spmm_shift<T>(c, p, lbT<T>(c), lamd, act, X, Y1);
 }
 // Device address of `scratch` on the current device, resolved once per
 // device (each device holds its own copy at its own address).
@@ -1870,29 +1958,58 @@ int ofks_set_x0(ofks_ctx *c, int32_t p, const double *X0, int32_t orth) {
     if (p > c->n) return fail(c, OFKS_EINVAL, "set_x0: p exceeds n");
     WsScope wss(c);
     c->has_x = false;   // until the new state is complete
-    free_blocks<double>(c);
-    free_blocks<float>(c);
-    dfree(c, c->active);
-    dfree(c, c->rz);
-    dfree(c, c->g2);
-    dfree(c, c->tw);
-    ws_restart(c);
+    // library memory of the same shape is taken over as it is (allocating and
+    // freeing gigabytes costs milliseconds, and at times the driver's clearing
+    // of what was freed holds the next allocation up for far longer)
+    const bool f32 = c->prm.precision == OFKS_F32;
+    const bool keep = !c->ws_base && c->blk_n == c->n && c->blk_p == p && c->blk_prec == c->prm.precision &&
+                      c->prec == c->prm.precision && (f32 ? c->f32_scratch && c->b32.Xt : c->b64.BX != nullptr);
+    if (!keep) {
+        free_blocks<double>(c);
+        free_blocks<float>(c);
+        dfree(c, c->active);
+        dfree(c, c->rz);
+        dfree(c, c->g2);
+        dfree(c, c->tw);
+        ws_restart(c);
+        c->blk_n = 0;
+    }
     c->p = p;
     c->prec = c->prm.precision;
-    dfree(c, c->g2);
-    dfree(c, c->tw);
-    CHK(walloc(c, &c->active, p));
-    CHK(walloc(c, &c->rz, p));
-    CHK(walloc(c, &c->g2, p));
-    CHK(walloc(c, &c->tw, p));
-    CHK(ensure_part(c, partials_needed(c, p)));
-    c->ws_f64_base = c->ws_off;
-    CHK(alloc_blocks<double>(c, true));   // the start block's setup; complete_blocks adds the rest
-    if (c->ws_base && c->prec == OFKS_F32) {
-        c->ws_f64_cap = ws_f64_region(c, p);
-        c->ws_off = c->ws_f64_base + c->ws_f64_cap;
+    if (!keep) {
+        CHK(walloc(c, &c->active, p));
+        CHK(walloc(c, &c->rz, p));
+        CHK(walloc(c, &c->g2, p));
+        CHK(walloc(c, &c->tw, p));
     }
-    Blocks<double> &B = c->b64;
+    // an FP32 run without a workspace forms its start block in the FP32 set's
+    // scratch, with the p x p factor and the column scales after the partials
+    const bool in_f32 = f32 && !c->ws_base;
+    const size_t npart = partials_needed(c, p);
+    CHK(ensure_part(c, npart + (in_f32 ? (size_t)p * p + p : 0)));
+    if (!keep && !in_f32) {
+        c->ws_f64_base = c->ws_off;
+        CHK(alloc_blocks<double>(c, true));   // the start block's setup; complete_blocks adds the rest
+        if (c->ws_base && f32) {
+            c->ws_f64_cap = ws_f64_region(c, p);
+            c->ws_off = c->ws_f64_base + c->ws_f64_cap;
+        }
+    }
+    if (!keep && in_f32) CHK(alloc_blocks<float>(c));
+    if (!c->ws_base) {
+        c->blk_n = c->n;
+        c->blk_p = p;
+        c->blk_prec = c->prec;
+    }
+    // X, B X (then X R^-1 over it) and the small arrays of the setup in FP64
+    Blocks<double> S64 = c->b64;
+    if (in_f32) {
+        S64.Xt = (double *)c->f32_scratch;
+        S64.BX = (double *)(c->f32_scratch + 2 * f32_piece((size_t)c->n * p));
+        S64.CC = c->part + npart;
+        S64.dinv = S64.CC + (size_t)p * p;
+    }
+    Blocks<double> &B = S64;
     HIPCHK(hipMemcpyAsync(B.Xt, X0, (size_t)c->n * p * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
     if (orth) {
         // Cholesky-based Gram-Schmidt: V^T B V = R^T R, X0 = V R^-1
@@ -1910,9 +2027,9 @@ int ofks_set_x0(ofks_ctx *c, int32_t p, const double *X0, int32_t orth) {
         CHK(upload<double>(c, B.dinv, ones));
         CHK(upload<double>(c, B.CC, Rinv));
         GradArgs ga{};
-        HIPCHK(launch_rowgemm<double>(c->stream, EPI_PLAIN, c->n, p, p, c->gemm_rows, B.Xt, B.dinv, B.CC, B.HX, ga,
+        HIPCHK(launch_rowgemm<double>(c->stream, EPI_PLAIN, c->n, p, p, c->gemm_rows, B.Xt, B.dinv, B.CC, B.BX, ga,
                                       nullptr));
-        std::swap(B.Xt, B.HX);
+        std::swap(B.Xt, B.BX);
     } else {
         // a block taken as given must have no column of zero B-norm
         CHK(spmm_pair<double>(c, p, c->hb, B.Xt, B.BX, nullptr, 1));
@@ -1921,15 +2038,17 @@ int ofks_set_x0(ofks_ctx *c, int32_t p, const double *X0, int32_t orth) {
         for (int i = 0; i < p; ++i)
             if (!(bn[i] > 0.0)) return fail(c, OFKS_EZERONORM, "set_x0: column %d has zero B-norm", i);
     }
-    if (c->prec == OFKS_F32) {
-        if (!c->hb32) CHK(ensure_f32_matrices(c));
-        else CHK(ensure_f32_matrices(c));
-        // free the FP64 products before the FP32 blocks exist (peak: X0, X and the FP32 blocks)
-        CHK(sync(c));
-        dfree(c, B.HX);
-        dfree(c, B.BX);
-        CHK(alloc_blocks<float>(c));
-        HIPCHK(launch_convert<double, float>(c->stream, c->n * (int64_t)p, B.Xt, c->b32.Xt));
+    if (!in_f32) c->b64 = S64;   // X and B X may have changed places
+    if (f32) {
+        CHK(ensure_f32_matrices(c));
+        if (!in_f32) {
+            // free the FP64 products before the FP32 blocks exist (peak: X0, X and the FP32 blocks)
+            CHK(sync(c));
+            dfree(c, c->b64.HX);
+            dfree(c, c->b64.BX);
+            CHK(alloc_blocks<float>(c));
+        }
+        HIPCHK(launch_convert<double, float>(c->stream, c->n * (int64_t)p, S64.Xt, c->b32.Xt));
         CHK(sync(c));
         free_blocks<double>(c);
     }
@@ -2190,30 +2309,19 @@ int ofks_precondition(ofks_ctx *c, int32_t p, const double *lam, const double *G
     if (m < 1) return fail(c, OFKS_EINVAL, "precondition: pcg_iters must be >= 1");
     const int64_t n = c->n;
     const size_t np = (size_t)n * p;
-    double *E = nullptr, *D = nullptr, *W = nullptr, *lamd = nullptr, *rzd = nullptr;
+    CallBlocks give_back{c};
+    char *blk = nullptr;
+    CHK(call_blocks(c, 3 * np * sizeof(double), &blk));
+    double *D = (double *)blk, *W = D + np, *E = W + np, *lamd = nullptr;
     uint8_t *act = nullptr;
-    CHK(dalloc(c, &E, np));
-    CHK(dalloc(c, &D, np));
-    CHK(dalloc(c, &W, np));
-    CHK(dalloc(c, &lamd, p));
-    CHK(dalloc(c, &rzd, (size_t)c->grid * p));
-    CHK(dalloc(c, &act, p));
-    std::vector<double> lv(lam, lam + p);
-    std::vector<uint8_t> ah(p);
-    for (int i = 0; i < p; ++i) ah[i] = lam[i] < 0.0 ? 1 : 0;
-    CHK(upload<double>(c, lamd, lv));
-    CHK(upload_bytes(c, act, ah.data(), p));
+    CHK(call_shifts<double>(c, p, lam, &lamd, &act));
+    // the start's partials of <G, J G>, where the steps leave theirs
+    const size_t off = cg_part_doubles(c, p);
+    CHK(ensure_part(c, off + (size_t)c->grid * p));
     int nrz = 0;
-    HIPCHK(launch_cg_start<double>(c->stream, c->grid, n, p, act, c->lhd, c->bd, lamd, G, D, P, rzd, &nrz));
-    CHK(pcg_run<double>(c, m, n, p, act, lamd, c->lb, D, W, P, E, rzd, nrz));
-    CHK(sync(c));
-    dfree(c, E);
-    dfree(c, D);
-    dfree(c, W);
-    dfree(c, lamd);
-    dfree(c, rzd);
-    dfree(c, act);
-    return OFKS_OK;
+    HIPCHK(launch_cg_start<double>(c->stream, c->grid, n, p, act, c->lhd, c->bd, lamd, G, D, P, c->part + off, &nrz));
+    CHK(pcg_run<double>(c, m, n, p, act, lamd, c->lb, D, W, P, E, c->part + off, nrz));
+    return sync(c);
 }
 
 int ofks_build_hamiltonian(ofks_ctx *c, int32_t p, const double *X, double *rho_q, double *eps_q, double *vxc_q,
@@ -2223,14 +2331,13 @@ int ofks_build_hamiltonian(ofks_ctx *c, int32_t p, const double *X, double *rho_
     if (p <= 0 || p > 1024 || !X) return fail(c, OFKS_EINVAL, "build_hamiltonian: bad arguments");
     if (!c->has_params) ofks_default_params(&c->prm);
     double *ones = nullptr;
-    CHK(dalloc(c, &ones, p));
+    CHK(call_vec(c, &ones));
     std::vector<double> o(p, 1.0);
     CHK(upload<double>(c, ones, o));
     const int keep = c->p;
     c->p = p;
     int rc = build_h<double>(c, X, ones);
     c->p = keep;
-    dfree(c, ones);
     CHK(rc);
     hipStream_t s = c->stream;
     const size_t bq = 4 * c->n_tets * sizeof(double);
@@ -2358,30 +2465,15 @@ int ofks_lp_apply(ofks_ctx *c, int32_t p, const double *lam, const double *G, do
     if (!c->has_system || !c->has_lhalf) return fail(c, OFKS_ESTATE, "lp_apply: needs an assembled system");
     if (!c->lp_ready) return fail(c, OFKS_ESTATE, "lp_apply: no weights");
     if (p <= 0 || p > 1024 || !lam || !G || !P) return fail(c, OFKS_EINVAL, "lp_apply: bad arguments");
-    const int keep = c->p;
-    c->p = p;
     double *lamd = nullptr, *g2 = nullptr;
     uint8_t *neg = nullptr;
-    CHK(dalloc(c, &lamd, p));
-    CHK(dalloc(c, &g2, p));
-    CHK(dalloc(c, &neg, p));
-    std::vector<double> lv(lam, lam + p);
-    std::vector<uint8_t> nh(p);
-    for (int i = 0; i < p; ++i) nh[i] = lam[i] < 0.0 ? 1 : 0;
-    CHK(upload<double>(c, lamd, lv));
-    CHK(upload_bytes(c, neg, nh.data(), p));
-    std::vector<double> gg;
-    int rc = coldot<double>(c, G, G, gg);
-    if (rc >= 0) rc = upload<double>(c, g2, gg);
-    c->p = keep;
-    CHK(rc);
+    CHK(call_shifts<double>(c, p, lam, &lamd, &neg, &g2));
+    CHK(ensure_part(c, (size_t)c->grid * p));
+    HIPCHK(launch_coldot<double>(c->stream, c->grid, c->n, p, G, G, c->part));
+    HIPCHK(launch_colsum(c->stream, c->grid, p, c->part, g2));
     HIPCHK(hipMemcpyAsync(P, G, (size_t)c->n * p * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(launch_lp_apply<double>(c->stream, c->n, p, P, c->lhd, c->bd, c->hd, lamd, neg, g2, c->lp_W, c->lp_norm));
-    CHK(sync(c));
-    dfree(c, lamd);
-    dfree(c, g2);
-    dfree(c, neg);
-    return OFKS_OK;
+    return sync(c);
 }
 
 // ---- graph learned preconditioner ---------------------------------------------
@@ -2392,18 +2484,6 @@ int col_sq(ofks_ctx *c, int p, const double *G, double *g2) {
     CHK(ensure_part(c, (size_t)c->grid * p));
     HIPCHK(launch_coldot<double>(c->stream, c->grid, c->n, p, G, G, c->part));
     HIPCHK(launch_colsum(c->stream, c->grid, p, c->part, g2));
-    return OFKS_OK;
-}
-
-// device shifts and identity-branch flags for host shifts lam[p]
-int gl_shifts(ofks_ctx *c, int p, const double *lam, double **lamd, uint8_t **neg) {
-    CHK(dalloc(c, lamd, p));
-    CHK(dalloc(c, neg, p));
-    std::vector<double> lv(lam, lam + p);
-    std::vector<uint8_t> nh(p);
-    for (int i = 0; i < p; ++i) nh[i] = lam[i] < 0.0 ? 1 : 0;
-    CHK(upload<double>(c, *lamd, lv));
-    CHK(upload_bytes(c, *neg, nh.data(), p));
     return OFKS_OK;
 }
 
@@ -2498,27 +2578,19 @@ int ofks_gl_apply(ofks_ctx *c, int32_t p, const double *lam, const double *G, do
     if (p <= 0 || p > 1024 || !lam || !G || !P) return fail(c, OFKS_EINVAL, "gl_apply: bad arguments");
     if (P == G) return fail(c, OFKS_EINVAL, "gl_apply: P must not alias G");
     const size_t np = (size_t)c->n * p;
-    double *lamd = nullptr, *g2 = nullptr, *Z = nullptr, *Q = nullptr;
+    CallBlocks give_back{c};
+    char *blk = nullptr;
+    CHK(call_blocks(c, np * (2 * sizeof(double) + sizeof(float)), &blk));
+    double *Z = (double *)blk, *Q = Z + np, *lamd = nullptr, *g2 = nullptr;
+    float *FT = (float *)(Q + np);
     uint8_t *neg = nullptr;
-    float *FT = nullptr;
-    CHK(gl_shifts(c, p, lam, &lamd, &neg));
-    CHK(dalloc(c, &g2, p));
-    CHK(dalloc(c, &Z, np));
-    CHK(dalloc(c, &Q, np));
-    CHK(dalloc(c, &FT, np));
+    CHK(call_shifts<double>(c, p, lam, &lamd, &neg, &g2));
     CHK(col_sq(c, p, G, g2));
     HIPCHK(launch_gl_heads<double>(c->stream, c->n, p, G, c->lhd, c->bd, c->hd, lamd, neg, g2, c->gl_W, c->gl_norm,
                                    Z, FT));
     CHK(spmm_shift<double>(c, p, c->lb, lamd, neg, Z, Q));
     HIPCHK(launch_gl_out<double>(c->stream, c->n, p, G, Z, FT, Q, c->lhd, c->bd, lamd, neg, P, (double *)nullptr));
-    CHK(sync(c));
-    dfree(c, lamd);
-    dfree(c, neg);
-    dfree(c, g2);
-    dfree(c, Z);
-    dfree(c, Q);
-    dfree(c, FT);
-    return OFKS_OK;
+    return sync(c);
 }
 
 int ofks_gl_loss_grad(ofks_ctx *c, int32_t p, const double *lam, const double *G, double *loss, double *grad) {
@@ -2528,15 +2600,11 @@ int ofks_gl_loss_grad(ofks_ctx *c, int32_t p, const double *lam, const double *G
     if (p <= 0 || p > 1024 || !lam || !G || !loss || !grad) return fail(c, OFKS_EINVAL, "gl_loss_grad: bad arguments");
     double *lamd = nullptr, *g2w = nullptr;
     uint8_t *neg = nullptr;
-    CHK(gl_shifts(c, p, lam, &lamd, &neg));
-    CHK(dalloc(c, &g2w, 2 * p));
+    CHK(call_shifts<double>(c, p, lam, &lamd, &neg, &g2w));
     CHK(gl_loss_grad_dev(c, p, G, lamd, neg, loss, g2w));
     std::vector<double> gr;
     CHK(download(c, gr, c->red, GL_NPAR_HOST));
     for (int k = 0; k < GL_NPAR_HOST; ++k) grad[k] = gr[k];
-    dfree(c, lamd);
-    dfree(c, neg);
-    dfree(c, g2w);
     return OFKS_OK;
 }
 
@@ -2634,12 +2702,10 @@ int ofks_lp_features(ofks_ctx *c, int32_t p, const double *G, float *dev_feat) {
     if (!c->has_system || !c->has_lhalf) return fail(c, OFKS_ESTATE, "lp_features: needs an assembled system");
     if (p <= 0 || p > 1024 || !G || !dev_feat) return fail(c, OFKS_EINVAL, "lp_features: bad arguments");
     double *g2 = nullptr;
-    CHK(dalloc(c, &g2, p));
+    CHK(call_vec(c, &g2));
     CHK(col_sq(c, p, G, g2));
     HIPCHK(launch_features(c->stream, c->n, p, G, c->lhd, c->bd, c->hd, g2, dev_feat));
-    CHK(sync(c));
-    dfree(c, g2);
-    return OFKS_OK;
+    return sync(c);
 }
 
 // ---- checkpoint / resume -------------------------------------------------------
@@ -2685,6 +2751,7 @@ template <typename T> int state_blocks(ofks_ctx *c, char *buf, size_t off, bool 
 int setup_blocks(ofks_ctx *c, int p, int prec) {
     WsScope wss(c);
     c->has_x = false;   // until the new state is complete
+    c->blk_n = 0;
     free_blocks<double>(c);
     free_blocks<float>(c);
     dfree(c, c->active);
