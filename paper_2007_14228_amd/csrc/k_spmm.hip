@@ -9,7 +9,7 @@
 //                  preconditioner T_l, eq. precondition-T), or, for a step of
 //                  its CG, W = J Q with the per-column dot products <D_l, Q_l>
 //                  and <Q_l, W_l>.
-//  k_spmv_dot    : q = A d and <d, q> for one vector (Hartree CG).
+//  k_cg_iter     : one Hartree CG iteration (one vector, FP64).
 //
 // Work mapping (wave64).  A row is owned by a group of LPR = 2^lpr_log2 lanes;
 // each lane covers V consecutive columns (one vector load of an X row slice)
@@ -436,44 +436,6 @@ template <typename K> int resident_grid(K kernel, int cap) {
     return cached < cap ? cached : cap;
 }
 
-// SpMV with the dot <d, A d> fused (Hartree CG); persistent grid, 16 lanes
-// per row (P1 rows hold about 15 entries): each lane takes every 16th entry
-// of the row with coalesced loads, the 16 partial sums are combined by
-// shuffles in a fixed order, and the group's first lane writes q_i and
-// accumulates d_i q_i.  Per-block partial written to part[block].
-__global__ __launch_bounds__(256) void k_spmv_dot(int64_t n, const int64_t *__restrict__ rp,
-                                                 const int32_t *__restrict__ col,
-                                                 const double *__restrict__ a,
-                                                 const double *__restrict__ d,
-                                                 double *__restrict__ q,
-                                                 double *__restrict__ part) {
-    __shared__ double red[256];
-    const int sub = threadIdx.x & 15;
-    double s = 0.0;
-    const int64_t rows_per_pass = (int64_t)gridDim.x * (blockDim.x / 16);
-    for (int64_t i = (int64_t)blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4); i - (threadIdx.x >> 4) < n;
-         i += rows_per_pass) {
-        double acc = 0.0;
-        if (i < n) {
-            const int64_t e1 = rp[i + 1];
-            for (int64_t e = rp[i] + sub; e < e1; e += 16) acc = fma(a[e], d[col[e]], acc);
-        }
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 16);
-        if (sub == 0 && i < n) {
-            q[i] = acc;
-            s = fma(d[i], acc, s);
-        }
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
 // ---------------------------------------------------------------------------
 // LDS-halo SpMM.  Plan block b owns the consecutive rows [row0[b], row0[b+1])
 // (at most HALO_RMAX, each with at most 64 entries) and their halo: the
@@ -791,6 +753,227 @@ k_spmm_halo(int64_t nb, int p, int cw, const int64_t *__restrict__ row0, const i
     }
 }
 
+// ---------------------------------------------------------------------------
+// One Hartree CG iteration in one kernel (one vector, FP64): the Jacobi-CG of
+// Chronopoulos and Gear, J. Comput. Appl. Math. 25 (1989), whose two dots come
+// from one product.  A row's state is u = M^-1 r, v = M^-1 A u, t = M^-1 A p
+// and p, 32 bytes together, M = diag dg.  With gamma = <r, u> and delta = <A
+// u, u> of the previous launch's partials,
+//   beta = gamma / gamma_old, alpha = gamma / (delta - beta gamma / alpha_old),
+//   t' = v + beta t, p' = u + beta p, x += alpha p', u' = u - alpha t',
+//   w = A u', v' = M^-1 w, partials of <r', u'>, <w, u'> and <r', r'>.
+// The product needs u' of the neighbours, which each workgroup forms itself
+// from their old states: the launch boundary between two iterations is the only
+// synchronisation.  Every workgroup sums all partials in one fixed order.  in
+// and out, pin and pout and the scalars' two slots alternate, so nothing is
+// overwritten that another workgroup still reads.  first: alpha = beta = 0 (v
+// = M^-1 A u of a new u), and the next launch takes beta = 0.
+//
+// With the halo plan (which a mesh's matrices always have: its rows hold at
+// most 64 entries) a state is read once per 64-row block (two to three times
+// in all) instead of once per entry, the columns are two-byte slots, and a
+// row's product reads LDS.  A team of 256 threads works on a plan block, a halo
+// slot a thread and sixteen lanes a row, with the next block's loads in flight.
+//
+// Bound by latency where a workgroup has one block or two (the launch, the
+// block's metadata, its states, the partials: 5.0e4 rows 9.2 us), and by
+// memory on top of that (2.0e5 rows, 58 MB: 15.8 us).  Before, with a product,
+// an update and a direction kernel: 17.1 and 25.1 us an iteration.  One block
+// a workgroup of 256 threads: 10.4 and 17.3 us (768 workgroups; 256 12.6 and
+// 26.5, 2048 11.9 and 21.3, for the partials that each must sum); 2, 3, 4
+// teams: 9.2, 9.0, 10.4 and 16.9, 16.5, 16.9.
+// ---------------------------------------------------------------------------
+#ifndef OFKS_CG_BLOCKS
+#define OFKS_CG_BLOCKS 256   // a multiple of 8, at most 256 (a partial a thread of a team)
+#endif
+#ifndef OFKS_CG_TEAMS
+#define OFKS_CG_TEAMS 3      // plan blocks a workgroup works on at once (2 to 4 fit; 4 spills)
+#endif
+struct CgIter {
+    int first, parity, np;
+    const double *dg;
+    const double2 *in;
+    double2 *out;
+    double *x, *sc;
+    const double *pin;
+    double *pout;
+};
+
+// sum over each sixteen lanes, to all of them
+__device__ __forceinline__ double row_sum(double v) {
+#define OFKS_ROR(N)                                                                                                  \
+    v += __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + N, 0xf, 0xf, true),              \
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + N, 0xf, 0xf, true));
+    OFKS_ROR(8) OFKS_ROR(4) OFKS_ROR(2) OFKS_ROR(1)
+#undef OFKS_ROR
+    return v;
+}
+
+// what a thread loads ahead for a plan block
+template <int ROUNDS, bool LONG> struct CgBlock {
+    int h, rb;
+    bool own;
+    int64_t e0[LONG ? HALO_SETS : 1];
+    int len[LONG ? HALO_SETS : 1];
+    double2 s0, s1;
+    double x, dg, a[HALO_SETS][ROUNDS];
+    int sl[HALO_SETS][ROUNDS];
+};
+
+template <int ROUNDS, bool LONG>
+__global__ __launch_bounds__(256 * OFKS_CG_TEAMS) void k_cg_iter(
+    int64_t nb, const int32_t *__restrict__ info, const int32_t *__restrict__ halo, const int64_t *__restrict__ brp,
+    const uint16_t *__restrict__ lcol, const double *__restrict__ a, CgIter c) {
+    static_assert(HALO_MAX <= 256 && HALO_RMAX == 64 && HALO_WAVES == 4, "one slot a thread of a team");
+    constexpr int W = 4 * OFKS_CG_TEAMS;
+    __shared__ double us_[OFKS_CG_TEAMS][256], ws_[OFKS_CG_TEAMS][HALO_RMAX], red[3][W];
+    const int team = threadIdx.x >> 8, tid = threadIdx.x & 255, li = tid & 15, g = tid >> 4;
+    double *us = us_[team], *ws = ws_[team];
+    // XCD x takes the plan blocks from x per on, OFKS_CG_TEAMS at a time and workgroup
+    const int64_t per = (nb + 7) / 8, base = (blockIdx.x % 8) * per, end = min(base + per, nb);
+    const int64_t step = (int64_t)(gridDim.x / 8) * OFKS_CG_TEAMS;
+    const int64_t k0 = base + (int64_t)(blockIdx.x / 8) * OFKS_CG_TEAMS;   // this round's first plan block
+    // metadata of block k (past the end: the last one, whose loads go unused)
+    int mh, mi;
+    int64_t me[HALO_SETS];
+    int ml[HALO_SETS];
+    auto meta = [&](int64_t k) __attribute__((always_inline)) {
+        k = min(k, nb - 1);
+        mh = halo[k * HALO_STRIDE + min(tid, HALO_STRIDE - 1)];
+        mi = info[k];
+        const int64_t *bp = brp + k * HALO_BRP + g;   // this lane's rows: 16 i + g
+#pragma unroll
+        for (int i = 0; i < HALO_SETS; ++i) {
+            me[i] = bp[16 * i];
+            ml[i] = (int)(bp[16 * i + 1] - me[i]);
+        }
+    };
+    auto data = [&](CgBlock<ROUNDS, LONG> &B, bool valid) __attribute__((always_inline)) {
+        B.h = mh;
+        B.rb = (mi >> 16) & 255;
+        B.own = valid && tid >= B.rb && tid < B.rb + ((mi >> 8) & 255);
+        B.s0 = c.in[2 * (int64_t)mh];
+        B.s1 = c.in[2 * (int64_t)mh + 1];
+        B.dg = 1.0;
+        B.x = 0.0;
+        if (B.own) {
+            B.x = c.x[B.h];
+            B.dg = c.dg[B.h];
+        }
+#pragma unroll
+        for (int i = 0; i < HALO_SETS; ++i) {
+            if (LONG) {
+                B.e0[i] = me[i];
+                B.len[i] = ml[i];
+            }
+#pragma unroll
+            for (int u = 0; u < ROUNDS; ++u) {
+                const bool on = 16 * u + li < ml[i];
+                const int64_t e = on ? me[i] + 16 * u + li : 0;   // entry 0 exists
+                B.a[i][u] = a[e];
+                B.sl[i][u] = lcol[e];
+                if (!on) {
+                    B.a[i][u] = 0.0;
+                    B.sl[i][u] = B.rb;
+                }
+            }
+        }
+    };
+    double ga = 0.0, de = 0.0, rr = 0.0, alpha = 0.0, beta = 0.0;
+    if (k0 < end) {
+        meta(k0 + team);
+        // every wave sums the partials itself (np <= 256): no barrier, and the first block's loads in flight
+        double pg[4], pd[4];
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int q = min(lane + 64 * j, c.np - 1);
+            pg[j] = c.pin[q];
+            pd[j] = c.pin[c.np + q];
+        }
+        const double go = c.sc[4 + 2 * c.parity], ao = c.sc[5 + 2 * c.parity];
+        CgBlock<ROUNDS, LONG> A, B;
+        data(A, k0 + team < end);
+        meta(k0 + team + step);
+        if (!c.first) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (lane + 64 * j >= c.np) pg[j] = pd[j] = 0.0;
+            const double gs = rows_sum(row_sum((pg[0] + pg[1]) + (pg[2] + pg[3])));
+            const double ds = rows_sum(row_sum((pd[0] + pd[1]) + (pd[2] + pd[3])));
+            beta = go > 0.0 ? gs / go : 0.0;
+            const double den = ao > 0.0 ? ds - beta * gs / ao : ds;
+            alpha = den > 0.0 ? gs / den : 0.0;
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                c.sc[4 + 2 * (c.parity ^ 1)] = gs;
+                c.sc[5 + 2 * (c.parity ^ 1)] = alpha;
+            }
+        } else if (blockIdx.x == 0 && threadIdx.x == 0) {
+            c.sc[4 + 2 * (c.parity ^ 1)] = 0.0;
+            c.sc[5 + 2 * (c.parity ^ 1)] = 0.0;
+        }
+        auto work = [&](CgBlock<ROUNDS, LONG> &B) __attribute__((always_inline)) {
+            const double t = fma(beta, B.s1.x, B.s0.y), un = fma(-alpha, t, B.s0.x);
+            us[tid] = un;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < HALO_SETS; ++i) {
+                double acc = 0.0;
+#pragma unroll
+                for (int u = 0; u < ROUNDS; ++u) acc = fma(B.a[i][u], us[B.sl[i][u]], acc);
+                if (LONG)
+                    for (int q = 16 * ROUNDS + li; q < B.len[i]; q += 16)
+                        acc = fma(a[B.e0[i] + q], us[lcol[B.e0[i] + q]], acc);
+                acc = row_sum(acc);
+                if (li == 0) ws[16 * i + g] = acc;
+            }
+            __syncthreads();
+            if (B.own) {
+                const double w = ws[tid - B.rb], r = B.dg * un, p = fma(beta, B.s1.y, B.s0.x);
+                if (!c.first) c.x[B.h] = fma(alpha, p, B.x);
+                c.out[2 * (int64_t)B.h] = make_double2(un, w / B.dg);
+                c.out[2 * (int64_t)B.h + 1] = make_double2(t, p);
+                ga = fma(r, un, ga);
+                de = fma(w, un, de);
+                rr = fma(r, r, rr);
+            }
+        };
+        // two sets of registers in turn: a block's loads are in flight while the one before is worked on
+        for (int64_t k = k0;; k += 2 * step) {
+            if (k + step < end) {
+                data(B, k + step + team < end);
+                meta(k + 2 * step + team);
+            }
+            work(A);
+            if (k + step >= end) break;
+            if (k + 2 * step < end) {
+                data(A, k + 2 * step + team < end);
+                meta(k + 3 * step + team);
+            }
+            work(B);
+            if (k + 2 * step >= end) break;
+        }
+    }
+    const double s[3] = {rows_sum(row_sum(ga)), rows_sum(row_sum(de)), rows_sum(row_sum(rr))};
+    if ((threadIdx.x & 63) == 0)
+        for (int j = 0; j < 3; ++j) red[j][threadIdx.x >> 6] = s[j];
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        double v = 0.0;
+        for (int j = 0; j < W; ++j) v += red[threadIdx.x][j];
+        c.pout[threadIdx.x * c.np + blockIdx.x] = v;
+    }
+}
+
+// The grid, and with it the number of partials: a multiple of 8, at most
+// OFKS_CG_BLOCKS, with the plan's blocks spread evenly.
+int cg_iter_blocks(int64_t nb) {
+    const int64_t per = ((nb + 7) / 8 + OFKS_CG_TEAMS - 1) / OFKS_CG_TEAMS, most = OFKS_CG_BLOCKS / 8;
+    const int64_t rounds = (per + most - 1) / most;
+    return (int)(8 * ((per + rounds - 1) / rounds));
+}
+int cg_iter_blocks_max() { return OFKS_CG_BLOCKS; }
+
 // out[g][c] = sum of rows [g G, (g + 1) G) of an nb x p partial matrix, in row
 // order; threads run over columns, so every read is coalesced.
 __global__ __launch_bounds__(256) void k_part_rows(int64_t nb, int p, int G, const double *__restrict__ in,
@@ -948,9 +1131,18 @@ hipError_t launch_spmm_shift(hipStream_t s, int mode, int grid, int64_t n, int p
     return launch_spmm_shift_mode<SHIFT_DOT, T>(s, grid, n, p, rp, col, lb, lam, active, lhd, bd, D, Q, part, blocks_used);
 }
 
-hipError_t launch_spmv_dot(hipStream_t s, int grid, int64_t n, const int64_t *rp, const int32_t *col,
-                           const double *a, const double *d, double *q, double *part) {
-    hipLaunchKernelGGL(k_spmv_dot, dim3(grid), dim3(256), 0, s, n, rp, col, a, d, q, part);
+// in, out: four doubles a row; pin, pout: 3 np doubles, np from cg_iter_blocks
+hipError_t launch_cg_iter(hipStream_t s, int np, int first, int parity, int64_t nb, int maxlen, const int32_t *info,
+                          const int32_t *halo, const int64_t *brp, const uint16_t *lcol, const double *a,
+                          const double *dg, const double *in, double *out, double *x, double *sc, const double *pin,
+                          double *pout) {
+    const CgIter c{first, parity, np, dg, (const double2 *)in, (double2 *)out, x, sc, pin, pout};
+    const dim3 block(256 * OFKS_CG_TEAMS);
+    if (maxlen <= 16)
+        hipLaunchKernelGGL((k_cg_iter<1, false>), dim3(np), block, 0, s, nb, info, halo, brp, lcol, a, c);
+    else if (maxlen <= 32)
+        hipLaunchKernelGGL((k_cg_iter<2, false>), dim3(np), block, 0, s, nb, info, halo, brp, lcol, a, c);
+    else hipLaunchKernelGGL((k_cg_iter<2, true>), dim3(np), block, 0, s, nb, info, halo, brp, lcol, a, c);
     return hipGetLastError();
 }
 

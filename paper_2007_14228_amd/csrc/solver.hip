@@ -63,8 +63,11 @@ hipError_t launch_spmm_shift(hipStream_t, int, int, int64_t, int, const int64_t 
                              const T *, const uint8_t *, const double *, const double *, const T *, T *, double *,
                              int *);
 enum { DUAL = 0, SHIFT = 1, SHIFT_CG = 2, SHIFT_DOT = 3 };   // product forms (k_spmm.hip)
-hipError_t launch_spmv_dot(hipStream_t, int, int64_t, const int64_t *, const int32_t *, const double *,
-                           const double *, double *, double *);
+hipError_t launch_cg_iter(hipStream_t, int, int, int, int64_t, int, const int32_t *, const int32_t *, const int64_t *,
+                          const uint16_t *, const double *, const double *, const double *, double *, double *,
+                          double *, const double *, double *);
+int cg_iter_blocks(int64_t nb);
+int cg_iter_blocks_max();
 template <typename T>
 hipError_t launch_spmm_halo(hipStream_t, int, int64_t, int, int, const int64_t *, const int32_t *, const int32_t *,
                             const int64_t *, const uint16_t *, const void *, const T *, T *, T *, int, const T *,
@@ -168,12 +171,9 @@ hipError_t launch_load_vec(hipStream_t, int64_t, const int32_t *, const int64_t 
                            const double *, const double *, double *);
 hipError_t launch_veff(hipStream_t, int64_t, const int32_t *, const int32_t *, const double *, const double *,
                        const double *, double *);
+hipError_t launch_cg_state(hipStream_t, int64_t, const double *, double *);
 hipError_t launch_cg_start(hipStream_t, int, int64_t, double, const double *, const double *, const double *,
-                           double *, double *, double *, double *);
-hipError_t launch_cg_xr(hipStream_t, int, int64_t, int, double *, int, const double *, const double *,
-                        const double *, const double *, double *, double *, double *);
-hipError_t launch_cg_dir(hipStream_t, int, int64_t, int, double *, const double *, const double *, const double *,
-                         double *);
+                           double *, double *, double *);
 hipError_t launch_dot(hipStream_t, int, int64_t, const double *, const double *, double *);
 // (k_gnn.hip)
 constexpr int GL_NPAR_HOST = 226;
@@ -262,7 +262,7 @@ struct ofks_ctx {
 
     // SCF work
     double *rho_q = nullptr, *eps_q = nullptr, *vxc_q = nullptr, *veff_q = nullptr, *bvec = nullptr,
-           *U = nullptr, *cg_r = nullptr, *cg_d = nullptr, *cg_q = nullptr, *cg_sc = nullptr,
+           *U = nullptr, *cg_st[2] = {nullptr, nullptr}, *cg_sc = nullptr,   // (cg_st: the Hartree CG's row states)
            *cg_part = nullptr;   // Hartree CG partial sums (fixed: the captured graph holds the pointer)
     double scf_parts[4] = {0, 0, 0, 0};  // int rho, int eps rho, int vxc rho, U.b/2
 
@@ -761,17 +761,6 @@ template <typename T> int coldot(ofks_ctx *c, const T *A, const T *B, std::vecto
 // ---------------------------------------------------------------------------
 // SCF: H(X) for X = Xs .* dinv (Section 2.2)
 // ---------------------------------------------------------------------------
-// Hartree CG grid: enough 256-thread blocks to fill the device (the vectors
-// are short, so the kernels are latency-bound); the fused reductions sum one
-// partial per block.
-#ifndef OFKS_CG_SPMV_BLOCKS
-#define OFKS_CG_SPMV_BLOCKS 2048   // the Hartree SpMV's grid
-#endif
-#ifndef OFKS_CG_UPD_BLOCKS
-#define OFKS_CG_UPD_BLOCKS 512     // the CG vector updates' grid: each of their blocks sums all the previous
-#endif                             // kernel's partials, so fewer blocks read far fewer (measured at n = 2e5)
-constexpr int CG_BLOCKS = OFKS_CG_SPMV_BLOCKS;
-
 void drop_cg_graph(ofks_ctx *c) {
     if (c->cg_graph) (void)hipGraphExecDestroy(c->cg_graph);
     c->cg_graph = nullptr;
@@ -779,31 +768,35 @@ void drop_cg_graph(ofks_ctx *c) {
 
 int poisson(ofks_ctx *c) {
     const int64_t n = c->n;
-    const int g = CG_BLOCKS, gu = OFKS_CG_UPD_BLOCKS;   // partials: <d, q> (g), then 3-wide update sums (gu)
-    static_assert(OFKS_CG_UPD_BLOCKS <= CG_BLOCKS, "partial buffer sized for CG_BLOCKS");
-    double *dqp = c->cg_part, *xrp = c->cg_part + g;
+    if (!c->halo_nb) return fail(c, OFKS_ESTATE, "Hartree CG: the mesh has no halo plan");   // its rows always fit one
+    const int np = cg_iter_blocks(c->halo_nb);
+    double *part[2] = {c->cg_part, c->cg_part + 3 * np};
+    // iteration j's launch: states from cg_st[in] to the other one, partials from part[j & 1]
+    auto iter = [&](hipStream_t s, int first, int in, int parity) {
+        return launch_cg_iter(s, np, first, parity, c->halo_nb, c->halo_maxlen, c->halo_info, c->halo_idx,
+                              c->halo_brp, c->halo_lcol, c->Lv, c->lhd, c->cg_st[in], c->cg_st[in ^ 1],
+                              c->U, c->cg_sc, part[parity], part[parity ^ 1]);
+    };
     {
         Scope sc(c, "poisson");
-        HIPCHK(launch_spmv_dot(c->stream, g, n, c->rp, c->col, c->Lv, c->U, c->cg_q, dqp));
         // Jacobi preconditioner diag(L/2): a constant multiple of diag(L) leaves the CG iterates unchanged
-        HIPCHK(launch_cg_start(c->stream, gu, n, 4.0 * M_PI, c->bvec, c->cg_q, c->lhd, c->cg_r, c->cg_d, xrp,
+        HIPCHK(launch_cg_state(c->stream, n, c->U, c->cg_st[0]));
+        HIPCHK(iter(c->stream, 1, 0, 1));
+        HIPCHK(launch_cg_start(c->stream, np, n, 4.0 * M_PI, c->bvec, c->lhd, c->cg_st[1], c->cg_st[0], c->cg_part,
                                c->cg_sc));
+        HIPCHK(iter(c->stream, 1, 0, 1));
     }
     std::vector<double> sc;
     CHK(download(c, sc, c->cg_sc, 3));
     double rr = sc[1], bb = sc[2];
     const double rt = c->poisson_tol_now > 0.0 ? c->poisson_tol_now : c->prm.poisson_rtol;
     const double tol2 = rt * rt * bb;
-    // ten CG iterations (30 launches; an even count, so <r, z> ends in sc[0]
-    // again), replayed as one graph when allowed
+    // ten CG iterations (an even count, so the state ends in cg_st[1] and the
+    // partials in part[0] again), replayed as one graph when allowed
     auto chunk = [&](hipStream_t s) -> hipError_t {
         for (int j = 0; j < 10; ++j) {
-            hipError_t e;
-            if ((e = launch_spmv_dot(s, g, n, c->rp, c->col, c->Lv, c->cg_d, c->cg_q, dqp)) != hipSuccess) return e;
-            if ((e = launch_cg_xr(s, gu, n, j & 1, c->cg_sc, g, dqp, c->cg_d, c->cg_q, c->lhd, c->U, c->cg_r, xrp)) !=
-                hipSuccess)
-                return e;
-            if ((e = launch_cg_dir(s, gu, n, j & 1, c->cg_sc, xrp, c->cg_r, c->lhd, c->cg_d)) != hipSuccess) return e;
+            const hipError_t e = iter(s, 0, (j & 1) ^ 1, j & 1);
+            if (e != hipSuccess) return e;
         }
         return hipSuccess;
     };
@@ -835,8 +828,9 @@ int poisson(ofks_ctx *c) {
             else HIPCHK(chunk(c->stream));
         }
         it += 10;
-        CHK(download(c, sc, c->cg_sc, 2));
-        rr = sc[1];
+        CHK(download(c, sc, part[0] + 2 * np, np));   // |r|^2's
+        rr = 0.0;
+        for (double v : sc) rr += v;
         if (!std::isfinite(rr)) return fail(c, OFKS_ENONFINITE, "Hartree CG diverged");
     }
     if (rr > tol2) return fail(c, OFKS_NOT_CONVERGED, "Hartree CG did not reach %g", rt);
@@ -1793,20 +1787,18 @@ int ofks_assemble(ofks_ctx *c) {
     dfree(c, c->veff_q);
     dfree(c, c->bvec);
     dfree(c, c->U);
-    dfree(c, c->cg_r);
-    dfree(c, c->cg_d);
-    dfree(c, c->cg_q);
+    dfree(c, c->cg_st[0]);
+    dfree(c, c->cg_st[1]);
     dfree(c, c->cg_sc);
     dfree(c, c->cg_part);
     // the quadrature-point arrays of the density (4 per tetrahedron, four
     // of them: 6.2 GB at n = 8e6) are allocated on first use (ensure_scf_work)
     CHK(dalloc(c, &c->bvec, n));
     CHK(dalloc(c, &c->U, n));
-    CHK(dalloc(c, &c->cg_r, n));
-    CHK(dalloc(c, &c->cg_d, n));
-    CHK(dalloc(c, &c->cg_q, n));
+    CHK(dalloc(c, &c->cg_st[0], 4 * n));
+    CHK(dalloc(c, &c->cg_st[1], 4 * n));
     CHK(dalloc(c, &c->cg_sc, 8));
-    CHK(dalloc(c, &c->cg_part, 4 * CG_BLOCKS));
+    CHK(dalloc(c, &c->cg_part, 2 * 3 * (size_t)cg_iter_blocks_max()));
     HIPCHK(hipMemsetAsync(c->U, 0, n * sizeof(double), s));
     CHK(build_halo_plan(c));
     c->has_system = true;
