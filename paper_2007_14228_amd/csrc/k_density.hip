@@ -92,15 +92,18 @@ __global__ __launch_bounds__(256) void k_density_xc(int64_t nt, int p, const int
 }
 
 // b_i = sum_{K ni i} sum_q |K|/4 rho(q) lambda_a(q)
-__global__ void k_load_vec(int64_t nn, const int32_t *__restrict__ dof, const int64_t *__restrict__ iptr,
-                           const int32_t *__restrict__ inc, const double *__restrict__ geom,
-                           const double *__restrict__ rho_q, double *__restrict__ b) {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= nn) return;
-    const int32_t i = dof[v];
-    if (i < 0) return;
+// (eight lanes a node; with one thread a node 217 us at 2.2e5 nodes)
+__global__ __launch_bounds__(256) void k_load_vec(int64_t nn, const int32_t *__restrict__ dof,
+                                                 const int64_t *__restrict__ iptr, const int32_t *__restrict__ inc,
+                                                 const double *__restrict__ geom, const double *__restrict__ rho_q,
+                                                 double *__restrict__ b) {
+    const int64_t v = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 3;
+    const int li = threadIdx.x & 7;
+    const int32_t i = v < nn ? dof[v] : -1;
+    if (i < 0) return;   // whole groups of eight
     double s = 0.0;
-    for (int64_t k = iptr[v]; k < iptr[v + 1]; ++k) {
+    const int64_t k1 = iptr[v + 1];
+    for (int64_t k = iptr[v] + li; k < k1; k += 8) {
         const int64_t t = inc[k] >> 2;
         const int a = inc[k] & 3;
         const double w = 0.25 * geom[13 * t];
@@ -108,7 +111,9 @@ __global__ void k_load_vec(int64_t nn, const int32_t *__restrict__ dof, const in
         for (int q = 0; q < 4; ++q) acc += rho_q[4 * t + q] * (q == a ? OFKS_QA : OFKS_QB);
         s += w * acc;
     }
-    b[i] = s;
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) s += __shfl_xor(s, off, 8);
+    if (li == 0) b[i] = s;
 }
 
 __global__ void k_veff(int64_t nt, const int32_t *__restrict__ tets, const int32_t *__restrict__ dof,
@@ -213,7 +218,7 @@ template hipError_t launch_density_xc<float>(hipStream_t, int, int64_t, int, con
 
 hipError_t launch_load_vec(hipStream_t s, int64_t nn, const int32_t *dof, const int64_t *iptr, const int32_t *inc,
                            const double *geom, const double *rho_q, double *b) {
-    hipLaunchKernelGGL(k_load_vec, dim3(nb_of(nn, 256)), dim3(256), 0, s, nn, dof, iptr, inc, geom, rho_q, b);
+    hipLaunchKernelGGL(k_load_vec, dim3(nb_of(8 * nn, 256)), dim3(256), 0, s, nn, dof, iptr, inc, geom, rho_q, b);
     return hipGetLastError();
 }
 hipError_t launch_veff(hipStream_t s, int64_t nt, const int32_t *tets, const int32_t *dof, const double *U,

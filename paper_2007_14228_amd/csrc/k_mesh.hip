@@ -3,9 +3,9 @@
 // element geometry, V_ext at quadrature points and the assembly of L, B and
 // potential matrices M(V).
 //
-// Assembly is a gather: the thread that owns row i walks the tetrahedra that
-// touch node i in ascending order and adds each element entry (a, b) into its
-// own row.  No atomics touch values, so every sum has a fixed order.
+// Assembly is a gather: the lane that owns an entry of row i walks the
+// tetrahedra that touch node i in ascending order and adds each element entry
+// of its column.  No atomics touch values, so every sum has a fixed order.
 // Incidence lists are filled with atomics (order unspecified) and then sorted
 // per node, which makes the CSR pattern and all values reproducible.
 #include "common.hpp"
@@ -201,7 +201,16 @@ __global__ void k_vext(int64_t nt, const double *__restrict__ xyz, const int32_t
 // Row-gather assembly.  mode 0: L, B, M(vq) and the interleaved pairs
 // hb = (L/2 + M, B), lb = (L/2, B), plus the diagonals.  mode 1: hb.x and
 // hdiag only (H = L/2 + M(vq) with L from Lv).
-__global__ __launch_bounds__(128) void k_assemble(int64_t nn, int mode, const int32_t *__restrict__ dof,
+//
+// Sixteen lanes a row.  A lane loads one of the node's tetrahedra and leaves
+// its DOFs and its four element entries of this row in LDS; then each lane,
+// the owner of one entry of the row, walks the sixteen tetrahedra in order and
+// adds those that hold its column.  Bound by the gathers of the element data
+// (each tetrahedron is read by its four nodes).  With one thread a row, the
+// row's sums in per-thread arrays (scratch memory) and a search of the row for
+// each element entry, mode 1 took 852 us at n = 2.0e5 (1.2e6 tetrahedra).
+template <int MODE>
+__global__ __launch_bounds__(256) void k_assemble(int64_t nn, const int32_t *__restrict__ dof,
                                                  const int64_t *__restrict__ iptr,
                                                  const int32_t *__restrict__ inc,
                                                  const int32_t *__restrict__ tets,
@@ -213,51 +222,75 @@ __global__ __launch_bounds__(128) void k_assemble(int64_t nn, int mode, const in
                                                  double2 *__restrict__ hb, double2 *__restrict__ lb,
                                                  double *__restrict__ lhd, double *__restrict__ bd,
                                                  double *__restrict__ hd) {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= nn) return;
-    const int32_t i = dof[v];
-    if (i < 0) return;
-    const int64_t r0 = row_ptr[i];
-    const int len = (int)(row_ptr[i + 1] - r0);
-    double lacc[OFKS_MAX_ROW], bacc[OFKS_MAX_ROW], macc[OFKS_MAX_ROW];
-    for (int k = 0; k < len; ++k) { lacc[k] = 0.0; bacc[k] = 0.0; macc[k] = 0.0; }
-    for (int64_t k = iptr[v]; k < iptr[v + 1]; ++k) {
-        const int64_t t = inc[k] >> 2;
-        const int a = inc[k] & 3;
-        const double *g = geom + 13 * t;
-        const double vol = g[0];
-        double w[4];
-        for (int q = 0; q < 4; ++q) w[q] = 0.25 * vol * vq[4 * t + q];
-        for (int b = 0; b < 4; ++b) {
-            const int32_t j = dof[tets[4 * t + b]];
-            if (j < 0) continue;
-            int pos = 0;
-            while (pos < len && col[r0 + pos] != j) ++pos;
-            if (pos == len) continue;   // cannot happen: the pattern came from the same incidence
-            double m = 0.0;
-            for (int q = 0; q < 4; ++q) m += w[q] * bary(q, a) * bary(q, b);
-            macc[pos] += m;
-            if (mode == 0) {
-                lacc[pos] += vol * (g[1 + 3 * a] * g[1 + 3 * b] + g[2 + 3 * a] * g[2 + 3 * b] +
-                                    g[3 + 3 * a] * g[3 + 3 * b]);
-                bacc[pos] += vol * (a == b ? 2.0 : 1.0) / 20.0;
+    // one row of lanes each, a tetrahedron's share of padding between the rows' banks
+    __shared__ int4 sd[16][17];
+    __shared__ double2 sm[16][17][2], sl[MODE == 0 ? 16 : 1][17][2], sb[MODE == 0 ? 16 : 1][17];
+    const int li = threadIdx.x & 15, g = threadIdx.x >> 4;
+    const int64_t v = (int64_t)blockIdx.x * 16 + g;
+    const int32_t i = v < nn ? dof[v] : -1;
+    if (i < 0) return;   // whole rows of lanes; no barrier below, a row of lanes shares LDS within its wave
+    const int64_t r0 = row_ptr[i], k0 = iptr[v];
+    const int len = (int)(row_ptr[i + 1] - r0), ninc = (int)(iptr[v + 1] - k0);
+    for (int c = 0; c < len; c += 16) {
+        const int64_t e = r0 + c + li;
+        const bool in = c + li < len;
+        const int32_t j = in ? col[e] : -2;
+        double lacc = 0.0, bacc = 0.0, macc = 0.0;
+        for (int kk = 0; kk < ninc; kk += 16) {
+            const int cnt = min(16, ninc - kk);
+            if (li < cnt) {
+                const int64_t t = inc[k0 + kk + li] >> 2;
+                const int a = inc[k0 + kk + li] & 3;
+                const int4 tv = ((const int4 *)tets)[t];
+                const double *gm = geom + 13 * t;
+                const double vol = gm[0];
+                double w[4], m[4];
+                for (int q = 0; q < 4; ++q) w[q] = 0.25 * vol * vq[4 * t + q];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    m[b] = 0.0;
+                    for (int q = 0; q < 4; ++q) m[b] += w[q] * bary(q, a) * bary(q, b);
+                }
+                sd[g][li] = make_int4(dof[tv.x], dof[tv.y], dof[tv.z], dof[tv.w]);
+                sm[g][li][0] = make_double2(m[0], m[1]);
+                sm[g][li][1] = make_double2(m[2], m[3]);
+                if (MODE == 0) {
+                    const double ax = gm[1 + 3 * a], ay = gm[2 + 3 * a], az = gm[3 + 3 * a];
+                    double l[4];
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+                        l[b] = vol * (ax * gm[1 + 3 * b] + ay * gm[2 + 3 * b] + az * gm[3 + 3 * b]);
+                    sl[g][li][0] = make_double2(l[0], l[1]);
+                    sl[g][li][1] = make_double2(l[2], l[3]);
+                    sb[g][li] = make_double2(vol * 2.0 / 20.0, vol * 1.0 / 20.0);
+                }
             }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            for (int u = 0; u < cnt; ++u) {
+                const int4 d = sd[g][u];
+                const double2 m0 = sm[g][u][0], m1 = sm[g][u][1];
+                macc += j == d.x ? m0.x : j == d.y ? m0.y : j == d.z ? m1.x : j == d.w ? m1.y : 0.0;
+                if (MODE == 0) {
+                    const double2 l0 = sl[g][u][0], l1 = sl[g][u][1], bb = sb[g][u];
+                    lacc += j == d.x ? l0.x : j == d.y ? l0.y : j == d.z ? l1.x : j == d.w ? l1.y : 0.0;
+                    // all of the node's tetrahedra hold its own column
+                    bacc += j == i ? bb.x : j == d.x || j == d.y || j == d.z || j == d.w ? bb.y : 0.0;
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
-    }
-    for (int k = 0; k < len; ++k) {
-        const int64_t e = r0 + k;
-        const bool diag = col[e] == i;
-        if (mode == 0) {
-            Lv[e] = lacc[k];
-            Bv[e] = bacc[k];
-            Mv[e] = macc[k];
-            hb[e] = make_double2(0.5 * lacc[k] + macc[k], bacc[k]);
-            lb[e] = make_double2(0.5 * lacc[k], bacc[k]);
-            if (diag) { lhd[i] = 0.5 * lacc[k]; bd[i] = bacc[k]; hd[i] = 0.5 * lacc[k] + macc[k]; }
+        if (!in) continue;
+        if (MODE == 0) {
+            Lv[e] = lacc;
+            Bv[e] = bacc;
+            Mv[e] = macc;
+            hb[e] = make_double2(0.5 * lacc + macc, bacc);
+            lb[e] = make_double2(0.5 * lacc, bacc);
+            if (j == i) { lhd[i] = 0.5 * lacc; bd[i] = bacc; hd[i] = 0.5 * lacc + macc; }
         } else {
-            const double h = 0.5 * Lv[e] + macc[k];
+            const double h = 0.5 * Lv[e] + macc;
             hb[e].x = h;
-            if (diag) hd[i] = h;
+            if (j == i) hd[i] = h;
         }
     }
 }
@@ -327,7 +360,7 @@ hipError_t launch_inc_fill(hipStream_t s, int64_t nt, const int32_t *tets, const
     return hipGetLastError();
 }
 hipError_t launch_inc_sort(hipStream_t s, int64_t nn, const int64_t *ptr, int32_t *inc, int32_t *err) {
-    hipLaunchKernelGGL(k_inc_sort, dim3(nblk(nn, 128)), dim3(128), 0, s, nn, ptr, inc, err);
+    hipLaunchKernelGGL(k_inc_sort, dim3(nblk(nn, 16)), dim3(256), 0, s, nn, ptr, inc, err);
     return hipGetLastError();
 }
 hipError_t launch_row_pattern(hipStream_t s, int64_t nn, int fill, const int32_t *dof, const int64_t *iptr,
@@ -351,8 +384,13 @@ hipError_t launch_assemble(hipStream_t s, int64_t nn, int mode, const int32_t *d
                            const int32_t *inc, const int32_t *tets, const double *geom, const double *vq,
                            const int64_t *rp, const int32_t *col, double *Lv, double *Bv, double *Mv,
                            double2 *hb, double2 *lb, double *lhd, double *bd, double *hd) {
-    hipLaunchKernelGGL(k_assemble, dim3(nblk(nn, 128)), dim3(128), 0, s, nn, mode, dof, iptr, inc, tets, geom,
-                       vq, rp, col, Lv, Bv, Mv, hb, lb, lhd, bd, hd);
+    const dim3 grid(nblk(nn, 16)), block(256);
+    if (mode == 0)
+        hipLaunchKernelGGL((k_assemble<0>), grid, block, 0, s, nn, dof, iptr, inc, tets, geom, vq, rp, col, Lv, Bv, Mv,
+                           hb, lb, lhd, bd, hd);
+    else
+        hipLaunchKernelGGL((k_assemble<1>), grid, block, 0, s, nn, dof, iptr, inc, tets, geom, vq, rp, col, Lv, Bv, Mv,
+                           hb, lb, lhd, bd, hd);
     return hipGetLastError();
 }
 hipError_t launch_pairs_to_f32(hipStream_t s, int64_t m, const double2 *a, float2 *b) {
