@@ -33,15 +33,29 @@ inline int halo_plan_build(int64_t n, const int64_t *rp, const int32_t *col, int
     if (n <= 0 || rp[0] != 0) { *where = 0; return HALO_BAD_ROWPTR; }
     const int64_t nnz = rp[n];
     if (hmax < 1 || hmax > 65536 || rmax < 1) { *where = 0; return HALO_BAD_PLAN; }
-    std::vector<int64_t> stamp(n, -1);   // b: in block b's halo; -(b + 2): counted for block b, not yet added
+    std::vector<int64_t> stamp(n, -1);   // b: in block b's halo
     std::vector<int32_t> slot(n, 0);
-    std::vector<int32_t> cur;
+    std::vector<int32_t> cur, words;
+    std::vector<uint64_t> bits((size_t)(n + 63) / 64, 0);
     P.lcol.assign((size_t)std::max<int64_t>(nnz, 0), 0);
     P.halo.reserve((size_t)(3.5 * n) + 64);
     int64_t b = 0, start = 0;
     auto close = [&](int64_t end) {
-        std::sort(cur.begin(), cur.end());
-        for (size_t k = 0; k < cur.size(); ++k) slot[cur[k]] = (int32_t)k;
+        // ascending order by way of a bitmap: only its few touched words are sorted
+        words.clear();
+        for (const int32_t c : cur) {
+            if (!bits[c >> 6]) words.push_back(c >> 6);
+            bits[c >> 6] |= uint64_t(1) << (c & 63);
+        }
+        std::sort(words.begin(), words.end());
+        int32_t k = 0;
+        for (const int32_t w : words) {
+            for (uint64_t m = bits[w]; m; m &= m - 1, ++k) {
+                cur[k] = 64 * w + __builtin_ctzll(m);
+                slot[cur[k]] = k;
+            }
+            bits[w] = 0;
+        }
         for (int64_t e = rp[start]; e < rp[end]; ++e) P.lcol[e] = (uint16_t)slot[col[e]];
         P.rbase.push_back(slot[start]);
         P.halo.insert(P.halo.end(), cur.begin(), cur.end());
@@ -55,25 +69,22 @@ inline int halo_plan_build(int64_t n, const int64_t *rp, const int32_t *col, int
         if (rp[r + 1] < rp[r] || rp[r + 1] > nnz) { *where = r; return HALO_BAD_ROWPTR; }
         if (rp[r + 1] - rp[r] > emax) { *where = r; P = HaloPlan(); return HALO_TOO_WIDE; }
         for (int pass = 0;; ++pass) {
-            int64_t fresh = 0;
-            for (int64_t e = rp[r]; e <= rp[r + 1]; ++e) {   // the entries, then the row itself
-                const int64_t cc = e < rp[r + 1] ? col[e] : r;
-                if (cc < 0 || cc >= n) { *where = e; return HALO_BAD_COLUMN; }
-                if (stamp[cc] != b && stamp[cc] != -(b + 2)) {
-                    stamp[cc] = -(b + 2);
-                    ++fresh;
+            if (r - start < rmax) {
+                const size_t mark = cur.size();
+                for (int64_t e = rp[r]; e <= rp[r + 1]; ++e) {   // the entries, then the row itself
+                    const int64_t cc = e < rp[r + 1] ? col[e] : r;
+                    if (cc < 0 || cc >= n) { *where = e; return HALO_BAD_COLUMN; }
+                    if (stamp[cc] != b) {
+                        stamp[cc] = b;
+                        cur.push_back((int32_t)cc);
+                    }
                 }
+                if ((int64_t)cur.size() <= hmax) break;
+                for (size_t k = mark; k < cur.size(); ++k) stamp[cur[k]] = -1;   // the row does not fit
+                cur.resize(mark);
             }
-            if ((int64_t)cur.size() + fresh <= hmax && r - start < rmax) break;
             if (pass == 1 || r == start) { *where = r; P = HaloPlan(); return HALO_TOO_WIDE; }
-            close(r);   // the row opens the next block; count it again there
-        }
-        for (int64_t e = rp[r]; e <= rp[r + 1]; ++e) {
-            const int32_t cc = e < rp[r + 1] ? col[e] : (int32_t)r;
-            if (stamp[cc] != b) {
-                stamp[cc] = b;
-                cur.push_back(cc);
-            }
+            close(r);   // the row opens the next block
         }
     }
     close(n);
