@@ -147,30 +147,57 @@ __global__ __launch_bounds__(256) void k_gl_out(int64_t n, int p, int lpr_log2, 
 }
 
 // ---------------------------------------------------------------------------
-// Training (FP64 blocks).  Rows are split into gridDim.x chunks; thread c of
-// a block owns column c (and c + 256, ...) of its chunk, so every per-column
-// partial has a fixed summation order.
+// Training (FP64 blocks).  Rows are split into gridDim.x chunks; a block's 256
+// threads take 256 / p whole rows of its chunk at a time (p columns, rows
+// adjoining, so every load is of consecutive elements), each thread one column,
+// and the row groups' sums meet in LDS in a fixed order.  (With a thread a
+// column, p = 16 left 240 threads idle: colsums 67 us, bwd1 150 us at n = 2e4.)
 // ---------------------------------------------------------------------------
+
+// Calls f(row, column, element) for this thread's elements of columns cb ..
+// and, with S per-thread sums in s, adds the row groups' up into out[j][column].
+template <int S, typename F, typename O>
+__device__ __forceinline__ void gl_columns(int64_t n, int p, const F &f, const O &out) {
+    __shared__ double red[S][256];
+    const int64_t chunk = (n + gridDim.x - 1) / gridDim.x;
+    const int64_t r0 = (int64_t)blockIdx.x * chunk, r1 = min(n, r0 + chunk);
+    for (int cb = 0; cb < p; cb += 256) {
+        const int w = min(p - cb, 256), rows = 256 / w;
+        const int r = threadIdx.x / w, c = cb + threadIdx.x - r * w;
+        double s[S];
+#pragma unroll
+        for (int j = 0; j < S; ++j) s[j] = 0.0;
+        if (r < rows)
+#pragma unroll 4
+            for (int64_t i = r0 + r; i < r1; i += rows) f(i, c, i * p + c, s);
+#pragma unroll
+        for (int j = 0; j < S; ++j) red[j][threadIdx.x] = s[j];
+        __syncthreads();
+        if (threadIdx.x < w)
+#pragma unroll
+            for (int j = 0; j < S; ++j) {
+                double v = 0.0;
+                for (int q = 0; q < rows; ++q) v += red[j][q * w + threadIdx.x];
+                out(j, cb + threadIdx.x, v);
+            }
+        __syncthreads();
+    }
+}
 
 // part[block][0..p) = sum g^2, part[block][p..2p) = sum g J g.
 __global__ __launch_bounds__(256) void k_gl_colsums(int64_t n, int p, const double *__restrict__ G,
                                                    const double *__restrict__ lhd, const double *__restrict__ bd,
                                                    const double *__restrict__ lam, const uint8_t *__restrict__ negl,
                                                    double *__restrict__ part) {
-    const int64_t chunk = (n + gridDim.x - 1) / gridDim.x;
-    const int64_t r0 = (int64_t)blockIdx.x * chunk, r1 = min(n, r0 + chunk);
-    for (int c = threadIdx.x; c < p; c += blockDim.x) {
-        double gg = 0.0, gjg = 0.0;
-        const bool on = negl[c] != 0;
-        for (int64_t i = r0; i < r1; ++i) {
-            const double g = G[i * p + c];
-            const double J = on ? 1.0 / (lhd[i] - lam[c] * bd[i]) : 1.0;
-            gg += g * g;
-            gjg += g * J * g;
-        }
-        part[(int64_t)blockIdx.x * 2 * p + c] = gg;
-        part[(int64_t)blockIdx.x * 2 * p + p + c] = gjg;
-    }
+    gl_columns<2>(
+        n, p,
+        [&](int64_t i, int c, int64_t e, double (&s)[2]) __attribute__((always_inline)) {
+            const double g = G[e];
+            const double J = negl[c] != 0 ? 1.0 / (lhd[i] - lam[c] * bd[i]) : 1.0;
+            s[0] += g * g;
+            s[1] += g * J * g;
+        },
+        [&](int j, int c, double v) { part[((int64_t)blockIdx.x * 2 + j) * p + c] = v; });
 }
 
 // dP = w (T P - G) into TP (in place), dR = ft J dP; loss partials per column:
@@ -181,32 +208,32 @@ __global__ __launch_bounds__(256) void k_gl_bwd1(int64_t n, int p, const double 
                                                 const double *__restrict__ bd, const double *__restrict__ lam,
                                                 const uint8_t *__restrict__ negl, const double *__restrict__ w,
                                                 double *__restrict__ dR, double *__restrict__ part) {
-    const int64_t chunk = (n + gridDim.x - 1) / gridDim.x;
-    const int64_t r0 = (int64_t)blockIdx.x * chunk, r1 = min(n, r0 + chunk);
-    for (int c = threadIdx.x; c < p; c += blockDim.x) {
-        const bool on = negl[c] != 0;
-        double acc = 0.0;
-        for (int64_t i = r0; i < r1; ++i) {
-            const int64_t e = i * p + c;
+    gl_columns<1>(
+        n, p,
+        [&](int64_t i, int c, int64_t e, double (&s)[1]) __attribute__((always_inline)) {
+            const bool on = negl[c] != 0;
             const double pv = P[e], g = G[e];
             const double tp = on ? TP[e] : pv;
-            acc += 0.5 * pv * tp - g * pv;
+            s[0] += 0.5 * pv * tp - g * pv;
             const double dp = w[c] * (tp - g);
             const double J = on ? 1.0 / (lhd[i] - lam[c] * bd[i]) : 1.0;
             TP[e] = dp;
             dR[e] = (double)FT[e] * J * dp;
-        }
-        part[(int64_t)blockIdx.x * p + c] = acc;
-    }
+        },
+        [&](int, int c, double v) { part[(int64_t)blockIdx.x * p + c] = v; });
 }
 
 // Parameter gradient: with dP (in DP), R, Z, dR and T dR (TDR, active
 // columns): dft = dP J R, dZ = dP - T dR, dfs = dZ Z, then backpropagation
 // through the heads.  Grid-stride over batches of 256 elements: thread t puts
-// element t's inputs x, hidden layer h and (dfs, dft) in LDS; then thread k
-// (< 226) adds parameter k's contributions of the whole batch to its own
-// FP64 sum, in element order.  part[block][GL_NPAR].
-constexpr int GL_LDS = 257;   // padded row of the batch arrays (bank spread)
+// element t's inputs x, hidden layer h and (dfs, dft) in LDS; then thread
+// (unit kk, group q), 32 by 8, takes unit kk's seven parameters (W1[kk][0..3],
+// b1[kk], W2[0..1][kk]) over the elements 8 u + q, one dz for all of them, in
+// FP64 sums; the groups' sums meet in LDS at the end, in a fixed order.
+// part[block][GL_NPAR].  Bound by the vector units (tanh, and the conversions
+// and FP64 additions: every FP32 product is added in FP64).  With a thread a
+// parameter, dz formed five times over: 184 us at 8.1e5 elements, now 55 us.
+constexpr int GL_LDS = 33;   // padded row of an element's hidden layer (bank spread)
 __global__ __launch_bounds__(256) void k_gl_bwd2(int64_t n, int p, const double *__restrict__ G,
                                                 const double *__restrict__ DP, const double *__restrict__ R,
                                                 const double *__restrict__ Z, const double *__restrict__ dR,
@@ -215,10 +242,15 @@ __global__ __launch_bounds__(256) void k_gl_bwd2(int64_t n, int p, const double 
                                                 const double *__restrict__ lam, const uint8_t *__restrict__ negl,
                                                 const double *__restrict__ g2, const float *__restrict__ W,
                                                 const float *__restrict__ norm, double *__restrict__ part) {
-    __shared__ float sx[4][GL_LDS], sh[GL_H][GL_LDS], sd[2][GL_LDS];
+    static_assert(GL_H == 32, "thread (unit, group)");
+    __shared__ float4 sx[256];
+    __shared__ float2 sd[256];
+    __shared__ double sh_[(256 * GL_LDS + 1) / 2];   // the batch's hidden layers; at the end the groups' sums
+    float *sh = (float *)sh_;
     const float *W2 = W + 5 * GL_H;
-    const int t = threadIdx.x;
-    double acc = 0.0;
+    const int t = threadIdx.x, kk = t & 31, q = t >> 5;
+    const float w0 = W2[kk], w1 = W2[GL_H + kk];
+    double acc[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, ab = 0.0;
     const int64_t m = n * p;
     for (int64_t e0 = (int64_t)blockIdx.x * 256; e0 < m; e0 += (int64_t)gridDim.x * 256) {
         const int64_t e = e0 + t;
@@ -233,41 +265,49 @@ __global__ __launch_bounds__(256) void k_gl_bwd2(int64_t n, int p, const double 
             gl_forward<true>(W, x, fs, ft, h);
             const double J = on ? 1.0 / (lhd[i] - lam[c] * bd[i]) : 1.0;
             const double dp = DP[e];
-            sd[1][t] = (float)(dp * J * R[e]);                         // dft
-            sd[0][t] = (float)((dp - (on ? TDR[e] : dR[e])) * Z[e]);   // dfs
+            sd[t] = make_float2((float)((dp - (on ? TDR[e] : dR[e])) * Z[e]),   // dfs
+                                (float)(dp * J * R[e]));                        // dft
+            sx[t] = make_float4(x[0], x[1], x[2], x[3]);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) sx[j][t] = x[j];
-#pragma unroll
-            for (int k = 0; k < GL_H; ++k) sh[k][t] = h[k];
+            for (int k = 0; k < GL_H; ++k) sh[t * GL_LDS + k] = h[k];
         } else {
-            sd[0][t] = sd[1][t] = 0.0f;
+            sd[t] = make_float2(0.0f, 0.0f);
+            sx[t] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) sx[j][t] = 0.0f;
-#pragma unroll
-            for (int k = 0; k < GL_H; ++k) sh[k][t] = 0.0f;
+            for (int k = 0; k < GL_H; ++k) sh[t * GL_LDS + k] = 0.0f;
         }
         __syncthreads();
-        if (t < GL_NPAR) {
-            if (t < 5 * GL_H) {          // W1[kk][j] (t < 128) or b1[kk]: through dz_kk
-                const int kk = t < 4 * GL_H ? t >> 2 : t - 4 * GL_H;
-                const int j = t & 3;
-                const float w0 = W2[kk], w1 = W2[GL_H + kk];
-                for (int u = 0; u < 256; ++u) {
-                    const float hv = sh[kk][u];
-                    const float dz = (sd[0][u] * w0 + sd[1][u] * w1) * (1.0f - hv * hv);
-                    acc += (double)(t < 4 * GL_H ? dz * sx[j][u] : dz);
-                }
-            } else if (t < 7 * GL_H) {   // W2[r][kk]
-                const int r = (t - 5 * GL_H) >> 5, kk = (t - 5 * GL_H) & (GL_H - 1);
-                for (int u = 0; u < 256; ++u) acc += (double)(sd[r][u] * sh[kk][u]);
-            } else {                     // b2[r]
-                const int r = t - 7 * GL_H;
-                for (int u = 0; u < 256; ++u) acc += (double)sd[r][u];
-            }
+#pragma unroll 4
+        for (int u = q; u < 256; u += 8) {
+            const float hv = sh[u * GL_LDS + kk];
+            const float2 d = sd[u];
+            const float4 x = sx[u];
+            const float dz = (d.x * w0 + d.y * w1) * (1.0f - hv * hv);
+            acc[0] += (double)(dz * x.x);
+            acc[1] += (double)(dz * x.y);
+            acc[2] += (double)(dz * x.z);
+            acc[3] += (double)(dz * x.w);
+            acc[4] += (double)dz;
+            acc[5] += (double)(d.x * hv);
+            acc[6] += (double)(d.y * hv);
+            if (kk < 2) ab += (double)(kk == 0 ? d.x : d.y);   // b2[kk]
         }
         __syncthreads();
     }
-    if (t < GL_NPAR) part[(int64_t)blockIdx.x * GL_NPAR + t] = acc;
+    // parameter order W1[kk][0..3], b1[kk], W2[0][kk], W2[1][kk], b2[0..1]
+    static_assert(8 * GL_NPAR <= (256 * GL_LDS + 1) / 2, "the groups' sums fit");
+    double *sums = sh_ + q * GL_NPAR;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sums[4 * kk + j] = acc[j];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) sums[(4 + j) * GL_H + kk] = acc[4 + j];
+    if (kk < 2) sums[7 * GL_H + kk] = ab;
+    __syncthreads();
+    if (t < GL_NPAR) {
+        double v = 0.0;
+        for (int g = 0; g < 8; ++g) v += sh_[g * GL_NPAR + t];
+        part[(int64_t)blockIdx.x * GL_NPAR + t] = v;
+    }
 }
 
 // Adam on npar parameters with gradient gsum * scale.
