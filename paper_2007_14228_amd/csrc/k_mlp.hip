@@ -15,6 +15,7 @@
 // hand-written forward/backward, per-block gradient partials summed in a
 // fixed order, and Adam.  All MLP arithmetic is FP32.
 #include "common.hpp"
+#include <algorithm>
 
 namespace ofks {
 
@@ -28,47 +29,57 @@ __device__ __forceinline__ float fast_tanh(float x) {
     return fmaf(-2.0f, __builtin_amdgcn_rcpf(e + 1.0f), 1.0f);
 }
 
-// f(x) for standardized x; params in global memory (uniform across lanes)
-__device__ __forceinline__ float lp_forward(const float *__restrict__ W, const float x[4]) {
-    const float *W1 = W, *b1 = W + 4 * LP_H, *W2 = W + 5 * LP_H;
-    const float b2 = W[6 * LP_H];
-    float f = b2;
-#pragma unroll 8
-    for (int k = 0; k < LP_H; ++k) {
-        float z = b1[k];
-        z = fmaf(W1[4 * k + 0], x[0], z);
-        z = fmaf(W1[4 * k + 1], x[1], z);
-        z = fmaf(W1[4 * k + 2], x[2], z);
-        z = fmaf(W1[4 * k + 3], x[3], z);
-        f = fmaf(W2[k], fast_tanh(z), f);
-    }
-    return f;
-}
-
-// In place: P <- exp(f) J G (G is in P).  rms2[c] = sum_i g_ic^2 (FP64), n rows.
-// norm = [mu0..mu3, sigma0..sigma3].  Same lane mapping as the block kernels.
+// P = exp(f) J G (P may be G).  rms2[c] = sum_i g_ic^2 (FP64), n rows.
+// norm = [mu0..mu3, sigma0..sigma3].
+//
+// f(x) for standardized x: z_k = b1_k + W1[k] x, f = b2 + sum_k W2_k tanh z_k.
+// A block takes LP_ROWS rows (more where few lanes serve one) and forms, once
+// per row, the three row inputs (two FP64 logarithms) and, once per column, the
+// root mean square, all into LDS; then 2^lpr_log2 lanes a row, each with four
+// columns or more, keep the row's part of z in registers, so a column costs one
+// FMA a hidden unit and its tanh.  The order of the roundings is that of the
+// plain sums.  Bound by the vector units (an exponential and a reciprocal a
+// hidden unit).  With a lane per column and the row's and column's FP64
+// functions formed for each element: 228 us at n = 2.0e5, p = 64.
+constexpr int LP_ROWS = 64, LP_COLS = 1024;
 template <typename T>
-__global__ __launch_bounds__(256) void k_lp_apply(int64_t n, int p, int lpr_log2, T *__restrict__ P,
+__global__ __launch_bounds__(256) void k_lp_apply(int64_t n, int p, int lpr_log2, const T *G, T *P,
                                                  const double *__restrict__ lhd, const double *__restrict__ bd,
                                                  const double *__restrict__ hd, const T *__restrict__ lam,
                                                  const uint8_t *__restrict__ negl, const double *__restrict__ g2,
                                                  const float *__restrict__ W, const float *__restrict__ norm) {
-    const int lpr = 1 << lpr_log2;
-    const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> lpr_log2;
-    const int lane = threadIdx.x & (lpr - 1);
-    if (row >= n) return;
-    const double l2 = lhd[row], b = bd[row];
-    float xn[3];
-    xn[0] = ((float)log(l2) - norm[0]) / norm[4];
-    xn[1] = ((float)log(b) - norm[1]) / norm[5];
-    xn[2] = ((float)((hd[row] - l2) / b) - norm[2]) / norm[6];
-    for (int c = lane; c < p; c += lpr) {
-        const T g = P[row * p + c];
-        const float rms = (float)sqrt(g2[c] / (double)n);
-        const float x[4] = {xn[0], xn[1], xn[2], (rms > 0.0f ? (float)g / rms - norm[3] : -norm[3]) / norm[7]};
-        const float s = __expf(lp_forward(W, x));
-        const T J = negl[c] ? T(1) / (T(l2) - lam[c] * T(b)) : T(1);
-        P[row * p + c] = (T)s * J * g;
+    __shared__ float sx[3][256], srms[LP_COLS];
+    __shared__ T sl[256], sb[256];
+    const float *W1 = W, *b1 = W + 4 * LP_H, *W2 = W + 5 * LP_H;
+    const int lane = threadIdx.x & ((1 << lpr_log2) - 1), pass = 256 >> lpr_log2, rows = max(LP_ROWS, pass);
+    const int64_t row0 = (int64_t)blockIdx.x * rows;
+    if (threadIdx.x < rows && row0 + threadIdx.x < n) {
+        const int64_t i = row0 + threadIdx.x;
+        const double l2 = lhd[i], b = bd[i];
+        sx[0][threadIdx.x] = ((float)log(l2) - norm[0]) / norm[4];
+        sx[1][threadIdx.x] = ((float)log(b) - norm[1]) / norm[5];
+        sx[2][threadIdx.x] = ((float)((hd[i] - l2) / b) - norm[2]) / norm[6];
+        sl[threadIdx.x] = T(l2);
+        sb[threadIdx.x] = T(b);
+    }
+    for (int c = threadIdx.x; c < p; c += 256) srms[c] = (float)sqrt(g2[c] / (double)n);
+    __syncthreads();
+    for (int r = threadIdx.x >> lpr_log2; r < rows && row0 + r < n; r += pass) {
+        const float x0 = sx[0][r], x1 = sx[1][r], x2 = sx[2][r];
+        float a[LP_H];
+#pragma unroll
+        for (int k = 0; k < LP_H; ++k)
+            a[k] = fmaf(W1[4 * k + 2], x2, fmaf(W1[4 * k + 1], x1, fmaf(W1[4 * k], x0, b1[k])));
+        const T l2 = sl[r], b = sb[r];
+        for (int c = lane; c < p; c += 1 << lpr_log2) {
+            const T g = G[(row0 + r) * p + c];
+            const float rms = srms[c], x3 = (rms > 0.0f ? (float)g / rms - norm[3] : -norm[3]) / norm[7];
+            float f = W[6 * LP_H];
+#pragma unroll
+            for (int k = 0; k < LP_H; ++k) f = fmaf(W2[k], fast_tanh(fmaf(W1[4 * k + 3], x3, a[k])), f);
+            const T J = negl[c] ? T(1) / (l2 - lam[c] * b) : T(1);
+            P[(row0 + r) * p + c] = (T)__expf(f) * J * g;
+        }
     }
 }
 
@@ -212,20 +223,16 @@ __global__ __launch_bounds__(256) void k_lp_stats(int64_t m, const float *__rest
 }
 
 // ---------------------------------------------------------------------------
-static inline int lp_ilog2c(int x) {
-    int l = 0;
-    while ((1 << l) < x) ++l;
-    return l;
-}
-
 template <typename T>
-hipError_t launch_lp_apply(hipStream_t s, int64_t n, int p, T *P, const double *lhd, const double *bd,
+hipError_t launch_lp_apply(hipStream_t s, int64_t n, int p, const T *G, T *P, const double *lhd, const double *bd,
                            const double *hd, const T *lam, const uint8_t *negl, const double *g2, const float *W,
                            const float *norm) {
-    int l2 = lp_ilog2c(p);
-    if (l2 > 6) l2 = 6;
-    const unsigned grid = (unsigned)(((n << l2) + 255) / 256);
-    hipLaunchKernelGGL((k_lp_apply<T>), dim3(grid), dim3(256), 0, s, n, p, l2, P, lhd, bd, hd, lam, negl, g2, W, norm);
+    if (p > LP_COLS) return hipErrorInvalidValue;
+    int l2 = 0;   // four columns a lane, or up to seven; at most a wave a row
+    while (l2 < 6 && (8 << l2) <= p) ++l2;
+    const int rows = std::max(LP_ROWS, 256 >> l2);
+    hipLaunchKernelGGL((k_lp_apply<T>), dim3((unsigned)((n + rows - 1) / rows)), dim3(256), 0, s, n, p, l2, G, P, lhd,
+                       bd, hd, lam, negl, g2, W, norm);
     return hipGetLastError();
 }
 
@@ -259,10 +266,10 @@ hipError_t launch_lp_stats(hipStream_t s, int grid, int64_t m, const float *S, d
     return hipGetLastError();
 }
 
-template hipError_t launch_lp_apply<double>(hipStream_t, int64_t, int, double *, const double *, const double *,
+template hipError_t launch_lp_apply<double>(hipStream_t, int64_t, int, const double *, double *, const double *, const double *,
                                             const double *, const double *, const uint8_t *, const double *,
                                             const float *, const float *);
-template hipError_t launch_lp_apply<float>(hipStream_t, int64_t, int, float *, const double *, const double *,
+template hipError_t launch_lp_apply<float>(hipStream_t, int64_t, int, const float *, float *, const double *, const double *,
                                            const double *, const float *, const uint8_t *, const double *,
                                            const float *, const float *);
 template hipError_t launch_lp_sample<double>(hipStream_t, int64_t, int, int64_t, int64_t, int64_t, int,

@@ -153,7 +153,7 @@ hipError_t launch_diag(hipStream_t, int64_t, const int64_t *, const int32_t *, c
                        int32_t *);
 // (k_mlp.hip)
 template <typename T>
-hipError_t launch_lp_apply(hipStream_t, int64_t, int, T *, const double *, const double *, const double *, const T *,
+hipError_t launch_lp_apply(hipStream_t, int64_t, int, const T *, T *, const double *, const double *, const double *, const T *,
                            const uint8_t *, const double *, const float *, const float *);
 template <typename T>
 hipError_t launch_lp_sample(hipStream_t, int64_t, int, int64_t, int64_t, int64_t, int, const T *, const T *,
@@ -1266,7 +1266,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
         if (!c->lp_ready) return fail(c, OFKS_ESTATE, "learned preconditioner: no weights (ofks_lp_set_weights)");
         HIPCHK(hipMemcpyAsync(c->g2, c->red + 1, p * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
         Scope sc(c, "mlp");
-        HIPCHK(launch_lp_apply<T>(c->stream, n, p, B.P, c->lhd, c->bd, c->hd, B.lam, c->active, c->g2, c->lp_W,
+        HIPCHK(launch_lp_apply<T>(c->stream, n, p, B.P, B.P, c->lhd, c->bd, c->hd, B.lam, c->active, c->g2, c->lp_W,
                                   c->lp_norm));
     }
 
@@ -2463,8 +2463,7 @@ int ofks_lp_apply(ofks_ctx *c, int32_t p, const double *lam, const double *G, do
     CHK(ensure_part(c, (size_t)c->grid * p));
     HIPCHK(launch_coldot<double>(c->stream, c->grid, c->n, p, G, G, c->part));
     HIPCHK(launch_colsum(c->stream, c->grid, p, c->part, g2));
-    HIPCHK(hipMemcpyAsync(P, G, (size_t)c->n * p * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-    HIPCHK(launch_lp_apply<double>(c->stream, c->n, p, P, c->lhd, c->bd, c->hd, lamd, neg, g2, c->lp_W, c->lp_norm));
+    HIPCHK(launch_lp_apply<double>(c->stream, c->n, p, G, P, c->lhd, c->bd, c->hd, lamd, neg, g2, c->lp_W, c->lp_norm));
     return sync(c);
 }
 
