@@ -144,42 +144,43 @@ __global__ __launch_bounds__(256) void k_cg_state(int64_t n, const double *__res
     st[2 * i + 1] = make_double2(0.0, 0.0);
 }
 
-// from v = M^-1 A x: u = M^-1 (rhs - A x), rhs = scale b; partials of |r|^2 and |rhs|^2
+// from v = M^-1 A x: u = M^-1 (rhs - A x), rhs = scale b; partials of |rhs|^2
 __global__ __launch_bounds__(256) void k_cg_start(int64_t n, double scale, const double *__restrict__ b,
                                                  const double *__restrict__ dg, const double2 *__restrict__ in,
                                                  double2 *__restrict__ st, double *__restrict__ part) {
-    double rr = 0.0, bb = 0.0;
+    double bb = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const double rhs = scale * b[i], r = fma(-dg[i], in[2 * i].y, rhs);
         st[2 * i] = make_double2(r / dg[i], 0.0);
         st[2 * i + 1] = make_double2(0.0, 0.0);
-        rr += r * r;
         bb += rhs * rhs;
     }
-    __shared__ double r2[2][256];
-    r2[0][threadIdx.x] = rr;
-    r2[1][threadIdx.x] = bb;
+    __shared__ double red[256];
+    red[threadIdx.x] = bb;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w)
-            for (int j = 0; j < 2; ++j) r2[j][threadIdx.x] += r2[j][threadIdx.x + w];
+        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x < 2) part[threadIdx.x * gridDim.x + blockIdx.x] = r2[threadIdx.x][0];
+    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// the sum of array j of nb partials into sc[j], j = blockIdx.x, in a fixed order
-__global__ __launch_bounds__(256) void k_cg_reduce(int nb, const double *__restrict__ part, double *__restrict__ sc) {
+// the iteration's bound sc[3] = rtol2 |rhs|^2 from nb partials, in a fixed order; nothing stopped yet
+__global__ __launch_bounds__(256) void k_cg_bound(int nb, double rtol2, const double *__restrict__ part,
+                                                  double *__restrict__ sc) {
     __shared__ double r[256];
     double a = 0.0;
-    for (int k = threadIdx.x; k < nb; k += 256) a += part[(int64_t)blockIdx.x * nb + k];
+    for (int k = threadIdx.x; k < nb; k += 256) a += part[k];
     r[threadIdx.x] = a;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if (threadIdx.x < w) r[threadIdx.x] += r[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) sc[blockIdx.x] = r[0];
+    if (threadIdx.x == 0) {
+        sc[0] = 0.0;
+        sc[3] = rtol2 * r[0];
+    }
 }
 
 // dot products for energies: part[block] = sum a .* b
@@ -230,12 +231,12 @@ hipError_t launch_cg_state(hipStream_t s, int64_t n, const double *x, double *st
     hipLaunchKernelGGL(k_cg_state, dim3(nb_of(n, 256)), dim3(256), 0, s, n, x, (double2 *)st);
     return hipGetLastError();
 }
-// sc[1] = |r|^2, sc[2] = |rhs|^2; part: 2 grid doubles
-hipError_t launch_cg_start(hipStream_t s, int grid, int64_t n, double scale, const double *b, const double *dg,
-                           const double *in, double *st, double *part, double *sc) {
+// part: grid doubles
+hipError_t launch_cg_start(hipStream_t s, int grid, int64_t n, double scale, double rtol2, const double *b,
+                           const double *dg, const double *in, double *st, double *part, double *sc) {
     hipLaunchKernelGGL(k_cg_start, dim3(grid), dim3(256), 0, s, n, scale, b, dg, (const double2 *)in, (double2 *)st,
                        part);
-    hipLaunchKernelGGL(k_cg_reduce, dim3(2), dim3(256), 0, s, grid, part, sc + 1);
+    hipLaunchKernelGGL(k_cg_bound, dim3(1), dim3(256), 0, s, grid, rtol2, part, sc);
     return hipGetLastError();
 }
 hipError_t launch_dot(hipStream_t s, int grid, int64_t n, const double *a, const double *b, double *part) {

@@ -767,7 +767,10 @@ k_spmm_halo(int64_t nb, int p, int cw, const int64_t *__restrict__ row0, const i
 // synchronisation.  Every workgroup sums all partials in one fixed order.  in
 // and out, pin and pout and the scalars' two slots alternate, so nothing is
 // overwritten that another workgroup still reads.  first: alpha = beta = 0 (v
-// = M^-1 A u of a new u), and the next launch takes beta = 0.
+// = M^-1 A u of a new u), and the next launch takes beta = 0.  check: the
+// launch stops, and those after it do, once <r', r'> of the last one is within
+// sc[3]; report (host memory) gets that sum, the bound and whether no iteration
+// went before, so the host can queue iterations ahead of knowing.
 //
 // With the halo plan (which a mesh's matrices always have: its rows hold at
 // most 64 entries) a state is read once per 64-row block (two to three times
@@ -790,13 +793,13 @@ k_spmm_halo(int64_t nb, int p, int cw, const int64_t *__restrict__ row0, const i
 #define OFKS_CG_TEAMS 3      // plan blocks a workgroup works on at once (2 to 4 fit; 4 spills)
 #endif
 struct CgIter {
-    int first, parity, np;
+    int first, check, parity, np;
     const double *dg;
     const double2 *in;
     double2 *out;
     double *x, *sc;
     const double *pin;
-    double *pout;
+    double *pout, *report;
 };
 
 // sum over each sixteen lanes, to all of them
@@ -829,6 +832,35 @@ __global__ __launch_bounds__(256 * OFKS_CG_TEAMS) void k_cg_iter(
     __shared__ double us_[OFKS_CG_TEAMS][256], ws_[OFKS_CG_TEAMS][HALO_RMAX], red[3][W];
     const int team = threadIdx.x >> 8, tid = threadIdx.x & 255, li = tid & 15, g = tid >> 4;
     double *us = us_[team], *ws = ws_[team];
+    const int lane = threadIdx.x & 63;
+    // this lane's share of array j of the partials (np <= 256), summed over the wave
+    auto partials = [&](int j, double (&v)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = c.pin[j * c.np + min(lane + 64 * u, c.np - 1)];
+    };
+    auto partials_sum = [&](double (&v)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (lane + 64 * u >= c.np) v[u] = 0.0;
+        return rows_sum(row_sum((v[0] + v[1]) + (v[2] + v[3])));
+    };
+    if (c.check) {
+        double v[4];
+        partials(2, v);
+        const double rr = partials_sum(v), tol2 = c.sc[3];
+        const bool stop = !(rr > tol2);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            c.sc[0] = stop ? 1.0 : 0.0;
+            __hip_atomic_store(c.report, rr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(c.report + 1, tol2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            // no iteration yet (a first launch leaves gamma 0)
+            __hip_atomic_store(c.report + 2, c.sc[4 + 2 * c.parity] == 0.0 ? 1.0 : 0.0, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        if (stop) return;
+    } else if (!c.first && c.sc[0] != 0.0) {
+        return;
+    }
     // XCD x takes the plan blocks from x per on, OFKS_CG_TEAMS at a time and workgroup
     const int64_t per = (nb + 7) / 8, base = (blockIdx.x % 8) * per, end = min(base + per, nb);
     const int64_t step = (int64_t)(gridDim.x / 8) * OFKS_CG_TEAMS;
@@ -882,25 +914,16 @@ __global__ __launch_bounds__(256 * OFKS_CG_TEAMS) void k_cg_iter(
     double ga = 0.0, de = 0.0, rr = 0.0, alpha = 0.0, beta = 0.0;
     if (k0 < end) {
         meta(k0 + team);
-        // every wave sums the partials itself (np <= 256): no barrier, and the first block's loads in flight
+        // every wave sums the partials itself: no barrier, and the first block's loads in flight
         double pg[4], pd[4];
-        const int lane = threadIdx.x & 63;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int q = min(lane + 64 * j, c.np - 1);
-            pg[j] = c.pin[q];
-            pd[j] = c.pin[c.np + q];
-        }
+        partials(0, pg);
+        partials(1, pd);
         const double go = c.sc[4 + 2 * c.parity], ao = c.sc[5 + 2 * c.parity];
         CgBlock<ROUNDS, LONG> A, B;
         data(A, k0 + team < end);
         meta(k0 + team + step);
         if (!c.first) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (lane + 64 * j >= c.np) pg[j] = pd[j] = 0.0;
-            const double gs = rows_sum(row_sum((pg[0] + pg[1]) + (pg[2] + pg[3])));
-            const double ds = rows_sum(row_sum((pd[0] + pd[1]) + (pd[2] + pd[3])));
+            const double gs = partials_sum(pg), ds = partials_sum(pd);
             beta = go > 0.0 ? gs / go : 0.0;
             const double den = ao > 0.0 ? ds - beta * gs / ao : ds;
             alpha = den > 0.0 ? gs / den : 0.0;
@@ -1132,11 +1155,11 @@ hipError_t launch_spmm_shift(hipStream_t s, int mode, int grid, int64_t n, int p
 }
 
 // in, out: four doubles a row; pin, pout: 3 np doubles, np from cg_iter_blocks
-hipError_t launch_cg_iter(hipStream_t s, int np, int first, int parity, int64_t nb, int maxlen, const int32_t *info,
+hipError_t launch_cg_iter(hipStream_t s, int np, int first, int check, int parity, int64_t nb, int maxlen, const int32_t *info,
                           const int32_t *halo, const int64_t *brp, const uint16_t *lcol, const double *a,
                           const double *dg, const double *in, double *out, double *x, double *sc, const double *pin,
-                          double *pout) {
-    const CgIter c{first, parity, np, dg, (const double2 *)in, (double2 *)out, x, sc, pin, pout};
+                          double *pout, double *report) {
+    const CgIter c{first, check, parity, np, dg, (const double2 *)in, (double2 *)out, x, sc, pin, pout, report};
     const dim3 block(256 * OFKS_CG_TEAMS);
     if (maxlen <= 16)
         hipLaunchKernelGGL((k_cg_iter<1, false>), dim3(np), block, 0, s, nb, info, halo, brp, lcol, a, c);

@@ -63,9 +63,9 @@ hipError_t launch_spmm_shift(hipStream_t, int, int, int64_t, int, const int64_t 
                              const T *, const uint8_t *, const double *, const double *, const T *, T *, double *,
                              int *);
 enum { DUAL = 0, SHIFT = 1, SHIFT_CG = 2, SHIFT_DOT = 3 };   // product forms (k_spmm.hip)
-hipError_t launch_cg_iter(hipStream_t, int, int, int, int64_t, int, const int32_t *, const int32_t *, const int64_t *,
+hipError_t launch_cg_iter(hipStream_t, int, int, int, int, int64_t, int, const int32_t *, const int32_t *, const int64_t *,
                           const uint16_t *, const double *, const double *, const double *, double *, double *,
-                          double *, const double *, double *);
+                          double *, const double *, double *, double *);
 int cg_iter_blocks(int64_t nb);
 int cg_iter_blocks_max();
 template <typename T>
@@ -172,7 +172,7 @@ hipError_t launch_load_vec(hipStream_t, int64_t, const int32_t *, const int64_t 
 hipError_t launch_veff(hipStream_t, int64_t, const int32_t *, const int32_t *, const double *, const double *,
                        const double *, double *);
 hipError_t launch_cg_state(hipStream_t, int64_t, const double *, double *);
-hipError_t launch_cg_start(hipStream_t, int, int64_t, double, const double *, const double *, const double *,
+hipError_t launch_cg_start(hipStream_t, int, int64_t, double, double, const double *, const double *, const double *,
                            double *, double *, double *);
 hipError_t launch_dot(hipStream_t, int, int64_t, const double *, const double *, double *);
 // (k_gnn.hip)
@@ -264,6 +264,8 @@ struct ofks_ctx {
     double *rho_q = nullptr, *eps_q = nullptr, *vxc_q = nullptr, *veff_q = nullptr, *bvec = nullptr,
            *U = nullptr, *cg_st[2] = {nullptr, nullptr}, *cg_sc = nullptr,   // (cg_st: the Hartree CG's row states)
            *cg_part = nullptr;   // Hartree CG partial sums (fixed: the captured graph holds the pointer)
+    double *cg_report = nullptr;         // pinned: what its last check saw
+    hipEvent_t cg_ev[2] = {nullptr, nullptr};
     double scf_parts[4] = {0, 0, 0, 0};  // int rho, int eps rho, int vxc rho, U.b/2
 
     // iteration
@@ -769,33 +771,33 @@ void drop_cg_graph(ofks_ctx *c) {
 int poisson(ofks_ctx *c) {
     const int64_t n = c->n;
     if (!c->halo_nb) return fail(c, OFKS_ESTATE, "Hartree CG: the mesh has no halo plan");   // its rows always fit one
+    if (!c->cg_report) HIPCHK(hipHostMalloc((void **)&c->cg_report, 3 * sizeof(double)));
+    for (hipEvent_t &e : c->cg_ev)
+        if (!e) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    const double rt = c->poisson_tol_now > 0.0 ? c->poisson_tol_now : c->prm.poisson_rtol;
     const int np = cg_iter_blocks(c->halo_nb);
     double *part[2] = {c->cg_part, c->cg_part + 3 * np};
     // iteration j's launch: states from cg_st[in] to the other one, partials from part[j & 1]
-    auto iter = [&](hipStream_t s, int first, int in, int parity) {
-        return launch_cg_iter(s, np, first, parity, c->halo_nb, c->halo_maxlen, c->halo_info, c->halo_idx,
+    auto iter = [&](hipStream_t s, int first, int check, int in, int parity) {
+        return launch_cg_iter(s, np, first, check, parity, c->halo_nb, c->halo_maxlen, c->halo_info, c->halo_idx,
                               c->halo_brp, c->halo_lcol, c->Lv, c->lhd, c->cg_st[in], c->cg_st[in ^ 1],
-                              c->U, c->cg_sc, part[parity], part[parity ^ 1]);
+                              c->U, c->cg_sc, part[parity], part[parity ^ 1], c->cg_report);
     };
     {
         Scope sc(c, "poisson");
         // Jacobi preconditioner diag(L/2): a constant multiple of diag(L) leaves the CG iterates unchanged
         HIPCHK(launch_cg_state(c->stream, n, c->U, c->cg_st[0]));
-        HIPCHK(iter(c->stream, 1, 0, 1));
-        HIPCHK(launch_cg_start(c->stream, np, n, 4.0 * M_PI, c->bvec, c->lhd, c->cg_st[1], c->cg_st[0], c->cg_part,
-                               c->cg_sc));
-        HIPCHK(iter(c->stream, 1, 0, 1));
+        HIPCHK(iter(c->stream, 1, 0, 0, 1));
+        HIPCHK(launch_cg_start(c->stream, np, n, 4.0 * M_PI, rt * rt, c->bvec, c->lhd, c->cg_st[1], c->cg_st[0],
+                               c->cg_part, c->cg_sc));
+        HIPCHK(iter(c->stream, 1, 0, 0, 1));
     }
-    std::vector<double> sc;
-    CHK(download(c, sc, c->cg_sc, 3));
-    double rr = sc[1], bb = sc[2];
-    const double rt = c->poisson_tol_now > 0.0 ? c->poisson_tol_now : c->prm.poisson_rtol;
-    const double tol2 = rt * rt * bb;
     // ten CG iterations (an even count, so the state ends in cg_st[1] and the
-    // partials in part[0] again), replayed as one graph when allowed
+    // partials in part[0] again), of which the first checks what the ten before
+    // reached; replayed as one graph when allowed
     auto chunk = [&](hipStream_t s) -> hipError_t {
         for (int j = 0; j < 10; ++j) {
-            const hipError_t e = iter(s, 0, (j & 1) ^ 1, j & 1);
+            const hipError_t e = iter(s, 0, j == 0, (j & 1) ^ 1, j & 1);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
@@ -820,18 +822,41 @@ int poisson(ofks_ctx *c) {
             return fail(c, OFKS_EHIP, "Hartree CG graph capture: %s", hipGetErrorString(e));
         }
     }
-    int it = 0;
-    while (rr > tol2 && it < c->prm.poisson_max_iter) {
-        {
+    // Two tens are in flight at a time: the device stops by itself, and a ten
+    // after that costs ten empty launches (25 us), while the host's look between
+    // two tens cost 15 us for each.
+    const int most = (std::max(c->prm.poisson_max_iter, 0) + 9) / 10;
+    int launched = 0, seen = 0;
+    double rr = 0.0, tol2 = 0.0;
+    bool fresh = true, stopped = false;   // fresh: no iteration yet
+    while (!stopped) {
+        while (launched < most && launched - seen < 2) {
             Scope s2(c, "poisson");
             if (c->prm.use_graphs) HIPCHK(hipGraphLaunch(c->cg_graph, c->stream));
             else HIPCHK(chunk(c->stream));
+            HIPCHK(hipEventRecord(c->cg_ev[launched++ & 1], c->stream));
         }
-        it += 10;
-        CHK(download(c, sc, part[0] + 2 * np, np));   // |r|^2's
-        rr = 0.0;
-        for (double v : sc) rr += v;
-        if (!std::isfinite(rr)) return fail(c, OFKS_ENONFINITE, "Hartree CG diverged");
+        if (seen < launched) {
+            HIPCHK(hipEventSynchronize(c->cg_ev[seen++ & 1]));
+            const volatile double *v = c->cg_report;   // this ten's check, or the next one's already
+            rr = v[0];
+            tol2 = v[1];
+            fresh = v[2] != 0.0;
+            stopped = !(rr > tol2) || (!std::isfinite(rr) && !fresh);
+        } else {   // what the last ten reached
+            std::vector<double> v, b;
+            CHK(download(c, v, part[0] + 2 * np, np));
+            CHK(download(c, b, c->cg_sc, 4));
+            rr = 0.0;
+            for (double x : v) rr += x;
+            tol2 = b[3];
+            fresh = launched == 0;
+            stopped = true;
+        }
+    }
+    if (!std::isfinite(rr) && !fresh) {
+        CHK(sync(c));
+        return fail(c, OFKS_ENONFINITE, "Hartree CG diverged");
     }
     if (rr > tol2) return fail(c, OFKS_NOT_CONVERGED, "Hartree CG did not reach %g", rt);
     return OFKS_OK;
@@ -1628,6 +1653,9 @@ int ofks_destroy(ofks_ctx *c) {
     c->allocs.clear();
     if (c->hbuf) (void)hipHostFree(c->hbuf);
     if (c->hup) (void)hipHostFree(c->hup);
+    if (c->cg_report) (void)hipHostFree(c->cg_report);
+    for (hipEvent_t e : c->cg_ev)
+        if (e) (void)hipEventDestroy(e);
     for (auto &pd : c->pending) {
         (void)hipEventDestroy(pd.a);
         (void)hipEventDestroy(pd.b);
