@@ -888,7 +888,9 @@ __global__ __launch_bounds__(256) void k_cg_scalars(int p, int ndq, const double
     if (beta) {
         const double a = (double)al;
         const double next = fma(a, fma(a, qw, -2.0 * dq), rz);
-        beta[c] = rz > 0.0 ? (T)(next / rz) : T(0);
+        // where one step takes <r, z> down to the rounding of the prediction (an
+        // exact solution reached early), the direction starts anew from z
+        beta[c] = next > (sizeof(T) == 8 ? 1e-12 : 1e-5) * rz ? (T)(next / rz) : T(0);
     }
 }
 
