@@ -988,6 +988,188 @@ __global__ __launch_bounds__(256 * OFKS_CG_TEAMS) void k_cg_iter(
     }
 }
 
+// ---------------------------------------------------------------------------
+// The inner CG of small blocks (FP64), one kernel an iteration: k_cg_iter's
+// recurrence for every column c of its own, T_c = L/2 - lambda_c B and M_c =
+// diag T_c.  A step of the three-kernel form is three launches of 3 to 6 us
+// whatever the size; this one is bound by the same latencies, once.
+//
+// A workgroup takes a plan block and CGB_COLS columns, a thread one column of
+// one row and of three halo rows; what does not depend on alpha and beta (the
+// states, sixteen entries of the row) is loaded while they are summed.  u, v, t
+// (in) and u2, v2, t2 (out) change places from launch to launch, as do pin and
+// pout (rows of 2 p: gamma, delta; a row per plan block) and the two slots of
+// sc (2 p each: gamma, alpha).  first: v2 = M^-1 T u.  last: x alone.
+// ---------------------------------------------------------------------------
+constexpr int CGB_COLS = 4, CGB_AHEAD = 16;
+struct CgBlockArgs {
+    int first, last, start, p, parity;   // start: the first iteration (x, p and t from zero)
+    const double *lhd, *bd, *lam;
+    const uint8_t *active;
+    const double *u, *v, *t;
+    double *u2, *v2, *t2, *d, *x, *sc;
+    const double *pin;
+    double *pout;
+};
+
+// sum over the workgroup's 64 rows of threads, to thread row 0 (both values)
+__device__ __forceinline__ void cgb_sum(double (&red)[2][256], double &a, double &b) {
+    // lanes of one column are four apart: by lane exchanges within a wave, then over the four waves
+#pragma unroll
+    for (int off = CGB_COLS; off < 64; off <<= 1) {
+        a += __shfl_xor(a, off);
+        b += __shfl_xor(b, off);
+    }
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    if (l < CGB_COLS) {
+        red[0][CGB_COLS * w + l] = a;
+        red[1][CGB_COLS * w + l] = b;
+    }
+    __syncthreads();
+    const int c = threadIdx.x & (CGB_COLS - 1);
+    a = (red[0][c] + red[0][CGB_COLS + c]) + (red[0][2 * CGB_COLS + c] + red[0][3 * CGB_COLS + c]);
+    b = (red[1][c] + red[1][CGB_COLS + c]) + (red[1][2 * CGB_COLS + c] + red[1][3 * CGB_COLS + c]);
+}
+
+__global__ __launch_bounds__(256) void k_cgb_iter(int64_t nb, const int64_t *__restrict__ row0,
+                                                 const int32_t *__restrict__ info, const int32_t *__restrict__ halo,
+                                                 const int64_t *__restrict__ brp, const uint16_t *__restrict__ lcol,
+                                                 const double2 *__restrict__ lb, CgBlockArgs c) {
+    constexpr int G = 256 / CGB_COLS, NS = (HALO_MAX + G - 1) / G;   // thread rows, halo rows a thread
+    static_assert(G == HALO_RMAX, "a matrix row a thread");
+    __shared__ double us[NS * G * CGB_COLS], red[2][256];
+    const int tid = threadIdx.x, cl = tid & (CGB_COLS - 1), g = tid / CGB_COLS;
+    const int64_t b = blockIdx.x;
+    const int col = (int)blockIdx.y * CGB_COLS + cl;
+    const bool in = col < c.p, on = in && c.active[in ? col : 0] != 0;
+    const double lm = c.lam[in ? col : 0];
+    int hr[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) hr[i] = halo[b * HALO_STRIDE + min(g + i * G, HALO_STRIDE - 1)];
+    const int inf = info[b], nr = (inf >> 8) & 255, rb = (inf >> 16) & 255;
+    const int64_t row = row0[b] + min(g, nr - 1), e0 = brp[b * HALO_BRP + g];
+    const int len = (int)(brp[b * HALO_BRP + g + 1] - e0);   // 0 past the block's rows
+    double ga = 0.0, de = 0.0;
+    if (!c.first && in)
+        for (int64_t k = g; k < nb; k += G) {
+            ga += c.pin[2 * k * c.p + col];
+            de += c.pin[(2 * k + 1) * c.p + col];
+        }
+    double2 w[CGB_AHEAD];
+    int lc[CGB_AHEAD];
+    if (!c.last)
+#pragma unroll
+        for (int j = 0; j < CGB_AHEAD; ++j) {
+            const int64_t e = j < len ? e0 + j : 0;   // entry 0 exists
+            w[j] = lb[e];
+            lc[j] = lcol[e];
+        }
+    double u[NS], v[NS], t[NS], d[NS], x[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        const int s = g + i * G;
+        const bool own = on && s >= rb && s < rb + nr;
+        const int64_t e = (int64_t)hr[i] * c.p + (in ? col : 0);
+        u[i] = on ? c.u[e] : 0.0;
+        v[i] = on && !c.first && !c.last ? c.v[e] : 0.0;
+        t[i] = on && !c.first && !c.last && !c.start ? c.t[e] : 0.0;
+        d[i] = own && !c.first && !c.start ? c.d[e] : 0.0;
+        x[i] = own && !c.first && !c.start ? c.x[e] : 0.0;
+    }
+    double alpha = 0.0, beta = 0.0;
+    if (!c.first) {
+        const double *so = c.sc + (size_t)2 * c.p * c.parity;
+        const double go = in && !c.start ? so[col] : 0.0, ao = in && !c.start ? so[c.p + col] : 0.0;
+        cgb_sum(red, ga, de);
+        beta = go > 0.0 ? ga / go : 0.0;
+        const double den = ao > 0.0 ? de - beta * ga / ao : de;
+        alpha = den > 0.0 ? ga / den : 0.0;
+        if (b == 0 && g == 0 && in) {
+            double *sn = c.sc + (size_t)2 * c.p * (c.parity ^ 1);
+            sn[col] = ga;
+            sn[c.p + col] = alpha;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        const int s = g + i * G;
+        const bool own = on && s >= rb && s < rb + nr;
+        const int64_t e = (int64_t)hr[i] * c.p + col;
+        const double tn = fma(beta, t[i], v[i]), un = fma(-alpha, tn, u[i]), dn = fma(beta, d[i], u[i]);
+        if (own && !c.first) {
+            c.x[e] = fma(alpha, dn, x[i]);
+            if (!c.last) {
+                c.d[e] = dn;
+                c.t2[e] = tn;
+                c.u2[e] = un;
+            }
+        }
+        us[s * CGB_COLS + cl] = un;
+    }
+    if (c.last) return;
+    __syncthreads();
+    ga = de = 0.0;
+    if (on && g < nr) {
+        double a1 = 0.0, a2 = 0.0;
+#pragma unroll
+        for (int j = 0; j < CGB_AHEAD; ++j)
+            if (j < len) {
+                const double un = us[lc[j] * CGB_COLS + cl];
+                a1 = fma(w[j].x, un, a1);
+                a2 = fma(w[j].y, un, a2);
+            }
+        for (int j = CGB_AHEAD; j < len; ++j) {
+            const double2 wj = lb[e0 + j];
+            const double un = us[(int)lcol[e0 + j] * CGB_COLS + cl];
+            a1 = fma(wj.x, un, a1);
+            a2 = fma(wj.y, un, a2);
+        }
+        const double q = fma(-lm, a2, a1), m = c.lhd[row] - lm * c.bd[row], un = us[(rb + g) * CGB_COLS + cl];
+        c.v2[row * c.p + col] = q / m;
+        ga = m * un * un;
+        de = q * un;
+    }
+    cgb_sum(red, ga, de);
+    if (g == 0 && in) {
+        c.pout[2 * b * c.p + col] = ga;
+        c.pout[(2 * b + 1) * c.p + col] = de;
+    }
+}
+
+// Workgroups of a launch; the partials are 4 p per plan block.
+int64_t cgb_blocks(int64_t nb, int p) { return nb * ((p + CGB_COLS - 1) / CGB_COLS); }
+
+// m iterations on D (M^-1 of the residual, zero in inactive columns) into X's
+// active columns.  W, E, D: n p values each; extra: 4 n p; part: 4 nb p; sc: 4 p.
+hipError_t launch_cgb(hipStream_t s, int m, int64_t n, int64_t nb, int p, const int64_t *row0, const int32_t *info,
+                      const int32_t *halo, const int64_t *brp, const uint16_t *lcol, const void *lb, const double *lhd,
+                      const double *bd, const double *lam, const uint8_t *active, double *D, double *W, double *E,
+                      double *X, double *extra, double *part, double *sc) {
+    if (m <= 0) return hipErrorInvalidValue;
+    const int64_t np = n * p;
+    const dim3 grid((unsigned)nb, (unsigned)((p + CGB_COLS - 1) / CGB_COLS));
+    double *st[2][3] = {{D, W, E}, {extra, extra + np, extra + 2 * np}}, *pt[2] = {part, part + 2 * nb * p};
+    CgBlockArgs c{1, 0, 0, p, 1, lhd, bd, lam, active, D, nullptr, nullptr, nullptr, W, nullptr, extra + 3 * np, X, sc,
+                  pt[1], pt[0]};
+    hipLaunchKernelGGL(k_cgb_iter, grid, dim3(256), 0, s, nb, row0, info, halo, brp, lcol, (const double2 *)lb, c);
+    c.first = 0;
+    for (int j = 0; j < m; ++j) {
+        c.start = j == 0;
+        c.last = j + 1 == m;
+        c.parity = j & 1;
+        c.u = st[j & 1][0];
+        c.v = st[j & 1][1];
+        c.t = st[j & 1][2];
+        c.u2 = st[(j & 1) ^ 1][0];
+        c.v2 = st[(j & 1) ^ 1][1];
+        c.t2 = st[(j & 1) ^ 1][2];
+        c.pin = pt[j & 1];
+        c.pout = pt[(j & 1) ^ 1];
+        hipLaunchKernelGGL(k_cgb_iter, grid, dim3(256), 0, s, nb, row0, info, halo, brp, lcol, (const double2 *)lb, c);
+    }
+    return hipGetLastError();
+}
+
 // The grid, and with it the number of partials: a multiple of 8, at most
 // OFKS_CG_BLOCKS, with the plan's blocks spread evenly.
 int cg_iter_blocks(int64_t nb) {
