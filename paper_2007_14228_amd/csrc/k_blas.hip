@@ -60,6 +60,63 @@ __global__ __launch_bounds__(256) void k_colsum_wide(int64_t nb, int64_t m_total
     if (k == 0 && m < m_total) out[m] = (red[0][cl] + red[1][cl]) + (red[2][cl] + red[3][cl]);
 }
 
+// The p x p algebra between the Gram and the row GEMM, a row a block: from the
+// sums G (rows St | Lt, of 2 p) and the column scales dn (null: 1 / sqrt of St's
+// diagonal where norm, else 1)
+//   S = sym(St) scaled, L = sym(Lt) scaled into SL (rows S | L, of 2 p),
+//   the row GEMM's matrix CC = [beta (S - I) - Lambda | -L] with Lambda's
+//   diagonal 2 L - S L + beta S (S - I) (plam: L), off the diagonal L,
+// and per row into info (5 arrays of p): St's diagonal, Lambda's, L's, the sum
+// of (S - I)^2, the entries that are not finite (S: 2048 each, L: 1).  On the host, the same took 3.5
+// ms at p = 512 with the transfers around it, while the device waited.
+template <typename T>
+__global__ __launch_bounds__(256) void k_multiplier(int p, int norm, int plam, double beta,
+                                                   const double *__restrict__ G, const double *__restrict__ dn,
+                                                   double *__restrict__ SL, T *__restrict__ CC,
+                                                   double *__restrict__ info) {
+    __shared__ double red[4][256];
+    const int a = blockIdx.x;
+    auto scale = [&](int i) {
+        return dn ? dn[i] : norm ? 1.0 / sqrt(G[(int64_t)i * 2 * p + i]) : 1.0;
+    };
+    const double da = scale(a);
+    double sl = 0.0, ss = 0.0, fe = 0.0, bad = 0.0, laa = 0.0;
+    for (int b = threadIdx.x; b < p; b += 256) {
+        const double db = scale(b), one = a == b ? 1.0 : 0.0;
+        const double S = 0.5 * (G[(int64_t)a * 2 * p + b] + G[(int64_t)b * 2 * p + a]) * da * db;
+        const double L = 0.5 * (G[(int64_t)a * 2 * p + p + b] + G[(int64_t)b * 2 * p + p + a]) * da * db;
+        SL[(int64_t)a * 2 * p + b] = S;
+        SL[(int64_t)a * 2 * p + p + b] = L;
+        if (a != b) CC[(int64_t)a * 2 * p + b] = (T)(beta * S - L);
+        CC[(int64_t)a * 2 * p + p + b] = (T)(-L);
+        sl += S * L;
+        ss += S * (S - one);
+        fe += (S - one) * (S - one);
+        bad += (isfinite(S) ? 0.0 : 2048.0) + (isfinite(L) ? 0.0 : 1.0);
+        if (a == b) laa = L;
+    }
+    red[0][threadIdx.x] = sl;
+    red[1][threadIdx.x] = ss;
+    red[2][threadIdx.x] = fe;
+    red[3][threadIdx.x] = bad;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (threadIdx.x < w)
+            for (int j = 0; j < 4; ++j) red[j][threadIdx.x] += red[j][threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == (a & 255)) {   // the thread that met the diagonal
+        const double raw = G[(int64_t)a * 2 * p + a], saa = 0.5 * (raw + raw) * da * da;
+        const double lam = plam ? laa : laa + (laa - red[0][0] + beta * red[1][0]);
+        CC[(int64_t)a * 2 * p + a] = (T)(beta * (saa - 1.0) - lam);
+        info[a] = raw;
+        info[p + a] = lam;
+        info[2 * p + a] = laa;
+        info[3 * p + a] = red[2][0];
+        info[4 * p + a] = red[3][0];
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Row GEMM with epilogues.  out[r][c] = sum_k A[r][k] sa[k] M[k][c] (+ addend)
 // for c in [0, N).  Tile: 16*MT rows x 16*NT columns; thread (ty, tx) owns
@@ -1273,6 +1330,13 @@ hipError_t launch_gram(hipStream_t s, int64_t n, int p, const GramPlan &g, const
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_multiplier(hipStream_t s, int p, int norm, int plam, double beta, const double *G, const double *dn,
+                             double *SL, T *CC, double *info) {
+    hipLaunchKernelGGL((k_multiplier<T>), dim3((unsigned)p), dim3(256), 0, s, p, norm, plam, beta, G, dn, SL, CC, info);
+    return hipGetLastError();
+}
+
 hipError_t launch_colsum(hipStream_t s, int64_t nb, int64_t m, const double *part, double *out) {
     if (m <= 0) return hipSuccess;
     // from 4096 columns on, 64 a block still leave a block for every fourth CU
@@ -1541,6 +1605,7 @@ template hipError_t launch_scale_copy<float, float>(hipStream_t, int64_t, int, c
 #define OFKS_INST(T)                                                                                  \
     template hipError_t launch_gram<T>(hipStream_t, int64_t, int, const GramPlan &, const T *, const T *, const T *, double *, size_t); \
     template hipError_t launch_rowgemm<T>(hipStream_t, int, int64_t, int, int, int, const T *, const T *, const T *, T *, GradArgs, int *); \
+    template hipError_t launch_multiplier<T>(hipStream_t, int, int, int, double, const double *, const double *, double *, T *, double *); \
     template hipError_t launch_coldot<T>(hipStream_t, int, int64_t, int, const T *, const T *, double *); \
     template hipError_t launch_bbdot<T>(hipStream_t, int, int64_t, int, const T *, const T *, const T *, const T *, const T *, double *); \
     template hipError_t launch_cg_step<T>(hipStream_t, int, int64_t, int, int, int, int, const T *, const T *, const T *, const T *, const uint8_t *, const double *, const double *, const T *, const T *, const T *, T *, T *, double *, int *); \

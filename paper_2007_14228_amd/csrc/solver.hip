@@ -107,6 +107,8 @@ GramPlan gram_plan(int64_t n, int p, int target_blocks);
 constexpr int GRAM_BLOCKS_F64 = 512, GRAM_BLOCKS_F32 = 2048;
 template <typename T>
 hipError_t launch_gram(hipStream_t, int64_t, int, const GramPlan &, const T *, const T *, const T *, double *, size_t);
+template <typename T>
+hipError_t launch_multiplier(hipStream_t, int, int, int, double, const double *, const double *, double *, T *, double *);
 hipError_t launch_colsum(hipStream_t, int64_t, int64_t, const double *, double *);
 template <typename T>
 hipError_t launch_rowgemm(hipStream_t, int, int64_t, int, int, int, const T *, const T *, const T *, T *,
@@ -282,6 +284,9 @@ struct ofks_ctx {
     uint8_t *active = nullptr;
     double *part = nullptr, *red = nullptr, *rz = nullptr;
     size_t part_cap = 0;
+    double *hsl = nullptr;   // pinned: S and Lambda0 of an iteration (SlCopy)
+    size_t hsl_cap = 0;
+    hipEvent_t hsl_ev = nullptr;
     double *hbuf = nullptr;  // pinned host buffer for downloads
     size_t hbuf_cap = 0;
     char *hup = nullptr;     // pinned upload staging, consumed by a cursor reset at each sync
@@ -661,7 +666,7 @@ int download(ofks_ctx *c, std::vector<double> &dst, const double *src, size_t co
 // Gram: S~ = X^T BX, L~ = X^T HX (host, FP64, not symmetrized)
 // ---------------------------------------------------------------------------
 template <typename T>
-int gram(ofks_ctx *c, const T *X, const T *BX, const T *HX, std::vector<double> &St, std::vector<double> &Lt) {
+int gram_sums(ofks_ctx *c, const T *X, const T *BX, const T *HX) {   // into c->red, rows St | Lt
     const int p = c->p;
     const size_t pp2 = (size_t)p * 2 * p;
     // size the split-K partials from the launch plan before launching
@@ -673,6 +678,13 @@ int gram(ofks_ctx *c, const T *X, const T *BX, const T *HX, std::vector<double> 
         HIPCHK(launch_gram<T>(c->stream, c->n, p, plan, X, BX, HX, c->part, c->part_cap));
     }
     HIPCHK(launch_colsum(c->stream, ns, (int64_t)pp2, c->part, c->red));
+    return OFKS_OK;
+}
+template <typename T>
+int gram(ofks_ctx *c, const T *X, const T *BX, const T *HX, std::vector<double> &St, std::vector<double> &Lt) {
+    const int p = c->p;
+    const size_t pp2 = (size_t)p * 2 * p;
+    CHK(gram_sums<T>(c, X, BX, HX));
     std::vector<double> G;
     CHK(download(c, G, c->red, pp2));
     St.assign((size_t)p * p, 0.0);
@@ -1005,6 +1017,41 @@ int ensure_gl_ft(ofks_ctx *c, size_t count) {
     return OFKS_OK;
 }
 
+#ifndef OFKS_DEVICE_MULT_P
+#define OFKS_DEVICE_MULT_P 64
+#endif
+int ensure_sl(ofks_ctx *c, size_t doubles) {
+    if (c->hsl_cap >= doubles) return OFKS_OK;
+    CHK(sync(c));
+    if (c->hsl) (void)hipHostFree(c->hsl);
+    c->hsl = nullptr;
+    c->hsl_cap = 0;
+    HIPCHK(hipHostMalloc((void **)&c->hsl, doubles * sizeof(double), hipHostMallocDefault));
+    if (!c->hsl_ev) HIPCHK(hipEventCreateWithFlags(&c->hsl_ev, hipEventDisableTiming));
+    c->hsl_cap = doubles;
+    return OFKS_OK;
+}
+// the copy of S | L0 on its way to c->hsl (p > 0); into c->S and c->L0 at the
+// latest when the iteration returns
+struct SlCopy {
+    ofks_ctx *c;
+    int p;
+    int take() {
+        if (p <= 0) return OFKS_OK;
+        const size_t q = (size_t)p;
+        p = 0;
+        HIPCHK(hipEventSynchronize(c->hsl_ev));
+        c->S.resize(q * q);
+        c->L0.resize(q * q);
+        for (size_t a = 0; a < q; ++a) {
+            std::copy_n(c->hsl + a * 2 * q, q, &c->S[a * q]);
+            std::copy_n(c->hsl + a * 2 * q + q, q, &c->L0[a * q]);
+        }
+        return OFKS_OK;
+    }
+    ~SlCopy() { (void)take(); }
+};
+
 template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) {
     Blocks<T> &B = blk<T>(c);
     const int p = c->p;
@@ -1045,57 +1092,98 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
         Scope sc(c, "spmm_dual");
         CHK(spmm_pair<T>(c, p, hbT<T>(c), B.Xt, B.HX, B.BX, 0));
     }
-    std::vector<double> St, Lt;
-    CHK(gram<T>(c, B.Xt, B.BX, B.HX, St, Lt));
-    const auto th0 = std::chrono::steady_clock::now();   // host p x p algebra from here to the uploads
-
-    // deferred normalization
-    std::vector<double> &dn = c->dinv_h;
-    if (!scf) {
-        dn.assign(p, 1.0);
-        if (c->k > 0 && !plam)
-            for (int i = 0; i < p; ++i) {
-                if (!(St[i * p + i] > 0.0)) return fail(c, OFKS_EZERONORM, "column %d has zero B-norm", i);
-                dn[i] = 1.0 / std::sqrt(St[i * p + i]);
-            }
-    }
-    std::vector<double> S(p * p), L0(p * p);
-    for (int a = 0; a < p; ++a)
-        for (int b = 0; b < p; ++b) {
-            S[a * p + b] = 0.5 * (St[a * p + b] + St[b * p + a]) * dn[a] * dn[b];
-            L0[a * p + b] = 0.5 * (Lt[a * p + b] + Lt[b * p + a]) * dn[a] * dn[b];
-        }
-    for (double v : S)
-        if (!std::isfinite(v)) return fail(c, OFKS_ENONFINITE, "non-finite X^T B X");
-    for (double v : L0)
-        if (!std::isfinite(v)) return fail(c, OFKS_ENONFINITE, "non-finite X^T H X");
-    double fea = 0.0;
-    for (int a = 0; a < p; ++a)
-        for (int b = 0; b < p; ++b) {
-            const double e = S[a * p + b] - (a == b ? 1.0 : 0.0);
-            fea += e * e;
-        }
-    fea = std::sqrt(fea);
     const double beta = c->prm.beta;
-    // eq. lambda2: only the diagonal of Lambda0 - S Lambda0 + beta S (S - I) is needed
-    std::vector<double> lam_diag(p);
-    std::vector<double> CC((size_t)p * 2 * p);
-    for (int i = 0; i < p; ++i) {
-        double sl = 0.0, ss = 0.0;
-        for (int k2 = 0; k2 < p; ++k2) {
-            sl += S[i * p + k2] * L0[k2 * p + i];
-            ss += S[i * p + k2] * (S[k2 * p + i] - (k2 == i ? 1.0 : 0.0));
+    std::vector<double> &dn = c->dinv_h;   // deferred normalization
+    std::vector<double> lam_diag(p), l0_diag(p);
+    double fea = 0.0;
+    // the p x p algebra: on the device from p = 64 on (two steps, on the device
+    // against the host, us: p = 16 863 and 840, p = 32 958 and 950, p = 64 2134 and
+    // 2149, p = 128 4077 and 4312, p = 256 10814 and 12529, p = 512 50114 and 65852)
+    const bool dev = p >= OFKS_DEVICE_MULT_P;
+    SlCopy sl{c, 0};
+    auto th0 = std::chrono::steady_clock::now();   // host p x p algebra from here to the uploads
+    if (dev) {
+        CHK(gram_sums<T>(c, B.Xt, B.BX, B.HX));
+        const size_t pp2 = (size_t)p * 2 * p;
+        CHK(ensure_part(c, pp2 + (size_t)6 * p));
+        CHK(ensure_sl(c, pp2));
+        double *SL = c->part, *info = SL + pp2, *dnd = nullptr;
+        const bool norm = !scf && c->k > 0 && !plam;
+        if (scf) {
+            dnd = info + (size_t)5 * p;
+            CHK(upload<double>(c, dnd, dn));
         }
-        lam_diag[i] = plam ? L0[i * p + i] : L0[i * p + i] + (L0[i * p + i] - sl + beta * ss);
+        HIPCHK(launch_multiplier<T>(c->stream, p, norm, plam, beta, c->red, dnd, SL, B.CC, info));
+        std::vector<double> in;
+        CHK(download(c, in, info, (size_t)5 * p));
+        // S and L0 follow while the host goes on; taken over when they are needed
+        HIPCHK(hipMemcpyAsync(c->hsl, SL, pp2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(hipEventRecord(c->hsl_ev, c->stream));
+        th0 = std::chrono::steady_clock::now();
+        if (!scf) dn.assign(p, 1.0);
+        double bad = 0.0;
+        for (int i = 0; i < p; ++i) {
+            if (norm) {
+                if (!(in[i] > 0.0)) return fail(c, OFKS_EZERONORM, "column %d has zero B-norm", i);
+                dn[i] = 1.0 / std::sqrt(in[i]);
+            }
+            lam_diag[i] = in[p + i];
+            l0_diag[i] = in[2 * p + i];
+            fea += in[3 * p + i];
+            bad += in[4 * p + i];
+        }
+        if (bad > 0.0) return fail(c, OFKS_ENONFINITE, "non-finite X^T %s X", bad >= 2048.0 ? "B" : "H");
+        fea = std::sqrt(fea);
+        sl.p = p;
+    } else {
+        std::vector<double> St, Lt;
+        CHK(gram<T>(c, B.Xt, B.BX, B.HX, St, Lt));
+        th0 = std::chrono::steady_clock::now();
+        if (!scf) {
+            dn.assign(p, 1.0);
+            if (c->k > 0 && !plam)
+                for (int i = 0; i < p; ++i) {
+                    if (!(St[i * p + i] > 0.0)) return fail(c, OFKS_EZERONORM, "column %d has zero B-norm", i);
+                    dn[i] = 1.0 / std::sqrt(St[i * p + i]);
+                }
+        }
+        std::vector<double> S(p * p), L0(p * p);
+        for (int a = 0; a < p; ++a)
+            for (int b = 0; b < p; ++b) {
+                S[a * p + b] = 0.5 * (St[a * p + b] + St[b * p + a]) * dn[a] * dn[b];
+                L0[a * p + b] = 0.5 * (Lt[a * p + b] + Lt[b * p + a]) * dn[a] * dn[b];
+            }
+        for (double v : S)
+            if (!std::isfinite(v)) return fail(c, OFKS_ENONFINITE, "non-finite X^T B X");
+        for (double v : L0)
+            if (!std::isfinite(v)) return fail(c, OFKS_ENONFINITE, "non-finite X^T H X");
+        for (int a = 0; a < p; ++a)
+            for (int b = 0; b < p; ++b) {
+                const double e = S[a * p + b] - (a == b ? 1.0 : 0.0);
+                fea += e * e;
+            }
+        fea = std::sqrt(fea);
+        // eq. lambda2: only the diagonal of Lambda0 - S Lambda0 + beta S (S - I) is needed
+        std::vector<double> CC((size_t)p * 2 * p);
+        for (int i = 0; i < p; ++i) {
+            double sl = 0.0, ss = 0.0;
+            for (int k2 = 0; k2 < p; ++k2) {
+                sl += S[i * p + k2] * L0[k2 * p + i];
+                ss += S[i * p + k2] * (S[k2 * p + i] - (k2 == i ? 1.0 : 0.0));
+            }
+            lam_diag[i] = plam ? L0[i * p + i] : L0[i * p + i] + (L0[i * p + i] - sl + beta * ss);
+        }
+        for (int a = 0; a < p; ++a)
+            for (int b = 0; b < p; ++b) {
+                const double lam_ab = (a == b) ? lam_diag[a] : L0[a * p + b];
+                CC[(size_t)a * 2 * p + b] = beta * (S[a * p + b] - (a == b ? 1.0 : 0.0)) - lam_ab;
+                CC[(size_t)a * 2 * p + p + b] = -L0[a * p + b];
+            }
+        for (int i = 0; i < p; ++i) l0_diag[i] = L0[i * p + i];
+        CHK(upload<T>(c, B.CC, CC));
+        c->S = std::move(S);
+        c->L0 = std::move(L0);
     }
-    for (int a = 0; a < p; ++a)
-        for (int b = 0; b < p; ++b) {
-            const double lam_ab = (a == b) ? lam_diag[a] : L0[a * p + b];
-            CC[(size_t)a * 2 * p + b] = beta * (S[a * p + b] - (a == b ? 1.0 : 0.0)) - lam_ab;
-            CC[(size_t)a * 2 * p + p + b] = -L0[a * p + b];
-        }
-    c->S = S;
-    c->L0 = L0;
 
     // energy of X^k (needed before the preconditioner choice in the learned form)
     const bool learned_form = c->prm.precond == OFKS_PRECOND_LEARNED || c->prm.precond == OFKS_PRECOND_GRAPH;
@@ -1103,7 +1191,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
     const int ee = learned_form ? 1 : std::max(1, c->prm.energy_every);
     if (scf) {
         double trl = 0.0;
-        for (int i = 0; i < p; ++i) trl += L0[i * p + i];
+        for (int i = 0; i < p; ++i) trl += l0_diag[i];
         energy = c->prm.occupation * trl - c->scf_parts[3] - c->scf_parts[2] + c->scf_parts[1] + c->Enuc;
     }
     // fixed H: tr(S^-1 Lambda0), O(p^3) on the host (15 ms at p = 512).  The learned
@@ -1113,6 +1201,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
         if (scf || c->k % ee != 0) return;
         const auto te = std::chrono::steady_clock::now();
         double tr;
+        if (sl.take() != OFKS_OK) return;
         if (dense::trace_sinv_a(c->S, c->L0, p, tr)) energy = tr;
         if (c->timing && !learned_form)   // (there the host timer around it counts it)
             c->timers["host"].ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - te).count();
@@ -1155,7 +1244,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
     std::vector<uint8_t> neg(p, 0);
     bool any_active = false;
     for (int i = 0; i < p; ++i) {
-        const double li = c->prm.precond_lambda == 0 ? lam_diag[i] : L0[i * p + i];
+        const double li = c->prm.precond_lambda == 0 ? lam_diag[i] : l0_diag[i];
         shift[i] = li;
         neg[i] = li < 0.0 ? 1 : 0;
         any_active |= use_paper && neg[i];
@@ -1168,7 +1257,6 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
         th.launches += 1;
     }
     if (!scf) CHK(upload<T>(c, B.dinv, dn));
-    CHK(upload<T>(c, B.CC, CC));
     CHK(upload<T>(c, B.lam, shift));
     CHK(upload_bytes(c, c->active, use_learned ? neg.data() : act.data(), p));
 
@@ -1687,6 +1775,8 @@ int ofks_destroy(ofks_ctx *c) {
     c->allocs.clear();
     if (c->hbuf) (void)hipHostFree(c->hbuf);
     if (c->hup) (void)hipHostFree(c->hup);
+    if (c->hsl) (void)hipHostFree(c->hsl);
+    if (c->hsl_ev) (void)hipEventDestroy(c->hsl_ev);
     if (c->cg_report) (void)hipHostFree(c->cg_report);
     for (hipEvent_t e : c->cg_ev)
         if (e) (void)hipEventDestroy(e);
