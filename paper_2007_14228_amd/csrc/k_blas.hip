@@ -306,9 +306,15 @@ __global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int gx, int
     if (q / tiles >= per || split >= splits) return;
     const int tile = (int)(q % tiles);
     const int a0 = tile % gx * TM, c0 = tile / gx * TN;
-    // a split takes every splits-th chunk of KC rows, so that all blocks read one
-    // window of rows (DRAM pages and channels evenly, whatever n is)
-    const int64_t r_begin = split * KC, stride = splits * KC;
+    // FP64: a split takes every splits-th chunk of KC rows, so that all blocks read
+    // one window of rows (DRAM pages and channels evenly, whatever n is).  FP32:
+    // adjoining rows, where orbitals are of one size and most sums stay small: the
+    // FP32 sums of rows from everywhere were off by half as much again (X after
+    // three steps at n = 5.1e5, p = 128: 5.3e-7 to 5.5e-7 here, 7.5e-7 to 8.8e-7).
+    constexpr bool FAR = sizeof(T) == 8;
+    const int64_t share = ((n + splits - 1) / splits + KC - 1) / KC * KC;
+    const int64_t r_begin = FAR ? split * KC : split * share, stride = FAR ? splits * KC : KC;
+    const int64_t r_end = FAR ? n : min(n, r_begin + share);
     const int p2 = 2 * p;
     acc_t acc[4][4];
 #pragma unroll
@@ -323,7 +329,7 @@ __global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int gx, int
             const int kk = e / TM, cc = e % TM;
             const int64_t r = r0 + kk;
             const int a = a0 + cc;
-            xr[j] = (r < n && a < p) ? X[r * p + a] : T(0);
+            xr[j] = (r < r_end && a < p) ? X[r * p + a] : T(0);
         }
 #pragma unroll
         for (int j = 0; j < EY; ++j) {
@@ -332,7 +338,7 @@ __global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int gx, int
             const int64_t r = r0 + kk;
             const int c = c0 + cc;
             T v = T(0);
-            if (r < n && c < p2) v = c < p ? BX[r * p + c] : HX[r * p + (c - p)];
+            if (r < r_end && c < p2) v = c < p ? BX[r * p + c] : HX[r * p + (c - p)];
             yr[j] = v;
         }
     };
@@ -349,13 +355,13 @@ __global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int gx, int
         }
     };
     int buf = 0;
-    if (r_begin < n) {
+    if (r_begin < r_end) {
         gload(r_begin);
         lstore(0);
     }
     __syncthreads();
-    for (int64_t r0 = r_begin; r0 < n; r0 += stride) {
-        const bool more = r0 + stride < n;
+    for (int64_t r0 = r_begin; r0 < r_end; r0 += stride) {
+        const bool more = r0 + stride < r_end;
         if (more) gload(r0 + stride);
 #pragma unroll
         for (int s4 = 0; s4 < KC / 4; ++s4) {
@@ -388,8 +394,8 @@ __global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, int p, int gx, int
         }
 }
 
-// Gram for p <= 64: every wave takes its share of the rows (every nth group of
-// 4 U, so that all waves read one window) and forms the whole product (or, BOTH false, X^T BX or X^T HX by blockIdx.y), so each element goes from memory
+// Gram for p <= 64: every wave takes its share of the rows (in FP64 every nth
+// group of 4 U, so that all waves read one window) and forms the whole product (or, BOTH false, X^T BX or X^T HX by blockIdx.y), so each element goes from memory
 // straight to the registers of one MFMA operand and nothing is staged in LDS:
 // at these widths the three blocks' bytes bound it, not the arithmetic.  NA:
 // 16-column tiles of X.  U steps of four rows are loaded while the U before
@@ -408,8 +414,12 @@ __global__ __launch_bounds__(64 * GW_WAVES) __attribute__((amdgpu_waves_per_eu(2
     __shared__ double red[GW_WAVES][256];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int li = lane & 15, lk = lane >> 4;
-    const int64_t stride = (int64_t)gridDim.x * GW_WAVES * 4 * U;
-    const int64_t r_begin = ((int64_t)blockIdx.x * GW_WAVES + w) * 4 * U;
+    // (rows from everywhere in FP64, adjoining ones in FP32, as in k_gram_mfma)
+    constexpr bool FAR = sizeof(T) == 8;
+    const int64_t waves = (int64_t)gridDim.x * GW_WAVES, wv = (int64_t)blockIdx.x * GW_WAVES + w;
+    const int64_t share = ((n + waves - 1) / waves + 4 * U - 1) / (4 * U) * (4 * U);
+    const int64_t r_begin = FAR ? wv * 4 * U : wv * share, stride = FAR ? waves * 4 * U : 4 * U;
+    const int64_t r_end = FAR ? n : min(n, r_begin + share);
     const T *Y[2] = {BOTH || blockIdx.y == 0 ? BX : HX, HX};
     int ca[NA];
 #pragma unroll
@@ -424,7 +434,7 @@ __global__ __launch_bounds__(64 * GW_WAVES) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t r = r0 + 4 * u + lk;
-            const bool in = r < n;
+            const bool in = r < r_end;
             const int64_t o = (in ? r : n - 1) * p;
 #pragma unroll
             for (int i = 0; i < NA; ++i) {
@@ -446,9 +456,9 @@ __global__ __launch_bounds__(64 * GW_WAVES) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
                 for (int j = 0; j < NB; ++j) acc[i][j] = mfma16x16x4(a[f][u][i], b[f][u][j], acc[i][j]);
     };
-    if (r_begin < n) {
+    if (r_begin < r_end) {
         load(0, r_begin);
-        for (int64_t r0 = r_begin; r0 < n; r0 += 2 * stride) {   // (rows past the end: the last row's address, zeros)
+        for (int64_t r0 = r_begin; r0 < r_end; r0 += 2 * stride) {   // (rows past the end: the last row's address, zeros)
             load(1, r0 + stride);
             mul(0);
             load(0, r0 + 2 * stride);
