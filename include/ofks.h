@@ -87,8 +87,8 @@ typedef struct {
     int32_t use_graphs;     /* 1: replay launch-bound inner loops (Hartree CG) as HIP graphs; 0: launch eagerly */
     int32_t algorithm;      /* 0: PCAL (Algorithm PCAL: eq. lambda2 multiplier, column B-normalization);
                                1: PLAM (Algorithm PLAM: Lambda = X^T H X (eq. multi), no normalization) */
-    int32_t spmm_mode;      /* sparse products: 0 auto (LDS-halo kernel for FP64 blocks with p >= 64 and
-                               FP32 blocks with p >= 96; row-gather otherwise);
+    int32_t spmm_mode;      /* sparse products: 0 auto (LDS-halo kernel for FP64 blocks with p >= 4 and
+                               FP32 blocks with p >= 33; row-gather otherwise);
                                1 row-gather kernel; 2 LDS-halo kernel (products then fail with OFKS_ESTATE
                                if the matrix has a row with more than 64 entries or more distinct columns
                                than the halo holds).  The kernels agree to rounding. */
@@ -402,7 +402,7 @@ int ofks_gl_feature_norm(ofks_ctx *ctx, float *host_norm);
  * recording and clears the totals. */
 int ofks_timing(ofks_ctx *ctx, int32_t enable);
 /* Totals for a kernel class: name is one of "spmm_dual", "spmm_shift",
- * "gram", "update_a", "update_b", "pcg_r", "pcg_dx", "density", "poisson",
+ * "gram", "update_a", "update_b", "pcg_dx", "pcg_sum", "density", "poisson",
  * "assemble_h", "bbdot", "mlp", "mlp_train", "graph", "graph_train", and "host" (the host's
  * p x p algebra of each iteration, wall time).  ms = summed duration, launches = count. */
 int ofks_timer_get(ofks_ctx *ctx, const char *name, double *ms, int64_t *launches);

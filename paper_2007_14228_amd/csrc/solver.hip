@@ -33,11 +33,10 @@
 #include "dense.hpp"
 #include "halo_plan.hpp"
 
-// Persistent grid of the partial-sum block kernels (k_pcg_r, k_bbdot,
+// Persistent grid of the partial-sum block kernels (k_cg_step, k_bbdot,
 // k_coldot, the PCG start), a multiple of the 8 XCDs.  At n = 2e6, p = 128
-// (FP64), 1024 blocks beat 2048 and 4096: k_pcg_r 1.26 -> 1.20 ms, k_bbdot
-// 1.46 -> 1.35 ms.  The row-gather shifted SpMM keeps its own grid (at most
-// its resident block count).
+// (FP64), 1024 blocks beat 2048 and 4096: k_bbdot 1.46 -> 1.35 ms.  The
+// row-gather shifted SpMM keeps its own grid (at most its resident block count).
 #ifndef OFKS_PART_GRID
 #define OFKS_PART_GRID 1024
 #endif
