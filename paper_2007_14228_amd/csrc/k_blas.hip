@@ -920,29 +920,29 @@ void k_rowgemm_mres(int64_t n, const T *__restrict__ A, const T *__restrict__ sa
 // Coefficients of a step, per column: alpha (0 when <d, T d> <= 0) from the sums
 // of the product's partials (rows of 2 p: <d, T d>, <T d, w>) and the current
 // <r, z> (from the step pass's partials, nrz rows of p), beta from the
-// prediction.  Eight columns a block, 32 threads a column, fixed order.
-template <typename T>
-__global__ __launch_bounds__(256) void k_cg_scalars(int p, int ndq, const double *__restrict__ dqp, int nrz,
+// prediction.  Eight columns a block, TPC threads a column, fixed order.
+template <typename T, int TPC>
+__global__ __launch_bounds__(8 * TPC) void k_cg_scalars(int p, int ndq, const double *__restrict__ dqp, int nrz,
                                                    const double *__restrict__ rzp, T *__restrict__ alpha,
                                                    T *__restrict__ beta) {
-    __shared__ double red[3][32][9];
+    __shared__ double red[3][TPC][9];
     const int cl = threadIdx.x & 7, k = threadIdx.x >> 3;
     const int c = blockIdx.x * 8 + cl;
     double s[3] = {0.0, 0.0, 0.0};
     if (c < p) {
 #pragma unroll 8
-        for (int r = k; r < ndq; r += 32) s[0] += dqp[(int64_t)r * 2 * p + c];
+        for (int r = k; r < ndq; r += TPC) s[0] += dqp[(int64_t)r * 2 * p + c];
         if (beta) {
 #pragma unroll 8
-            for (int r = k; r < ndq; r += 32) s[1] += dqp[(int64_t)r * 2 * p + p + c];
+            for (int r = k; r < ndq; r += TPC) s[1] += dqp[(int64_t)r * 2 * p + p + c];
         }
 #pragma unroll 8
-        for (int r = k; r < nrz; r += 32) s[2] += rzp[(int64_t)r * p + c];
+        for (int r = k; r < nrz; r += TPC) s[2] += rzp[(int64_t)r * p + c];
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) red[d][k][cl] = s[d];
     __syncthreads();
-    for (int w = 16; w > 0; w >>= 1) {
+    for (int w = TPC / 2; w > 0; w >>= 1) {
         if (k < w)
 #pragma unroll
             for (int d = 0; d < 3; ++d) red[d][k][cl] += red[d][k + w][cl];
@@ -1581,7 +1581,9 @@ hipError_t launch_cg_start(hipStream_t s, int grid, int64_t n, int p, const uint
 template <typename T>
 hipError_t launch_cg_scalars(hipStream_t s, int p, int ndq, const double *dqp, int nrz, const double *rzp, T *alpha,
                              T *beta) {
-    hipLaunchKernelGGL((k_cg_scalars<T>), dim3((unsigned)((p + 7) / 8)), dim3(256), 0, s, p, ndq, dqp, nrz, rzp, alpha, beta);
+    const dim3 grid((unsigned)((p + 7) / 8));
+    if (ndq > 256) hipLaunchKernelGGL((k_cg_scalars<T, 128>), grid, dim3(1024), 0, s, p, ndq, dqp, nrz, rzp, alpha, beta);
+    else hipLaunchKernelGGL((k_cg_scalars<T, 32>), grid, dim3(256), 0, s, p, ndq, dqp, nrz, rzp, alpha, beta);
     return hipGetLastError();
 }
 

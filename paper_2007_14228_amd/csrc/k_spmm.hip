@@ -1354,9 +1354,15 @@ hipError_t launch_cg_iter(hipStream_t s, int np, int first, int check, int parit
 // Halo-SpMM launch: nb blocks of the plan (grid padded to whole XCD slabs).
 // SHIFT_CG and SHIFT_DOT leave *rows_out rows of 2 p partial dots at the start
 // of part: sums over groups of HALO_G plan blocks (formed from the per-block
-// rows that follow them), or the blocks' own rows where there are few.
+// rows that follow them), or the blocks' own rows up to OFKS_HALO_DIRECT of them
+// (ten inner CG iterations, us, own rows against grouped: n = 2.4e4 (381 blocks),
+// p = 64 350 and 380; 4.3e4 (670), p = 16 284 and 303; 6.4e4 (1000), p = 11 376
+// and 396; 1.2e5 (1838), p = 16 497 and 499; 2.1e5 (3209), p = 16 733 and 710).
 // part_capacity in doubles.
-constexpr int HALO_G = 64, HALO_DIRECT = 256;
+#ifndef OFKS_HALO_DIRECT
+#define OFKS_HALO_DIRECT 1536
+#endif
+constexpr int HALO_G = 64, HALO_DIRECT = OFKS_HALO_DIRECT;
 static int64_t halo_grid(int64_t nb) { return (nb + 7) / 8 * 8; }
 
 size_t spmm_halo_part_doubles(int64_t nb, int p) {

@@ -91,3 +91,46 @@ def test_iterations_past_the_solution_change_nothing(mode):
         # the quotient's few roundings, twice over for the steps' remainders
         assert np.abs(P - ref).max() <= 1e-14 * np.abs(ref).max()
         s.close()
+
+
+@pytest.mark.parametrize("n", [250 * 64, 257 * 64, 1536 * 64, 1537 * 64 + 1])
+def test_partial_sums_on_both_sides_of_their_groupings(n):
+    """Three iterations on tridiagonal matrices, with as many plan blocks as the
+    dots' partials change their way to the sum at, against the same in FP64."""
+    import scipy.sparse as sp
+    import torch
+    from paper_2007_14228_amd import Solver
+    print(f"[gpu] cg partials n={n}", flush=True)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    rng = np.random.default_rng(n)
+    mats = []
+    for _ in range(2):
+        o = rng.uniform(-1, 1, n - 1)
+        mats.append(sp.diags([o, rng.uniform(3, 4, n), o], [-1, 0, 1]).tocsr())
+    L, B = mats
+    s = Solver()
+    s.csr_load(dev(L.indptr.astype(np.int64)), dev(L.indices.astype(np.int32)), dev(L.data), dev(B.data), dev(L.data))
+    s.set_params(precond="paper", pcg_iters=3, spmm_mode="halo")
+    p = 12
+    G, lam = rng.standard_normal((n, p)), -rng.uniform(0.1, 3.0, p)
+    P = s.precondition(lam, dev(G)).cpu().numpy()
+    for c in range(p):
+        ref = _cg_sparse(L - lam[c] * B, G[:, c], 3)
+        # sums of 1e5 terms by trees and a few dozen roundings a value, condition number below 7
+        assert np.abs(P[:, c] - ref).max() <= 1e-13 * np.abs(ref).max(), c
+    s.close()
+
+
+def _cg_sparse(T, g, m):
+    J = 1.0 / T.diagonal()
+    x, r = np.zeros_like(g), g.copy()
+    d = J * r
+    rz = r @ d
+    for _ in range(m):
+        q = T @ d
+        a = rz / (d @ q)
+        x, r = x + a * d, r - a * q
+        z = J * r
+        new = r @ z
+        d, rz = z + new / rz * d, new
+    return x
