@@ -864,7 +864,7 @@ __global__ __launch_bounds__(256 * OFKS_CG_TEAMS) void k_cg_iter(
     // XCD x takes the plan blocks from x per on, OFKS_CG_TEAMS at a time and workgroup
     const int64_t per = (nb + 7) / 8, base = (blockIdx.x % 8) * per, end = min(base + per, nb);
     const int64_t step = (int64_t)(gridDim.x / 8) * OFKS_CG_TEAMS;
-    const int64_t k0 = base + (int64_t)(blockIdx.x / 8) * OFKS_CG_TEAMS;   // this round's first plan block
+    const int64_t k0 = base + (int64_t)(blockIdx.x / 8) * OFKS_CG_TEAMS;   // the turn's first plan block
     // metadata of block k (past the end: the last one, whose loads go unused)
     int mh, mi;
     int64_t me[HALO_SETS];

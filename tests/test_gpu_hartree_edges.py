@@ -76,3 +76,27 @@ def test_hartree_potential_at_tile_edges(which, graphs):
         assert np.linalg.norm(rhs - L @ U) <= 1.001 * rtol * np.linalg.norm(rhs) + slack
         X *= 1.1
     s.close()
+
+
+@pytest.mark.parametrize("graphs", [0, 1])
+def test_hartree_iteration_limit_is_kept(graphs):
+    """Too few iterations are an error, whatever was queued ahead; the next solve
+    goes on from the potential that they left and reaches its bound."""
+    import torch
+    from paper_2007_14228_amd import Solver
+    mesh = _cube(20)
+    w = wl.Workload("edge", mesh, np.array([2.0]), np.array([[0.31, 0.17, 0.23]]), p=1, beta=1.0, scf=True, seed=0)
+    print(f"[gpu] hartree limit graphs={graphs}", flush=True)
+    s = Solver()
+    s.load_workload(w)
+    X = torch.from_numpy(np.random.default_rng(3).standard_normal((mesh.n_dofs, 1))).cuda()
+    prm = dict(beta=w.beta, precond="paper", scf=1, use_graphs=graphs, poisson_rtol=1e-11)
+    for limit in (1, 10, 11, 20):                          # one ten, one, two, two: none is enough
+        s.set_params(poisson_max_iter=limit, **prm)
+        with pytest.raises(RuntimeError, match="Hartree CG"):
+            s.build_hamiltonian(X)
+    s.set_params(poisson_max_iter=5000, **prm)
+    a = s.build_hamiltonian(X)["U"].cpu().numpy()
+    b = s.build_hamiltonian(X)["U"].cpu().numpy()          # starts at the solution: nothing to do
+    assert np.isfinite(a).all() and np.array_equal(a, b)
+    s.close()
