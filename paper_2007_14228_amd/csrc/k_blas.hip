@@ -11,6 +11,7 @@
 //  k_cg_x        its last update of x
 //  k_cg_start    its start from a block G
 //  k_cg_scalars  its alpha and beta per column on the device
+//  k_cg_beta     its beta from the real sums where the prediction cannot give it (FP32)
 //  k_bbdot       <S,Y>, <Y,Y>, <S,S>, ||P||^2, ||X||^2 for the BB step
 //  k_update_b    X~ = X - P / eta with X = X~ D^-1; keeps X as X^{k-1}
 //  k_coldot      per-column sums of A .* B (column B-norms)
@@ -20,6 +21,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "cg_step.hpp"
 
 namespace ofks {
 
@@ -127,6 +129,7 @@ enum { EPI_PLAIN = 0, EPI_GRAD = 1, EPI_GRAD_PCG = 2, EPI_GRAD_NORM = 3 };
 struct GradArgs {
     const void *HX;       // n x p, unnormalized (scaled by dinv here)
     void *P;              // out: gradient (no CG) / identity-branch columns
+    void *R;              // out: CG residual r = G (active columns)
     void *D;              // out: CG direction d = J G (active columns)
     const double *lhd;    // diag(L/2), n
     const double *bd;     // diag(B), n
@@ -213,6 +216,7 @@ __global__ __launch_bounds__(256) void k_rowgemm(int64_t n, int p, int N, const 
                         if (ga.active[c]) {
                             const T jinv = T(1) / (T(ga.lhd[r]) - lamv[c] * T(ga.bd[r]));
                             const T z = v * jinv;
+                            ((T *)ga.R)[r * p + c] = v;
                             ((T *)ga.D)[r * p + c] = z;
                             rz[j] += (double)v * (double)z;
                         } else {
@@ -536,6 +540,7 @@ void k_rowgemm_mfma(int64_t n, int p, int N, const T *__restrict__ A, const T *_
     __syncthreads();
     const T *__restrict__ HX = (const T *)ga.HX;
     T *__restrict__ Pout = (T *)ga.P;
+    T *__restrict__ Rout = (T *)ga.R;
     T *__restrict__ Dout = (T *)ga.D;
 
     // K-chunk staging, software-pipelined: the values of the next chunk (of
@@ -655,6 +660,7 @@ void k_rowgemm_mfma(int64_t n, int p, int N, const T *__restrict__ A, const T *_
                 } else {  // EPI_GRAD_PCG
                     if (act_s[cl]) {
                         const T z = v * (T(1) / (ld - lmc_s[cl] * bdv));
+                        Rout[r * p + c] = v;
                         Dout[r * p + c] = z;
                         rz[t] += (double)v * (double)z;
                     } else {
@@ -756,6 +762,7 @@ void k_rowgemm_mres(int64_t n, const T *__restrict__ A, const T *__restrict__ sa
     __syncthreads();
     const T *__restrict__ HX = (const T *)ga.HX;
     T *__restrict__ Pout = (T *)ga.P;
+    T *__restrict__ Rout = (T *)ga.R;
     T *__restrict__ Dout = (T *)ga.D;
     // columns of this block below P (gradient) or at and above P (residual):
     // per tile t, known at compile time with one column set, per block with two
@@ -837,6 +844,7 @@ void k_rowgemm_mres(int64_t n, const T *__restrict__ A, const T *__restrict__ sa
             }
             if (r >= n) continue;
             T *prow = Pout + r * P + li;
+            T *rrow = Rout + r * P + li;
             T *drow = Dout + r * P + li;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
@@ -853,6 +861,7 @@ void k_rowgemm_mres(int64_t n, const T *__restrict__ A, const T *__restrict__ sa
                 } else {  // EPI_GRAD_PCG
                     if (act_s[cl]) {
                         const T z = v * (T(1) / (ldi - lmc_s[cl] * bdi));
+                        rrow[hc] = v;
                         drow[hc] = z;
                         rz[t] += (double)v * (double)z;
                     } else {
@@ -901,30 +910,29 @@ void k_rowgemm_mres(int64_t n, const T *__restrict__ A, const T *__restrict__ sa
 // Inner CG of the paper preconditioner: x_l = T_l^-1 g_l by m Jacobi-CG steps,
 // all columns together, arranged for the fewest passes over the blocks.  With
 // z_j = J r_j the recurrences r' = r - alpha T d, d' = J r' + beta d give
-//   z_j     = d_j - beta_{j-1} d_{j-1}
-//   z_{j+1} = z_j - alpha_j w_j,   w_j = J T d_j   (from the product kernel)
+//   z_j     = d_j - beta_{j-1} d_{j-1}   (z_0 = J g)
+//   z_{j+1} = z_j - alpha_j J q_j,   q_j = T d_j   (from the product kernel)
 //   d_{j+1} = z_{j+1} + beta_j d_j
-// so neither r nor z is stored: a step reads w_j, d_j, d_{j-1} and writes
-// d_{j+1} over d_{j-1}.  beta_j = <r_{j+1}, z_{j+1}> / <r_j, z_j> is needed in
-// the pass that forms z_{j+1}; its numerator is predicted from the product's
-// dots as rz_j - 2 alpha <d, T d> + alpha^2 <T d, w>, while the pass sums the
-// real one, which the next step uses, so no prediction feeds another.  x takes
-// two directions at a time, every second step, from the values the pass holds
-// anyway.  Block passes for m = 10: 65 (products 19, directions 35, x 11)
-// against 85 with r and the directions kept for one sum at the end, without
-// the m - 1 extra blocks of that form.
-// Measured against 80-bit arithmetic on Kuhn and irregular matrices, shifts
-// -0.05 to -1000, m = 10: relative error 1.9e-16 to 4.8e-16 (two-term form
-// 1.8e-16 to 3.1e-16), FP32 blocks 0.8e-7 to 1.7e-7 (0.9e-7 to 1.7e-7).
+// so neither r nor z is stored: a step reads q_j, d_j, d_{j-1} (the first one q_0,
+// d_0 and g) and writes d_{j+1} over d_{j-1}.  beta_j = <r_{j+1}, z_{j+1}> /
+// <r_j, z_j> is needed in the pass that forms z_{j+1}; its numerator is predicted
+// from the product's dots as rz_j - 2 alpha <d, T d> + alpha^2 <T d, J T d>, while
+// the pass sums the real one, which the next step uses, so no prediction feeds
+// another.  x takes two directions at a time, every second step, from the values
+// the pass holds anyway.  Block passes for m = 10: 66 (products 19, directions 36,
+// x 11), and one more for g, against 85 with r and the directions kept for one
+// sum at the end, without the m - 1 extra blocks of that form.
+// (The arithmetic and its errors: cg_step.hpp.)
 
-// Coefficients of a step, per column: alpha (0 when <d, T d> <= 0) from the sums
-// of the product's partials (rows of 2 p: <d, T d>, <T d, w>) and the current
-// <r, z> (from the step pass's partials, nrz rows of p), beta from the
-// prediction.  Eight columns a block, TPC threads a column, fixed order.
+// Coefficients of a step, per column (cg_coef), from the sums of the product's
+// partials (rows of 2 p: <d, T d>, <T d, J T d>) and the current <r, z> (from the
+// step pass's partials, nrz rows of p).  beta null: the last step.  aux (FP32): p
+// values of the first <r, z>, then p of old.  Eight columns a block, TPC threads a
+// column, fixed order.
 template <typename T, int TPC>
-__global__ __launch_bounds__(8 * TPC) void k_cg_scalars(int p, int ndq, const double *__restrict__ dqp, int nrz,
+__global__ __launch_bounds__(8 * TPC) void k_cg_scalars(int p, int start, int ndq, const double *__restrict__ dqp, int nrz,
                                                    const double *__restrict__ rzp, T *__restrict__ alpha,
-                                                   T *__restrict__ beta) {
+                                                   T *__restrict__ beta, double *__restrict__ aux) {
     __shared__ double red[3][TPC][9];
     const int cl = threadIdx.x & 7, k = threadIdx.x >> 3;
     const int c = blockIdx.x * 8 + cl;
@@ -950,27 +958,63 @@ __global__ __launch_bounds__(8 * TPC) void k_cg_scalars(int p, int ndq, const do
     }
     if (k || c >= p) return;
     const double dq = red[0][0][cl], qw = red[1][0][cl], rz = red[2][0][cl];
-    const T al = dq > 0.0 ? (T)(rz / dq) : T(0);
-    alpha[c] = al;
+    if (sizeof(T) == 4 && start) aux[c] = rz;
+    const CgCoef<T> k0 = cg_coef<T>(dq, qw, rz, sizeof(T) == 4 && !start ? aux[c] : 0.0);
+    alpha[c] = k0.alpha;
     if (beta) {
-        const double a = (double)al;
-        const double next = fma(a, fma(a, qw, -2.0 * dq), rz);
-        // where one step takes <r, z> down to the rounding of the prediction (an
-        // exact solution reached early), the direction starts anew from z
-        beta[c] = next > (sizeof(T) == 8 ? 1e-12 : 1e-5) * rz ? (T)(next / rz) : T(0);
+        beta[c] = k0.beta;
+        if (sizeof(T) == 4) aux[p + c] = k0.old;
+    }
+}
+
+// Columns with old[c] > 0 (none as a rule, and the launch ends at once):
+// beta = <r', z'> / old from the step's partials, d' += beta d, beta[c] for the
+// next step.  Same mapping as k_cg_step.
+template <int V>
+__global__ __launch_bounds__(256) void k_cg_beta(int64_t n, int p, int lpr_log2, int nrz, const double *__restrict__ rzp,
+                                                const double *__restrict__ old, float *__restrict__ beta,
+                                                const float *__restrict__ D, float *__restrict__ Dn) {
+    const int lpr = 1 << lpr_log2;
+    const int groups = blockDim.x >> lpr_log2;
+    const int g = threadIdx.x >> lpr_log2;
+    const int lane = threadIdx.x & (lpr - 1);
+    const int c0 = ((int)blockIdx.y * lpr + lane) * V;
+    if (c0 >= p) return;
+    float be[V];
+    bool any = false;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        be[v] = 0.0f;
+        const double o = old[c0 + v];
+        if (o > 0.0) {
+            double s = 0.0;
+            for (int r = 0; r < nrz; ++r) s += rzp[(int64_t)r * p + c0 + v];
+            be[v] = (float)(s / o);
+            any = true;
+            if (blockIdx.x == 0 && g == 0) beta[c0 + v] = be[v];
+        }
+    }
+    if (!any) return;
+    for (int64_t row = (int64_t)blockIdx.x * groups + g; row < n; row += (int64_t)gridDim.x * groups) {
+        float d[V], dn[V];
+        load_vec<float, V>(D + row * p + c0, d);
+        load_vec<float, V>(Dn + row * p + c0, dn);
+#pragma unroll
+        for (int v = 0; v < V; ++v) dn[v] = be[v] != 0.0f ? fmaf(be[v], d[v], dn[v]) : dn[v];
+        store_vec<float, V>(Dn + row * p + c0, dn);
     }
 }
 
 // One step's block pass (above) on the columns of blockIdx.y's range; persistent
-// over rows; part[blockIdx.x][c] = <z', z' / J>.  FIRST: j = 0 (no d_{-1}; Dm is
-// only written).  XUP: x += alpha_{j-1} d_{j-1} + alpha_j d_j (xfirst: from
-// zero), in the order of the running sum.  Columns that are not active keep x
-// and get nothing of d.  Memory-bound (n = 1e6, p = 128, FP64: 4 or 6 passes in
-// 880 us on average, 5.7 TB/s).  W, D and Dm go past the caches (nontemporal):
-// nothing of them is read again before the next gigabyte; so kept, the pass
-// took 945 us (FP32, n = 5.1e5: 223 against 193), k_cg_x 696 against 618,
-// k_bbdot 590 against 525, k_update_b 690 against 646 (its Xt, rewritten in
-// place, is faster through the caches).
+// over rows; part[blockIdx.x][c] = <z', z' / J>.  FIRST: j = 0 (Dm holds g).
+// XUP: x += alpha_{j-1} d_{j-1} + alpha_j d_j (xfirst: from zero).  Columns that
+// are not active keep x and get nothing of d.  Memory-bound with the vector units
+// not far behind (n = 1e6, p = 128, FP64: 4 or 6 passes in 983 us on average; FP32,
+// n = 5.1e5: 200 us; with every operation rounded 900 and 190).  W, D and Dm go
+// past the caches (nontemporal): nothing of them is read again before the next
+// gigabyte; through the caches the rounded form took 945 us (FP32: 223 against
+// 193), k_cg_x 696 against 618, k_bbdot 590 against 525, k_update_b 690 against
+// 646 (there the load of Xt, rewritten in place, goes through the caches).
 template <typename T, int V, bool FIRST, bool XUP>
 __global__ __launch_bounds__(256) void k_cg_step(int64_t n, int p, int lpr_log2, int xfirst,
                                                 const T *__restrict__ alpha, const T *__restrict__ beta,
@@ -1008,7 +1052,7 @@ __global__ __launch_bounds__(256) void k_cg_step(int64_t n, int p, int lpr_log2,
             T w[V], d[V], dm[V], x[V];
             load_nt<T, V>(W + o, w);
             load_nt<T, V>(D + o, d);
-            if (!FIRST) load_nt<T, V>(Dm + o, dm);
+            load_nt<T, V>(Dm + o, dm);
             if (XUP) {
                 if (xfirst && all) {
 #pragma unroll
@@ -1020,15 +1064,13 @@ __global__ __launch_bounds__(256) void k_cg_step(int64_t n, int p, int lpr_log2,
             const T ld = (T)lhd[row], bdv = (T)bd[row];
 #pragma unroll
             for (int v = 0; v < V; ++v) {   // selects, not branches, per column
-                const T z = fma(-al[v], w[v], FIRST ? d[v] : fma(-bm[v], dm[v], d[v]));
-                const double zd = (double)z;
-                const double t = zd * zd * (double)(ld - lm[v] * bdv);
+                const T dg = ld - lm[v] * bdv;
+                T dn;
+                const double z = cg_element<FIRST>(w[v], d[v], dm[v], dg, al[v], be[v], bm[v], dn);
+                const double t = z * z * (double)dg;
                 dot[v] = on[v] ? dot[v] + t : dot[v];
-                if (XUP) {
-                    const T x1 = xfirst ? am[v] * dm[v] : fma(am[v], dm[v], x[v]);
-                    x[v] = on[v] ? fma(al[v], d[v], x1) : x[v];
-                }
-                dm[v] = on[v] ? fma(be[v], d[v], z) : (FIRST ? T(0) : dm[v]);
+                if (XUP) x[v] = on[v] ? cg_x2(xfirst ? T(0) : x[v], am[v], dm[v], al[v], d[v]) : x[v];
+                dm[v] = on[v] ? dn : (FIRST ? T(0) : dm[v]);
             }
             store_nt<T, V>(Dm + o, dm);
             if (XUP) store_nt<T, V>(X + o, x);
@@ -1078,9 +1120,8 @@ __global__ __launch_bounds__(256) void k_cg_x(int64_t n, int p, int lpr_log2, in
         if (Dm) load_vec<T, V>(alpham + c0, am);
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            T nx;
-            if (Dm) nx = fma(a[v], d[v], xfirst ? am[v] * dm[v] : fma(am[v], dm[v], x[v]));
-            else nx = xfirst ? a[v] * d[v] : fma(a[v], d[v], x[v]);
+            const T xv = xfirst ? T(0) : x[v];
+            const T nx = Dm ? cg_x2(xv, am[v], dm[v], a[v], d[v]) : fma(a[v], d[v], xv);
             x[v] = on[v] ? nx : x[v];
         }
         store_nt<T, V>(X + o, x);
@@ -1088,13 +1129,13 @@ __global__ __launch_bounds__(256) void k_cg_x(int64_t n, int p, int lpr_log2, in
 }
 
 // Start of the columnwise CG of the preconditioner from x = 0 and a block G:
-// d = J G on active columns, P = G on the others; part[blockIdx.x][c] = <g, J g>.
-// Same mapping as k_cg_step.
+// r = G and d = J G on active columns, P = G on the others; part[blockIdx.x][c] =
+// <g, J g>.  Same mapping as k_cg_step.  (P may be G: r is a block of its own.)
 template <typename T, int V>
 __global__ __launch_bounds__(256) void k_cg_start(int64_t n, int p, int lpr_log2, const uint8_t *__restrict__ active,
                                                  const double *__restrict__ lhd, const double *__restrict__ bd,
-                                                 const T *__restrict__ lam, const T *__restrict__ G,
-                                                 T *__restrict__ D, T *__restrict__ P, double *__restrict__ part) {
+                                                 const T *__restrict__ lam, const T *G, T *__restrict__ R,
+                                                 T *__restrict__ D, T *P, double *__restrict__ part) {
     __shared__ double red[256 * V];
     const int lpr = 1 << lpr_log2;
     const int groups = blockDim.x >> lpr_log2;
@@ -1123,6 +1164,7 @@ __global__ __launch_bounds__(256) void k_cg_start(int64_t n, int p, int lpr_log2
                 dot[v] = on[v] ? fma((double)gv[v], (double)d[v], dot[v]) : 0.0;
                 if (!on[v]) P[o + v] = gv[v];
             }
+            store_vec<T, V>(R + o, gv);
             store_vec<T, V>(D + o, d);
         }
 #pragma unroll
@@ -1569,21 +1611,32 @@ hipError_t launch_cg_x(hipStream_t s, int64_t n, int p, int xfirst, const T *alp
 
 template <typename T>
 hipError_t launch_cg_start(hipStream_t s, int grid, int64_t n, int p, const uint8_t *active, const double *lhd,
-                           const double *bd, const T *lam, const T *G, T *D, T *P, double *part, int *rows) {
+                           const double *bd, const T *lam, const T *G, T *R, T *D, T *P, double *part, int *rows) {
     const RowGrid g = row_grid<T>(n, p, grid, G, P);
     *rows = g.gx;
-    if (g.v == 1) hipLaunchKernelGGL((k_cg_start<T, 1>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, active, lhd, bd, lam, G, D, P, part);
-    else if (g.v == 2) hipLaunchKernelGGL((k_cg_start<T, 2>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, active, lhd, bd, lam, G, D, P, part);
-    else if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((k_cg_start<T, 4>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, active, lhd, bd, lam, G, D, P, part);
+    if (g.v == 1) hipLaunchKernelGGL((k_cg_start<T, 1>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, active, lhd, bd, lam, G, R, D, P, part);
+    else if (g.v == 2) hipLaunchKernelGGL((k_cg_start<T, 2>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, active, lhd, bd, lam, G, R, D, P, part);
+    else if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((k_cg_start<T, 4>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, active, lhd, bd, lam, G, R, D, P, part);
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_cg_scalars(hipStream_t s, int p, int ndq, const double *dqp, int nrz, const double *rzp, T *alpha,
-                             T *beta) {
+hipError_t launch_cg_scalars(hipStream_t s, int p, int start, int ndq, const double *dqp, int nrz, const double *rzp,
+                             T *alpha, T *beta, double *aux) {
     const dim3 grid((unsigned)((p + 7) / 8));
-    if (ndq > 256) hipLaunchKernelGGL((k_cg_scalars<T, 128>), grid, dim3(1024), 0, s, p, ndq, dqp, nrz, rzp, alpha, beta);
-    else hipLaunchKernelGGL((k_cg_scalars<T, 32>), grid, dim3(256), 0, s, p, ndq, dqp, nrz, rzp, alpha, beta);
+    if (ndq > 256)
+        hipLaunchKernelGGL((k_cg_scalars<T, 128>), grid, dim3(1024), 0, s, p, start, ndq, dqp, nrz, rzp, alpha, beta, aux);
+    else hipLaunchKernelGGL((k_cg_scalars<T, 32>), grid, dim3(256), 0, s, p, start, ndq, dqp, nrz, rzp, alpha, beta, aux);
+    return hipGetLastError();
+}
+
+// D, Dn: the library's own blocks
+hipError_t launch_cg_beta(hipStream_t s, int grid, int64_t n, int p, int nrz, const double *rzp, const double *old,
+                          float *beta, const float *D, float *Dn) {
+    const RowGrid g = row_grid<float>(n, p, grid, nullptr, nullptr);
+    if (g.v == 1) hipLaunchKernelGGL((k_cg_beta<1>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, nrz, rzp, old, beta, D, Dn);
+    else if (g.v == 2) hipLaunchKernelGGL((k_cg_beta<2>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, nrz, rzp, old, beta, D, Dn);
+    else hipLaunchKernelGGL((k_cg_beta<4>), dim3(g.gx, g.gy), dim3(256), 0, s, n, p, g.l2, nrz, rzp, old, beta, D, Dn);
     return hipGetLastError();
 }
 
@@ -1622,12 +1675,13 @@ template hipError_t launch_scale_copy<float, float>(hipStream_t, int64_t, int, c
     template hipError_t launch_bbdot<T>(hipStream_t, int, int64_t, int, const T *, const T *, const T *, const T *, const T *, double *); \
     template hipError_t launch_cg_step<T>(hipStream_t, int, int64_t, int, int, int, int, const T *, const T *, const T *, const T *, const uint8_t *, const double *, const double *, const T *, const T *, const T *, T *, T *, double *, int *); \
     template hipError_t launch_cg_x<T>(hipStream_t, int64_t, int, int, const T *, const T *, const uint8_t *, const T *, const T *, T *); \
-    template hipError_t launch_cg_scalars<T>(hipStream_t, int, int, const double *, int, const double *, T *, T *); \
+    template hipError_t launch_cg_scalars<T>(hipStream_t, int, int, int, const double *, int, const double *, T *, T *, double *); \
     template hipError_t launch_update_b<T>(hipStream_t, int64_t, int, const T *, T, const T *, T *, T *);
 OFKS_INST(double)
 OFKS_INST(float)
 template hipError_t launch_cg_start<double>(hipStream_t, int, int64_t, int, const uint8_t *, const double *,
-                                            const double *, const double *, const double *, double *, double *, double *, int *);
+                                            const double *, const double *, const double *, double *, double *, double *,
+                                            double *, int *);
 template hipError_t launch_convert<double, float>(hipStream_t, int64_t, const double *, float *);
 template hipError_t launch_convert<float, double>(hipStream_t, int64_t, const float *, double *);
 

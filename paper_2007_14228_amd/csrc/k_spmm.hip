@@ -6,9 +6,8 @@
 //                  (f64) or 8-byte (f32) load feeds both products; with one
 //                  output the caller selects which of the pair is used.
 //  k_spmm_shift  : Q[:,l] = (L/2 - lam_l B) D[:,l] (operator of the paper's
-//                  preconditioner T_l, eq. precondition-T), or, for a step of
-//                  its CG, W = J Q with the per-column dot products <D_l, Q_l>
-//                  and <Q_l, W_l>.
+//                  preconditioner T_l, eq. precondition-T); for a step of its
+//                  CG with the per-column dot products <D_l, Q_l> and <Q_l, J Q_l>.
 //  k_cg_iter     : one Hartree CG iteration (one vector, FP64).
 //
 // Work mapping (wave64).  A row is owned by a group of LPR = 2^lpr_log2 lanes;
@@ -57,10 +56,10 @@ __device__ __forceinline__ void stream_store_vec(T *__restrict__ p, const T (&in
 }
 
 // What the shifted product forms from q = (A1 - lam_c A2) d on the active
-// columns (zero elsewhere): SHIFT writes q; SHIFT_CG writes w = J q, J the
-// inverse of the operator's diagonal (lhd - lam_c bd), and sums <d, q> and
-// <q, w> over the rows of a block (part[block][0..p), [p..2p)); SHIFT_DOT, the
-// last step of a CG, only sums <d, q>.
+// columns (zero elsewhere): SHIFT writes q; SHIFT_CG writes q and sums <d, q> and
+// <q, J q> over the rows of a block (part[block][0..p), [p..2p)), J the inverse
+// of the operator's diagonal (lhd - lam_c bd); SHIFT_DOT, the last step of a CG,
+// only sums <d, q>.
 enum { DUAL = 0, SHIFT = 1, SHIFT_CG = 2, SHIFT_DOT = 3 };
 
 template <typename T> struct pair_t;
@@ -149,7 +148,7 @@ __device__ __forceinline__ T shift_value(bool on, T a1, T a2, T lm, T ld, T bdv,
     if (MODE == SHIFT_DOT) return q;
     const T w = on ? q / (ld - lm * bdv) : T(0);
     qw = on ? fma((double)q, (double)w, qw) : qw;
-    return w;
+    return q;
 }
 
 // Workgroups are dispatched to the 8 XCDs round-robin (block b on XCD b % 8).

@@ -85,6 +85,7 @@ int halo_row_ptr_stride();
 struct GradArgs {
     const void *HX;
     void *P;
+    void *R;
     void *D;
     const double *lhd;
     const double *bd;
@@ -129,9 +130,10 @@ template <typename T>
 hipError_t launch_cg_x(hipStream_t, int64_t, int, int, const T *, const T *, const uint8_t *, const T *, const T *, T *);
 template <typename T>
 hipError_t launch_cg_start(hipStream_t, int, int64_t, int, const uint8_t *, const double *, const double *, const T *,
-                           const T *, T *, T *, double *, int *);
+                           const T *, T *, T *, T *, double *, int *);
 template <typename T>
-hipError_t launch_cg_scalars(hipStream_t, int, int, const double *, int, const double *, T *, T *);
+hipError_t launch_cg_scalars(hipStream_t, int, int, int, const double *, int, const double *, T *, T *, double *);
+hipError_t launch_cg_beta(hipStream_t, int, int64_t, int, int, const double *, const double *, float *, const float *, float *);
 template <typename S, typename D>
 hipError_t launch_convert(hipStream_t, int64_t, const S *, D *);
 template <typename S, typename D>
@@ -963,9 +965,10 @@ bool cgb_choice(const ofks_ctx *c, int p) { return c->prm.spmm_mode != 1 && p <=
 // one PCAL iteration
 // ---------------------------------------------------------------------------
 // P = T^-1 G columnwise by m Jacobi-CG iterations from zero (eq. precondition-T),
-// in the three-term form of k_cg_step.  On entry D = J G on active columns and
-// rz (nrz rows of p) holds partials of <G, J G>; X holds the identity-branch
-// columns already.  W is scratch for the products, E for every second direction.
+// in the three-term form of k_cg_step.  On entry D = J G and E = G on active
+// columns and rz (nrz rows of p) holds partials of <G, J G>; X holds the
+// identity-branch columns already.  W is scratch for the products; E takes
+// every second direction.
 template <typename T>
 int pcg_run(ofks_ctx *c, int m, int64_t n, int p, const uint8_t *act, const T *lam, const void *lb, T *D, T *W, T *X,
             T *E, const double *rz, int nrz) {
@@ -983,6 +986,7 @@ int pcg_run(ofks_ctx *c, int m, int64_t n, int p, const uint8_t *act, const T *l
     double *rzp = c->part + off;
     // coefficients of the current and the previous step, in the sums' scratch
     T *coef = (T *)c->red;
+    double *aux = c->red + 4 * CALL_MAX_P;   // 2 p: k_cg_scalars' own
     for (int j = 0; j < m; ++j) {
         const bool more = j + 1 < m;   // the last iteration needs no new direction
         T *al = coef + (size_t)(j & 1) * p, *be = coef + (size_t)(2 + (j & 1)) * p;
@@ -990,12 +994,14 @@ int pcg_run(ofks_ctx *c, int m, int64_t n, int p, const uint8_t *act, const T *l
         T *Dj = j & 1 ? E : D, *Dm = j & 1 ? D : E;
         int used = 0;
         CHK(spmm_shift<T>(c, more ? SHIFT_CG : SHIFT_DOT, p, lb, lam, act, Dj, W, &used));
-        HIPCHK(launch_cg_scalars<T>(c->stream, p, used, c->part, nrz, rz, al, more ? be : nullptr));
+        HIPCHK(launch_cg_scalars<T>(c->stream, p, j == 0, used, c->part, nrz, rz, al, more ? be : nullptr, aux));
         if (more) {
             Scope sc(c, "pcg_dx");
             HIPCHK(launch_cg_step<T>(c->stream, c->grid, n, p, j == 0, j & 1, j == 1, al, be, alm, bem, act, c->lhd,
                                      c->bd, lam, W, Dj, Dm, X, rzp, &nrz));
             rz = rzp;
+            if constexpr (std::is_same<T, float>::value)
+                HIPCHK(launch_cg_beta(c->stream, c->grid, n, p, nrz, rz, aux + p, be, Dj, Dm));
         } else {
             // x has taken the directions before this one in pairs (0, 1), (2, 3), ...
             Scope sc(c, "pcg_sum");
@@ -1266,7 +1272,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
     CHK(ensure_part(c, (size_t)c->gemm_rows * gy * (1 + p)));
     {
         // built after the partial buffer is final: it carries that pointer
-        GradArgs ga{B.HX, B.P, B.D, c->lhd, c->bd, B.lam, c->active, c->part};
+        GradArgs ga{B.HX, B.P, B.R, B.D, c->lhd, c->bd, B.lam, c->active, c->part};
         {
             Scope sc(c, "update_a");
             HIPCHK(launch_rowgemm<T>(c->stream, epi, n, p, 2 * p, c->gemm_rows, B.BX, B.dinv, B.CC, nullptr, ga,
@@ -1320,7 +1326,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
     if (c->gl_cap && std::is_same<T, double>::value && use_paper && any_active && c->gl_cap_count < c->gl_cap_max &&
         c->k % c->gl_cap_every == 0) {
         double *slot = c->gl_cap + (size_t)c->gl_cap_count * n * p;
-        GradArgs gn{B.HX, slot, B.D, c->lhd, c->bd, B.lam, c->active, c->part};
+        GradArgs gn{B.HX, slot, B.R, B.D, c->lhd, c->bd, B.lam, c->active, c->part};
         HIPCHK(launch_rowgemm<T>(c->stream, EPI_GRAD_NORM, n, p, 2 * p, c->gemm_rows, B.BX, B.dinv, B.CC, nullptr, gn,
                                  &gx));
         c->gl_cap_lam.insert(c->gl_cap_lam.end(), shift.begin(), shift.end());
@@ -1329,7 +1335,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
     // training samples: keep G (and its column norms) before the CG overwrites it
     const bool collect = c->lp_buf && use_paper && any_active && c->lp_count < c->lp_cap;
     if (collect) {
-        GradArgs gn{B.HX, B.P, B.D, c->lhd, c->bd, B.lam, c->active, c->part};
+        GradArgs gn{B.HX, B.P, B.R, B.D, c->lhd, c->bd, B.lam, c->active, c->part};
         HIPCHK(launch_rowgemm<T>(c->stream, EPI_GRAD_NORM, n, p, 2 * p, c->gemm_rows, B.BX, B.dinv, B.CC, nullptr, gn,
                                  &gx));
         HIPCHK(launch_colsum(c->stream, (int64_t)gx * gy, 1 + p, c->part, c->red));
@@ -2462,7 +2468,7 @@ int ofks_precondition(ofks_ctx *c, int32_t p, const double *lam, const double *G
     const size_t off = cg_part_doubles(c, p);
     CHK(ensure_part(c, off + (size_t)c->grid * p));
     int nrz = 0;
-    HIPCHK(launch_cg_start<double>(c->stream, c->grid, n, p, act, c->lhd, c->bd, lamd, G, D, P, c->part + off, &nrz));
+    HIPCHK(launch_cg_start<double>(c->stream, c->grid, n, p, act, c->lhd, c->bd, lamd, G, E, D, P, c->part + off, &nrz));
     CHK(pcg_run<double>(c, m, n, p, act, lamd, c->lb, D, W, P, E, c->part + off, nrz));
     return sync(c);
 }
