@@ -1,4 +1,4 @@
-// Arithmetic of one step of the inner CG (k_cg_step, k_cg_x, k_cg_scalars): the
+// Arithmetic of one step of the inner CG (k_cg_step, k_cg_x, k_cg_scalars, k_cgb_iter): the
 // element's recurrences and the column's coefficients.  Plain C++ apart from the
 // annotations, so that the host tests replay it with g++.
 //
@@ -70,6 +70,16 @@ OFKS_HD double cg_x2(double x, double am, double dm, double al, double d) {
 }
 OFKS_HD float cg_x2(float x, float am, float dm, float al, float d) {
     return (float)std::fma((double)al, (double)d, std::fma((double)am, (double)dm, (double)x));
+}
+
+// x + al d for an x carried as x + lo: the new x, and lo for the next (last: x is all)
+OFKS_HD double cg_carry(double x, double &lo, double al, double d, bool last) {
+#pragma clang fp contract(off)
+    const double a = al * d, ae = std::fma(al, d, -a);
+    const double s = x + a, t = s - x, l = ((x - (s - t)) + (a - t)) + (lo + ae);
+    const double h = s + l;
+    lo = last ? 0.0 : l - (h - s);
+    return h;
 }
 
 // A column's coefficients from its sums dq = <d, T d>, qw = <T d, J T d>, rz =

@@ -24,6 +24,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "cg_step.hpp"
 
 // Tuning: neighbour loads in flight per wave for one-column-chunk rows, and
 // whether streamed data (CSR entries read once, outputs written once) use
@@ -988,46 +989,51 @@ __global__ __launch_bounds__(256 * OFKS_CG_TEAMS) void k_cg_iter(
 }
 
 // ---------------------------------------------------------------------------
-// The inner CG of small blocks (FP64), one kernel an iteration: k_cg_iter's
-// recurrence for every column c of its own, T_c = L/2 - lambda_c B and M_c =
-// diag T_c.  A step of the three-kernel form is three launches of 3 to 6 us
-// whatever the size; this one is bound by the same latencies, once.
+// The inner CG of small blocks (FP64), one kernel an iteration, for every column c
+// of its own: T_c = L/2 - lambda_c B, M_c = diag T_c.  The two-term recurrences in
+// d, r and q = T d; a launch sums the previous one's partials of <d, q>, <q, M^-1
+// q> and <r, M^-1 r>, takes alpha and the predicted beta from them (cg_coef), forms
+//   r' = r - alpha q, d' = M^-1 r' + beta d   on the plan block's halo rows,
+//   x += alpha d, q' = T d' and the new partials   on its own rows.
+// A step of the three-kernel form is three launches of 3 to 6 us whatever the
+// size; this one is bound by the same latencies, once.
+//
+// x is carried in twice the digits (its low part in a block of its own).  Error
+// of ten steps on graded meshes (80-bit sums): 0.86 times that of the two-term
+// recurrence; with M^-1 T p from a recurrence of its own (one product for both
+// dots, as in k_cg_iter) it was 1.68 times, up to 5.4.
 //
 // A workgroup takes a plan block and CGB_COLS columns, a thread one column of
 // one row and of three halo rows; what does not depend on alpha and beta (the
-// states, sixteen entries of the row) is loaded while they are summed.  u, v, t
-// (in) and u2, v2, t2 (out) change places from launch to launch, as do pin and
-// pout (rows of 2 p: gamma, delta; a row per plan block) and the two slots of
-// sc (2 p each: gamma, alpha).  first: v2 = M^-1 T u.  last: x alone.
+// states, sixteen entries of the row) is loaded while they are summed.  d, r, q
+// (in) and d2, r2, q2 (out) change places from launch to launch, as do pin and
+// pout (rows of 3 p a plan block).  first: q of d alone.  last: x alone.
 // ---------------------------------------------------------------------------
 constexpr int CGB_COLS = 4, CGB_AHEAD = 16;
 struct CgBlockArgs {
-    int first, last, start, p, parity;   // start: the first iteration (x, p and t from zero)
+    int first, last, start, p;   // start: the first iteration (x from zero)
     const double *lhd, *bd, *lam;
     const uint8_t *active;
-    const double *u, *v, *t;
-    double *u2, *v2, *t2, *d, *x, *sc;
+    const double *d, *r, *q;
+    double *d2, *r2, *q2, *x, *xl;
     const double *pin;
     double *pout;
 };
 
-// sum over the workgroup's 64 rows of threads, to thread row 0 (both values)
-__device__ __forceinline__ void cgb_sum(double (&red)[2][256], double &a, double &b) {
+// sums of three values over the workgroup's 64 rows of threads, to all of them
+__device__ __forceinline__ void cgb_sum(double (&red)[3][16], double (&v)[3]) {
     // lanes of one column are four apart: by lane exchanges within a wave, then over the four waves
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, c = threadIdx.x & (CGB_COLS - 1);
 #pragma unroll
-    for (int off = CGB_COLS; off < 64; off <<= 1) {
-        a += __shfl_xor(a, off);
-        b += __shfl_xor(b, off);
-    }
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    if (l < CGB_COLS) {
-        red[0][CGB_COLS * w + l] = a;
-        red[1][CGB_COLS * w + l] = b;
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+        for (int off = CGB_COLS; off < 64; off <<= 1) v[k] += __shfl_xor(v[k], off);
+        if (l < CGB_COLS) red[k][CGB_COLS * w + l] = v[k];
     }
     __syncthreads();
-    const int c = threadIdx.x & (CGB_COLS - 1);
-    a = (red[0][c] + red[0][CGB_COLS + c]) + (red[0][2 * CGB_COLS + c] + red[0][3 * CGB_COLS + c]);
-    b = (red[1][c] + red[1][CGB_COLS + c]) + (red[1][2 * CGB_COLS + c] + red[1][3 * CGB_COLS + c]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        v[k] = (red[k][c] + red[k][CGB_COLS + c]) + (red[k][2 * CGB_COLS + c] + red[k][3 * CGB_COLS + c]);
 }
 
 __global__ __launch_bounds__(256) void k_cgb_iter(int64_t nb, const int64_t *__restrict__ row0,
@@ -1036,7 +1042,8 @@ __global__ __launch_bounds__(256) void k_cgb_iter(int64_t nb, const int64_t *__r
                                                  const double2 *__restrict__ lb, CgBlockArgs c) {
     constexpr int G = 256 / CGB_COLS, NS = (HALO_MAX + G - 1) / G;   // thread rows, halo rows a thread
     static_assert(G == HALO_RMAX, "a matrix row a thread");
-    __shared__ double us[NS * G * CGB_COLS], red[2][256];
+    static_assert(CGB_COLS * 4 == 16, "cgb_sum");
+    __shared__ double ds[NS * G * CGB_COLS], red[2][3][16];
     const int tid = threadIdx.x, cl = tid & (CGB_COLS - 1), g = tid / CGB_COLS;
     const int64_t b = blockIdx.x;
     const int col = (int)blockIdx.y * CGB_COLS + cl;
@@ -1048,12 +1055,11 @@ __global__ __launch_bounds__(256) void k_cgb_iter(int64_t nb, const int64_t *__r
     const int inf = info[b], nr = (inf >> 8) & 255, rb = (inf >> 16) & 255;
     const int64_t row = row0[b] + min(g, nr - 1), e0 = brp[b * HALO_BRP + g];
     const int len = (int)(brp[b * HALO_BRP + g + 1] - e0);   // 0 past the block's rows
-    double ga = 0.0, de = 0.0;
+    double sum[3] = {0.0, 0.0, 0.0};   // <d, q>, <q, M^-1 q>, <r, M^-1 r>
     if (!c.first && in)
-        for (int64_t k = g; k < nb; k += G) {
-            ga += c.pin[2 * k * c.p + col];
-            de += c.pin[(2 * k + 1) * c.p + col];
-        }
+        for (int64_t k = g; k < nb; k += G)
+#pragma unroll
+            for (int u = 0; u < 3; ++u) sum[u] += c.pin[(3 * k + u) * c.p + col];
     double2 w[CGB_AHEAD];
     int lc[CGB_AHEAD];
     if (!c.last)
@@ -1063,105 +1069,104 @@ __global__ __launch_bounds__(256) void k_cgb_iter(int64_t nb, const int64_t *__r
             w[j] = lb[e];
             lc[j] = lcol[e];
         }
-    double u[NS], v[NS], t[NS], d[NS], x[NS];
+    double d[NS], r[NS], q[NS], iv[NS], x[NS], xl[NS];   // (iv: M^-1)
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
         const int s = g + i * G;
         const bool own = on && s >= rb && s < rb + nr;
         const int64_t e = (int64_t)hr[i] * c.p + (in ? col : 0);
-        u[i] = on ? c.u[e] : 0.0;
-        v[i] = on && !c.first && !c.last ? c.v[e] : 0.0;
-        t[i] = on && !c.first && !c.last && !c.start ? c.t[e] : 0.0;
-        d[i] = own && !c.first && !c.start ? c.d[e] : 0.0;
+        d[i] = on ? c.d[e] : 0.0;
+        r[i] = on && !c.last ? c.r[e] : 0.0;
+        q[i] = on && !c.first && !c.last ? c.q[e] : 0.0;
+        iv[i] = c.last ? 1.0 : 1.0 / (c.lhd[hr[i]] - lm * c.bd[hr[i]]);
         x[i] = own && !c.first && !c.start ? c.x[e] : 0.0;
+        xl[i] = own && !c.first && !c.start ? c.xl[e] : 0.0;
     }
-    double alpha = 0.0, beta = 0.0;
+    const double ivr = c.last ? 1.0 : 1.0 / (c.lhd[row] - lm * c.bd[row]);
+    CgCoef<double> k{0.0, 0.0, 0.0};
     if (!c.first) {
-        const double *so = c.sc + (size_t)2 * c.p * c.parity;
-        const double go = in && !c.start ? so[col] : 0.0, ao = in && !c.start ? so[c.p + col] : 0.0;
-        cgb_sum(red, ga, de);
-        beta = go > 0.0 ? ga / go : 0.0;
-        const double den = ao > 0.0 ? de - beta * ga / ao : de;
-        alpha = den > 0.0 ? ga / den : 0.0;
-        if (b == 0 && g == 0 && in) {
-            double *sn = c.sc + (size_t)2 * c.p * (c.parity ^ 1);
-            sn[col] = ga;
-            sn[c.p + col] = alpha;
-        }
+        cgb_sum(red[0], sum);
+        k = cg_coef<double>(sum[0], sum[1], sum[2], 0.0);
+        sum[2] = 0.0;
     }
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
         const int s = g + i * G;
         const bool own = on && s >= rb && s < rb + nr;
         const int64_t e = (int64_t)hr[i] * c.p + col;
-        const double tn = fma(beta, t[i], v[i]), un = fma(-alpha, tn, u[i]), dn = fma(beta, d[i], u[i]);
-        if (own && !c.first) {
-            c.x[e] = fma(alpha, dn, x[i]);
-            if (!c.last) {
-                c.d[e] = dn;
-                c.t2[e] = tn;
-                c.u2[e] = un;
+        const double rn = fma(-k.alpha, q[i], r[i]), z = rn * iv[i];   // (first: alpha = 0)
+        const double dn = c.first ? d[i] : fma(k.beta, d[i], z);
+        if (own) {
+            sum[2] = fma(rn, z, sum[2]);
+            if (!c.first) {
+                double lo = xl[i];
+                c.x[e] = cg_carry(x[i], lo, k.alpha, d[i], c.last);
+                if (!c.last) {
+                    c.xl[e] = lo;
+                    c.d2[e] = dn;
+                    c.r2[e] = rn;
+                }
             }
         }
-        us[s * CGB_COLS + cl] = un;
+        ds[s * CGB_COLS + cl] = on ? dn : 0.0;
     }
     if (c.last) return;
     __syncthreads();
-    ga = de = 0.0;
+    sum[0] = sum[1] = 0.0;
     if (on && g < nr) {
         double a1 = 0.0, a2 = 0.0;
 #pragma unroll
         for (int j = 0; j < CGB_AHEAD; ++j)
             if (j < len) {
-                const double un = us[lc[j] * CGB_COLS + cl];
-                a1 = fma(w[j].x, un, a1);
-                a2 = fma(w[j].y, un, a2);
+                const double dn = ds[lc[j] * CGB_COLS + cl];
+                a1 = fma(w[j].x, dn, a1);
+                a2 = fma(w[j].y, dn, a2);
             }
         for (int j = CGB_AHEAD; j < len; ++j) {
             const double2 wj = lb[e0 + j];
-            const double un = us[(int)lcol[e0 + j] * CGB_COLS + cl];
-            a1 = fma(wj.x, un, a1);
-            a2 = fma(wj.y, un, a2);
+            const double dn = ds[(int)lcol[e0 + j] * CGB_COLS + cl];
+            a1 = fma(wj.x, dn, a1);
+            a2 = fma(wj.y, dn, a2);
         }
-        const double q = fma(-lm, a2, a1), m = c.lhd[row] - lm * c.bd[row], un = us[(rb + g) * CGB_COLS + cl];
-        c.v2[row * c.p + col] = q / m;
-        ga = m * un * un;
-        de = q * un;
+        const double qn = fma(-lm, a2, a1);
+        c.q2[row * c.p + col] = qn;
+        sum[0] = ds[(rb + g) * CGB_COLS + cl] * qn;
+        sum[1] = qn * (qn * ivr);
     }
-    cgb_sum(red, ga, de);
-    if (g == 0 && in) {
-        c.pout[2 * b * c.p + col] = ga;
-        c.pout[(2 * b + 1) * c.p + col] = de;
-    }
+    cgb_sum(red[1], sum);
+    if (g == 0 && in)
+#pragma unroll
+        for (int u = 0; u < 3; ++u) c.pout[(3 * b + u) * c.p + col] = sum[u];
 }
 
-// Workgroups of a launch; the partials are 4 p per plan block.
+// Workgroups of a launch.
 int64_t cgb_blocks(int64_t nb, int p) { return nb * ((p + CGB_COLS - 1) / CGB_COLS); }
+// doubles of the blocks and partials that a width p takes beside the caller's blocks
+size_t cgb_doubles(int64_t n, int64_t nb, int p) { return (size_t)(4 * n + 6 * nb) * p; }
 
-// m iterations on D (M^-1 of the residual, zero in inactive columns) into X's
-// active columns.  W, E, D: n p values each; extra: 4 n p; part: 4 nb p; sc: 4 p.
+// m iterations on D (M^-1 R; R the residual at x = 0) into X's active columns.
+// D, R, Q: n p values each, overwritten; extra: cgb_doubles.
 hipError_t launch_cgb(hipStream_t s, int m, int64_t n, int64_t nb, int p, const int64_t *row0, const int32_t *info,
                       const int32_t *halo, const int64_t *brp, const uint16_t *lcol, const void *lb, const double *lhd,
-                      const double *bd, const double *lam, const uint8_t *active, double *D, double *W, double *E,
-                      double *X, double *extra, double *part, double *sc) {
+                      const double *bd, const double *lam, const uint8_t *active, double *D, double *R, double *Q,
+                      double *X, double *extra) {
     if (m <= 0) return hipErrorInvalidValue;
     const int64_t np = n * p;
     const dim3 grid((unsigned)nb, (unsigned)((p + CGB_COLS - 1) / CGB_COLS));
-    double *st[2][3] = {{D, W, E}, {extra, extra + np, extra + 2 * np}}, *pt[2] = {part, part + 2 * nb * p};
-    CgBlockArgs c{1, 0, 0, p, 1, lhd, bd, lam, active, D, nullptr, nullptr, nullptr, W, nullptr, extra + 3 * np, X, sc,
-                  pt[1], pt[0]};
+    double *st[2][3] = {{D, R, Q}, {extra, extra + np, extra + 2 * np}};
+    double *part = extra + 4 * np, *pt[2] = {part, part + 3 * nb * p};
+    CgBlockArgs c{1, 0, 0, p, lhd, bd, lam, active, D, R, nullptr, nullptr, nullptr, Q, X, extra + 3 * np, pt[1], pt[0]};
     hipLaunchKernelGGL(k_cgb_iter, grid, dim3(256), 0, s, nb, row0, info, halo, brp, lcol, (const double2 *)lb, c);
     c.first = 0;
     for (int j = 0; j < m; ++j) {
         c.start = j == 0;
         c.last = j + 1 == m;
-        c.parity = j & 1;
-        c.u = st[j & 1][0];
-        c.v = st[j & 1][1];
-        c.t = st[j & 1][2];
-        c.u2 = st[(j & 1) ^ 1][0];
-        c.v2 = st[(j & 1) ^ 1][1];
-        c.t2 = st[(j & 1) ^ 1][2];
+        c.d = st[j & 1][0];
+        c.r = st[j & 1][1];
+        c.q = st[j & 1][2];
+        c.d2 = st[(j & 1) ^ 1][0];
+        c.r2 = st[(j & 1) ^ 1][1];
+        c.q2 = st[(j & 1) ^ 1][2];
         c.pin = pt[j & 1];
         c.pout = pt[(j & 1) ^ 1];
         hipLaunchKernelGGL(k_cgb_iter, grid, dim3(256), 0, s, nb, row0, info, halo, brp, lcol, (const double2 *)lb, c);

@@ -67,9 +67,10 @@ hipError_t launch_cg_iter(hipStream_t, int, int, int, int, int64_t, int, const i
                           double *, const double *, double *, double *);
 int cg_iter_blocks(int64_t nb);
 int64_t cgb_blocks(int64_t nb, int p);
+size_t cgb_doubles(int64_t n, int64_t nb, int p);
 hipError_t launch_cgb(hipStream_t, int, int64_t, int64_t, int, const int64_t *, const int32_t *, const int32_t *,
                       const int64_t *, const uint16_t *, const void *, const double *, const double *, const double *,
-                      const uint8_t *, double *, double *, double *, double *, double *, double *, double *);
+                      const uint8_t *, double *, double *, double *, double *, double *);
 int cg_iter_blocks_max();
 template <typename T>
 hipError_t launch_spmm_halo(hipStream_t, int, int64_t, int, int, const int64_t *, const int32_t *, const int32_t *,
@@ -271,7 +272,7 @@ struct ofks_ctx {
     double *rho_q = nullptr, *eps_q = nullptr, *vxc_q = nullptr, *veff_q = nullptr, *bvec = nullptr,
            *U = nullptr, *cg_st[2] = {nullptr, nullptr}, *cg_sc = nullptr,   // (cg_st: the Hartree CG's row states)
            *cg_part = nullptr;   // Hartree CG partial sums (fixed: the captured graph holds the pointer)
-    double *cgb_blk = nullptr;           // with the plan: the small inner CG's four blocks and partials
+    double *cgb_blk = nullptr;           // with the plan: the small inner CG's own blocks and partials
     int cgb_p = 0;                       // and the widest block that it takes (0: none)
     double *cg_report = nullptr;         // pinned: what its last check saw
     hipEvent_t cg_ev[2] = {nullptr, nullptr};
@@ -954,11 +955,12 @@ double bb_eta(int rule, int k, double sy, double yy, double ss, double eta_prev,
 
 // Small FP64 blocks take the inner CG with one kernel an iteration
 // (k_cgb_iter), up to OFKS_CGB_BLOCKS workgroups of it: a call of 10 iterations
-// on Kuhn meshes took (here against three kernels an iteration, us; workgroups)
-// n = 3375, p = 4 102 against 181 (53), p = 16 132 against 183 (212), p = 64
-// 205 against 201 (848); n = 15625, p = 4 124 against 248 (245), p = 16 263
-// against 246 (980); n = 42875, p = 4 174 against 280 (670), n = 117649, p = 4
-// 502 against 433 (1839).  Not where spmm_mode asks for the gathering product.
+// on graded meshes took (here against three kernels an iteration, us; workgroups)
+// n = 3375, p = 4 112 against 172 (57), p = 16 137 against 168 (228), p = 48 179
+// against 199 (684), p = 64 222 against 204 (912); n = 8000, p = 16 181 against 195
+// (536), p = 24 239 against 220 (804); n = 15625, p = 8 181 against 192 (522), p =
+// 11 245 against 239 (783); n = 42875, p = 4 188 against 249 (715).  Not where
+// spmm_mode asks for the gathering product.
 bool cgb_choice(const ofks_ctx *c, int p) { return c->prm.spmm_mode != 1 && p <= c->cgb_p; }
 
 // ---------------------------------------------------------------------------
@@ -974,10 +976,9 @@ int pcg_run(ofks_ctx *c, int m, int64_t n, int p, const uint8_t *act, const T *l
             T *E, const double *rz, int nrz) {
     if constexpr (std::is_same<T, double>::value) {
         if (cgb_choice(c, p)) {
-            double *part = c->cgb_blk + (size_t)4 * n * p;
             Scope sc(c, "pcg_dx");
             HIPCHK(launch_cgb(c->stream, m, n, c->halo_nb, p, c->halo_row0, c->halo_info, c->halo_idx, c->halo_brp,
-                              c->halo_lcol, lb, c->lhd, c->bd, lam, act, D, W, E, X, c->cgb_blk, part, c->red));
+                              c->halo_lcol, lb, c->lhd, c->bd, lam, act, D, E, W, X, c->cgb_blk));
             return OFKS_OK;
         }
     }
@@ -1666,7 +1667,7 @@ int build_halo_plan(ofks_ctx *c) {
     c->halo_nb = nb;
     // the small inner CG's own blocks, of the widest block that it takes (at most 6 MB)
     while (c->cgb_p < 1024 && c->cgb_p < n && cgb_blocks(nb, c->cgb_p + 1) <= OFKS_CGB_BLOCKS) ++c->cgb_p;
-    if (c->cgb_p) CHK(dalloc(c, &c->cgb_blk, (size_t)4 * (n + nb) * c->cgb_p));
+    if (c->cgb_p) CHK(dalloc(c, &c->cgb_blk, cgb_doubles(n, nb, c->cgb_p)));
     return OFKS_OK;
 }
 

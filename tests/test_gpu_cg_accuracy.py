@@ -95,6 +95,19 @@ def test_block_form_is_as_accurate_as_the_two_term_form(mode, p):
     assert np.concatenate(ratios).mean() <= 1.0
 
 
+def test_one_kernel_form_is_as_accurate_as_the_two_term_form():
+    ratios = []
+    for cells, grade in ((12, 2.0), (12, 5.0), (14, 4.0)):
+        for seed in range(3):
+            print(f"[gpu] cg accuracy, small blocks, grade={grade} seed={seed}", flush=True)
+            s = _solver(cells, grade)
+            got, two, _ = _errors(s, "auto", 8, seed)
+            ratios.append(got / two)
+            s.close()
+    # 72 ratios that scatter by 0.15
+    assert np.concatenate(ratios).mean() <= 1.0
+
+
 @pytest.mark.parametrize("mode", ["auto", "gather"])
 @pytest.mark.parametrize("p", [4, 96])
 def test_unaligned_blocks_give_the_same(mode, p):
