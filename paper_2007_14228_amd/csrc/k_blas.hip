@@ -45,21 +45,36 @@ __global__ __launch_bounds__(256) void k_colsum(int64_t nb, int64_t m_total,
 
 // The same sums for many columns (the Gram's p x 2p): 64 columns a block, four
 // threads a column, so that every access takes whole cache lines (a block per
-// column reads 8 bytes of each).  n = 1e6, p = 128: 121 -> 11 us together with
-// the fewer row splits of the FP64 Gram.
+// column reads 8 bytes of each).  The additions' errors are carried along, since
+// four threads' long chains lose more than the 256 short ones above (p = 48: 1.2e-16
+// of the diagonal without them, 0.6e-16 with 256 chains, 0.4e-16 so).  n = 1e6, p =
+// 128, 1024 splits: 41 us, 6.5 TB/s (a block per column: 121 us).
+struct TwoSum {
+    double s = 0.0, e = 0.0;   // sum s + e
+    __device__ __forceinline__ void add(double v) {
+#pragma clang fp contract(off)
+        const double h = s + v, t = h - s;
+        e += (s - (h - t)) + (v - t);
+        s = h;
+    }
+};
 __global__ __launch_bounds__(256) void k_colsum_wide(int64_t nb, int64_t m_total, const double *__restrict__ part,
                                                     double *__restrict__ out) {
-    __shared__ double red[4][64];
+    __shared__ double red[2][4][64];
     const int cl = threadIdx.x & 63, k = threadIdx.x >> 6;
     const int64_t m = (int64_t)blockIdx.x * 64 + cl;
-    double s = 0.0;
+    TwoSum a;
     if (m < m_total) {
 #pragma unroll 8
-        for (int64_t b = k; b < nb; b += 4) s += part[b * m_total + m];
+        for (int64_t b = k; b < nb; b += 4) a.add(part[b * m_total + m]);
     }
-    red[k][cl] = s;
+    red[0][k][cl] = a.s;
+    red[1][k][cl] = a.e;
     __syncthreads();
-    if (k == 0 && m < m_total) out[m] = (red[0][cl] + red[1][cl]) + (red[2][cl] + red[3][cl]);
+    if (k == 0 && m < m_total) {
+        for (int q = 1; q < 4; ++q) a.add(red[0][q][cl]);
+        out[m] = a.s + (a.e + ((red[1][1][cl] + red[1][2][cl]) + red[1][3][cl]));
+    }
 }
 
 // The p x p algebra between the Gram and the row GEMM, a row a block: from the

@@ -102,10 +102,12 @@ struct GramPlan {
     int64_t splits;
 };
 GramPlan gram_plan(int64_t n, int p, int target_blocks);
-// Blocks of the Gram (p > 64): FP64 one round of the two that fit on each of 256
-// CUs, which leaves a quarter of the partials of 2048 blocks (n = 1e6, p = 128:
-// 67 MB); FP32 partials are FP32 sums, so their rows per split stay few.
-constexpr int GRAM_BLOCKS_F64 = 512, GRAM_BLOCKS_F32 = 2048;
+// Blocks of the Gram (p > 64), and with them its row splits: a split's sums are
+// chains of as many additions as it has fours of rows, so few splits cost
+// digits.  n = 5.1e5, p = 128, FP64, the call: 2048 blocks 788 us, error of the
+// elements off the diagonal 1.06e-18 (rms, of the columns' norms); 1024 733 us,
+// 1.49e-18; 512, one round on 256 CUs, 716 us, 2.11e-18.
+constexpr int GRAM_BLOCKS = 2048;
 template <typename T>
 hipError_t launch_gram(hipStream_t, int64_t, int, const GramPlan &, const T *, const T *, const T *, double *, size_t);
 template <typename T>
@@ -672,7 +674,7 @@ int gram_sums(ofks_ctx *c, const T *X, const T *BX, const T *HX) {   // into c->
     const int p = c->p;
     const size_t pp2 = (size_t)p * 2 * p;
     // size the split-K partials from the launch plan before launching
-    const GramPlan plan = gram_plan(c->n, p, sizeof(T) == 8 ? GRAM_BLOCKS_F64 : GRAM_BLOCKS_F32);
+    const GramPlan plan = gram_plan(c->n, p, GRAM_BLOCKS);
     CHK(ensure_part(c, (size_t)plan.splits * pp2));
     const int64_t ns = plan.splits;
     {
@@ -706,7 +708,7 @@ size_t cg_part_doubles(ofks_ctx *c, int p) {
 }
 
 size_t partials_needed(ofks_ctx *c, int p) {
-    const GramPlan plan = gram_plan(c->n, p, GRAM_BLOCKS_F32);   // the larger of the two
+    const GramPlan plan = gram_plan(c->n, p, GRAM_BLOCKS);
     const size_t gy = rowgemm_grid_y(2 * p);
     size_t need = (size_t)plan.splits * p * 2 * p;
     need = std::max(need, (size_t)c->gemm_rows * gy * (1 + p));
@@ -2435,7 +2437,7 @@ int ofks_gram_noalloc(ofks_ctx *c, int32_t p, const double *X, const double *HX,
     // tiles would not fit beside their column sum
     const size_t pp2 = (size_t)p * 2 * p;
     const int64_t max_splits = (int64_t)(NOALLOC_SCRATCH_DOUBLES / pp2) - 1;
-    GramPlan plan = gram_plan(c->n, p, GRAM_BLOCKS_F64);
+    GramPlan plan = gram_plan(c->n, p, GRAM_BLOCKS);
     if (plan.splits > max_splits) plan = gram_plan(c->n, p, (int)(max_splits * plan.gx * plan.gy));
     if (plan.splits < 1 || plan.splits > max_splits)
         return fail(c, OFKS_EINTERNAL, "gram_noalloc: no split plan fits the scratch");
