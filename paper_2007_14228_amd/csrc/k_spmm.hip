@@ -24,6 +24,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "cg_report.hpp"
 #include "cg_step.hpp"
 
 // Tuning: neighbour loads in flight per wave for one-column-chunk rows, and
@@ -769,8 +770,9 @@ k_spmm_halo(int64_t nb, int p, int cw, const int64_t *__restrict__ row0, const i
 // overwritten that another workgroup still reads.  first: alpha = beta = 0 (v
 // = M^-1 A u of a new u), and the next launch takes beta = 0.  check: the
 // launch stops, and those after it do, once <r', r'> of the last one is within
-// sc[3]; report (host memory) gets that sum, the bound and whether no iteration
-// went before, so the host can queue iterations ahead of knowing.
+// sc[3]; report (host memory) gets that sum with whether no iteration went before
+// (cg_report_word), and the bound, so the host can queue iterations ahead of
+// knowing.
 //
 // With the halo plan (which a mesh's matrices always have: its rows hold at
 // most 64 entries) a state is read once per 64-row block (two to three times
@@ -851,10 +853,9 @@ __global__ __launch_bounds__(256 * OFKS_CG_TEAMS) void k_cg_iter(
         const bool stop = !(rr > tol2);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             c.sc[0] = stop ? 1.0 : 0.0;
-            __hip_atomic_store(c.report, rr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            // (no iteration yet: a first launch leaves gamma 0)
             __hip_atomic_store(c.report + 1, tol2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            // no iteration yet (a first launch leaves gamma 0)
-            __hip_atomic_store(c.report + 2, c.sc[4 + 2 * c.parity] == 0.0 ? 1.0 : 0.0, __ATOMIC_RELAXED,
+            __hip_atomic_store(c.report, cg_report_word(rr, c.sc[4 + 2 * c.parity] == 0.0), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_SYSTEM);
         }
         if (stop) return;

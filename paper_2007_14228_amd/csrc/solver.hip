@@ -30,6 +30,7 @@
 
 #include "../../include/ofks.h"
 #include "common.hpp"
+#include "cg_report.hpp"
 #include "dense.hpp"
 #include "halo_plan.hpp"
 
@@ -793,7 +794,7 @@ void drop_cg_graph(ofks_ctx *c) {
 int poisson(ofks_ctx *c) {
     const int64_t n = c->n;
     if (!c->halo_nb) return fail(c, OFKS_ESTATE, "Hartree CG: the mesh has no halo plan");   // its rows always fit one
-    if (!c->cg_report) HIPCHK(hipHostMalloc((void **)&c->cg_report, 3 * sizeof(double)));
+    if (!c->cg_report) HIPCHK(hipHostMalloc((void **)&c->cg_report, 2 * sizeof(double)));
     for (hipEvent_t &e : c->cg_ev)
         if (!e) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     const double rt = c->poisson_tol_now > 0.0 ? c->poisson_tol_now : c->prm.poisson_rtol;
@@ -849,9 +850,9 @@ int poisson(ofks_ctx *c) {
     // two tens cost 15 us for each.
     const int most = (std::max(c->prm.poisson_max_iter, 0) + 9) / 10;
     int launched = 0, seen = 0;
-    double rr = 0.0, tol2 = 0.0;
-    bool fresh = true, stopped = false;   // fresh: no iteration yet
-    while (!stopped) {
+    double tol2 = 0.0;
+    CgSeen now{0.0, false, false};
+    while (!now.stop) {
         while (launched < most && launched - seen < 2) {
             Scope s2(c, "poisson");
             if (c->prm.use_graphs) HIPCHK(hipGraphLaunch(c->cg_graph, c->stream));
@@ -861,25 +862,24 @@ int poisson(ofks_ctx *c) {
         if (seen < launched) {
             HIPCHK(hipEventSynchronize(c->cg_ev[seen++ & 1]));
             const volatile double *v = c->cg_report;   // this ten's check, or the next one's already
-            rr = v[0];
             tol2 = v[1];
-            fresh = v[2] != 0.0;
-            stopped = !(rr > tol2) || (!std::isfinite(rr) && !fresh);
+            now = cg_report_seen(v[0], tol2);
         } else {   // what the last ten reached
             std::vector<double> v, b;
             CHK(download(c, v, part[0] + 2 * np, np));
             CHK(download(c, b, c->cg_sc, 4));
-            rr = 0.0;
+            double rr = 0.0;
             for (double x : v) rr += x;
             tol2 = b[3];
-            fresh = launched == 0;
-            stopped = true;
+            now = cg_report_seen(cg_report_word(rr, launched == 0), tol2);
+            now.stop = true;
         }
     }
-    if (!std::isfinite(rr) && !fresh) {
+    if (now.diverged) {
         CHK(sync(c));
         return fail(c, OFKS_ENONFINITE, "Hartree CG diverged");
     }
+    const double rr = now.rr;
     if (rr > tol2) return fail(c, OFKS_NOT_CONVERGED, "Hartree CG did not reach %g", rt);
     return OFKS_OK;
 }
