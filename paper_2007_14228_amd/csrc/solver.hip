@@ -1129,7 +1129,7 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
         HIPCHK(hipEventRecord(c->hsl_ev, c->stream));
         th0 = std::chrono::steady_clock::now();
         if (!scf) dn.assign(p, 1.0);
-        double bad = 0.0;
+        bool bad_b = false, bad = false;   // a row's code: 2048 for each entry of S, 1 for each of its at most 1024 of L0
         for (int i = 0; i < p; ++i) {
             if (norm) {
                 if (!(in[i] > 0.0)) return fail(c, OFKS_EZERONORM, "column %d has zero B-norm", i);
@@ -1138,9 +1138,10 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
             lam_diag[i] = in[p + i];
             l0_diag[i] = in[2 * p + i];
             fea += in[3 * p + i];
-            bad += in[4 * p + i];
+            bad_b |= in[4 * p + i] >= 2048.0;
+            bad |= in[4 * p + i] > 0.0;
         }
-        if (bad > 0.0) return fail(c, OFKS_ENONFINITE, "non-finite X^T %s X", bad >= 2048.0 ? "B" : "H");
+        if (bad) return fail(c, OFKS_ENONFINITE, "non-finite X^T %s X", bad_b ? "B" : "H");
         fea = std::sqrt(fea);
         sl.p = p;
     } else {
