@@ -128,4 +128,28 @@ inline int halo_plan_check(int64_t n, const int64_t *rp, const int32_t *col, int
     return HALO_OK;
 }
 
+// Whether the LDS-halo product of a block of p columns of `elem` bytes beats the
+// row-gather product, by the plan's halo rows per matrix row (15-entry rows:
+// Z-order numbering 3.1, Delaunay meshes so numbered 3.7, lexicographic 7.2,
+// Z-order shuffled within windows of 64, 128, 256 and 1024 rows 3.4, 7.3, 10.4
+// and 13.2, random 14.3).  Each halo row is staged whatever its use, while the
+// gathered rows come from caches.  Measured, gather against halo, us, n = 2.05e5:
+//   up to 5: FP64 from p = 4 on (Z-order, dual product: p = 4 66 and 47, 11 73 and
+//     57, 32 74 and 53, 128 274 and 164), FP32 from p = 33 on (33 161 and 61, 64 63
+//     and 51, 128 151 and 77), below which a row of X fills a small part of the
+//     staged 256-byte slots
+//   up to 9: FP64 from p = 24 on (lexicographic, dual and shifted product: p = 8 51
+//     and 64, 58 and 74; 16 51 and 63, 60 and 72; 24 74 and 64, 86 and 73; 64 156 and
+//     111, 147 and 114); FP32 past p = 128 and at odd p, where the gather takes
+//     single values (33 162 and 94, 175 and 105; 64 64 and 68, 75 and 85; 128 138 and
+//     118, 115 and 137; 160 187 and 154, 224 and 180)
+//   above: FP64 from p = 64 on (random: p = 11 98 and 156, 110 and 173; 48 200 and
+//     234, 198 and 238; 64 265 and 253, 258 and 254; 128 511 and 492, 513 and 462);
+//     FP32 never (96 198 and 232, 199 and 272; 160 319 and 368, 327 and 412)
+inline bool halo_product_pays(int64_t n, int64_t halo_rows, int p, int elem) {
+    if (halo_rows <= 5 * n) return elem == 8 ? p >= 4 : p >= 33;
+    if (halo_rows <= 9 * n) return elem == 8 ? p >= 24 : p > 128 || (p >= 33 && p % 2);
+    return elem == 8 && p >= 64;
+}
+
 }  // namespace ofks

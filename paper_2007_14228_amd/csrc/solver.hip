@@ -265,6 +265,7 @@ struct ofks_ctx {
     // columns (halo) and each entry's slot in its block's halo
     int halo_maxlen = 0;                  // the longest row's entries
     int64_t halo_nb = 0;                  // 0: no plan (a row alone exceeds the halo capacity)
+    int64_t halo_rows = 0;                // all blocks' halo rows
     int64_t *halo_row0 = nullptr;
     int32_t *halo_info = nullptr;         // per block: halo rows | rows << 8 | halo slot of its first row << 16
     int32_t *halo_idx = nullptr;          // per block: its halo rows, padded to a fixed stride
@@ -719,20 +720,14 @@ size_t partials_needed(ofks_ctx *c, int p) {
     return need;
 }
 
-// SpMM kernel choice (spmm_mode 0), as measured on Kuhn grids of 1e3 to 1e6
-// rows and an irregular pattern: the LDS-halo kernel for FP64 blocks with p >= 4
-// (dual product at n = 3.4e5: p = 11 76 against 101 us, 32 79 against 135, 64
-// 147 against 257, 128 259 against 466; level at p = 8 and 16) and FP32 blocks
-// with p >= 33 (33: 84 against 252 us, 64: 71 against 122, 128: 113 against
-// 236).  Below, a row of X fills a small part of the staged 256-byte slots
-// (FP32 p = 16: 55 against 50 us) and the row-gather kernel serves.
-// spmm_mode 1 (gather) or 2 (halo) forces one.  Returns 1: halo, 0: gather,
-// -1: halo forced but no plan exists.
+// SpMM kernel choice: spmm_mode 0 the one that the plan and the width speak for
+// (halo_product_pays), 1 (gather) or 2 (halo) that one.  Returns 1: halo, 0:
+// gather, -1: halo forced but no plan exists.
 int halo_choice(ofks_ctx *c, int p, size_t elem) {
     const int m = c->prm.spmm_mode;
     if (m == 1) return 0;
     if (m == 2) return c->halo_nb ? 1 : -1;
-    return c->halo_nb && (elem == 8 ? p >= 4 : p >= 33) ? 1 : 0;
+    return c->halo_nb && halo_product_pays(c->n, c->halo_rows, p, (int)elem) ? 1 : 0;
 }
 
 // Y1 = A1 X, Y2 = A2 X (Y2 = NULL: A1 X or A2 X by sel) for the pair matrix w.
@@ -1668,6 +1663,7 @@ int build_halo_plan(ofks_ctx *c) {
     HIPCHK(hipMemcpyAsync(c->halo_brp, bpad.data(), bpad.size() * sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     c->halo_nb = nb;
+    c->halo_rows = (int64_t)P.halo.size();
     // the small inner CG's own blocks, of the widest block that it takes (at most 6 MB)
     while (c->cgb_p < 1024 && c->cgb_p < n && cgb_blocks(nb, c->cgb_p + 1) <= OFKS_CGB_BLOCKS) ++c->cgb_p;
     if (c->cgb_p) CHK(dalloc(c, &c->cgb_blk, cgb_doubles(n, nb, c->cgb_p)));
