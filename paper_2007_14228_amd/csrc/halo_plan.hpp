@@ -152,4 +152,14 @@ inline bool halo_product_pays(int64_t n, int64_t halo_rows, int p, int elem) {
     return elem == 8 && p >= 64;
 }
 
+// Whether the one-kernel Hartree CG iteration, which reads a row's state once per
+// halo that it lies in, beats product, update and direction kernels.  Ten
+// iterations, us, here against those three: Z-order n = 1.0e5 108 and 191, 5.1e5
+// 293 and 432, 2.0e6 1336 and 1686; lexicographic 1.0e5 142 and 194, 2.1e5 (1.5e6
+// halo rows) 227 and 262, 5.1e5 (3.7e6) 467 and 429, 2.0e6 2108 and 1692; random
+// 4.3e4 (0.6e6) 140 and 159, 1.0e5 (1.5e6) 265 and 221, 1.0e6 2612 and 1841.
+inline bool halo_cg_pays(int64_t n, int64_t halo_rows) {
+    return halo_rows <= 4 * n || halo_rows <= 1000000 || (halo_rows <= 8 * n && halo_rows <= 2000000);
+}
+
 }  // namespace ofks

@@ -9,7 +9,8 @@
 //  k_load_vec   : b_i = int rho phi_i (row gather over incident tetrahedra).
 //  k_veff       : V_eff(q) = V_ext(q) + sum_a U_a lambda_a(q) + v_xc(q).
 //  Hartree CG   : L U = 4 pi b by Jacobi-preconditioned CG with the step
-//                 scalars kept on the device (k_cg_state, k_cg_start; k_cg_iter).
+//                 scalars kept on the device (k_cg_state, k_cg_start; k_cg_iter;
+//                 or k_spmv_dot, k_cg_xr, k_cg_dir).
 #include "common.hpp"
 
 namespace ofks {
@@ -183,6 +184,131 @@ __global__ __launch_bounds__(256) void k_cg_bound(int nb, double rtol2, const do
     }
 }
 
+// ---------------------------------------------------------------------------
+// The Hartree CG of scattered numberings (halo_cg_pays): after the product
+// (k_spmv_dot) an update and a direction kernel, on r, d, q of their own.
+// Scalars in sc[]: 0 rz, 1 rr, 2 bb, 3 alpha, 4 beta, 5 dq, 6 rz of the odd
+// iterations.  part holds per-block partials.
+// ---------------------------------------------------------------------------
+__device__ void block_sum2(double a, double b, double *out_a, double *out_b) {
+    __shared__ double ra[256], rb[256];
+    ra[threadIdx.x] = a;
+    rb[threadIdx.x] = b;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (threadIdx.x < w) { ra[threadIdx.x] += ra[threadIdx.x + w]; rb[threadIdx.x] += rb[threadIdx.x + w]; }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) { *out_a = ra[0]; *out_b = rb[0]; }
+}
+
+// r = rhs_scale * b - q ; d = r / diag ; partials rz, rr, and bb = |rhs|^2
+__global__ __launch_bounds__(256) void k_cg_rows_start(int64_t n, double scale, const double *__restrict__ b,
+                                                 const double *__restrict__ q, const double *__restrict__ dg,
+                                                 double *__restrict__ r, double *__restrict__ d,
+                                                 double *__restrict__ part) {
+    double rz = 0.0, rr = 0.0, bb = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const double rhs = scale * b[i];
+        const double ri = rhs - q[i];
+        const double z = ri / dg[i];
+        r[i] = ri;
+        d[i] = z;
+        rz += ri * z;
+        rr += ri * ri;
+        bb += rhs * rhs;
+    }
+    __shared__ double r3[3][256];
+    r3[0][threadIdx.x] = rz;
+    r3[1][threadIdx.x] = rr;
+    r3[2][threadIdx.x] = bb;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (threadIdx.x < w)
+            for (int j = 0; j < 3; ++j) r3[j][threadIdx.x] += r3[j][threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x < 3) part[3 * blockIdx.x + threadIdx.x] = r3[threadIdx.x][0];
+}
+
+// sums the 3-wide partials of nb blocks in a fixed order into sc[0..2]
+__global__ __launch_bounds__(256) void k_cg_rows_sums(int nb, const double *__restrict__ part, double *__restrict__ sc) {
+    __shared__ double r[3][256];
+    double a = 0, b = 0, c = 0;
+    for (int k = threadIdx.x; k < nb; k += 256) { a += part[3 * k]; b += part[3 * k + 1]; c += part[3 * k + 2]; }
+    r[0][threadIdx.x] = a; r[1][threadIdx.x] = b; r[2][threadIdx.x] = c;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (threadIdx.x < w) for (int j = 0; j < 3; ++j) r[j][threadIdx.x] += r[j][threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) { sc[0] = r[0][0]; sc[1] = r[1][0]; sc[2] = r[2][0]; }
+}
+
+// Fixed-order sum of part[k * stride + off], k < nb, computed identically by
+// every block that calls it (all 256 threads; the result is returned to all).
+__device__ __forceinline__ double block_fixed_sum(int nb, int stride, int off, const double *__restrict__ part) {
+    __shared__ double r[256];
+    double a = 0.0;
+    for (int k = threadIdx.x; k < nb; k += 256) a += part[(int64_t)k * stride + off];
+    r[threadIdx.x] = a;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (threadIdx.x < w) r[threadIdx.x] += r[threadIdx.x + w];
+        __syncthreads();
+    }
+    const double v = r[0];
+    __syncthreads();
+    return v;
+}
+
+// One CG iteration after q = L d (partials dq[nb]): every block forms
+// alpha = rz / <d, q> from the partials itself (same fixed order in every
+// block), then x += alpha d, r -= alpha q, partials of <r, z> and <r, r>.
+// rz is read from sc[0] or sc[6] by iteration parity (k_cg_dir writes the
+// other slot, so no block overwrites a value another block still reads).
+__global__ __launch_bounds__(256) void k_cg_xr(int64_t n, int parity, double *__restrict__ sc, int nb,
+                                              const double *__restrict__ dq, const double *__restrict__ d,
+                                              const double *__restrict__ q, const double *__restrict__ dg,
+                                              double *__restrict__ x, double *__restrict__ r,
+                                              double *__restrict__ part) {
+    const double dqs = block_fixed_sum(nb, 1, 0, dq);
+    const double rz_old = sc[parity ? 6 : 0];
+    const double alpha = dqs > 0.0 ? rz_old / dqs : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc[3] = alpha;
+        sc[5] = dqs;
+    }
+    double rz = 0.0, rr = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        x[i] = fma(alpha, d[i], x[i]);
+        const double ri = fma(-alpha, q[i], r[i]);
+        r[i] = ri;
+        rz += ri * ri / dg[i];
+        rr += ri * ri;
+    }
+    block_sum2(rz, rr, &part[3 * blockIdx.x], &part[3 * blockIdx.x + 1]);
+}
+
+// beta = <r, z>_new / <r, z>_old from the k_cg_xr partials (formed in every
+// block), d = z + beta d; block 0 stores <r, z>_new in the other parity slot
+// and <r, r> in sc[1] (the host's convergence check).
+__global__ __launch_bounds__(256) void k_cg_dir(int64_t n, int parity, double *__restrict__ sc, int nb,
+                                               const double *__restrict__ part, const double *__restrict__ r,
+                                               const double *__restrict__ dg, double *__restrict__ d) {
+    const double rz_new = block_fixed_sum(nb, 3, 0, part);
+    const double rr = block_fixed_sum(nb, 3, 1, part);
+    const double rz_old = sc[parity ? 6 : 0];
+    const double beta = rz_old > 0.0 ? rz_new / rz_old : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc[parity ? 0 : 6] = rz_new;
+        sc[1] = rr;
+        sc[4] = beta;
+    }
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        d[i] = fma(beta, d[i], r[i] / dg[i]);
+}
+
 // dot products for energies: part[block] = sum a .* b
 __global__ __launch_bounds__(256) void k_dot(int64_t n, const double *__restrict__ a, const double *__restrict__ b,
                                             double *__restrict__ part) {
@@ -237,6 +363,23 @@ hipError_t launch_cg_start(hipStream_t s, int grid, int64_t n, double scale, dou
     hipLaunchKernelGGL(k_cg_start, dim3(grid), dim3(256), 0, s, n, scale, b, dg, (const double2 *)in, (double2 *)st,
                        part);
     hipLaunchKernelGGL(k_cg_bound, dim3(1), dim3(256), 0, s, grid, rtol2, part, sc);
+    return hipGetLastError();
+}
+hipError_t launch_cg_rows_start(hipStream_t s, int grid, int64_t n, double scale, const double *b, const double *q,
+                                const double *dg, double *r, double *d, double *part, double *sc) {
+    hipLaunchKernelGGL(k_cg_rows_start, dim3(grid), dim3(256), 0, s, n, scale, b, q, dg, r, d, part);
+    hipLaunchKernelGGL(k_cg_rows_sums, dim3(1), dim3(256), 0, s, grid, part, sc);
+    return hipGetLastError();
+}
+// nb_dq: the number of <d, q> partials (the product's grid)
+hipError_t launch_cg_xr(hipStream_t s, int grid, int64_t n, int parity, double *sc, int nb_dq, const double *dq,
+                        const double *d, const double *q, const double *dg, double *x, double *r, double *part) {
+    hipLaunchKernelGGL(k_cg_xr, dim3(grid), dim3(256), 0, s, n, parity, sc, nb_dq, dq, d, q, dg, x, r, part);
+    return hipGetLastError();
+}
+hipError_t launch_cg_dir(hipStream_t s, int grid, int64_t n, int parity, double *sc, const double *part,
+                         const double *r, const double *dg, double *d) {
+    hipLaunchKernelGGL(k_cg_dir, dim3(grid), dim3(256), 0, s, n, parity, sc, grid, part, r, dg, d);
     return hipGetLastError();
 }
 hipError_t launch_dot(hipStream_t s, int grid, int64_t n, const double *a, const double *b, double *part) {

@@ -8,7 +8,8 @@
 //  k_spmm_shift  : Q[:,l] = (L/2 - lam_l B) D[:,l] (operator of the paper's
 //                  preconditioner T_l, eq. precondition-T); for a step of its
 //                  CG with the per-column dot products <D_l, Q_l> and <Q_l, J Q_l>.
-//  k_cg_iter     : one Hartree CG iteration (one vector, FP64).
+//  k_cg_iter     : one Hartree CG iteration (one vector, FP64), and
+//  k_spmv_dot    : q = A d and <d, q> for that of scattered numberings.
 //
 // Work mapping (wave64).  A row is owned by a group of LPR = 2^lpr_log2 lanes;
 // each lane covers V consecutive columns (one vector load of an X row slice)
@@ -754,6 +755,44 @@ k_spmm_halo(int64_t nb, int p, int cw, const int64_t *__restrict__ row0, const i
     }
 }
 
+// SpMV with the dot <d, A d> fused (Hartree CG); persistent grid, 16 lanes
+// per row (P1 rows hold about 15 entries): each lane takes every 16th entry
+// of the row with coalesced loads, the 16 partial sums are combined by
+// shuffles in a fixed order, and the group's first lane writes q_i and
+// accumulates d_i q_i.  Per-block partial written to part[block].
+__global__ __launch_bounds__(256) void k_spmv_dot(int64_t n, const int64_t *__restrict__ rp,
+                                                 const int32_t *__restrict__ col,
+                                                 const double *__restrict__ a,
+                                                 const double *__restrict__ d,
+                                                 double *__restrict__ q,
+                                                 double *__restrict__ part) {
+    __shared__ double red[256];
+    const int sub = threadIdx.x & 15;
+    double s = 0.0;
+    const int64_t rows_per_pass = (int64_t)gridDim.x * (blockDim.x / 16);
+    for (int64_t i = (int64_t)blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4); i - (threadIdx.x >> 4) < n;
+         i += rows_per_pass) {
+        double acc = 0.0;
+        if (i < n) {
+            const int64_t e1 = rp[i + 1];
+            for (int64_t e = rp[i] + sub; e < e1; e += 16) acc = fma(a[e], d[col[e]], acc);
+        }
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 16);
+        if (sub == 0 && i < n) {
+            q[i] = acc;
+            s = fma(d[i], acc, s);
+        }
+    }
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = blockDim.x / 2; w > 0; w >>= 1) {
+        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+}
+
 // ---------------------------------------------------------------------------
 // One Hartree CG iteration in one kernel (one vector, FP64): the Jacobi-CG of
 // Chronopoulos and Gear, J. Comput. Appl. Math. 25 (1989), whose two dots come
@@ -1353,6 +1392,12 @@ hipError_t launch_cg_iter(hipStream_t s, int np, int first, int check, int parit
     else if (maxlen <= 32)
         hipLaunchKernelGGL((k_cg_iter<2, false>), dim3(np), block, 0, s, nb, info, halo, brp, lcol, a, c);
     else hipLaunchKernelGGL((k_cg_iter<2, true>), dim3(np), block, 0, s, nb, info, halo, brp, lcol, a, c);
+    return hipGetLastError();
+}
+
+hipError_t launch_spmv_dot(hipStream_t s, int grid, int64_t n, const int64_t *rp, const int32_t *col,
+                           const double *a, const double *d, double *q, double *part) {
+    hipLaunchKernelGGL(k_spmv_dot, dim3(grid), dim3(256), 0, s, n, rp, col, a, d, q, part);
     return hipGetLastError();
 }
 

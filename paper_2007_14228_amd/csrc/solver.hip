@@ -63,6 +63,8 @@ hipError_t launch_spmm_shift(hipStream_t, int, int, int64_t, int, const int64_t 
                              const T *, const uint8_t *, const double *, const double *, const T *, T *, double *,
                              int *);
 enum { DUAL = 0, SHIFT = 1, SHIFT_CG = 2, SHIFT_DOT = 3 };   // product forms (k_spmm.hip)
+hipError_t launch_spmv_dot(hipStream_t, int, int64_t, const int64_t *, const int32_t *, const double *,
+                           const double *, double *, double *);
 hipError_t launch_cg_iter(hipStream_t, int, int, int, int, int64_t, int, const int32_t *, const int32_t *, const int64_t *,
                           const uint16_t *, const double *, const double *, const double *, double *, double *,
                           double *, const double *, double *, double *);
@@ -182,6 +184,12 @@ hipError_t launch_load_vec(hipStream_t, int64_t, const int32_t *, const int64_t 
                            const double *, const double *, double *);
 hipError_t launch_veff(hipStream_t, int64_t, const int32_t *, const int32_t *, const double *, const double *,
                        const double *, double *);
+hipError_t launch_cg_rows_start(hipStream_t, int, int64_t, double, const double *, const double *, const double *,
+                                double *, double *, double *, double *);
+hipError_t launch_cg_xr(hipStream_t, int, int64_t, int, double *, int, const double *, const double *,
+                        const double *, const double *, double *, double *, double *);
+hipError_t launch_cg_dir(hipStream_t, int, int64_t, int, double *, const double *, const double *, const double *,
+                         double *);
 hipError_t launch_cg_state(hipStream_t, int64_t, const double *, double *);
 hipError_t launch_cg_start(hipStream_t, int, int64_t, double, double, const double *, const double *, const double *,
                            double *, double *, double *);
@@ -274,7 +282,7 @@ struct ofks_ctx {
 
     // SCF work
     double *rho_q = nullptr, *eps_q = nullptr, *vxc_q = nullptr, *veff_q = nullptr, *bvec = nullptr,
-           *U = nullptr, *cg_st[2] = {nullptr, nullptr}, *cg_sc = nullptr,   // (cg_st: the Hartree CG's row states)
+           *U = nullptr, *cg_st[2] = {nullptr, nullptr}, *cg_sc = nullptr,   // (cg_st: the Hartree CG's row states or vectors)
            *cg_part = nullptr;   // Hartree CG partial sums (fixed: the captured graph holds the pointer)
     double *cgb_blk = nullptr;           // with the plan: the small inner CG's own blocks and partials
     int cgb_p = 0;                       // and the widest block that it takes (0: none)
@@ -786,9 +794,82 @@ void drop_cg_graph(ofks_ctx *c) {
     c->cg_graph = nullptr;
 }
 
+// ten iterations (chunk) as the graph that the solves of this system replay
+template <typename F> int capture_cg(ofks_ctx *c, const F &chunk) {
+    if (!c->prm.use_graphs || c->cg_graph) return OFKS_OK;
+    // captured on a private stream (the context's stream may be the null
+    // stream, which cannot be captured); every node is a kernel launch
+    hipStream_t cs = nullptr;
+    HIPCHK(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
+    hipGraph_t gr = nullptr;
+    hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+        const hipError_t el = chunk(cs);
+        e = hipStreamEndCapture(cs, &gr);
+        if (e == hipSuccess) e = el;
+    }
+    if (e == hipSuccess) e = hipGraphInstantiate(&c->cg_graph, gr, nullptr, nullptr, 0);
+    if (gr) (void)hipGraphDestroy(gr);
+    (void)hipStreamDestroy(cs);
+    if (e != hipSuccess) {
+        c->cg_graph = nullptr;
+        return fail(c, OFKS_EHIP, "Hartree CG graph capture: %s", hipGetErrorString(e));
+    }
+    return OFKS_OK;
+}
+
+// The Hartree CG's grids on scattered numberings: enough 256-thread blocks to fill
+// the device (the vectors are short, so the kernels are latency-bound); each block
+// of an update sums all the previous kernel's partials, so fewer of those read
+// far fewer (measured at n = 2e5).
+constexpr int CG_ROWS_SPMV = 2048, CG_ROWS_UPD = 512;
+
+// L U = 4 pi b by three kernels an iteration (halo_cg_pays: where one does not serve)
+int poisson_rows(ofks_ctx *c) {
+    const int64_t n = c->n;
+    const int g = CG_ROWS_SPMV, gu = CG_ROWS_UPD;   // partials: <d, q> (g), then 3-wide update sums (gu)
+    double *dqp = c->cg_part, *xrp = c->cg_part + g;
+    double *r = c->cg_st[0], *d = r + n, *q = d + n;
+    {
+        Scope sc(c, "poisson");
+        HIPCHK(launch_spmv_dot(c->stream, g, n, c->rp, c->col, c->Lv, c->U, q, dqp));
+        // Jacobi preconditioner diag(L/2): a constant multiple of diag(L) leaves the CG iterates unchanged
+        HIPCHK(launch_cg_rows_start(c->stream, gu, n, 4.0 * M_PI, c->bvec, q, c->lhd, r, d, xrp, c->cg_sc));
+    }
+    std::vector<double> sc;
+    CHK(download(c, sc, c->cg_sc, 3));
+    double rr = sc[1];
+    const double bb = sc[2], rt = c->poisson_tol_now > 0.0 ? c->poisson_tol_now : c->prm.poisson_rtol;
+    const double tol2 = rt * rt * bb;
+    // ten CG iterations (30 launches; an even count, so <r, z> ends in sc[0] again)
+    auto chunk = [&](hipStream_t s) -> hipError_t {
+        for (int j = 0; j < 10; ++j) {
+            hipError_t e;
+            if ((e = launch_spmv_dot(s, g, n, c->rp, c->col, c->Lv, d, q, dqp)) != hipSuccess) return e;
+            if ((e = launch_cg_xr(s, gu, n, j & 1, c->cg_sc, g, dqp, d, q, c->lhd, c->U, r, xrp)) != hipSuccess) return e;
+            if ((e = launch_cg_dir(s, gu, n, j & 1, c->cg_sc, xrp, r, c->lhd, d)) != hipSuccess) return e;
+        }
+        return hipSuccess;
+    };
+    CHK(capture_cg(c, chunk));
+    for (int it = 0; rr > tol2 && it < c->prm.poisson_max_iter; it += 10) {
+        {
+            Scope s2(c, "poisson");
+            if (c->prm.use_graphs) HIPCHK(hipGraphLaunch(c->cg_graph, c->stream));
+            else HIPCHK(chunk(c->stream));
+        }
+        CHK(download(c, sc, c->cg_sc, 2));
+        rr = sc[1];
+        if (!std::isfinite(rr)) return fail(c, OFKS_ENONFINITE, "Hartree CG diverged");
+    }
+    if (rr > tol2) return fail(c, OFKS_NOT_CONVERGED, "Hartree CG did not reach %g", rt);
+    return OFKS_OK;
+}
+
 int poisson(ofks_ctx *c) {
     const int64_t n = c->n;
-    if (!c->halo_nb) return fail(c, OFKS_ESTATE, "Hartree CG: the mesh has no halo plan");   // its rows always fit one
+    // (a mesh always has a plan: its rows hold at most 64 entries)
+    if (!c->halo_nb || !halo_cg_pays(n, c->halo_rows)) return poisson_rows(c);
     if (!c->cg_report) HIPCHK(hipHostMalloc((void **)&c->cg_report, 2 * sizeof(double)));
     for (hipEvent_t &e : c->cg_ev)
         if (!e) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -820,26 +901,7 @@ int poisson(ofks_ctx *c) {
         }
         return hipSuccess;
     };
-    if (c->prm.use_graphs && !c->cg_graph) {
-        // captured on a private stream (the context's stream may be the null
-        // stream, which cannot be captured); every node is a kernel launch
-        hipStream_t cs = nullptr;
-        HIPCHK(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-        hipGraph_t gr = nullptr;
-        hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-        if (e == hipSuccess) {
-            const hipError_t el = chunk(cs);
-            e = hipStreamEndCapture(cs, &gr);
-            if (e == hipSuccess) e = el;
-        }
-        if (e == hipSuccess) e = hipGraphInstantiate(&c->cg_graph, gr, nullptr, nullptr, 0);
-        if (gr) (void)hipGraphDestroy(gr);
-        (void)hipStreamDestroy(cs);
-        if (e != hipSuccess) {
-            c->cg_graph = nullptr;
-            return fail(c, OFKS_EHIP, "Hartree CG graph capture: %s", hipGetErrorString(e));
-        }
-    }
+    CHK(capture_cg(c, chunk));
     // Two tens are in flight at a time: the device stops by itself, and a ten
     // after that costs ten empty launches (25 us), while the host's look between
     // two tens cost 15 us for each.
@@ -1955,7 +2017,7 @@ int ofks_assemble(ofks_ctx *c) {
     CHK(dalloc(c, &c->cg_st[0], 4 * n));
     CHK(dalloc(c, &c->cg_st[1], 4 * n));
     CHK(dalloc(c, &c->cg_sc, 8));
-    CHK(dalloc(c, &c->cg_part, 2 * 3 * (size_t)cg_iter_blocks_max()));
+    CHK(dalloc(c, &c->cg_part, std::max<size_t>(2 * 3 * (size_t)cg_iter_blocks_max(), CG_ROWS_SPMV + 3 * CG_ROWS_UPD)));
     HIPCHK(hipMemsetAsync(c->U, 0, n * sizeof(double), s));
     CHK(build_halo_plan(c));
     c->has_system = true;
