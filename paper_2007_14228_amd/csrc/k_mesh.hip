@@ -360,7 +360,7 @@ hipError_t launch_inc_fill(hipStream_t s, int64_t nt, const int32_t *tets, const
     return hipGetLastError();
 }
 hipError_t launch_inc_sort(hipStream_t s, int64_t nn, const int64_t *ptr, int32_t *inc, int32_t *err) {
-    hipLaunchKernelGGL(k_inc_sort, dim3(nblk(nn, 16)), dim3(256), 0, s, nn, ptr, inc, err);
+    hipLaunchKernelGGL(k_inc_sort, dim3(nblk(nn, 128)), dim3(128), 0, s, nn, ptr, inc, err);
     return hipGetLastError();
 }
 hipError_t launch_row_pattern(hipStream_t s, int64_t nn, int fill, const int32_t *dof, const int64_t *iptr,
