@@ -198,6 +198,14 @@ __global__ void k_vext(int64_t nt, const double *__restrict__ xyz, const int32_t
     }
 }
 
+// What the lanes of a row share through LDS is in order within their wave: they
+// take the same trips through the loops around it, so all of them are here, and
+// nothing is moved across.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Row-gather assembly.  mode 0: L, B, M(vq) and the interleaved pairs
 // hb = (L/2 + M, B), lb = (L/2, B), plus the diagonals.  mode 1: hb.x and
 // hdiag only (H = L/2 + M(vq) with L from Lv).
@@ -228,7 +236,7 @@ __global__ __launch_bounds__(256) void k_assemble(int64_t nn, const int32_t *__r
     const int li = threadIdx.x & 15, g = threadIdx.x >> 4;
     const int64_t v = (int64_t)blockIdx.x * 16 + g;
     const int32_t i = v < nn ? dof[v] : -1;
-    if (i < 0) return;   // whole rows of lanes; no barrier below, a row of lanes shares LDS within its wave
+    if (i < 0) return;   // whole rows of lanes; no workgroup barrier below
     const int64_t r0 = row_ptr[i], k0 = iptr[v];
     const int len = (int)(row_ptr[i + 1] - r0), ninc = (int)(iptr[v + 1] - k0);
     for (int c = 0; c < len; c += 16) {
@@ -265,7 +273,7 @@ __global__ __launch_bounds__(256) void k_assemble(int64_t nn, const int32_t *__r
                     sb[g][li] = make_double2(vol * 2.0 / 20.0, vol * 1.0 / 20.0);
                 }
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            wave_sync();
             for (int u = 0; u < cnt; ++u) {
                 const int4 d = sd[g][u];
                 const double2 m0 = sm[g][u][0], m1 = sm[g][u][1];
@@ -277,7 +285,7 @@ __global__ __launch_bounds__(256) void k_assemble(int64_t nn, const int32_t *__r
                     bacc += j == i ? bb.x : j == d.x || j == d.y || j == d.z || j == d.w ? bb.y : 0.0;
                 }
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            wave_sync();
         }
         if (!in) continue;
         if (MODE == 0) {
