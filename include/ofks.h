@@ -405,7 +405,8 @@ int ofks_timing(ofks_ctx *ctx, int32_t enable);
 /* Totals for a kernel class: name is one of "spmm_dual", "spmm_shift",
  * "gram", "update_a", "update_b", "pcg_dx", "pcg_sum", "density", "poisson",
  * "assemble_h", "bbdot", "mlp", "mlp_train", "graph", "graph_train", and "host" (the host's
- * p x p algebra of each iteration, wall time).  ms = summed duration, launches = count. */
+ * p x p algebra of each iteration, wall time).  ms = summed duration, launches = count;
+ * 0 and 0 for any other name (also "pcg_r", a pass that "pcg_dx" now holds). */
 int ofks_timer_get(ofks_ctx *ctx, const char *name, double *ms, int64_t *launches);
 
 #ifdef __cplusplus
