@@ -20,7 +20,12 @@
  *    iteration's state in set_x0 and, lazily, in the first steps (the rest
  *    of the FP64 blocks, the precision switch, SCF and graph-form arrays),
  *    all freed in ofks_destroy.  With a caller workspace (ofks_set_workspace)
- *    the iteration's state is carved from it instead.
+ *    the iteration's state is carved from it instead.  Beside that state a
+ *    context keeps, workspace or not, until ofks_destroy: scratch of the
+ *    single calls up to 256 MiB (more is freed when the call returns), and
+ *    with the system the halo plan and up to 6 MB for the inner CG of small
+ *    blocks.  Without a workspace ofks_set_x0 takes the blocks of the previous
+ *    start over where n, p and the precision are the same.
  *  - Blocks X (n x p) are row-major: the p values of one DOF are contiguous.
  *    n counts interior (non-Dirichlet) nodes, numbered in node order.
  *  - CSR matrices: row_ptr int64[n+1], col int32[nnz], columns sorted

@@ -477,9 +477,10 @@ template <typename K> int resident_grid(K kernel, int cap) {
 // us, dual product 945 -> 745 us; n = 5.1e5, p = 128, FP32: 286 -> 192 and 297
 // -> 189 us.  The shifted product moves 2.7 GB (1.24 times what it must) at
 // 4.4 TB/s, the dual product 3.8 GB at 5.0 TB/s (a copy: 4.8), so memory
-// bounds it.  Block shapes tried, FP64 shifted product in us: (halo rows,
-// rows, waves per SIMD) (200, 64, 3) 741 with the call around it, (120, 32, 4)
-// 788, (148, 48, 4) 835, (240, 64, 2) 818, (76, 16, 6) 851; workgroups that
+// bounds it.  Block shapes tried, FP64 shifted product in us with the call
+// around it: (halo rows, rows, waves per SIMD) (200, 64, 3) 741, (120, 32, 4) 788,
+// (148, 48, 4) 835, (240, 64, 2) 818, (76, 16, 6) 851; (192, 64, 3), which leaves
+// the LDS room for the partials, against (200, 64, 3) later 656 and 657; workgroups that
 // walk several blocks with the next one's loads in flight drift apart, and
 // the widened window misses L2 (794, 2.4 to 3.4 GB fetched instead of 1.7).
 // ---------------------------------------------------------------------------
@@ -820,12 +821,12 @@ __global__ __launch_bounds__(256) void k_spmv_dot(int64_t n, const int64_t *__re
 // slot a thread and sixteen lanes a row, with the next block's loads in flight.
 //
 // Bound by latency where a workgroup has one block or two (the launch, the
-// block's metadata, its states, the partials: 5.0e4 rows 9.2 us), and by
-// memory on top of that (2.0e5 rows, 58 MB: 15.8 us).  Before, with a product,
-// an update and a direction kernel: 17.1 and 25.1 us an iteration.  One block
-// a workgroup of 256 threads: 10.4 and 17.3 us (768 workgroups; 256 12.6 and
-// 26.5, 2048 11.9 and 21.3, for the partials that each must sum); 2, 3, 4
-// teams: 9.2, 9.0, 10.4 and 16.9, 16.5, 16.9.
+// block's metadata, its states, the partials) and by memory on top of that.  An
+// iteration in a captured ten, us, here against product, update and direction
+// kernels: 5.1e4 rows 9.7 and 16.7, 6.4e4 9.8 and 17.2, 2.05e5 (60 MB) 17.7 and
+// 27.1.  Plan blocks a workgroup at once, 2, 3, 4: 8.2, 9.7, 9.0; 9.7, 9.8, 11.3;
+// 17.9, 17.7, 17.9.  One block a workgroup of 256 threads was 1.1 us slower at the
+// small end (768 workgroups; more of them pay for the partials that each must sum).
 // ---------------------------------------------------------------------------
 #ifndef OFKS_CG_BLOCKS
 #define OFKS_CG_BLOCKS 256   // a multiple of 8, at most 256 (a partial a thread of a team)

@@ -422,7 +422,7 @@ template <typename T> int walloc(ofks_ctx *c, T **out, size_t count) {
 }
 
 // bytes that walloc takes for a set of nblk blocks of n x p elements of
-// `elem` bytes and their five per-column arrays (alloc_blocks' layout)
+// `elem` bytes, their two per-column arrays (dinv, lam) and the p x 2p CC (alloc_blocks' layout)
 size_t ws_piece(size_t bytes) { return (std::max<size_t>(bytes, 1) + 255) & ~size_t(255); }
 size_t ws_block_set(size_t n, size_t p, size_t elem, int nblk) {
     return nblk * ws_piece(n * p * elem) + 2 * ws_piece(p * elem) + ws_piece(2 * p * p * elem);
