@@ -1181,7 +1181,10 @@ template <typename T> int iterate(ofks_ctx *c, ofks_iter_stats *st, bool *stop) 
         HIPCHK(launch_multiplier<T>(c->stream, p, norm, plam, beta, c->red, dnd, SL, B.CC, info));
         std::vector<double> in;
         CHK(download(c, in, info, (size_t)5 * p));
-        // S and L0 follow while the host goes on; taken over when they are needed
+        // S and L0 follow while the host goes on; taken over when they are needed (at
+        // the latest in a destructor: their room is made here, where it may fail)
+        c->S.reserve((size_t)p * p);
+        c->L0.reserve((size_t)p * p);
         HIPCHK(hipMemcpyAsync(c->hsl, SL, pp2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
         HIPCHK(hipEventRecord(c->hsl_ev, c->stream));
         th0 = std::chrono::steady_clock::now();
