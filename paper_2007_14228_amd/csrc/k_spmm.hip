@@ -844,14 +844,14 @@ struct CgIter {
     double *pout, *report;
 };
 
+// v + the v of the lane N further on in each sixteen
+template <int N> __device__ __forceinline__ double row_ror_add(double v) {
+    return v + __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + N, 0xf, 0xf, true),
+                                __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + N, 0xf, 0xf, true));
+}
 // sum over each sixteen lanes, to all of them
 __device__ __forceinline__ double row_sum(double v) {
-#define OFKS_ROR(N)                                                                                                  \
-    v += __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + N, 0xf, 0xf, true),              \
-                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + N, 0xf, 0xf, true));
-    OFKS_ROR(8) OFKS_ROR(4) OFKS_ROR(2) OFKS_ROR(1)
-#undef OFKS_ROR
-    return v;
+    return row_ror_add<1>(row_ror_add<2>(row_ror_add<4>(row_ror_add<8>(v))));
 }
 
 // what a thread loads ahead for a plan block
@@ -1040,7 +1040,7 @@ __global__ __launch_bounds__(256 * OFKS_CG_TEAMS) void k_cg_iter(
 // size; this one is bound by the same latencies, once.
 //
 // x is carried in twice the digits (its low part in a block of its own).  Error
-// of ten steps on graded meshes (80-bit sums): 0.86 times that of the two-term
+// of ten steps on graded meshes (80-bit sums): 0.84 times that of the two-term
 // recurrence; with M^-1 T p from a recurrence of its own (one product for both
 // dots, as in k_cg_iter) it was 1.68 times, up to 5.4.
 //
@@ -1063,12 +1063,12 @@ struct CgBlockArgs {
 
 // sums of three values over the workgroup's 64 rows of threads, to all of them
 __device__ __forceinline__ void cgb_sum(double (&red)[3][16], double (&v)[3]) {
-    // lanes of one column are four apart: by lane exchanges within a wave, then over the four waves
+    // lanes of one column are four apart: on the vector units within a wave, then over the four waves
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63, c = threadIdx.x & (CGB_COLS - 1);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-#pragma unroll
-        for (int off = CGB_COLS; off < 64; off <<= 1) v[k] += __shfl_xor(v[k], off);
+        v[k] = row_ror_add<4>(row_ror_add<8>(v[k]));
+        v[k] = rows_sum(v[k]);
         if (l < CGB_COLS) red[k][CGB_COLS * w + l] = v[k];
     }
     __syncthreads();
@@ -1096,11 +1096,11 @@ __global__ __launch_bounds__(256) void k_cgb_iter(int64_t nb, const int64_t *__r
     const int inf = info[b], nr = (inf >> 8) & 255, rb = (inf >> 16) & 255;
     const int64_t row = row0[b] + min(g, nr - 1), e0 = brp[b * HALO_BRP + g];
     const int len = (int)(brp[b * HALO_BRP + g + 1] - e0);   // 0 past the block's rows
-    double sum[3] = {0.0, 0.0, 0.0};   // <d, q>, <q, M^-1 q>, <r, M^-1 r>
-    if (!c.first && in)
-        for (int64_t k = g; k < nb; k += G)
+    // partials of <d, q>, <q, M^-1 q>, <r, M^-1 r>: the first 64 plan blocks' now
+    double sum[3] = {0.0, 0.0, 0.0};
+    if (!c.first && in && g < nb)
 #pragma unroll
-            for (int u = 0; u < 3; ++u) sum[u] += c.pin[(3 * k + u) * c.p + col];
+        for (int u = 0; u < 3; ++u) sum[u] = c.pin[(3 * (int64_t)g + u) * c.p + col];
     double2 w[CGB_AHEAD];
     int lc[CGB_AHEAD];
     if (!c.last)
@@ -1126,6 +1126,10 @@ __global__ __launch_bounds__(256) void k_cgb_iter(int64_t nb, const int64_t *__r
     const double ivr = c.last ? 1.0 : 1.0 / (c.lhd[row] - lm * c.bd[row]);
     CgCoef<double> k{0.0, 0.0, 0.0};
     if (!c.first) {
+        if (in)
+            for (int64_t b2 = g + G; b2 < nb; b2 += G)
+#pragma unroll
+                for (int u = 0; u < 3; ++u) sum[u] += c.pin[(3 * b2 + u) * c.p + col];
         cgb_sum(red[0], sum);
         k = cg_coef<double>(sum[0], sum[1], sum[2], 0.0);
         sum[2] = 0.0;

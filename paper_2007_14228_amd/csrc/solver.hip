@@ -1015,10 +1015,10 @@ double bb_eta(int rule, int k, double sy, double yy, double ss, double eta_prev,
 // Small FP64 blocks take the inner CG with one kernel an iteration
 // (k_cgb_iter), up to OFKS_CGB_BLOCKS workgroups of it: a call of 10 iterations
 // on graded meshes took (here against three kernels an iteration, us; workgroups)
-// n = 3375, p = 4 112 against 172 (57), p = 16 137 against 168 (228), p = 48 179
-// against 199 (684), p = 64 222 against 204 (912); n = 8000, p = 16 181 against 195
-// (536), p = 24 239 against 220 (804); n = 15625, p = 8 181 against 192 (522), p =
-// 11 245 against 239 (783); n = 42875, p = 4 188 against 249 (715).  Not where
+// n = 3375, p = 4 113 against 166 (57), p = 16 135 against 168 (228), p = 48 176
+// against 199 (684), p = 64 214 against 204 (912); n = 8000, p = 16 182 against 194
+// (536), p = 24 230 against 216 (804); n = 15625, p = 8 180 against 192 (522), p =
+// 11 236 against 236 (783); n = 42875, p = 4 183 against 248 (715).  Not where
 // spmm_mode asks for the gathering product.
 bool cgb_choice(const ofks_ctx *c, int p) { return c->prm.spmm_mode != 1 && p <= c->cgb_p; }
 
