@@ -1040,7 +1040,7 @@ __global__ __launch_bounds__(256 * OFKS_CG_TEAMS) void k_cg_iter(
 // size; this one is bound by the same latencies, once.
 //
 // x is carried in twice the digits (its low part in a block of its own).  Error
-// of ten steps on graded meshes (80-bit sums): 0.84 times that of the two-term
+// of ten steps on graded meshes (80-bit sums): 0.83 times that of the two-term
 // recurrence; with M^-1 T p from a recurrence of its own (one product for both
 // dots, as in k_cg_iter) it was 1.68 times, up to 5.4.
 //
